@@ -343,7 +343,7 @@ __global__ __launch_bounds__(256) void k_claim_sorted(const int32_t* __restrict_
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g < n_total; g += stride) {
     const SegIdx s = seg_index(offsets, n_filters, n_total, g);
-    if (s.n < min_len) continue;  // permuted in LDS by k_permute_staged
+    if (s.n < min_len) continue;  // permuted in LDS by k_permute_lds
     const int64_t ai = anc_at(a, s, s.i, bad);
     const int64_t prev = (s.i == 0) ? -1 : anc_at(a, s, s.i - 1, bad);
     int32_t* ds = d + s.base;
@@ -526,100 +526,299 @@ __global__ __launch_bounds__(256) void k_resolve(int64_t n_total,
   }
 }
 
-// Segments of at most CAP particles, one workgroup each, entirely in LDS: the
-// claim vector d (minimum claimer per slot, by LDS atomic minimum), then the
-// marked ancestry e overwrites d (a claimed-slot bitmap keeps what resolve
-// needs of d), then every slot resolves as in k_resolve.  Global traffic is
-// the ancestry read and the permutation written.
-constexpr int kPermThreads = 1024;
+// Segments of at most CAP <= 65536 particles, one workgroup each, entirely in
+// LDS (local indices fit 16 bits).  A thread takes the same quads of four
+// consecutive positions in every pass, so that loads and stores are 16 bytes
+// a lane and what it learns about its own quads stays in registers.  Code 10
+// needs of the claims only which slots are claimed and which positions won:
+//   sorted     a position wins when it starts a run (a_i > a_{i-1}); one pass
+//              gives the winners and a byte per claimed slot (plain stores,
+//              where one bit per slot would serialise the atomics of a run);
+//              the order is verified on the way, and an input that is not
+//              sorted takes the other path
+//   any order  an LDS atomic minimum per slot, in windows of the buffer
+// Then the ancestry sits in LDS as 16-bit entries, with the winner bit in bit
+// 15 up to 32768 particles and in a bitmap beyond, and every unclaimed slot
+// walks backwards as in k_resolve, an LDS read per step instead of a read
+// beyond the L2: kLockstep steps for the four chains of a quad together, and
+// the few longer chains from a list at the end, one a lane (in lockstep to
+// their end, a wave's longest chain would hold all its lanes in every round).
+// Global traffic: the ancestry once (sorted,
+// up to 32768 particles; else twice or more), the permutation once.  Bound by
+// the latency of those loads and of the walk.  Measured per call against 32-bit
+// claims in LDS up to 16384 particles and the global kernels beyond: 1024
+// segments of 16384 107 -> 42 us sorted, 79 -> 50 us unsorted; 600 of 30000
+// 426 -> 67 and 1064 -> 79 us; 4096 ragged ones of 256 .. 65536 (4.8e7
+// particles) 1.48 -> 0.39 and 3.18 -> 0.45 ms.
+constexpr int kLockstep = 6;
+constexpr int kPermShort = 2048;      // batches: segments of the 256-thread tier
+constexpr int kPermMid = 16384;       // two workgroups of 1024 threads to a CU
+constexpr int kPermLong = 32768;      // 96 KB: one pass over a sorted ancestry
+constexpr int kPermBatchMax = 65536;  // batches: segments permuted in LDS
+constexpr int64_t kPermLongTotal = 1 << 21;  // batches: particles from which kPermMid is passed
 // Single vectors up to these lengths are permuted in LDS by one workgroup
-// (one launch instead of two to four); beyond them the multi-workgroup
-// kernels are faster (measured on MI355X: the crossover lies near 2^10
-// particles for a sorted ancestry and 2^12 for an unsorted one).
-constexpr int kPermSingleMax = 4096;
-constexpr int kPermSingleMaxSorted = 1024;
+// (one launch instead of two to five); beyond them the multi-workgroup
+// kernels are faster (kernel time at 8192 sorted, y = 0 / 4: 9.0 / 5.8 us,
+// 16384: 21 / 8 against 11.4 / 7.2 us of two launches; unsorted 16384: 14 / 13
+// against 19 us of five).
+constexpr int kPermSingleMax = 16384;
+constexpr int kPermSingleMaxSorted = 8192;
+constexpr int kPermSmallWorkspace = 4096;  // up to here a workspace has no room for buckets
 
-template <int CAP>
-__global__ __launch_bounds__(kPermThreads) void k_permute_staged(
+// LDS bytes of the shared buffer: 16-bit entries and claim bytes side by side
+// up to kPermLong, one after the other in the same place beyond.
+constexpr int perm_buffer(int cap) {
+  return cap <= kPermShort ? 4 * cap : cap <= kPermLong ? 3 * cap : 2 * cap;
+}
+
+// Four consecutive positions from 4 q (entries past n: own index).  Segments
+// start anywhere, so the 16-byte access is only 4-byte aligned.
+typedef int32_t Quad __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ void load_quad(const int32_t* __restrict__ as, uint32_t q, uint32_t n,
+                                          int32_t (&v)[4]) {
+  const uint32_t i = 4 * q;
+  if (i + 4 <= n) {
+    const Quad t = *reinterpret_cast<const Quad*>(as + i);
+    v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
+  } else {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = i + k < n ? as[i + k] : (int32_t)(i + k);
+  }
+}
+
+template <int CAP, int THREADS>
+__global__ __launch_bounds__(THREADS) void k_permute_lds(
     const int32_t* __restrict__ a, int64_t n_total, const int64_t* __restrict__ offsets,
-    uint32_t n_filters, int32_t* __restrict__ c, uint32_t* __restrict__ flags) {
-  __shared__ int32_t de[CAP];
-  __shared__ uint32_t claimed[CAP / 32];
-  constexpr int kPer = CAP / kPermThreads;  // particles per thread
-  const uint32_t f = blockIdx.x;
-  const int64_t base = offsets ? offsets[f] : 0;
-  const int64_t n64 = offsets ? offsets[f + 1] - base : n_total;
-  if (n64 <= 0 || n64 > CAP) return;  // long segments: global kernels
-  const int32_t n = (int32_t)n64;
-  const int tid = (int)threadIdx.x;
+    int64_t above, int64_t upto, bool sorted, int32_t* __restrict__ c,
+    uint32_t* __restrict__ flags) {
+  constexpr int kBytes = perm_buffer(CAP);
+  constexpr uint32_t WIN = kBytes / 4;         // slots of a claim window
+  constexpr bool kOnePass = kBytes >= 3 * CAP;  // entries and claim bytes fit together
+  constexpr uint32_t kStep = 4 * THREADS;
+  constexpr uint32_t kSlow = CAP <= kPermShort ? 256 : 3 * THREADS;
+  static_assert(CAP <= 65536 && CAP / (4 * THREADS) <= 16 && WIN % kStep == 0,
+                "16-bit indices, 16 quads a thread, windows of whole rounds");
+  __shared__ __align__(16) uint8_t buf[kBytes];
+  __shared__ uint32_t won[CAP / 32];
+  __shared__ uint32_t slow[kSlow], n_slow;
+  const int64_t base = offsets ? offsets[blockIdx.x] : 0;
+  const int64_t n64 = offsets ? offsets[blockIdx.x + 1] - base : n_total;
+  if (n64 <= above || n64 > upto || n64 > CAP) return;  // another launch's segment
+  const uint32_t n = (uint32_t)n64, nq = (n + 3) / 4;
+  const bool packed = CAP <= 32768 || n <= 32768u;
+  const uint32_t tid = threadIdx.x, lane = lane_id();
+  const int32_t* __restrict__ as = a + base;
+  uint16_t* const e = reinterpret_cast<uint16_t*>(buf);
   bool bad = false;
   // ancestor of local position i; out-of-range values count as i
-  auto anc = [&](int32_t i) -> int32_t {
-    const int32_t v = a[base + i];
-    return (v < 0 || v >= n) ? i : v;
+  auto anc = [&](uint32_t i, int32_t v) -> uint32_t {
+    const bool out = (uint32_t)v >= n && i < n;
+    bad |= out;
+    return out ? i : (uint32_t)v;
   };
-#pragma unroll
-  for (int q = 0; q < kPer; ++q) {
-    const int32_t i = tid + q * kPermThreads;
-    de[i] = n;
-    if (q * kPermThreads < CAP / 32 && i < CAP / 32) claimed[i] = 0u;
-  }
-  __syncthreads();
-#pragma unroll
-  for (int q = 0; q < kPer; ++q) {
-    const int32_t i = tid + q * kPermThreads;
-    if (i < n) {
-      const int32_t v = a[base + i];
-      if (v < 0 || v >= n) bad = true;
-      atomicMin(&de[(v < 0 || v >= n) ? i : v], i);
-    }
-  }
-  __syncthreads();
-  int32_t ev[kPer];
-#pragma unroll
-  for (int q = 0; q < kPer; ++q) {
-    const int32_t i = tid + q * kPermThreads;
-    ev[q] = 0;
-    if (i < n) {
-      const int32_t ai = anc(i);
-      ev[q] = de[ai] == i ? ai : -1 - ai;
-      if (de[i] < n) atomicOr(&claimed[i >> 5], 1u << (i & 31));
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int q = 0; q < kPer; ++q) {
-    const int32_t i = tid + q * kPermThreads;
-    if (i < n) de[i] = ev[q];
-  }
-  __syncthreads();
-  bool broken = false;
-#pragma unroll
-  for (int q = 0; q < kPer; ++q) {
-    const int32_t j = tid + q * kPermThreads;
-    if (j >= n) continue;
-    if ((claimed[j >> 5] >> (j & 31)) & 1u) {
-      c[base + j] = j;
-      continue;
-    }
-    int32_t ey = de[j];
-    int32_t steps = 0;
-    bool br = false;
-    while (ey >= 0) {
-      ey = de[ey];
-      if (++steps > n) {
-        br = true;
-        break;
+  // the end of the chain that stands at winner y (its winner bit read already)
+  auto walk = [&](uint32_t y) -> uint32_t {
+    if (packed) {
+      y = e[y];
+      while (y & 0x8000u) y = e[y & 0x7FFFu];
+    } else {
+      uint32_t more = 1u;
+      while (more) {
+        more = (won[y >> 5] >> (y & 31u)) & 1u;
+        y = e[y];
       }
     }
-    broken |= br;
-    c[base + j] = br ? j : -1 - ey;
+    return y;
+  };
+  if (tid == 0) n_slow = 0;  // (ordered by the barriers before the walk)
+  auto put_quad = [&](uint32_t q, const uint32_t (&v)[4], uint32_t nib) {
+    const uint32_t w0 = (nib & 1u) << 15, w1 = (nib & 2u) << 30, w2 = (nib & 4u) << 13,
+                   w3 = (nib & 8u) << 28;
+    reinterpret_cast<uint2*>(e)[q] =
+        make_uint2(v[0] | (v[1] << 16) | w0 | w1, v[2] | (v[3] << 16) | w2 | w3);
+  };
+  // bits 4 r .. 4 r + 3: of the thread's quad tid + r THREADS, which positions
+  // won their claims / which slots are claimed
+  uint64_t mine_won = 0, mine_claimed = 0;
+  if (sorted) {
+    uint8_t* const cb = kOnePass ? buf + 2 * CAP : buf;
+    for (uint32_t k = tid; k < (n + 15) / 16; k += THREADS)
+      reinterpret_cast<uint4*>(cb)[k] = make_uint4(0u, 0u, 0u, 0u);
+    __syncthreads();
+    bool down = false;
+#pragma unroll 2
+    for (uint32_t r = 0; r * THREADS < nq; ++r) {
+      const uint32_t q = r * THREADS + tid;
+      int32_t x[4];
+      uint32_t v[4], nib = 0;
+      load_quad(as, q, n, x);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[k] = anc(4 * q + k, x[k]);
+      uint32_t first = 0xFFFFFFFFu;  // -1 before position 0
+      if (lane == 0 && q > 0 && q < nq) first = anc(4 * q - 1, as[4 * q - 1]);
+      int32_t prev = (int32_t)wave_shift_up_u32(v[3], first);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const bool in = 4 * q + k < n;
+        down |= in && (int32_t)v[k] < prev;
+        if (in && (int32_t)v[k] > prev) {
+          cb[v[k]] = 1;
+          nib |= 1u << k;
+        }
+        prev = (int32_t)v[k];
+      }
+      mine_won |= (uint64_t)nib << (4 * r);
+      if (kOnePass && q < nq) put_quad(q, v, nib);
+      if (!packed) {  // the walk reads other threads' winners: the nibbles of eight lanes
+        uint32_t w = nib << (4 * (lane & 7u));
+        w |= dpp_u32<kDppXor1>(0u, w);
+        w |= dpp_u32<kDppXor2>(0u, w);
+        w |= dpp_u32<kDppHalfMirror>(0u, w);
+        if ((lane & 7u) == 0 && q < nq) won[q >> 3] = w;
+      }
+    }
+    sorted = !__syncthreads_or(down ? 1 : 0);
+    if (sorted) {
+      for (uint32_t r = 0; r * THREADS < nq; ++r) {
+        const uint32_t q = r * THREADS + tid;
+        if (q < nq) {
+          const uint32_t x = reinterpret_cast<const uint32_t*>(cb)[q];
+          const uint32_t nib = (x | (x >> 7) | (x >> 14) | (x >> 21)) & 15u;
+          mine_claimed |= (uint64_t)nib << (4 * r);
+        }
+      }
+    }
   }
-  if (flags) {
-    const uint32_t fl = (bad || broken) ? FLAG_BAD_ANCESTOR : 0u;
-    const uint32_t b = wave_reduce(fl, OpOr());
-    if (b && lane_id() == 0) atomicOr(flags, b);
+  if (!sorted) {
+    uint32_t* const d = reinterpret_cast<uint32_t*>(buf);
+    for (uint32_t k = tid; k < (n + 31) / 32; k += THREADS) won[k] = 0;
+    mine_won = 0;
+    for (uint32_t w0 = 0; w0 < n; w0 += WIN) {
+      const uint32_t ns = min(WIN, n - w0);
+      __syncthreads();  // the buffer is free
+      for (uint32_t k = tid; k < (ns + 3) / 4; k += THREADS)
+        reinterpret_cast<uint4*>(d)[k] =
+            make_uint4(0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu);
+      __syncthreads();
+#pragma unroll 2
+      for (uint32_t q = tid; q < nq; q += THREADS) {
+        int32_t x[4];
+        load_quad(as, q, n, x);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const uint32_t i = 4 * q + k, s = anc(i, x[k]) - w0;
+          if (s < ns && i < n) atomicMin(&d[s], i);
+        }
+      }
+      __syncthreads();
+      for (uint32_t k = tid; k < (ns + 3) / 4; k += THREADS) {
+        const uint4 t = reinterpret_cast<const uint4*>(d)[k];
+        const uint32_t w[4] = {t.x, t.y, t.z, t.w};
+        uint32_t nib = 0;
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+          if (w[m] < n) {
+            nib |= 1u << m;
+            atomicOr(&won[w[m] >> 5], 1u << (w[m] & 31u));
+          }
+        }
+        mine_claimed |= (uint64_t)nib << (4 * ((w0 / 4 + k - tid) / THREADS));
+      }
+    }
+    __syncthreads();
+    for (uint32_t r = 0; r * THREADS < nq; ++r) {
+      const uint32_t q = r * THREADS + tid;
+      if (q < nq) mine_won |= (uint64_t)((won[q >> 3] >> (4 * (q & 7u))) & 15u) << (4 * r);
+    }
   }
+  if (!(kOnePass && sorted)) {
+    __syncthreads();  // the buffer is free
+#pragma unroll 2
+    for (uint32_t r = 0; r * THREADS < nq; ++r) {
+      const uint32_t q = r * THREADS + tid;
+      if (q >= nq) break;
+      int32_t x[4];
+      uint32_t v[4];
+      load_quad(as, q, n, x);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[k] = anc(4 * q + k, x[k]);
+      put_quad(q, v, packed ? (uint32_t)(mine_won >> (4 * r)) & 15u : 0u);
+    }
+  }
+  __syncthreads();
+  for (uint32_t r = 0; r * THREADS < nq; ++r) {
+    const uint32_t q = r * THREADS + tid;
+    if (q >= nq) break;
+    const uint2 t = reinterpret_cast<const uint2*>(e)[q];
+    const uint32_t cl = (uint32_t)(mine_claimed >> (4 * r)) & 15u;
+    uint32_t y[4] = {t.x & 0xFFFFu, t.x >> 16, t.y & 0xFFFFu, t.y >> 16};
+    const uint32_t j = 4 * q;
+    uint32_t left = 0;  // chains that go on after kLockstep steps
+    if (packed) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if ((cl >> k) & 1u || j + k >= n) y[k] = (j + k) & 0x7FFFu;
+      for (int s = 0; s < kLockstep && ((y[0] | y[1] | y[2] | y[3]) & 0x8000u); ++s) {
+        uint32_t z[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) z[k] = e[y[k] & 0x7FFFu];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) y[k] = (y[k] & 0x8000u) ? z[k] : y[k];
+      }
+#pragma unroll
+      for (int k = 0; k < 4; ++k) left |= ((y[k] >> 15) & 1u) << k;
+    } else {
+      left = (uint32_t)(mine_won >> (4 * r)) & 15u & ~cl;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        if ((cl >> k) & 1u || j + k >= n) {
+          y[k] = (j + k) & 0xFFFFu;
+          left &= ~(1u << k);
+        }
+      }
+      for (int s = 0; s < kLockstep && left; ++s) {
+        uint32_t z[4], m[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          z[k] = e[y[k]];
+          m[k] = won[y[k] >> 5];
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const bool go = (left >> k) & 1u;
+          const uint32_t more = (m[k] >> (y[k] & 31u)) & 1u;
+          left = go && !more ? left & ~(1u << k) : left;
+          y[k] = go ? z[k] : y[k];
+        }
+      }
+    }
+    if (left) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        if ((left >> k) & 1u) {
+          const uint32_t at = atomicAdd(&n_slow, 1u);
+          if (at < kSlow) slow[at] = ((j + k) << 16) | (y[k] & (packed ? 0x7FFFu : 0xFFFFu));
+          else y[k] = walk(y[k] & (packed ? 0x7FFFu : 0xFFFFu));
+        }
+      }
+    }
+    if (j + 4 <= n) {
+      Quad o;
+      o.x = (int32_t)y[0]; o.y = (int32_t)y[1]; o.z = (int32_t)y[2]; o.w = (int32_t)y[3];
+      *reinterpret_cast<Quad*>(c + base + j) = o;
+    } else {
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (j + k < n) c[base + j + k] = (int32_t)y[k];
+    }
+  }
+  __syncthreads();  // also orders the chains' slots after the quads stored above
+  const uint32_t ns = min(n_slow, (uint32_t)kSlow);
+  for (uint32_t t = tid; t < ns; t += THREADS) {
+    const uint32_t s = slow[t];
+    c[base + (s >> 16)] = (int32_t)walk(s & 0xFFFFu);
+  }
+  if (flags && ballot(bad) != 0 && lane == 0) atomicOr(flags, FLAG_BAD_ANCESTOR);
 }
 
 // ---------------------------------------------------------------- bucketed claim
@@ -911,13 +1110,13 @@ size_t permute_workspace_min_bytes(int64_t n_total) {
   return 2 * align256((size_t)n_total * sizeof(int32_t));
 }
 size_t permute_workspace_bytes(int64_t n_total, uint32_t n_filters) {
-  if (n_filters <= 1 && n_total > kPermSingleMax && bucket_claim_fits(n_total))
+  if (n_filters <= 1 && n_total > kPermSmallWorkspace && bucket_claim_fits(n_total))
     return bucket_geom(n_total).bytes;
   return permute_workspace_min_bytes(n_total);
 }
 
 // Batches whose segments fit in LDS, and short single vectors, are permuted
-// there (k_permute_staged, one workgroup per segment); longer segments go
+// there (k_permute_lds, one workgroup per segment); longer segments go
 // through the global kernels.  max_len: longest segment (0 = unknown).
 hipError_t launch_permute(const int32_t* a, int64_t n_total, const int64_t* offsets,
                           uint32_t n_filters, int64_t max_len, bool sorted, int32_t* c, void* ws,
@@ -928,26 +1127,52 @@ hipError_t launch_permute(const int32_t* a, int64_t n_total, const int64_t* offs
   int64_t min_len = 0;  // shorter segments are done in LDS
   if (!(offsets && n_filters > 1) && n_total <= (sorted ? kPermSingleMaxSorted : kPermSingleMax)) {
     // a short single vector: one workgroup, one launch
-    hipLaunchKernelGGL(k_permute_staged<kPermSingleMax>, dim3(1), dim3(kPermThreads), 0, stream,
-                       a, n_total, nullptr, 1u, c, flags);
+    hipLaunchKernelGGL((k_permute_lds<kPermMid, 1024>), dim3(1), dim3(1024), 0, stream, a, n_total,
+                       (const int64_t*)nullptr, (int64_t)0, (int64_t)kPermSingleMax, sorted, c,
+                       flags);
     return hipGetLastError();
   }
   if (offsets && n_filters > 1) {
-    // segments up to the tuned length in LDS, the longer ones below
-    const int cap = tuning().batch_permute_lds_max;
-    if (cap == 4096)
-      hipLaunchKernelGGL(k_permute_staged<4096>, dim3(n_filters), dim3(kPermThreads), 0, stream,
-                         a, n_total, offsets, n_filters, c, flags);
-    else if (cap == 8192)
-      hipLaunchKernelGGL(k_permute_staged<8192>, dim3(n_filters), dim3(kPermThreads), 0, stream,
-                         a, n_total, offsets, n_filters, c, flags);
-    else
-      hipLaunchKernelGGL(k_permute_staged<16384>, dim3(n_filters), dim3(kPermThreads), 0, stream,
-                         a, n_total, offsets, n_filters, c, flags);
+    // four tiers by segment length, each launch taking its own segments:
+    // short ones in 256-thread workgroups (eight to a CU), those up to the
+    // tuned length in 1024 threads (two to a CU), those up to 32768 and to
+    // 65536 in 1024 threads (one to a CU); longer ones below.  A tier takes
+    // the shorter segments too, and their launches fall away, when there are
+    // none (every segment has the full length) or when all segments together
+    // do not fill the chip once.  The one workgroup of a long segment takes
+    // 30 to 70 us, so below kPermLongTotal particles the global kernels,
+    // spread over the chip, run the long ones (four of 60000: 22 against 67
+    // us; 256 of them 313 against 68 us).
+    const int64_t mid = tuning().batch_permute_lds_max;
+    const bool equal = max_len > 0 && max_len * (int64_t)n_filters == n_total;
+    const bool spread = n_total < kPermLongTotal;
+    const int64_t top = spread ? mid : kPermBatchMax;
+    const int64_t upto[4] = {kPermShort, mid, kPermLong, kPermBatchMax};
+    constexpr uint32_t kSlots[4] = {0, 512, 256, 256};  // workgroups the chip holds at once
+    const int64_t need = max_len > 0 ? (max_len < top ? max_len : top) : top;
+    int64_t above = 0;
+    for (int t = 0; t < 4 && above < need; ++t) {
+      if (upto[t] < need && (equal || n_filters <= kSlots[upto[1] < need ? (upto[2] < need ? 3 : 2) : 1]))
+        continue;
+      const dim3 g(n_filters);
+      if (t == 0)
+        hipLaunchKernelGGL((k_permute_lds<kPermShort, 256>), g, dim3(256), 0, stream, a, n_total,
+                           offsets, above, upto[t], sorted, c, flags);
+      else if (t == 1)
+        hipLaunchKernelGGL((k_permute_lds<kPermMid, 1024>), g, dim3(1024), 0, stream, a, n_total,
+                           offsets, above, upto[t], sorted, c, flags);
+      else if (t == 2)
+        hipLaunchKernelGGL((k_permute_lds<kPermLong, 1024>), g, dim3(1024), 0, stream, a, n_total,
+                           offsets, above, upto[t], sorted, c, flags);
+      else
+        hipLaunchKernelGGL((k_permute_lds<kPermBatchMax, 1024>), g, dim3(1024), 0, stream, a,
+                           n_total, offsets, above, upto[t], sorted, c, flags);
+      above = upto[t];
+    }
     hipError_t e0 = hipGetLastError();
     if (e0 != hipSuccess) return e0;
-    if (max_len > 0 && max_len <= cap) return hipSuccess;
-    min_len = cap + 1;
+    if (max_len > 0 && max_len <= top) return hipSuccess;
+    min_len = top + 1;
   }
   if (sorted) {
     hipLaunchKernelGGL(k_claim_sorted, dim3(grid), dim3(256), 0, stream, a, n_total, offsets,

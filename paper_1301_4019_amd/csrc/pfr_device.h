@@ -292,6 +292,9 @@ __device__ __forceinline__ T wave_reduce(T v, Op op) {
 // (to rows 2 and 3), and a shift of the whole wave by one lane.  A lane whose
 // source lies outside its row, or whose row ROW_MASK leaves out, gets `old`.
 constexpr int kDppShr1 = 0x111, kDppShr2 = 0x112, kDppShr4 = 0x114, kDppShr8 = 0x118;
+// (kDppXor1 / kDppXor2: lane l ^ 1 / l ^ 2 of its quad; kDppHalfMirror: lane
+// 7 - l of its row's half)
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141;
 constexpr int kDppBcast15 = 0x142, kDppBcast31 = 0x143, kDppWaveShr1 = 0x138;
 
 template <int CTRL, int ROW_MASK = 0xF>
