@@ -217,10 +217,13 @@ PFR_API int resample_systematic(const void* w, pfr_dtype dtype, const pfr_segmen
  * No collective operation: the chains are independent, so the output does
  * not depend on the launch shape.  Segments of up to 16K (float32) or 8K
  * (float64) weights, and with pfr_segments.max_len set up to 32K / 16K, are
- * staged in LDS.  The workspace (may be NULL, ws_bytes 0) holds, for a single
+ * staged in LDS, and of segments up to 256K 16-bit bounds of the weights.  The
+ * workspace (may be NULL, ws_bytes 0) holds, for a single
  * long vector of less than 2^31 bytes of weights, a table of power-of-two
  * weight bounds per bucket of particles that lets most rejected proposals
- * skip the load of w_j; it changes the speed, never the result. */
+ * skip the load of w_j, and for a batch with B_dev the running cost of its
+ * segments, by which the work is split; it changes the speed, never the
+ * result. */
 PFR_API int resample_metropolis(const void* w, pfr_dtype dtype, const pfr_segments* seg, int32_t B,
                         const int32_t* B_dev, pfr_rng rng, int32_t* ancestors, void* ws,
                         size_t ws_bytes, void* stream);

@@ -95,9 +95,29 @@ __device__ __forceinline__ void metropolis_accept(const MGroup& g, uint32_t& k, 
 // its chains is an LDS read.  Longer segments load from global memory, with
 // the gathers of the next group of steps in flight while the current group
 // is decided.  The chains do not depend on the launch shape.
+// Four consecutive weights; a segment starts anywhere, so the wide access is
+// aligned to one weight only.
+template <typename T>
+struct alignas(sizeof(T)) Weights4 {
+  T v[4];
+};
+template <typename T>
+__device__ __forceinline__ Weights4<T> load_weights4(const T* __restrict__ w) {
+  typedef T V __attribute__((ext_vector_type(4), aligned(sizeof(T))));
+  const V t = *reinterpret_cast<const V*>(w);
+  return Weights4<T>{{t.x, t.y, t.z, t.w}};
+}
+
+// A segment of n weights into LDS (16-byte aligned), 16 bytes a lane.
 template <typename T>
 __device__ __forceinline__ void stage_weights(const T* __restrict__ w, uint32_t n, T* sw) {
-  for (uint32_t k = threadIdx.x; k < n; k += blockDim.x) sw[k] = w[k];
+#pragma unroll 4
+  for (uint32_t q = threadIdx.x; q < n / 4; q += blockDim.x) {
+    const Weights4<T> t = load_weights4(w + 4 * q);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) sw[4 * q + k] = t.v[k];
+  }
+  if (threadIdx.x < (n & 3u)) sw[(n & ~3u) + threadIdx.x] = w[(n & ~3u) + threadIdx.x];
 }
 
 template <typename T>
@@ -114,64 +134,6 @@ __device__ __forceinline__ uint32_t metropolis_chain(const T* ws, Key key, uint3
     metropolis_accept<T>(g, k, wk);
   }
   return k;
-}
-
-template <typename T, int CAP, int THREADS>
-__global__ __launch_bounds__(THREADS) void k_metropolis_staged(
-    const T* __restrict__ w, int64_t n_total, const int64_t* __restrict__ offsets,
-    uint32_t n_filters, int32_t B, const int32_t* __restrict__ B_dev, Key key, uint32_t offset,
-    uint32_t filter_base, int32_t* __restrict__ a, int64_t chunk, int64_t min_len,
-    int64_t max_len) {
-  __shared__ T sw[CAP > 0 ? CAP : 1];
-  offset = counter_offset(key, offset);
-  const int64_t p0 = (int64_t)blockIdx.x * chunk;
-  const int64_t p1 = p0 + chunk < n_total ? p0 + chunk : n_total;
-  uint32_t f = offsets ? find_segment(offsets, n_filters, p0) : 0u;
-  for (int64_t g0 = p0; g0 < p1; ++f) {
-    const int64_t base = offsets ? offsets[f] : 0;
-    const int64_t end = offsets ? offsets[f + 1] : n_total;
-    const int64_t q1 = end < p1 ? end : p1;
-    if (q1 <= g0) continue;  // empty segment
-    const uint32_t n = (uint32_t)(end - base);
-    if (end - base < min_len || end - base > max_len) {  // another launch runs this segment
-      g0 = q1;
-      continue;
-    }
-    const int32_t steps = B_dev ? B_dev[f] : B;
-    const uint32_t filt = filter_base + f;
-    if (CAP > 0 && n <= (uint32_t)CAP) {
-      __syncthreads();  // the previous segment's chains are done with sw
-      stage_weights(w + base, n, sw);
-      __syncthreads();
-      for (int64_t g = g0 + threadIdx.x; g < q1; g += THREADS)
-        a[g] = (int32_t)metropolis_chain(sw, key, (uint32_t)(g - base), filt, offset, n, steps);
-    } else if (CAP > 0) {  // a long segment in a staged launch: plain chains
-      for (int64_t g = g0 + threadIdx.x; g < q1; g += THREADS)
-        a[g] = (int32_t)metropolis_chain(w + base, key, (uint32_t)(g - base), filt, offset, n,
-                                         steps);
-    } else {
-      for (int64_t g = g0 + threadIdx.x; g < q1; g += THREADS) {
-        const uint32_t i = (uint32_t)(g - base);
-        const T* __restrict__ ws = w + base;
-        uint32_t k = i;
-        double wk = (double)ws[i];
-        const int32_t groups = (steps + 3) / 4;
-        const PhiloxLane pl = philox_lane(key, i, filt, offset);
-        MGroup ga, gb;
-        if (groups > 0) metropolis_fetch(ws, key, i, pl, filt, offset, n, steps, 0, ga);
-        for (int32_t m = 0; m < groups; m += 2) {
-          if (m + 1 < groups)
-            metropolis_fetch(ws, key, i, pl, filt, offset, n, steps, m + 1, gb);
-          metropolis_accept<T>(ga, k, wk);
-          if (m + 2 < groups)
-            metropolis_fetch(ws, key, i, pl, filt, offset, n, steps, m + 2, ga);
-          if (m + 1 < groups) metropolis_accept<T>(gb, k, wk);
-        }
-        a[g] = (int32_t)k;
-      }
-    }
-    g0 = q1;
-  }
 }
 
 // ------------------------------------------------------------------ bound table
@@ -344,12 +306,148 @@ __device__ BoundTable load_bound_table(const uint32_t* __restrict__ nib_g,
   return t;
 }
 
-// Metropolis with the bound table.  A skip needs the exact current w_k, so
+// A bound per particle (or per 2 or 4 of them) in LDS, for a segment too long
+// for its weights to be staged: 16 bits, twice what the 32-bit weights would
+// leave room for.  The bound is the weight rounded up to 16 leading bits of
+// its format (binary32: 7 fraction bits, binary64: 4), so nearly every
+// proposal that it cannot reject is accepted, and the loads of w_j that are
+// left are about the accepted moves.  Invalid weights never cause a skip that
+// the exact test would not take (their code is the largest, or the comparison
+// fails), so the result is the plain chain's for any input.  Measured on 256
+// segments of 60000 binary32 weights against plain chains, whose gathers miss
+// the L2: B = 354 133 -> 735 G steps/s, B = 16 130 -> 509.
+constexpr uint32_t kCodes = 65536;  // 128 KB
+constexpr uint32_t kCodesMaxShift = 2;
+__device__ __forceinline__ uint32_t bound16(float v) {
+  return (uint32_t)(((uint64_t)__float_as_uint(v) + 0xFFFFu) >> 16);  // -NaN: 0x10000, cut to 0xFFFF
+}
+__device__ __forceinline__ uint32_t bound16(double v) {
+  const uint64_t b = (uint64_t)__double_as_longlong(v);
+  return weight_ok(v) ? (uint32_t)((b + 0xFFFFFFFFFFFFull) >> 48) & 0x7FFFu : 0x7FF0u;
+}
+
+template <typename T>
+struct CodeTable {
+  const uint16_t* code;  // LDS
+  uint32_t shift;        // particle j's bound is code[j >> shift]
+  // True when p = fl(u w_k) shows u w_k > w_j: the high word of p (as a signed
+  // number: a negative or zero p never rejects) exceeds that of the bound in
+  // binary64, so p >= bound (1 + 2^-20), far above the rounding of p.
+  __device__ __forceinline__ bool rejects(double u, double wk, uint32_t j) const {
+    const uint32_t c = code[j >> shift];
+    const int32_t hi = sizeof(T) == 4 ? (int32_t)((c << 13) + 0x38000000u) : (int32_t)(c << 16);
+    return (int32_t)((uint64_t)__double_as_longlong(u * wk) >> 32) > hi;
+  }
+};
+
+template <typename T>
+__device__ __forceinline__ CodeTable<T> stage_codes(const T* __restrict__ w, uint32_t n,
+                                                    uint16_t* code) {
+  CodeTable<T> t{code, 0};
+  while (((n - 1) >> t.shift) >= kCodes) ++t.shift;
+  auto enc = [](T v) -> uint32_t {
+    const uint32_t c = bound16(v);
+    return c > 0xFFFFu ? 0xFFFFu : c;
+  };
+  if (t.shift == 0) {
+#pragma unroll 4
+    for (uint32_t q = threadIdx.x; q < n / 4; q += blockDim.x) {
+      const Weights4<T> x = load_weights4(w + 4 * q);
+      reinterpret_cast<uint2*>(code)[q] =
+          make_uint2(enc(x.v[0]) | (enc(x.v[1]) << 16), enc(x.v[2]) | (enc(x.v[3]) << 16));
+    }
+    if (threadIdx.x < (n & 3u)) {
+      const uint32_t j = (n & ~3u) + threadIdx.x;
+      code[j] = (uint16_t)enc(w[j]);
+    }
+  } else {
+    for (uint32_t b = threadIdx.x; b <= (n - 1) >> t.shift; b += blockDim.x) {
+      uint32_t c = 0;
+      for (uint32_t j = b << t.shift; j < min((b + 1) << t.shift, n); ++j) c = max(c, enc(w[j]));
+      code[b] = (uint16_t)c;
+    }
+  }
+  return t;
+}
+
+// Metropolis with a bound table.  A skip needs the exact current w_k, so
 // the gathers cannot be issued ahead of the decisions of earlier steps;
 // instead each lane runs K independent chains in lockstep: at every step the
 // chains whose proposal the table cannot reject issue their loads together
-// and the K decisions follow.  Particles of the chunk: lane l runs
-// p0 + l + c * kTableThreads for c < K.
+// and the K decisions follow.  Lane l runs the particles i0 + l + c STRIDE,
+// c < K, below i1, of the segment of n weights ws (wv: its buffer view).
+template <typename T, int K, int STRIDE, typename Table>
+__device__ __forceinline__ void metropolis_lockstep(const T* __restrict__ ws,
+                                                    __amdgpu_buffer_rsrc_t wv, uint32_t n,
+                                                    int32_t B, Key key, uint32_t filter,
+                                                    uint32_t offset, const Table& tab,
+                                                    uint32_t i0, uint32_t i1,
+                                                    int32_t* __restrict__ as) {
+  const uint32_t ib = i0 + threadIdx.x;
+  if (ib >= i1) return;
+  uint32_t k[K];
+  double wk[K];
+  PhiloxLane pl[K];
+#pragma unroll
+  for (int c = 0; c < K; ++c) {
+    // a dead chain (past the end) runs a copy of the lane's first and is not stored
+    const uint32_t i = ib + c * STRIDE;
+    k[c] = i < i1 ? i : ib;
+    wk[c] = (double)ws[k[c]];
+    pl[c] = philox_lane(key, k[c], filter, offset);
+  }
+  for (int32_t m = 0; 4 * m < B; ++m) {
+    const int32_t left = B - 4 * m;
+    const int ncall = left >= 4 ? 3 : (3 * left + 3) / 4;
+    const int nq = left >= 4 ? 4 : left;
+    uint32_t x[K][12];
+#pragma unroll
+    for (int c = 0; c < K; ++c) {
+#pragma unroll
+      for (int c3 = 0; c3 < 3; ++c3) {
+        if (c3 < ncall) {
+          // step, filter and offset are the same on every lane (one segment)
+          const uint4 v =
+              philox_lane_call(pl[c], key, DOM_TRIAL, (uint32_t)(3 * m + c3), filter, offset);
+          x[c][4 * c3 + 0] = v.x;
+          x[c][4 * c3 + 1] = v.y;
+          x[c][4 * c3 + 2] = v.z;
+          x[c][4 * c3 + 3] = v.w;
+        }
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      if (q < nq) {
+        uint32_t j[K];
+        double u[K], v[K];
+        bool need[K];
+#pragma unroll
+        for (int c = 0; c < K; ++c) {
+          j[c] = index_draw(x[c][3 * q], x[c][3 * q + 1], n);
+          u[c] = u_accept(x[c][3 * q + 2]);
+          need[c] = !tab.rejects(u[c], wk[c], j[c]);
+        }
+        // the K gathers go out together; lanes with nothing to load read zero
+#pragma unroll
+        for (int c = 0; c < K; ++c)
+          v[c] = (double)buffer_gather<T>(wv, need[c] ? j[c] * (uint32_t)sizeof(T) : kNoLoad);
+#pragma unroll
+        for (int c = 0; c < K; ++c) {
+          // selects, not a branch: the gathered value is used on every lane,
+          // so the gathers cannot be sunk into per-chain branches
+          const bool acc = need[c] & accept_exact<T>(u[c], wk[c], v[c]);
+          k[c] = acc ? j[c] : k[c];
+          wk[c] = acc ? v[c] : wk[c];
+        }
+      }
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < K; ++c)
+    if (ib + c * STRIDE < i1) as[ib + c * STRIDE] = (int32_t)k[c];
+}
+
 template <typename T, int K>
 __global__ __launch_bounds__(kTableThreads) void k_metropolis_table(
     const T* __restrict__ w, int64_t n, int32_t B, Key key, uint32_t offset, uint32_t filter,
@@ -362,71 +460,153 @@ __global__ __launch_bounds__(kTableThreads) void k_metropolis_table(
   const __amdgpu_buffer_rsrc_t wv = buffer_view(w, (uint32_t)(n * (int64_t)sizeof(T)));
   const int64_t p0 = (int64_t)blockIdx.x * chunk;
   const int64_t p1 = p0 + chunk < n ? p0 + chunk : n;
-  for (int64_t gb = p0 + threadIdx.x; gb < p1; gb += (int64_t)K * kTableThreads) {
-    uint32_t idx[K], k[K];
-    double wk[K];
-    bool live[K];
-    PhiloxLane pl[K];
-#pragma unroll
-    for (int c = 0; c < K; ++c) {
-      const int64_t g = gb + (int64_t)c * kTableThreads;
-      live[c] = g < p1;
-      idx[c] = (uint32_t)(live[c] ? g : gb);
-      k[c] = idx[c];
-      wk[c] = (double)w[idx[c]];
-      pl[c] = philox_lane(key, idx[c], filter, offset);
+  for (int64_t g = p0; g < p1; g += (int64_t)K * kTableThreads)
+    metropolis_lockstep<T, K, kTableThreads>(w, wv, (uint32_t)n, B, key, filter, offset, tab,
+                                             (uint32_t)g, (uint32_t)p1, a);
+}
+
+// ------------------------------------------------------------------ staged Metropolis
+// Workgroups go to the eight XCDs in turn, each with its own L2.  Chunk index
+// of a workgroup such that runs of about 65536 particles (whole segments, in a
+// batch) stay on one XCD: their weights are then read from its L2, where
+// chunks dealt out one by one would keep a copy of every segment in flight in
+// all eight.
+__device__ __forceinline__ int64_t xcd_chunk(int64_t chunk) {
+  const uint32_t G = (uint32_t)max((int64_t)1, 65536 / chunk);
+  const uint32_t b = blockIdx.x, s0 = b - b % (8 * G);
+  if (s0 + 8 * G > gridDim.x) return b;  // the last, partial group of runs
+  const uint32_t r = b - s0;
+  return s0 + (r & 7u) * G + (r >> 3);
+}
+
+// A batch whose segments have their own step counts is cut by cost instead of
+// by particles: chunk t starts where the cost prefix, a segment's particles
+// times its steps (and two for the rest), reaches t / gridDim of the total,
+// rounded to whole passes of the workgroup.  Equal chunks leave the chip
+// waiting for the last ones of B = 354 (4096 ragged vectors
+// of 256 .. 65536 particles, B = 4 .. 354: 4.94 against 3.87 ms).
+__global__ __launch_bounds__(1024) void k_cost_prefix(const int64_t* __restrict__ offsets,
+                                                      uint32_t n_filters,
+                                                      const int32_t* __restrict__ B,
+                                                      uint64_t* __restrict__ cost) {
+  __shared__ uint64_t s_w[1024 / kWave];
+  const uint32_t wave = threadIdx.x / kWave, lane = lane_id();
+  uint64_t carry = 0;
+  for (uint32_t f0 = 0; f0 < n_filters; f0 += 1024) {
+    const uint32_t f = f0 + threadIdx.x;
+    const uint64_t x = f < n_filters ? (uint64_t)(offsets[f + 1] - offsets[f]) *
+                                           (uint64_t)(max(B[f], 0) + 2)
+                                     : 0ull;
+    const uint64_t incl = wave_incl_add_u64(x);
+    if (lane == kWave - 1) s_w[wave] = incl;
+    __syncthreads();
+    uint64_t before = carry + incl - x;
+    for (uint32_t w2 = 0; w2 < 1024 / kWave; ++w2) {
+      before += w2 < wave ? s_w[w2] : 0ull;
+      carry += s_w[w2];
     }
-    for (int32_t m = 0; 4 * m < B; ++m) {
-      const int32_t left = B - 4 * m;
-      const int ncall = left >= 4 ? 3 : (3 * left + 3) / 4;
-      const int nq = left >= 4 ? 4 : left;
-      uint32_t x[K][12];
-#pragma unroll
-      for (int c = 0; c < K; ++c) {
-#pragma unroll
-        for (int c3 = 0; c3 < 3; ++c3) {
-          if (c3 < ncall) {
-            // step, filter and offset are the same on every lane (one vector)
-            const uint4 v =
-                philox_lane_call(pl[c], key, DOM_TRIAL, (uint32_t)(3 * m + c3), filter, offset);
-            x[c][4 * c3 + 0] = v.x;
-            x[c][4 * c3 + 1] = v.y;
-            x[c][4 * c3 + 2] = v.z;
-            x[c][4 * c3 + 3] = v.w;
-          }
+    if (f < n_filters) cost[f] = before;
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) cost[n_filters] = carry;
+}
+
+// First particle of chunk t of `chunks` (whole waves call it).
+__device__ __forceinline__ int64_t cost_start(const uint64_t* __restrict__ cost,
+                                              const int64_t* __restrict__ offsets,
+                                              uint32_t n_filters, int64_t n_total, uint32_t t,
+                                              uint32_t chunks, uint32_t cap) {
+  if (t == 0) return 0;
+  if (t >= chunks) return n_total;
+  const uint64_t total = cost[n_filters], q = total / chunks, r = total % chunks;
+  const uint64_t target = q * t + r * t / chunks;
+  const uint32_t f = wave_find_segment(cost, n_filters, target);
+  const uint64_t n = (uint64_t)(offsets[f + 1] - offsets[f]);
+  const uint64_t span = cost[f + 1] - cost[f];
+  // (of equal prefixes the last is found: f's cost is positive unless no cost follows)
+  uint64_t i = span ? (target - cost[f]) / (span / n) : 0ull;
+  const uint64_t unit = n > cap ? 2048 : 1024;
+  i = (i + unit / 2) / unit * unit;
+  return offsets[f] + (int64_t)(i < n ? i : n);
+}
+
+template <typename T, int CAP, int THREADS>
+__global__ __launch_bounds__(THREADS) void k_metropolis_staged(
+    const T* __restrict__ w, int64_t n_total, const int64_t* __restrict__ offsets,
+    uint32_t n_filters, int32_t B, const int32_t* __restrict__ B_dev, Key key, uint32_t offset,
+    uint32_t filter_base, int32_t* __restrict__ a, int64_t chunk,
+    const uint64_t* __restrict__ cost) {
+  // 128 KB of weights, or 65536 codes of a segment longer than that
+  constexpr bool kCoded = CAP * sizeof(T) == 2 * kCodes;
+  __shared__ __align__(16) T sw[CAP > 0 ? CAP : 1];
+  offset = counter_offset(key, offset);
+  const int64_t t = offsets ? xcd_chunk(chunk) : (int64_t)blockIdx.x;
+  int64_t p0 = t * chunk, p1 = p0 + chunk < n_total ? p0 + chunk : n_total;
+  if (cost) {
+    p0 = cost_start(cost, offsets, n_filters, n_total, (uint32_t)t, gridDim.x, CAP);
+    p1 = cost_start(cost, offsets, n_filters, n_total, (uint32_t)t + 1, gridDim.x, CAP);
+    if (p0 >= p1) return;
+  }
+  uint32_t f = offsets ? wave_find_segment(offsets, n_filters, p0) : 0u;
+  for (int64_t g0 = p0; g0 < p1; ++f) {
+    const int64_t base = offsets ? offsets[f] : 0;
+    const int64_t end = offsets ? offsets[f + 1] : n_total;
+    const int64_t q1 = end < p1 ? end : p1;
+    if (q1 <= g0) continue;  // empty segment
+    const uint32_t n = (uint32_t)(end - base);
+    const int32_t steps = B_dev ? B_dev[f] : B;
+    const uint32_t filt = filter_base + f;
+    if (CAP > 0 && n <= (uint32_t)CAP) {
+      __syncthreads();  // the previous segment's chains are done with sw
+      stage_weights(w + base, n, sw);
+      __syncthreads();
+      for (int64_t g = g0 + threadIdx.x; g < q1; g += THREADS)
+        a[g] = (int32_t)metropolis_chain(sw, key, (uint32_t)(g - base), filt, offset, n, steps);
+    } else if (kCoded && n <= kCodes << kCodesMaxShift) {
+      uint16_t* const code = reinterpret_cast<uint16_t*>(sw);
+      __syncthreads();
+      const CodeTable<T> tab = stage_codes(w + base, n, code);
+      __syncthreads();
+      const __amdgpu_buffer_rsrc_t wv = buffer_view(w + base, n * (uint32_t)sizeof(T));
+      const uint32_t i1 = (uint32_t)(q1 - base);
+      for (uint32_t i0 = (uint32_t)(g0 - base); i0 < i1;) {
+        // two chains a lane, or one for what is left (four spill registers)
+        if (i1 - i0 > THREADS) {
+          metropolis_lockstep<T, 2, THREADS>(w + base, wv, n, steps, key, filt, offset, tab, i0,
+                                             i1, a + base);
+          i0 += 2 * THREADS;
+        } else {
+          metropolis_lockstep<T, 1, THREADS>(w + base, wv, n, steps, key, filt, offset, tab, i0,
+                                             i1, a + base);
+          i0 += THREADS;
         }
       }
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        if (q < nq) {
-          uint32_t j[K];
-          double u[K], v[K];
-          bool need[K];
-#pragma unroll
-          for (int c = 0; c < K; ++c) {
-            j[c] = index_draw(x[c][3 * q], x[c][3 * q + 1], (uint32_t)n);
-            u[c] = u_accept(x[c][3 * q + 2]);
-            // a dead chain (past the chunk end) runs a copy of chain gb and is not stored
-            need[c] = !tab.rejects(u[c], wk[c], j[c]);
-          }
-          // the K gathers go out together; lanes with nothing to load read zero
-#pragma unroll
-          for (int c = 0; c < K; ++c)
-            v[c] = (double)buffer_gather<T>(wv, need[c] ? j[c] * (uint32_t)sizeof(T) : kNoLoad);
-#pragma unroll
-          for (int c = 0; c < K; ++c) {
-            // selects, not a branch: the gathered value is used on every lane,
-            // so the gathers cannot be sunk into per-chain branches
-            const bool acc = need[c] & accept_exact<T>(u[c], wk[c], v[c]);
-            k[c] = acc ? j[c] : k[c];
-            wk[c] = acc ? v[c] : wk[c];
-          }
+    } else if (CAP > 0) {  // a longer segment in a staged launch: plain chains
+      for (int64_t g = g0 + threadIdx.x; g < q1; g += THREADS)
+        a[g] = (int32_t)metropolis_chain(w + base, key, (uint32_t)(g - base), filt, offset, n,
+                                         steps);
+    } else {
+      for (int64_t g = g0 + threadIdx.x; g < q1; g += THREADS) {
+        const uint32_t i = (uint32_t)(g - base);
+        const T* __restrict__ ws = w + base;
+        uint32_t k = i;
+        double wk = (double)ws[i];
+        const int32_t groups = (steps + 3) / 4;
+        const PhiloxLane pl = philox_lane(key, i, filt, offset);
+        MGroup ga, gb;
+        if (groups > 0) metropolis_fetch(ws, key, i, pl, filt, offset, n, steps, 0, ga);
+        for (int32_t m = 0; m < groups; m += 2) {
+          if (m + 1 < groups)
+            metropolis_fetch(ws, key, i, pl, filt, offset, n, steps, m + 1, gb);
+          metropolis_accept<T>(ga, k, wk);
+          if (m + 2 < groups)
+            metropolis_fetch(ws, key, i, pl, filt, offset, n, steps, m + 2, ga);
+          if (m + 1 < groups) metropolis_accept<T>(gb, k, wk);
         }
+        a[g] = (int32_t)k;
       }
     }
-#pragma unroll
-    for (int c = 0; c < K; ++c)
-      if (live[c]) a[gb + (int64_t)c * kTableThreads] = (int32_t)k[c];
+    g0 = q1;
   }
 }
 
@@ -752,35 +932,37 @@ template <typename T>
 hipError_t launch_metropolis_t(const void* wv, int64_t n_total, const int64_t* offsets,
                                uint32_t n_filters, int64_t max_len, int32_t B,
                                const int32_t* B_dev, Key key, uint32_t offset,
-                               uint32_t filter_base, int32_t* a, hipStream_t stream) {
+                               uint32_t filter_base, int32_t* a, uint64_t* cost,
+                               hipStream_t stream) {
   const T* w = (const T*)wv;
   constexpr int per_kb = 1024 / (int)sizeof(T);
   const int cap = staged_capacity<T>(max_len, n_total, n_filters);
-  constexpr int64_t kAll = INT64_MAX;
-  auto global_launch = [&](int64_t min_len) {
+  const uint64_t* const uniform = nullptr;
+  auto global_launch = [&]() {
     const int64_t chunk = tuning().metropolis_chunk;
     hipLaunchKernelGGL((k_metropolis_staged<T, 0, 256>), dim3((unsigned)((n_total + chunk - 1) / chunk)),
                        dim3(256), 0, stream, w, n_total, offsets, n_filters, B, B_dev, key, offset,
-                       filter_base, a, chunk, min_len, kAll);
+                       filter_base, a, chunk, uniform);
     return hipGetLastError();
   };
   if (cap == 0) {
-    // one vector of up to 128 KB of weights: staged as below (one workgroup
-    // per CU for the LDS), otherwise chains gather from global memory
-    if ((!offsets || n_filters <= 1) && n_total <= 128 * per_kb) {
+    // one vector of up to 128 KB of weights, or of up to 65536 codes: staged
+    // as below (one workgroup per CU for the LDS), otherwise chains gather
+    // from global memory.  Staging the codes pays from about a dozen steps
+    // (60000 binary32 weights, 16 / 354 steps: global 30 / 541 us, staged
+    // 14 / 105 us; at 4 steps the staging is most of the call).
+    const bool one = !offsets || n_filters <= 1;
+    if (one && (n_total <= 128 * per_kb || (n_total <= (int64_t)kCodes && (B_dev || B >= 12)))) {
       const int64_t chunk1 = 256;
       hipLaunchKernelGGL((k_metropolis_staged<T, 128 * per_kb, 256>),
                          dim3((unsigned)((n_total + chunk1 - 1) / chunk1)), dim3(256), 0, stream,
                          w, n_total, offsets, n_filters, B, B_dev, key, offset, filter_base, a,
-                         chunk1, (int64_t)0, kAll);
+                         chunk1, uniform);
       return hipGetLastError();
     }
-    return global_launch(0);
+    return global_launch();
   }
-  // segments longer than the LDS tier run in the same launch, from global
-  // memory (a second, pipelined launch for them measured slower on ragged
-  // batches: its chunks hold several long chains per lane)
-  const int64_t hi = kAll;
+  // segments longer than the LDS tier run in the same launch
   if (!offsets || n_filters <= 1) {
     // one short vector: every workgroup stages all of it and runs 256 of its
     // chains, one per lane, so that long chains (large B) spread over many CUs
@@ -790,27 +972,53 @@ hipError_t launch_metropolis_t(const void* wv, int64_t n_total, const int64_t* o
     if (cap == 16 * per_kb)
       hipLaunchKernelGGL((k_metropolis_staged<T, 16 * per_kb, 256>), grid1, dim3(256), 0, stream,
                          w, n_total, offsets, n_filters, B, B_dev, key, offset, filter_base, a,
-                         chunk1, (int64_t)0, hi);
+                         chunk1, uniform);
     else
       hipLaunchKernelGGL((k_metropolis_staged<T, 64 * per_kb, 256>), grid1, dim3(256), 0, stream,
                          w, n_total, offsets, n_filters, B, B_dev, key, offset, filter_base, a,
-                         chunk1, (int64_t)0, hi);
+                         chunk1, uniform);
     return hipGetLastError();
   }
-  const int64_t chunk = tuning().batch_metropolis_chunk;
+  if (n_total <= 256 * 256) {
+    // a small batch: one chain per lane and 256 chains per workgroup, as for
+    // one short vector, so that its long chains spread over the chip
+    const dim3 grid1((unsigned)((n_total + 255) / 256));
+    if (cap == 16 * per_kb)
+      hipLaunchKernelGGL((k_metropolis_staged<T, 16 * per_kb, 256>), grid1, dim3(256), 0, stream,
+                         w, n_total, offsets, n_filters, B, B_dev, key, offset, filter_base, a,
+                         (int64_t)256, uniform);
+    else if (cap == 64 * per_kb)
+      hipLaunchKernelGGL((k_metropolis_staged<T, 64 * per_kb, 256>), grid1, dim3(256), 0, stream,
+                         w, n_total, offsets, n_filters, B, B_dev, key, offset, filter_base, a,
+                         (int64_t)256, uniform);
+    else
+      hipLaunchKernelGGL((k_metropolis_staged<T, 128 * per_kb, 256>), grid1, dim3(256), 0, stream,
+                         w, n_total, offsets, n_filters, B, B_dev, key, offset, filter_base, a,
+                         (int64_t)256, uniform);
+    return hipGetLastError();
+  }
+  // the tuned chunk, less where it would leave CUs idle (two workgroups each)
+  int64_t chunk = (n_total / 512 + 1023) / 1024 * 1024;
+  if (chunk > tuning().batch_metropolis_chunk) chunk = tuning().batch_metropolis_chunk;
+  if (chunk < 1024) chunk = 1024;
+  if (cost && B_dev && n_filters <= 16384)
+    hipLaunchKernelGGL(k_cost_prefix, dim3(1), dim3(1024), 0, stream, offsets, n_filters, B_dev,
+                       cost);
+  else
+    cost = nullptr;
   const dim3 grid((unsigned)((n_total + chunk - 1) / chunk));
   if (cap == 16 * per_kb)
     hipLaunchKernelGGL((k_metropolis_staged<T, 16 * per_kb, 1024>), grid, dim3(1024), 0, stream, w,
                        n_total, offsets, n_filters, B, B_dev, key, offset, filter_base, a, chunk,
-                       (int64_t)0, hi);
+                       (const uint64_t*)cost);
   else if (cap == 64 * per_kb)
     hipLaunchKernelGGL((k_metropolis_staged<T, 64 * per_kb, 1024>), grid, dim3(1024), 0, stream, w,
                        n_total, offsets, n_filters, B, B_dev, key, offset, filter_base, a, chunk,
-                       (int64_t)0, hi);
+                       (const uint64_t*)cost);
   else
     hipLaunchKernelGGL((k_metropolis_staged<T, 128 * per_kb, 1024>), grid, dim3(1024), 0, stream,
                        w, n_total, offsets, n_filters, B, B_dev, key, offset, filter_base, a,
-                       chunk, (int64_t)0, hi);
+                       chunk, (const uint64_t*)cost);
   return hipGetLastError();
 }
 
@@ -852,6 +1060,13 @@ size_t alt_workspace_bytes(bool f64, int64_t n_total, uint32_t n_filters, int64_
   const bool t = f64 ? use_table<double>(n_total, n_filters, max_len)
                      : use_table<float>(n_total, n_filters, max_len);
   return t ? table_geom(n_total).bytes : 0;
+}
+
+// Metropolis: the same, and for a batch the cost prefix of its segments.
+size_t metropolis_workspace_bytes(bool f64, int64_t n_total, uint32_t n_filters,
+                                  int64_t max_len) {
+  if (n_filters > 1) return (((size_t)n_filters + 1) * sizeof(uint64_t) + 255) & ~(size_t)255;
+  return alt_workspace_bytes(f64, n_total, n_filters, max_len);
 }
 
 template <typename T>
@@ -897,7 +1112,7 @@ hipError_t launch_metropolis_table(const T* w, int64_t n, int32_t B, Key key, ui
   if (chunk <= kTableThreads)
     hipLaunchKernelGGL((k_metropolis_table<T, 1>), grid, dim3(kTableThreads), 0, stream, w, n, B,
                        key, offset, filter, a, chunk, nib, cm, g.nb, g.shift);
-  else if (chunk <= 2 * kTableThreads)
+  else if (chunk <= 2 * kTableThreads || sizeof(T) == 8)
     hipLaunchKernelGGL((k_metropolis_table<T, 2>), grid, dim3(kTableThreads), 0, stream, w, n, B,
                        key, offset, filter, a, chunk, nib, cm, g.nb, g.shift);
   else
@@ -920,10 +1135,15 @@ hipError_t launch_metropolis(bool f64, const void* w, int64_t n_total, const int
                                          a, ws, stream)
                : launch_metropolis_table((const float*)w, n_total, B, key, offset, filter_base, a,
                                          ws, stream);
+  // a batch's workspace holds the cost prefix of its segments
+  uint64_t* cost = ws && n_filters > 1 &&
+                           ws_bytes >= metropolis_workspace_bytes(f64, n_total, n_filters, max_len)
+                       ? (uint64_t*)ws
+                       : nullptr;
   return f64 ? launch_metropolis_t<double>(w, n_total, offsets, n_filters, max_len, B, B_dev, key,
-                                           offset, filter_base, a, stream)
+                                           offset, filter_base, a, cost, stream)
              : launch_metropolis_t<float>(w, n_total, offsets, n_filters, max_len, B, B_dev, key,
-                                          offset, filter_base, a, stream);
+                                          offset, filter_base, a, cost, stream);
 }
 
 

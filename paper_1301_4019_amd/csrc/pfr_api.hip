@@ -162,6 +162,7 @@ size_t pfr_workspace_bytes(pfr_op op, const pfr_segments* seg, pfr_dtype dtype) 
       if (!uses_scan_workspace(s)) return 0;
       return scan_layout(s.n_total, op == PFR_OP_MULTINOMIAL).total;
     case PFR_OP_METROPOLIS:
+      return metropolis_workspace_bytes(dtype == PFR_F64, s.n_total, s.n_filters, s.max_len);
     case PFR_OP_REJECTION:
       return alt_workspace_bytes(dtype == PFR_F64, s.n_total, s.n_filters, s.max_len);
     case PFR_OP_OFFSPRING_TO_ANCESTORS:

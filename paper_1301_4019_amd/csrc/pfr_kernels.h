@@ -113,6 +113,7 @@ hipError_t launch_fscan_batched(int scheme, int prec, bool f64, const void* w, i
 // max_len: longest segment (0 = unknown); segments that fit in LDS are staged.
 // ws (may be NULL) holds the weight-bound table of a long single vector.
 size_t alt_workspace_bytes(bool f64, int64_t n_total, uint32_t n_filters, int64_t max_len);
+size_t metropolis_workspace_bytes(bool f64, int64_t n_total, uint32_t n_filters, int64_t max_len);
 hipError_t launch_metropolis(bool f64, const void* w, int64_t n_total, const int64_t* offsets,
                              uint32_t n_filters, int64_t max_len, int32_t B, const int32_t* B_dev,
                              Key key, uint32_t offset, uint32_t filter_base, int32_t* a, void* ws,
