@@ -90,8 +90,25 @@ int check_hint(const int32_t* a, const SegInfo& s, int32_t* sorted_hint, uint32_
       launch_check_sorted(a, s.n_total, s.offsets, s.n_filters, dev_flags, (hipStream_t)stream));
 }
 
-size_t lgssm_offsets_bytes(int32_t n_filters) {
-  return (((size_t)n_filters + 1) * sizeof(int64_t) + 255) & ~(size_t)255;
+// A filter's workspace: the FilterState parts (256-byte aligned each), then
+// what a resampler and the permutation share.
+size_t lgssm_state_bytes(int32_t n_filters) {
+  const size_t F1 = (size_t)n_filters + 1;
+  return ((F1 * sizeof(int64_t) + 255) & ~(size_t)255) + 256 +
+         kFilterTableBytes + 2 * ((F1 * sizeof(uint32_t) + 255) & ~(size_t)255);
+}
+FilterState lgssm_state(void* ws, int32_t n_filters) {
+  const size_t F1 = (size_t)n_filters + 1;
+  char* p = (char*)ws;
+  FilterState st;
+  st.offsets = (int64_t*)p;
+  p += (F1 * sizeof(int64_t) + 255) & ~(size_t)255;
+  st.done = (uint32_t*)p;
+  st.tables = p + 256;
+  p += 256 + kFilterTableBytes;
+  st.bstart = (uint32_t*)p;
+  st.estart = (uint32_t*)(p + ((F1 * sizeof(uint32_t) + 255) & ~(size_t)255));
+  return st;
 }
 
 size_t dtype_size(pfr_dtype dt) { return dt == PFR_F64 ? 8 : 4; }
@@ -584,7 +601,7 @@ size_t lgssm_workspace_bytes(int32_t n_filters, int32_t n) {
   const int64_t total = (int64_t)n_filters * n;
   const size_t perm = permute_workspace_bytes(total, (uint32_t)n_filters);
   const size_t seg = seg_layout(total, (uint32_t)n_filters, true).total;
-  return lgssm_offsets_bytes(n_filters) + (perm > seg ? perm : seg);
+  return lgssm_state_bytes(n_filters) + (perm > seg ? perm : seg);
 }
 
 int lgssm_init(const pfr_lgssm* model, int32_t n_filters, int32_t n, pfr_rng rng, float* x,
@@ -599,7 +616,7 @@ int lgssm_init(const pfr_lgssm* model, int32_t n_filters, int32_t n, pfr_rng rng
   key.offset_dev = nullptr;
   return launch_result(launch_lgssm_init(n_filters, n, model->s0, key, rng.offset,
                                          rng.filter_base, x, w, log_z, B_dev, t_dev,
-                                         (int64_t*)ws, (hipStream_t)stream));
+                                         lgssm_state(ws, n_filters), (hipStream_t)stream));
 }
 
 int lgssm_step(const pfr_lgssm* model, pfr_op scheme, pfr_precision precision, int32_t n_filters,
@@ -619,8 +636,9 @@ int lgssm_step(const pfr_lgssm* model, pfr_op scheme, pfr_precision precision, i
   const int64_t total = (int64_t)n_filters * n;
   if (overlaps(ancestors, (size_t)total * 4, permuted, (size_t)total * 4)) return PFR_EINVAL;
   const hipStream_t st = (hipStream_t)stream;
-  const int64_t* offsets = (const int64_t*)ws;
-  void* perm_ws = (char*)ws + lgssm_offsets_bytes(n_filters);
+  const FilterState state = lgssm_state(ws, n_filters);
+  const int64_t* offsets = state.offsets;
+  void* perm_ws = (char*)ws + lgssm_state_bytes(n_filters);
   // the resampler at step t uses counter offset t
   Key rkey = make_key(rng);
   rkey.offset_dev = t_dev;
@@ -642,7 +660,8 @@ int lgssm_step(const pfr_lgssm* model, pfr_op scheme, pfr_precision precision, i
       // the resampler's workspace is free again before the permutation uses it
       e = precision == PFR_SCAN_EXACT
               ? launch_scan_segmented(sch, false, w, total, offsets, nf, rkey, 0u,
-                                      rng.filter_base, ancestors, perm_ws, dev_flags, st)
+                                      rng.filter_base, ancestors, perm_ws, dev_flags, st,
+                                      state.bstart, state.estart)
               : launch_fscan_batched(sch, (int)precision, false, w, total, offsets, nf, rkey, 0u,
                                      rng.filter_base, ancestors, dev_flags, st);
     }
@@ -654,7 +673,7 @@ int lgssm_step(const pfr_lgssm* model, pfr_op scheme, pfr_precision precision, i
   Key nkey = make_key(rng);
   nkey.offset_dev = nullptr;
   return launch_result(launch_lgssm_move(n_filters, n, model->phi, model->q, model->r,
-                                         log(0.01), y, T, t_dev, nkey, rng.offset,
+                                         log(0.01), y, T, t_dev, state, nkey, rng.offset,
                                          rng.filter_base, permuted, x, w, log_z, B_dev, dev_flags,
                                          st));
 }

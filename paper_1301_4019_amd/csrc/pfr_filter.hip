@@ -24,37 +24,133 @@ namespace pfr {
 
 namespace {
 
-constexpr int kFT = 512;  // threads per filter workgroup
+// ---------------------------------------------------------------- functions
+// The move needs a logarithm, a square root, a cosine and an exponential per
+// particle in binary64; the general library functions (argument reduction for
+// any argument, special cases) were most of its time.  Here the arguments are
+// known: u1 = y 2^-32 with y a whole number in [1, 2^32], an angle that is a
+// whole number of 2^-32 turns, and a log-weight at most 0.  The errors are a
+// few units in the last place of binary64, as the library's.
+//   -log u1   y = m 2^e; a table of 128 intervals of m gives rc ~ 1 / m and
+//             -log rc, and log(m rc) is a short series in r = m rc - 1 (m from
+//             sqrt 2 up counts as m / 2, so that u1 near 1 keeps its relative
+//             precision: kk = 0, -log rc = 0)
+//   cos       a table of 256 angles and the addition theorem
+//   exp       2^k e^r, |r| <= ln 2 / 2, the exponential series to r^13 / 13!
+//             (below 2^-52 of the sum beyond)
+// lgssm_init forms the tables in the workspace; a workgroup copies them to LDS.
+constexpr int kLogBins = 128, kCosBins = 256;
+constexpr int kHalfBin = 53;  // m from 1 + 53/128 = 1.4140625 on
+constexpr double kLn2Hi = 0x1.62e42fefa3800p-1;   // ln 2 to 42 bits: times 0..32 exact
+constexpr double kLn2Lo = 0x1.ef35793c76730p-45;  // ln 2 - kLn2Hi
 
-__device__ __forceinline__ double normal_bm(uint32_t x0, uint32_t x1) {
-  const double u1 = ((double)x0 + 1.0) * 0x1p-32;
-  const double u2 = (double)x1 * 0x1p-32;
-  return sqrt(-2.0 * log(u1)) * cos(6.283185307179586 * u2);
+struct MathTables {
+  double2 lg[kLogBins];  // rc (times 1/2 where m counts as m / 2), -log rc
+  double2 cs[kCosBins];  // cosine and sine of 2 pi i / 256
+};
+
+__device__ __forceinline__ void fill_tables(MathTables* T, int tid, int threads) {
+  for (int i = tid; i < kCosBins; i += threads)
+    T->cs[i] = make_double2(cospi(i * (2.0 / kCosBins)), sinpi(i * (2.0 / kCosBins)));
+  for (int i = tid; i < kLogBins; i += threads) {
+    const bool half = i >= kHalfBin;
+    const double c = (1.0 + (i + 0.5) / kLogBins) * (half ? 0.5 : 1.0);
+    // the intervals at 1: rc = 1, so that log u1 = log(1 + r) there
+    const double rc = (i == 0 || i == kLogBins - 1) ? 1.0 : (double)(float)(1.0 / c);
+    T->lg[i] = make_double2(half ? 0.5 * rc : rc, rc == 1.0 ? 0.0 : -log(rc));
+  }
+}
+static_assert(sizeof(MathTables) == kFilterTableBytes, "table bytes of the filter state");
+__device__ __forceinline__ void load_tables(MathTables* T, const void* __restrict__ src, int tid,
+                                            int threads) {
+  for (int i = tid; i < (int)(sizeof(MathTables) / 16); i += threads)
+    reinterpret_cast<uint4*>(T)[i] = reinterpret_cast<const uint4*>(src)[i];
 }
 
-__device__ double block_max(double v, double* slot) {
+// -log((x + 1) 2^-32)
+__device__ __forceinline__ double neg_log_u1(uint32_t x, const MathTables* T) {
+  const uint64_t yb = (uint64_t)__double_as_longlong((double)x + 1.0);
+  const uint32_t hi = (uint32_t)(yb >> 32);
+  const uint32_t i = (hi >> 13) & (kLogBins - 1);
+  const double m = __longlong_as_double(
+      (long long)((yb & 0xFFFFFFFFFFFFFull) | 0x3FF0000000000000ull));
+  const int kk = 1023 + 32 - (int)(hi >> 20) - (i >= (uint32_t)kHalfBin ? 1 : 0);
+  const double2 t = T->lg[i];
+  const double r = __fma_rn(m, t.x, -1.0);  // |r| below 2^-7
+  double p = __fma_rn(r, 1.0 / 7.0, -1.0 / 6.0);
+  p = __fma_rn(p, r, 1.0 / 5.0);
+  p = __fma_rn(p, r, -1.0 / 4.0);
+  p = __fma_rn(p, r, 1.0 / 3.0);
+  p = __fma_rn(p, r, -1.0 / 2.0);
+  const double log1 = __fma_rn(p * r, r, r);  // log(1 + r)
+  const double kd = (double)kk;
+  return __fma_rn(kd, kLn2Hi, __fma_rn(kd, kLn2Lo, -t.y) - log1);
+}
+
+// Square root of t = 0 or 2^-40 < t < 2^10: the reciprocal square root
+// estimate, a coupled Newton step (Goldschmidt), then one on the root.
+__device__ __forceinline__ double sqrt_pos(double t) {
+  const double y = __builtin_amdgcn_rsq(t);
+  double g = t * y, h = 0.5 * y;
+  double d = __fma_rn(-h, g, 0.5);
+  g = __fma_rn(g, d, g);
+  h = __fma_rn(h, d, h);
+  d = __fma_rn(-g, g, t);
+  g = __fma_rn(d, h, g);
+  return t == 0.0 ? 0.0 : g;
+}
+
+// cos(2 pi x 2^-32)
+__device__ __forceinline__ double cos_turns(uint32_t x, const MathTables* T) {
+  const uint32_t v = x + 0x800000u;
+  const double2 t = T->cs[v >> 24];
+  const double d = (double)((int32_t)(v & 0xFFFFFFu) - 0x800000) * (6.283185307179586 * 0x1p-32);
+  const double z = d * d;
+  const double cm = z * __fma_rn(z, __fma_rn(z, -1.0 / 720.0, 1.0 / 24.0), -0.5);  // cos d - 1
+  const double s3 = __fma_rn(z, __fma_rn(z, -1.0 / 5040.0, 1.0 / 120.0), -1.0 / 6.0);
+  const double sn = __fma_rn(d * z, s3, d);
+  return __fma_rn(t.x, cm, __fma_rn(-t.y, sn, t.x));
+}
+
+// exp(x) for x <= 0 (NaN stays NaN)
+__device__ __forceinline__ double exp_neg(double x) {
+  x = x < -800.0 ? -800.0 : x;  // below -746 the result is 0
+  const double k = rint(x * 1.4426950408889634);
+  const double rh = __fma_rn(k, -kLn2Hi, x), rl = k * kLn2Lo;  // rh exact
+  const double r = rh - rl, rest = (rh - r) - rl;
+  double p = __fma_rn(r, 1.0 / 6227020800.0, 1.0 / 479001600.0);
+  p = __fma_rn(p, r, 1.0 / 39916800.0);
+  p = __fma_rn(p, r, 1.0 / 3628800.0);
+  p = __fma_rn(p, r, 1.0 / 362880.0);
+  p = __fma_rn(p, r, 1.0 / 40320.0);
+  p = __fma_rn(p, r, 1.0 / 5040.0);
+  p = __fma_rn(p, r, 1.0 / 720.0);
+  p = __fma_rn(p, r, 1.0 / 120.0);
+  p = __fma_rn(p, r, 1.0 / 24.0);
+  p = __fma_rn(p, r, 1.0 / 6.0);
+  p = __fma_rn(p, r, 0.5);
+  p = __fma_rn(p * r, r, rest);  // e^(r + rest) - 1 - r
+  return ldexp(1.0 + (r + p), (int)k);
+}
+
+__device__ __forceinline__ double normal_bm(uint32_t x0, uint32_t x1, const MathTables* T) {
+  return sqrt_pos(2.0 * neg_log_u1(x0, T)) * cos_turns(x1, T);
+}
+
+template <int THREADS, typename Op>
+__device__ double block_reduce(double v, double* slot, Op op) {
   const int wave = (int)threadIdx.x / kWave, lane = (int)threadIdx.x % kWave;
-  v = wave_reduce(v, OpMax());
+  v = wave_reduce(v, op);
   __syncthreads();
   if (lane == 0) slot[wave] = v;
   __syncthreads();
   double t = slot[0];
-  for (int w2 = 1; w2 < kFT / kWave; ++w2) t = t > slot[w2] ? t : slot[w2];
+  for (int w2 = 1; w2 < THREADS / kWave; ++w2) t = op(t, slot[w2]);
   __syncthreads();
   return t;
 }
 
-__device__ double block_sum(double v, double* slot) {
-  const int wave = (int)threadIdx.x / kWave, lane = (int)threadIdx.x % kWave;
-  v = wave_reduce(v, OpAdd());
-  __syncthreads();
-  if (lane == 0) slot[wave] = v;
-  __syncthreads();
-  double t = slot[0];
-  for (int w2 = 1; w2 < kFT / kWave; ++w2) t += slot[w2];
-  __syncthreads();
-  return t;
-}
+constexpr int kFT = 512;  // threads per workgroup of the initialisation
 
 __global__ __launch_bounds__(kFT) void k_lg_init(int32_t n_filters, int32_t n, double s0, Key key,
                                                  uint32_t offset, uint32_t filter_base,
@@ -62,22 +158,37 @@ __global__ __launch_bounds__(kFT) void k_lg_init(int32_t n_filters, int32_t n, d
                                                  double* __restrict__ logz,
                                                  int32_t* __restrict__ B_dev,
                                                  uint32_t* __restrict__ t_dev,
-                                                 int64_t* __restrict__ offsets) {
+                                                 int64_t* __restrict__ offsets,
+                                                 uint32_t* __restrict__ done,
+                                                 uint32_t* __restrict__ bstart,
+                                                 uint32_t* __restrict__ estart,
+                                                 MathTables* __restrict__ tables) {
+  __shared__ MathTables T;
+  fill_tables(&T, (int)threadIdx.x, kFT);
+  __syncthreads();
+  if (blockIdx.x == 0)
+    for (int i = (int)threadIdx.x; i < (int)(sizeof(MathTables) / 16); i += kFT)
+      reinterpret_cast<uint4*>(tables)[i] = reinterpret_cast<const uint4*>(&T)[i];
   const int64_t total = (int64_t)n_filters * n;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g < total; g += stride) {
     const int32_t f = (int32_t)(g / n), i = (int32_t)(g - (int64_t)f * n);
     const uint4 u = draw(key, (uint32_t)i, DOM_INIT, 0, filter_base + (uint32_t)f, offset);
-    x[g] = (float)(s0 * normal_bm(u.x, u.y));
+    x[g] = (float)(s0 * normal_bm(u.x, u.y, &T));
     w[g] = 1.0f;
   }
   for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g <= n_filters; g += stride) {
     offsets[g] = g * n;
+    bstart[g] = (uint32_t)(g * ((n + kBlock - 1) / kBlock));
+    estart[g] = (uint32_t)(g * ((n + 1 + kBlock - 1) / kBlock));
     if (g < n_filters) {
       logz[g] = 0.0;
       B_dev[g] = 1;
     }
-    if (g == 0) *t_dev = 1u;
+    if (g == 0) {
+      *t_dev = 1u;
+      *done = 0u;
+    }
   }
 }
 
@@ -87,50 +198,147 @@ __global__ __launch_bounds__(kFT) void k_lg_init(int32_t n_filters, int32_t n, d
 // inv_r = 1 / r in binary64: the scaled residual is (y - x) * inv_r, one
 // multiply where a division would cost a dozen VALU instructions (it may
 // differ from (y - x) / r in the last bit).
-__global__ __launch_bounds__(kFT) void k_lg_move(int32_t n, double phi, double q, double inv_r,
-                                                 double log_norm, double log_eps,
-                                                 const double* __restrict__ y, int32_t T,
-                                                 const uint32_t* __restrict__ t_dev, Key key,
-                                                 uint32_t offset, uint32_t filter_base,
-                                                 const int32_t* __restrict__ c,
-                                                 float* __restrict__ x, float* __restrict__ w,
-                                                 double* __restrict__ logz,
-                                                 int32_t* __restrict__ B_dev,
-                                                 uint32_t* __restrict__ flags) {
-  __shared__ double slot[kFT / kWave];
+// Filters of up to CAP particles keep their new states in LDS until the
+// largest log-weight is known: the states are gathered from x, all of them
+// before any is written, so the copy needs no pass of its own, and x is read
+// and written once.  Longer filters (CAP = 0) copy first and go through x
+// twice.  A thread takes quads of consecutive particles.  Every workgroup
+// counts itself once it has read t; the last one advances it.  VALU bound
+// (about 150 instructions a particle, a Philox call among them): 1024 filters of
+// 16384 188 -> 99 us (library functions, three passes over x).
+typedef float QuadF __attribute__((ext_vector_type(4), aligned(4)));
+typedef int32_t QuadI __attribute__((ext_vector_type(4), aligned(4)));
+
+template <int CAP, int THREADS>
+__global__ __launch_bounds__(THREADS) void k_lg_move(int32_t n, double phi, double q,
+                                                     double inv_r, double log_norm,
+                                                     double log_eps,
+                                                     const double* __restrict__ y, int32_t T,
+                                                     uint32_t* __restrict__ t_dev,
+                                                     uint32_t* __restrict__ done,
+                                                     const void* __restrict__ tables, Key key,
+                                                     uint32_t offset, uint32_t filter_base,
+                                                     const int32_t* __restrict__ c,
+                                                     float* __restrict__ x,
+                                                     float* __restrict__ w,
+                                                     double* __restrict__ logz,
+                                                     int32_t* __restrict__ B_dev,
+                                                     uint32_t* __restrict__ flags) {
+  __shared__ MathTables tab;
+  __shared__ double slot[THREADS / kWave];
+  __shared__ __align__(16) float xs[CAP > 0 ? CAP : 4];
   const uint32_t f = blockIdx.x;
   const int64_t base = (int64_t)f * n;
   const uint32_t t = *t_dev;
+  const int tid = (int)threadIdx.x;
+  __syncthreads();  // every thread has read t
+  if (tid == 0 && atomicAdd(done, 1u) == gridDim.x - 1u) {
+    *done = 0u;
+    *t_dev = t + 1u;
+  }
   if (t < 1u || t > (uint32_t)T) {  // no observation for this step
-    if (flags && f == 0 && threadIdx.x == 0) atomicOr(flags, FLAG_BAD_STEP);
+    if (flags && f == 0 && tid == 0) atomicOr(flags, FLAG_BAD_STEP);
     return;
   }
   const double yt = y[t - 1];
-  const int tid = (int)threadIdx.x;
-  // in-place copy: slots that are read satisfy c_j = j and are never written
-  for (int32_t i = tid; i < n; i += kFT) {
-    const int32_t ci = c[base + i];
-    if (ci != i) x[base + i] = x[base + ci];
+  const int32_t* __restrict__ cf = c + base;
+  float* __restrict__ xf = x + base;
+  float* __restrict__ wf = w + base;
+  const int32_t nq = (n + 3) / 4;
+  load_tables(&tab, tables, tid, THREADS);
+  if (CAP == 0) {
+    // in-place copy: slots that are read satisfy c_j = j and are never written
+    for (int32_t i = tid; i < n; i += THREADS) {
+      const int32_t ci = cf[i];
+      if (ci != i) xf[i] = xf[ci];
+    }
   }
   __syncthreads();
-  double mx = -__builtin_huge_val();
-  for (int32_t i = tid; i < n; i += kFT) {
-    const uint4 u = draw(key, (uint32_t)i, DOM_NOISE, t, filter_base + f, offset);
-    const float xn = (float)(phi * (double)x[base + i] + q * normal_bm(u.x, u.y));
-    x[base + i] = xn;
+  // the squared scaled residual d^2; the log-weight is -d^2 / 2 + log_norm, so
+  // the smallest d^2 gives the largest one, and lw - max lw = (min d^2 - d^2) / 2
+  auto residual2 = [&](float xn) -> double {
     const double d = (yt - (double)xn) * inv_r;
-    const double lw = -0.5 * d * d + log_norm;
-    mx = lw > mx ? lw : mx;
+    return d * d;
+  };
+  double least = __builtin_huge_val();
+  for (int32_t qd = tid; qd < nq; qd += THREADS) {
+    const int32_t i0 = 4 * qd;
+    const bool whole = i0 + 4 <= n;
+    float xo[4];
+    if (CAP > 0) {
+      int32_t ci[4];
+      if (whole) {
+        const QuadI v = *reinterpret_cast<const QuadI*>(cf + i0);
+        ci[0] = v.x; ci[1] = v.y; ci[2] = v.z; ci[3] = v.w;
+      } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) ci[k] = i0 + k < n ? cf[i0 + k] : 0;
+      }
+#pragma unroll
+      for (int k = 0; k < 4; ++k) xo[k] = xf[ci[k]];
+    } else {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) xo[k] = i0 + k < n ? xf[i0 + k] : 0.0f;
+    }
+    float xn[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const uint4 u = draw(key, (uint32_t)(i0 + k), DOM_NOISE, t, filter_base + f, offset);
+      xn[k] = (float)(phi * (double)xo[k] + q * normal_bm(u.x, u.y, &tab));
+    }
+    if (!whole) {  // past the end: an infinite residual, weight 0
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (i0 + k >= n) xn[k] = __builtin_huge_valf();
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) least = fmin(least, residual2(xn[k]));
+    if (CAP > 0) {
+      *reinterpret_cast<float4*>(xs + i0) = make_float4(xn[0], xn[1], xn[2], xn[3]);
+    } else {
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (i0 + k < n) xf[i0 + k] = xn[k];
+    }
   }
-  mx = block_max(mx, slot);
+  least = block_reduce<THREADS>(least, slot, OpMin());  // (its barriers: all states were read)
+  const double mx = -0.5 * least + log_norm;
   double sum = 0.0;
-  for (int32_t i = tid; i < n; i += kFT) {
-    const double d = (yt - (double)x[base + i]) * inv_r;
-    const double e = exp((-0.5 * d * d + log_norm) - mx);
-    w[base + i] = (float)e;
-    sum += e;
+  for (int32_t qd = tid; qd < nq; qd += THREADS) {
+    const int32_t i0 = 4 * qd;
+    float xn[4], wn[4];
+    if (CAP > 0) {
+      const float4 v = *reinterpret_cast<const float4*>(xs + i0);
+      xn[0] = v.x; xn[1] = v.y; xn[2] = v.z; xn[3] = v.w;
+    } else {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) xn[k] = i0 + k < n ? xf[i0 + k] : __builtin_huge_valf();
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const double e = exp_neg(__fma_rn(-0.5, residual2(xn[k]), 0.5 * least));
+      wn[k] = (float)e;
+      sum += e;
+    }
+    if (i0 + 4 <= n) {
+      QuadF v;
+      v.x = wn[0]; v.y = wn[1]; v.z = wn[2]; v.w = wn[3];
+      *reinterpret_cast<QuadF*>(wf + i0) = v;
+      if (CAP > 0) {
+        v.x = xn[0]; v.y = xn[1]; v.z = xn[2]; v.w = xn[3];
+        *reinterpret_cast<QuadF*>(xf + i0) = v;
+      }
+    } else {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        if (i0 + k < n) {
+          wf[i0 + k] = wn[k];
+          if (CAP > 0) xf[i0 + k] = xn[k];
+        }
+      }
+    }
   }
-  sum = block_sum(sum, slot);
+  sum = block_reduce<THREADS>(sum, slot, OpAdd());
   if (tid == 0) {
     const double beta = sum / (double)n;
     logz[f] += mx + log(beta);
@@ -140,37 +348,39 @@ __global__ __launch_bounds__(kFT) void k_lg_move(int32_t n, double phi, double q
   }
 }
 
-__global__ void k_lg_tick(uint32_t* __restrict__ t_dev) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) *t_dev += 1u;
-}
-
 }  // namespace
 
 hipError_t launch_lgssm_init(int32_t n_filters, int32_t n, double s0, Key key, uint32_t offset,
                              uint32_t filter_base, float* x, float* w, double* logz,
-                             int32_t* B_dev, uint32_t* t_dev, int64_t* offsets,
+                             int32_t* B_dev, uint32_t* t_dev, const FilterState& st,
                              hipStream_t stream) {
   const int64_t total = (int64_t)n_filters * n;
   int64_t grid = (total + kFT - 1) / kFT;
   if (grid < 1) grid = 1;
-  if (grid > 65536) grid = 65536;
+  if (grid > 2048) grid = 2048;  // each workgroup forms the tables first
   hipLaunchKernelGGL(k_lg_init, dim3((uint32_t)grid), dim3(kFT), 0, stream, n_filters, n, s0, key,
-                     offset, filter_base, x, w, logz, B_dev, t_dev, offsets);
+                     offset, filter_base, x, w, logz, B_dev, t_dev, st.offsets, st.done,
+                     st.bstart, st.estart, (MathTables*)st.tables);
   return hipGetLastError();
 }
 
 hipError_t launch_lgssm_move(int32_t n_filters, int32_t n, double phi, double q, double r,
                              double log_eps, const double* y, int32_t T, uint32_t* t_dev,
-                             Key key, uint32_t offset, uint32_t filter_base, const int32_t* c,
-                             float* x, float* w, double* logz, int32_t* B_dev, uint32_t* flags,
-                             hipStream_t stream) {
+                             const FilterState& st, Key key, uint32_t offset,
+                             uint32_t filter_base, const int32_t* c, float* x, float* w,
+                             double* logz, int32_t* B_dev, uint32_t* flags, hipStream_t stream) {
   const double log_norm = -log(r) - 0.5 * log(6.283185307179586);
-  hipLaunchKernelGGL(k_lg_move, dim3((uint32_t)n_filters), dim3(kFT), 0, stream, n, phi, q,
-                     1.0 / r, log_norm, log_eps, y, T, t_dev, key, offset, filter_base, c, x, w,
-                     logz, B_dev, flags);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_lg_tick, dim3(1), dim3(64), 0, stream, t_dev);
+  auto launch = [&](auto kernel, int threads) {
+    hipLaunchKernelGGL(kernel, dim3((uint32_t)n_filters), dim3(threads), 0, stream, n, phi, q,
+                       1.0 / r, log_norm, log_eps, y, T, t_dev, st.done, st.tables, key, offset,
+                       filter_base,
+                       c, x, w, logz, B_dev, flags);
+  };
+  // by LDS: eleven, two and one workgroups to a CU, and filters too long for it
+  if (n <= 2048) launch(k_lg_move<2048, 256>, 256);
+  else if (n <= 16384) launch(k_lg_move<16384, 1024>, 1024);
+  else if (n <= 32768) launch(k_lg_move<32768, 1024>, 1024);
+  else launch(k_lg_move<0, 1024>, 1024);
   return hipGetLastError();
 }
 

@@ -76,7 +76,8 @@ SegLayout seg_layout(int64_t n_total, uint32_t n_filters, bool multinomial);
 hipError_t launch_scan_segmented(int scheme, bool f64, const void* w, int64_t n_total,
                                  const int64_t* offsets, uint32_t n_filters, Key key,
                                  uint32_t offset, uint32_t filter_base, int32_t* a, void* ws,
-                                 uint32_t* flags, hipStream_t stream);
+                                 uint32_t* flags, hipStream_t stream,
+                                 uint32_t* bstart = nullptr, uint32_t* estart = nullptr);
 size_t batch_scan_lds_bytes();
 
 hipError_t launch_scan(int scheme, bool f64, const void* w, int64_t n, Key key, uint32_t offset,
@@ -173,15 +174,25 @@ hipError_t launch_prc_weights(bool f64, const void* w, int64_t n_total, const in
                               uint32_t n_filters, double v_max, const double* v_max_dev,
                               const int32_t* a, void* w_out, hipStream_t stream);
 
+// What a filter keeps in its workspace from one step to the next, written by
+// lgssm_init: segment offsets, the block prefixes of the collective schemes
+// (bstart, estart: n_filters + 1 each), the move's count of workgroups and its
+// function tables.
+constexpr size_t kFilterTableBytes = 6144;
+struct FilterState {
+  int64_t* offsets;
+  uint32_t *done, *bstart, *estart;
+  void* tables;
+};
 hipError_t launch_lgssm_init(int32_t n_filters, int32_t n, double s0, Key key, uint32_t offset,
                              uint32_t filter_base, float* x, float* w, double* logz,
-                             int32_t* B_dev, uint32_t* t_dev, int64_t* offsets,
+                             int32_t* B_dev, uint32_t* t_dev, const FilterState& st,
                              hipStream_t stream);
 hipError_t launch_lgssm_move(int32_t n_filters, int32_t n, double phi, double q, double r,
                              double log_eps, const double* y, int32_t T, uint32_t* t_dev,
-                             Key key, uint32_t offset, uint32_t filter_base, const int32_t* c,
-                             float* x, float* w, double* logz, int32_t* B_dev, uint32_t* flags,
-                             hipStream_t stream);
+                             const FilterState& st, Key key, uint32_t offset,
+                             uint32_t filter_base, const int32_t* c, float* x, float* w,
+                             double* logz, int32_t* B_dev, uint32_t* flags, hipStream_t stream);
 
 hipError_t launch_zero_u32(uint32_t* p, size_t count, hipStream_t stream);
 

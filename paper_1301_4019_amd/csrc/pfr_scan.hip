@@ -1638,19 +1638,23 @@ hipError_t launch_batched_scheme(int scheme, const void* w, int64_t n_total,
 template <typename T, int SCHEME>
 hipError_t launch_segmented_t(const T* w, int64_t n_total, const int64_t* offsets,
                               uint32_t n_filters, Key key, uint32_t offset, uint32_t filter_base,
-                              int32_t* a, void* ws, uint32_t* flags, hipStream_t stream) {
+                              int32_t* a, void* ws, uint32_t* flags, uint32_t* bstart,
+                              uint32_t* estart, hipStream_t stream) {
   constexpr bool multi = SCHEME == SCHEME_MULTINOMIAL;
   const SegLayout L = seg_layout(n_total, n_filters, multi);
   char* base = (char*)ws;
-  uint32_t* bstart = (uint32_t*)(base + L.bstart);
-  uint32_t* estart = multi ? (uint32_t*)(base + L.estart) : nullptr;
   BlockRec* recs = (BlockRec*)(base + L.recs);
   uint64_t* esums = (uint64_t*)(base + L.esums);
   uint64_t* evals = multi ? (uint64_t*)(base + L.evals) : nullptr;
-  hipLaunchKernelGGL(k_seg_prefix, dim3(1), dim3(kT), 0, stream, offsets, n_filters, bstart,
-                     estart);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  hipError_t e = hipSuccess;
+  if (!bstart) {  // (else the caller keeps the block prefixes)
+    bstart = (uint32_t*)(base + L.bstart);
+    estart = multi ? (uint32_t*)(base + L.estart) : nullptr;
+    hipLaunchKernelGGL(k_seg_prefix, dim3(1), dim3(kT), 0, stream, offsets, n_filters, bstart,
+                       estart);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
   const uint32_t wgs_b = (L.grid_b + kWavesPerWG - 1) / kWavesPerWG;
   if constexpr (multi)
     hipLaunchKernelGGL((k_seg_records<T, multi>), dim3(L.grid_b + L.grid_e), dim3(kT), 0, stream,
@@ -1682,18 +1686,22 @@ template <typename T>
 hipError_t launch_segmented_scheme(int scheme, const void* w, int64_t n_total,
                                    const int64_t* offsets, uint32_t n_filters, Key key,
                                    uint32_t offset, uint32_t filter_base, int32_t* a, void* ws,
-                                   uint32_t* flags, hipStream_t stream) {
+                                   uint32_t* flags, uint32_t* bstart, uint32_t* estart,
+                                   hipStream_t stream) {
   const T* wt = (const T*)w;
   switch (scheme) {
     case SCHEME_MULTINOMIAL:
       return launch_segmented_t<T, SCHEME_MULTINOMIAL>(wt, n_total, offsets, n_filters, key,
-                                                       offset, filter_base, a, ws, flags, stream);
+                                                       offset, filter_base, a, ws, flags, bstart,
+                                                       estart, stream);
     case SCHEME_STRATIFIED:
       return launch_segmented_t<T, SCHEME_STRATIFIED>(wt, n_total, offsets, n_filters, key,
-                                                      offset, filter_base, a, ws, flags, stream);
+                                                      offset, filter_base, a, ws, flags, bstart,
+                                                       estart, stream);
     default:
       return launch_segmented_t<T, SCHEME_SYSTEMATIC>(wt, n_total, offsets, n_filters, key,
-                                                      offset, filter_base, a, ws, flags, stream);
+                                                      offset, filter_base, a, ws, flags, bstart,
+                                                       estart, stream);
   }
 }
 
@@ -1720,11 +1728,14 @@ SegLayout seg_layout(int64_t n_total, uint32_t n_filters, bool multinomial) {
 hipError_t launch_scan_segmented(int scheme, bool f64, const void* w, int64_t n_total,
                                  const int64_t* offsets, uint32_t n_filters, Key key,
                                  uint32_t offset, uint32_t filter_base, int32_t* a, void* ws,
-                                 uint32_t* flags, hipStream_t stream) {
+                                 uint32_t* flags, hipStream_t stream, uint32_t* bstart,
+                                 uint32_t* estart) {
   return f64 ? launch_segmented_scheme<double>(scheme, w, n_total, offsets, n_filters, key,
-                                               offset, filter_base, a, ws, flags, stream)
+                                               offset, filter_base, a, ws, flags, bstart, estart,
+                                               stream)
              : launch_segmented_scheme<float>(scheme, w, n_total, offsets, n_filters, key,
-                                              offset, filter_base, a, ws, flags, stream);
+                                              offset, filter_base, a, ws, flags, bstart, estart,
+                                               stream);
 }
 
 ScanLayout scan_layout(int64_t n, bool multinomial) {
