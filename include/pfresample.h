@@ -283,8 +283,8 @@ PFR_API size_t pfr_resample_permuted_workspace_bytes(pfr_op scheme, const pfr_se
  * followed by permute_ancestors (sorted_hint set for the collective schemes)
  * would write, with the same flags.  For a long single vector of an exact
  * collective scheme (multinomial, stratified, systematic: sorted ancestries)
- * the emission writes the claim vector and the marked ancestry itself, so
- * only the resolve pass follows; the other
+ * the emission writes the claimed slots itself, so only the resolve pass
+ * follows; the other
  * cases run the two steps one after the other (claiming inside Metropolis and
  * rejection, with atomics beside their random weight loads, measured slower
  * than the separate claim pass on MI355X). */
@@ -446,7 +446,8 @@ typedef struct {
     int32_t batch_scan_wg_max_len;  /* collective, exact prefix: a batch whose longest segment is
                                        at most this runs one workgroup per segment even with a
                                        workspace, longer ones block-parallel
-                                       [0, PFR_MAX_BATCH_SEGMENT] */
+                                       [0, PFR_MAX_BATCH_SEGMENT]; the stratified and systematic
+                                       schemes do so up to 16384 in any case */
     int32_t batch_stage_max_kb;     /* Metropolis / rejection: largest LDS tier for staging a
                                        segment's weights (16, 64 or 128 KB); longer segments
                                        gather from global memory in the same launch */

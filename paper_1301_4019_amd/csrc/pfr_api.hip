@@ -5,6 +5,7 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <algorithm>
 #include <atomic>
 #include <mutex>
 
@@ -18,7 +19,7 @@ namespace {
 // access holds the lock, and readers get a copy.
 std::mutex g_tuning_mu;
 // the values the autotuner chose on MI355X (gfx950), also in tuning.json
-Tuning g_tuning = {4096, 256, 60, 1, 256, 2048, 0, 128, 8192, 1024, 16384};
+Tuning g_tuning = {4096, 1024, 60, 1, 256, 2048, 0, 128, 8192, 1024, 16384};
 }  // namespace
 
 Tuning tuning() {
@@ -140,8 +141,12 @@ int collective(int scheme, const void* w, pfr_dtype dtype, const pfr_segments* s
     // a batch with a workspace runs block-parallel, without one (or when
     // its longest segment is short) in one workgroup per segment; the
     // results are the same
-    if (s.n_filters > 1 && ws &&
-        !(s.max_len > 0 && s.max_len <= tuning().batch_scan_wg_max_len)) {
+    // (short segments of the strata schemes always: one launch that reads the
+    // weights once, 65536 segments of 256 186 against 535 us)
+    const int64_t one_wg = scheme == SCHEME_MULTINOMIAL
+                               ? tuning().batch_scan_wg_max_len
+                               : std::max<int64_t>(kOneWgMax, tuning().batch_scan_wg_max_len);
+    if (s.n_filters > 1 && ws && !(s.max_len > 0 && s.max_len <= one_wg)) {
       const SegLayout SL = seg_layout(s.n_total, s.n_filters, scheme == SCHEME_MULTINOMIAL);
       if (ws_bytes < SL.total || !aligned256(ws)) return PFR_EWORKSPACE;
       if (overlaps(ws, SL.total, a, (size_t)s.n_total * 4)) return PFR_EINVAL;
@@ -150,8 +155,8 @@ int collective(int scheme, const void* w, pfr_dtype dtype, const pfr_segments* s
                                                  rng.filter_base, a, ws, dev_flags, st));
     }
     return launch_result(launch_scan_batched(scheme, dtype == PFR_F64, w, s.n_total, s.offsets,
-                                             s.n_filters, key, rng.offset, rng.filter_base, a,
-                                             dev_flags, st));
+                                             s.n_filters, s.max_len, key, rng.offset,
+                                             rng.filter_base, a, dev_flags, st));
   }
   const ScanLayout L = scan_layout(s.n_total, scheme == SCHEME_MULTINOMIAL);
   if (!ws || ws_bytes < L.total) return PFR_EWORKSPACE;
@@ -567,9 +572,10 @@ int resample_permuted(pfr_op scheme, const void* w, pfr_dtype dtype, const pfr_s
                                                                          : SCHEME_SYSTEMATIC,
                                            dtype == PFR_F64, w, s.n_total, make_key(rng),
                                            rng.offset, rng.filter_base, ancestors, rws, dev_flags,
-                                           permute_claims(ws), permute_marks(ws, s.n_total), st));
+                                           (uint32_t*)ws, st));
     if (rc) return rc;
-    return launch_result(launch_resolve(s.n_total, permuted, ws, dev_flags, st));
+    return launch_result(
+        launch_resolve_sorted(ancestors, s.n_total, (const uint32_t*)ws, permuted, st));
   }
   // the two steps one after the other
   switch (scheme) {
@@ -658,7 +664,10 @@ int lgssm_step(const pfr_lgssm* model, pfr_op scheme, pfr_precision precision, i
                       : scheme == PFR_OP_STRATIFIED ? SCHEME_STRATIFIED
                                                     : SCHEME_SYSTEMATIC;
       // the resampler's workspace is free again before the permutation uses it
-      e = precision == PFR_SCAN_EXACT
+      e = precision == PFR_SCAN_EXACT && n <= kOneWgMax && sch != SCHEME_MULTINOMIAL
+              ? launch_scan_batched(sch, false, w, total, offsets, nf, n, rkey, 0u,
+                                    rng.filter_base, ancestors, dev_flags, st)
+          : precision == PFR_SCAN_EXACT
               ? launch_scan_segmented(sch, false, w, total, offsets, nf, rkey, 0u,
                                       rng.filter_base, ancestors, perm_ws, dev_flags, st,
                                       state.bstart, state.estart)
@@ -682,7 +691,7 @@ void pfr_tuning_defaults(pfr_tuning* t) {
   if (!t) return;
   t->version = PFR_TUNING_VERSION;
   t->single_wg_max = 4096;
-  t->direct_max_blocks = 256;
+  t->direct_max_blocks = 1024;
   t->metropolis_table_min_B = 60;
   t->rejection_table = 1;
   t->rejection_per_wave = 256;

@@ -1155,6 +1155,128 @@ __global__ __launch_bounds__(kClaimThreads) void k_bucket_claim(
   }
 }
 
+// ---------------------------------------------------------------- resolve, sorted ancestry
+// The walk of k_resolve on a sorted ancestry itself, with one bit per slot for
+// the claims: position y won its claim when it starts its run (a_y != a_{y-1},
+// two neighbouring words), so neither the claim vector nor the marked ancestry
+// is written and read.  A chain moves by the ancestry's drift, of the order of
+// sqrt(n), per step.  Up to kWindowMax particles a workgroup therefore holds
+// the ancestry around its tile of slots in LDS, where most chains stay (a step
+// costs an LDS read instead of one beyond the L2): kWinSteps steps for the four
+// chains of a quad together, then the longer ones from a list, one a lane.
+// Chains that leave the window go on in global memory, as do all of them in
+// longer vectors.
+constexpr int kWinThreads = 512;
+constexpr uint32_t kWinTile = 4 * kWinThreads;     // slots
+constexpr uint32_t kWinHalo = 3072;                // positions on either side
+constexpr uint32_t kWinSpan = kWinTile + 2 * kWinHalo;
+constexpr int kWinSteps = 8;
+constexpr uint32_t kWinSlow = 1024;                // entries of the list
+constexpr int64_t kWindowMax = 1 << 21;
+constexpr uint32_t kWon = 0x80000000u;
+
+// a_y with the winner bit, from global memory
+__device__ __forceinline__ uint32_t marked_at(const int32_t* __restrict__ a, uint32_t y) {
+  const uint32_t v = (uint32_t)a[y];
+  const uint32_t p = y > 0 ? (uint32_t)a[y - 1] : 0xFFFFFFFFu;
+  return v != p ? v | kWon : v;
+}
+
+__global__ __launch_bounds__(kWinThreads) void k_resolve_window(const int32_t* __restrict__ a,
+                                                                uint32_t n,
+                                                                const uint32_t* __restrict__ claim,
+                                                                int32_t* __restrict__ c) {
+  __shared__ __align__(16) uint32_t win[kWinSpan];
+  __shared__ uint2 slow[kWinSlow];
+  __shared__ uint32_t n_slow;
+  const uint32_t tid = threadIdx.x, lane = lane_id();
+  const uint32_t t0 = blockIdx.x * kWinTile;
+  const uint32_t lo = t0 > kWinHalo ? t0 - kWinHalo : 0u;
+  const uint32_t hi = min(n, t0 + kWinTile + kWinHalo), span = hi - lo;
+  if (tid == 0) n_slow = 0;
+  const uint32_t j = t0 + 4 * tid;
+  const uint32_t cl = j < n ? (claim[j >> 5] >> (j & 31u)) & 15u : 0u;
+#pragma unroll
+  for (uint32_t r = 0; r < kWinSpan / kWinTile; ++r) {
+    const uint32_t q = r * kWinThreads + tid;  // whole waves: the shift below reads lane - 1
+    int32_t x[4];
+    load_quad(a + lo, q, span, x);
+    uint32_t first = 0xFFFFFFFFu;
+    if (lane == 0 && lo + 4 * q > 0 && 4 * q < span) first = (uint32_t)a[lo + 4 * q - 1];
+    uint32_t prev = wave_shift_up_u32((uint32_t)x[3], first);
+    uint32_t m[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      m[k] = (uint32_t)x[k] != prev ? (uint32_t)x[k] | kWon : (uint32_t)x[k];
+      prev = (uint32_t)x[k];
+    }
+    reinterpret_cast<uint4*>(win)[q] = make_uint4(m[0], m[1], m[2], m[3]);
+  }
+  __syncthreads();
+  // the end of the chain that goes on at position y
+  auto walk = [&](uint32_t y) -> uint32_t {
+    while (true) {
+      const uint32_t m = y - lo < span ? win[y - lo] : marked_at(a, y);
+      if (!(m & kWon)) return m;
+      y = m & ~kWon;
+    }
+  };
+  if (j < n) {
+    const uint4 t = reinterpret_cast<const uint4*>(win)[(j - lo) / 4];
+    uint32_t y[4] = {t.x, t.y, t.z, t.w};
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if ((cl >> k) & 1u || j + k >= n) y[k] = j + k;
+    for (int s = 0; s < kWinSteps && ((y[0] | y[1] | y[2] | y[3]) & kWon); ++s) {
+      uint32_t z[4];
+      bool in[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const uint32_t i = (y[k] & ~kWon) - lo;
+        in[k] = (y[k] & kWon) && i < span;
+        z[k] = win[in[k] ? i : 0u];
+      }
+#pragma unroll
+      for (int k = 0; k < 4; ++k) y[k] = in[k] ? z[k] : y[k];
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if (y[k] & kWon) {
+        const uint32_t at = atomicAdd(&n_slow, 1u);
+        if (at < kWinSlow) slow[at] = make_uint2(j + k, y[k] & ~kWon);
+        else y[k] = walk(y[k] & ~kWon);
+      }
+    }
+    if (j + 4 <= n) {
+      Quad o;
+      o.x = (int32_t)y[0]; o.y = (int32_t)y[1]; o.z = (int32_t)y[2]; o.w = (int32_t)y[3];
+      *reinterpret_cast<Quad*>(c + j) = o;
+    } else {
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (j + k < n) c[j + k] = (int32_t)y[k];
+    }
+  }
+  __syncthreads();  // also orders the chains' slots after the quads stored above
+  const uint32_t ns = min(n_slow, kWinSlow);
+  for (uint32_t t = tid; t < ns; t += kWinThreads) {
+    const uint2 e = slow[t];
+    c[e.x] = (int32_t)walk(e.y);
+  }
+}
+
+__global__ __launch_bounds__(256) void k_resolve_sorted(const int32_t* __restrict__ a, int64_t n,
+                                                        const uint32_t* __restrict__ claim,
+                                                        int32_t* __restrict__ c) {
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < n; j += stride) {
+    uint32_t m = marked_at(a, (uint32_t)j);  // in flight with the claim word
+    if ((claim[j >> 5] >> (j & 31)) & 1u) m = (uint32_t)j;
+    while (m & kWon) m = marked_at(a, m & ~kWon);
+    c[j] = (int32_t)m;
+  }
+}
+
 int grid_for(int64_t n) {
   int64_t b = (n + 255) / 256;
   if (b > 65536) b = 65536;
@@ -1298,16 +1420,15 @@ hipError_t launch_permute(const int32_t* a, int64_t n_total, const int64_t* offs
   return hipGetLastError();
 }
 
-int32_t* permute_claims(void* ws) { return (int32_t*)ws; }
-int32_t* permute_marks(void* ws, int64_t n_total) {
-  return (int32_t*)((char*)ws + align256((size_t)n_total * sizeof(int32_t)));
-}
-
-hipError_t launch_resolve(int64_t n_total, int32_t* c, void* ws, uint32_t* flags,
-                          hipStream_t stream) {
-  hipLaunchKernelGGL(k_resolve, dim3(grid_for(n_total)), dim3(256), 0, stream, n_total,
-                     (const int64_t*)nullptr, 1u, (int64_t)0, permute_claims(ws),
-                     permute_marks(ws, n_total), c, flags);
+// The permutation workspace is at least 8 bytes per particle: room for the
+// bits of whole blocks from 1025 particles on.
+hipError_t launch_resolve_sorted(const int32_t* a, int64_t n, const uint32_t* claim, int32_t* c,
+                                 hipStream_t stream) {
+  if (n <= kWindowMax)
+    hipLaunchKernelGGL(k_resolve_window, dim3((unsigned)((n + kWinTile - 1) / kWinTile)),
+                       dim3(kWinThreads), 0, stream, a, (uint32_t)n, claim, c);
+  else
+    hipLaunchKernelGGL(k_resolve_sorted, dim3(grid_for(n)), dim3(256), 0, stream, a, n, claim, c);
   return hipGetLastError();
 }
 

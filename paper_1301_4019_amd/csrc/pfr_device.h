@@ -346,6 +346,16 @@ __device__ __forceinline__ int32_t wave_incl_max_i32(int32_t x) {
   x = max(x, (int32_t)dpp_u32<kDppBcast31, 0xC>(m1, (uint32_t)x));
   return x;
 }
+// Largest / or of unsigned values over the wave, the same on every lane.
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t x) {
+  x = max(x, dpp_u32<kDppShr1>(0u, x));
+  x = max(x, dpp_u32<kDppShr2>(0u, x));
+  x = max(x, dpp_u32<kDppShr4>(0u, x));
+  x = max(x, dpp_u32<kDppShr8>(0u, x));
+  x = max(x, dpp_u32<kDppBcast15, 0xA>(0u, x));
+  x = max(x, dpp_u32<kDppBcast31, 0xC>(0u, x));
+  return readlane_u32(x, kWave - 1);
+}
 // The value of the previous lane (lane 0 gets `first`).
 __device__ __forceinline__ uint32_t wave_shift_up_u32(uint32_t v, uint32_t first) {
   return dpp_u32<kDppWaveShr1>(first, v);

@@ -84,9 +84,11 @@ hipError_t launch_scan(int scheme, bool f64, const void* w, int64_t n, Key key, 
                        uint32_t filter, int32_t* a, void* ws, uint32_t* flags,
                        hipStream_t stream);
 hipError_t launch_scan_batched(int scheme, bool f64, const void* w, int64_t n_total,
-                               const int64_t* offsets, uint32_t n_filters, Key key,
-                               uint32_t offset, uint32_t filter_base, int32_t* a, uint32_t* flags,
-                               hipStream_t stream);
+                               const int64_t* offsets, uint32_t n_filters, int64_t max_len,
+                               Key key, uint32_t offset, uint32_t filter_base, int32_t* a,
+                               uint32_t* flags, hipStream_t stream);
+// Longest segment that the strata schemes resample in one workgroup and launch.
+constexpr int64_t kOneWgMax = 16384;
 
 // Code 5 with independent uniforms (single vectors, exact prefix).
 size_t multinomial_iid_workspace_bytes(int64_t n);
@@ -131,17 +133,14 @@ hipError_t launch_offspring_to_ancestors(const int32_t* o, int64_t n_total, cons
                                          uint32_t* flags, hipStream_t stream);
 size_t permute_workspace_bytes(int64_t n_total, uint32_t n_filters);
 size_t permute_workspace_min_bytes(int64_t n_total);
-// The rest of Code 10 after an emission that wrote the claim vector and the
-// marked ancestry itself (launch_scan_claimed): the resolve pass over a
-// single vector.  permute_claims / permute_marks locate d and e in a
-// permutation workspace.
-int32_t* permute_claims(void* ws);
-int32_t* permute_marks(void* ws, int64_t n_total);
-hipError_t launch_resolve(int64_t n_total, int32_t* c, void* ws, uint32_t* flags,
-                          hipStream_t stream);
+// The rest of Code 10 after an emission that wrote the claimed slots itself,
+// a bit per particle (launch_scan_claimed; whole blocks of 1024 bits): the
+// resolve pass over the sorted ancestry of a single vector.
+hipError_t launch_resolve_sorted(const int32_t* a, int64_t n, const uint32_t* claim, int32_t* c,
+                                 hipStream_t stream);
 hipError_t launch_scan_claimed(int scheme, bool f64, const void* w, int64_t n, Key key,
                                uint32_t offset, uint32_t filter, int32_t* a, void* ws,
-                               uint32_t* flags, int32_t* d, int32_t* e, hipStream_t stream);
+                               uint32_t* flags, uint32_t* claim, hipStream_t stream);
 // Precondition checks (pfr_check.hip): OR violations into flags (may be null)
 // and into the library's per-GPU check word; take_check_word waits for the
 // stream, returns the word and clears it.

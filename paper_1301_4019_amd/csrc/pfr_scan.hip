@@ -20,28 +20,29 @@
 // rounding is the final map r = n * I / I_total to binary64, itself monotone
 // with r = n at the end.
 //
-// One vector: one wave handles one block, 16 consecutive weights per lane
-// (four 16-byte loads for float32), four waves per workgroup.  Passes:
-//   records one record per block (validity, block scale, quantised sum), and
-//           one sum per exponential-spacing block of the multinomial scheme
-//           (whose points are kept for the emission).
-//   carries one workgroup of 1024 threads turns the records into the global
-//           scale, the exact carries C_b and the total, and scans the
-//           exponential-block sums.  With at most direct_max_blocks blocks
-//           and no exponential blocks this step is folded into the emission:
-//           every emit workgroup reduces all records itself, which costs less
-//           than one more launch.
+// Short vectors and short segments of a batch (up to 4096 and 16384 weights,
+// stratified and systematic): one workgroup each, one launch (k_scan_one).
+// One vector beyond that:
+//   records one record per block (validity, block scale, quantised sum), one
+//           wave per block, and one sum per exponential-spacing block of the
+//           multinomial scheme (whose points are kept for the emission).
+//   carries turn the records into the global scale, the exact carries C_b and
+//           the total, and scan the exponential-block sums.  With at most
+//           direct_max_blocks blocks and no exponential blocks this step is
+//           folded into the emission: every emit workgroup reduces all records
+//           itself, which costs less than one more launch.
 //   emit    each block rebuilds its exact prefix, I = C_b + local prefix, and
-//           r = n I / Q (a wave scan through DPP).  Stratified / systematic:
-//           every particle computes its cumulative offspring
-//           O_i = #{s : q_s <= r_i} in O(1), and the block's output range
-//           [O(C_b), O(C_b+1)) is filled through LDS markers and a wave
-//           max-scan, then written coalesced.  Multinomial: each block reads
-//           the exponential blocks whose points fall in its r-range and
-//           settles its particles with interleaved binary searches in LDS.
-// The workgroup-per-block variants (256 threads, 4 weights per thread) serve
-// the single-workgroup path of short vectors and the batch kernels.
-// Ragged batches run the same steps inside one workgroup per filter.
+//           r = n I / Q: one block per workgroup of four waves with its own
+//           carries, one block per wave (16 consecutive weights per lane)
+//           after the carries pass.  Stratified / systematic: every particle
+//           computes its cumulative offspring O_i = #{s : q_s <= r_i} in O(1),
+//           and the block's output range [O(C_b), O(C_b+1)) is filled through
+//           LDS markers and a max-scan, then written coalesced.  Multinomial:
+//           each block reads the exponential blocks whose points fall in its
+//           r-range and settles its particles with interleaved binary searches
+//           in LDS.
+// Ragged batches of longer segments run the same steps over all blocks of all
+// segments, or inside one workgroup per segment.
 #include "pfr_kernels.h"
 
 namespace pfr {
@@ -355,7 +356,7 @@ __device__ void carry_group(bool weights, uint32_t g, uint32_t m,
 // 9.7 us, is slower than three in parallel with the count, 8.8 us).
 constexpr uint32_t kFewGroups = 1;
 
-template <bool MULTI>
+template <bool MULTI, bool TOP = true>
 __global__ __launch_bounds__(kT) void k_carry_groups(uint32_t nb, uint32_t nbe, uint32_t G,
                                                      const BlockRec* __restrict__ recs,
                                                      const uint64_t* __restrict__ esums,
@@ -368,7 +369,7 @@ __global__ __launch_bounds__(kT) void k_carry_groups(uint32_t nb, uint32_t nbe, 
   __shared__ u128 s_w[kNW];
   __shared__ uint32_t s_u[2 * kNW];
   __shared__ uint32_t s_last;
-  if (G + (MULTI ? Ge : 0u) <= kFewGroups) {
+  if (TOP && G + (MULTI ? Ge : 0u) <= kFewGroups) {
     for (uint32_t g = 0; g < G; ++g) {
       carry_group(true, g, nb, recs, esums, P, groups, s_w, s_u);
       __syncthreads();  // the scratch is reused; the group records are read by all
@@ -387,6 +388,7 @@ __global__ __launch_bounds__(kT) void k_carry_groups(uint32_t nb, uint32_t nbe, 
   const uint32_t g = weights ? blockIdx.x : blockIdx.x - G;
   carry_group(weights, g, weights ? nb : nbe, recs, esums, weights ? P : PE,
               weights ? groups : egroups, s_w, s_u);
+  if (!TOP) return;
   if (threadIdx.x == 0) {
     // the last group to finish (the records pass zeroed the count) runs the
     // top level: release this group's record, count it, acquire the others
@@ -644,12 +646,10 @@ __device__ __forceinline__ void block_r_wave(const T* __restrict__ w, int64_t n,
 // the block's outputs are [O_lo, O_hi) and particle P0 + 16 lane + v takes
 // [Op[v], O[v]).  A marker at the first output of every run, a max-scan (16
 // values per lane in registers, then over the wave), the result written back
-// to LDS and stored row by row (coalesced).  With e_out also the marked
-// ancestry of Code 10's Prepermute (run starts keep i, the others -1 - i).
+// to LDS and stored row by row (coalesced).
 __device__ __forceinline__ void expand_wave(const uint32_t (&O)[kWPer], const uint32_t (&Op)[kWPer],
                                             uint32_t O_lo, uint32_t O_hi, int64_t P0, int64_t n,
-                                            int32_t* __restrict__ a_out, int32_t* M,
-                                            int32_t* __restrict__ e_out) {
+                                            int32_t* __restrict__ a_out, int32_t* M) {
   const int lane = (int)lane_id();
   O_hi = min(O_hi, (uint32_t)n);  // (never binds: every O is at most n)
   int32_t carry = -1;  // particle covering the first output of the chunk
@@ -668,17 +668,13 @@ __device__ __forceinline__ void expand_wave(const uint32_t (&O)[kWPer], const ui
     }
     wave_lds_sync();
     int32_t m[kWPer];
-    uint32_t marked = 0;  // bit k: position 16 lane + k starts a run
 #pragma unroll
     for (int k = 0; k < kWPer / 4; ++k) {
       const int4 t = M4[k];
       m[4 * k] = t.x; m[4 * k + 1] = t.y; m[4 * k + 2] = t.z; m[4 * k + 3] = t.w;
     }
 #pragma unroll
-    for (int k = 0; k < kWPer; ++k) {
-      marked |= (m[k] >= 0 ? 1u : 0u) << k;
-      if (k > 0) m[k] = max(m[k], m[k - 1]);
-    }
+    for (int k = 1; k < kWPer; ++k) m[k] = max(m[k], m[k - 1]);
     const int32_t incl = wave_incl_max_i32(m[kWPer - 1]);
     const int32_t before = max(carry, (int32_t)wave_shift_up_u32((uint32_t)incl, 0xFFFFFFFFu));
 #pragma unroll
@@ -687,35 +683,35 @@ __device__ __forceinline__ void expand_wave(const uint32_t (&O)[kWPer], const ui
     wave_lds_sync();
 #pragma unroll
     for (int k = 0; k < kWPer / 4; ++k) {
-      int4 t;
-      if (e_out) {
-        t = make_int4(2 * m[4 * k] + (int)((marked >> (4 * k)) & 1u),
-                      2 * m[4 * k + 1] + (int)((marked >> (4 * k + 1)) & 1u),
-                      2 * m[4 * k + 2] + (int)((marked >> (4 * k + 2)) & 1u),
-                      2 * m[4 * k + 3] + (int)((marked >> (4 * k + 3)) & 1u));
-      } else {
-        t = make_int4(m[4 * k], m[4 * k + 1], m[4 * k + 2], m[4 * k + 3]);
-      }
-      M4[k] = t;
+      M4[k] = make_int4(m[4 * k], m[4 * k + 1], m[4 * k + 2], m[4 * k + 3]);
     }
     wave_lds_sync();
     int32_t* __restrict__ a_chunk = a_out + cs;  // the same on every lane
 #pragma unroll
     for (int j = 0; j < kWPer; ++j) {
       const uint32_t p = (uint32_t)lane + (uint32_t)j * kWave;
-      if (p < len) {
-        const int32_t v = M[p];
-        if (e_out) {
-          const int32_t i = P0_32 + (v >> 1);
-          a_chunk[p] = i;
-          e_out[cs + p] = (v & 1) ? i : -1 - i;
-        } else {
-          a_chunk[p] = P0_32 + v;
-        }
-      }
+      if (p < len) a_chunk[p] = P0_32 + M[p];
     }
     wave_lds_sync();
   }
+}
+
+// The claimed slots of the wave's block, 16 bits a lane.
+__device__ __forceinline__ void wave_claim_bits(const uint32_t (&O)[kWPer],
+                                                const uint32_t (&Op)[kWPer], int64_t P0,
+                                                uint32_t* __restrict__ claim) {
+  uint32_t bits = 0;
+#pragma unroll
+  for (int v = 0; v < kWPer; ++v) bits |= (O[v] > Op[v] ? 1u : 0u) << v;
+  reinterpret_cast<uint16_t*>(claim)[(P0 >> 4) + lane_id()] = (uint16_t)bits;
+}
+// The identity of a zero or invalid total over a block: every position claims
+// its own slot.  Called by `threads` consecutive threads, the first one t = 0.
+__device__ __forceinline__ void block_identity(int64_t P0, int64_t n, int t, int threads,
+                                               int32_t* __restrict__ a,
+                                               uint32_t* __restrict__ claim) {
+  for (int64_t i = P0 + t; i < min(P0 + kBlock, n); i += threads) a[i] = (int32_t)i;
+  if (claim && t < kBlock / 32) claim[(P0 >> 5) + t] = 0xFFFFFFFFu;
 }
 
 template <bool SYSTEMATIC>
@@ -727,21 +723,22 @@ struct StrataWaveLds {
 // Stratified / systematic emission of one block by one wave: the block's
 // particles are P0 .. P0 + cnt - 1 of a vector of n, with exclusive exact
 // carry Cb and inclusive Cb1 at global scale gscale, total Q.  Writes a_out[s]
-// = P0 + i for every s in [O_{i-1}, O_i); with d_out and e_out also the claim
-// vector and the marked ancestry of Code 10's Prepermute (as emit_strata).
+// = P0 + i for every s in [O_{i-1}, O_i); with claim also the claimed slots of
+// Code 10's Prepermute, one bit per particle (the output is sorted, so a slot
+// is claimed when its particle has offspring; the winners, the first positions
+// of the runs, show in the ancestry itself).
 template <typename T, bool SYSTEMATIC>
 __device__ __forceinline__ void emit_block_wave(const T* __restrict__ w, int64_t n, int64_t P0,
                                                 const BlockRec rec, u128 Cb, u128 Cb1,
                                                 int32_t gscale, u128 Q, Key key, uint32_t filter,
                                                 uint32_t offset, int32_t* __restrict__ a_out,
                                                 StrataWaveLds<SYSTEMATIC>* L,
-                                                int32_t* __restrict__ d_out,
-                                                int32_t* __restrict__ e_out) {
+                                                uint32_t* __restrict__ claim) {
   const int lane = (int)lane_id();
   const int cnt = (int)min((int64_t)kBlock, n - P0);
   BlockR R;
   block_r_wave(w, n, P0, rec, Cb, Cb1, gscale, Q, R, L->M);
-  if (!(R.hi > R.lo) && !d_out) return;  // an empty range has no outputs
+  if (!(R.hi > R.lo) && !claim) return;  // an empty range has no outputs
 
   // stratum offsets of the strata the block's range touches
   const int64_t m_lo = (int64_t)floor(R.lo);
@@ -807,14 +804,8 @@ __device__ __forceinline__ void emit_block_wave(const T* __restrict__ w, int64_t
 #pragma unroll
   for (int v = 1; v < kWPer; ++v) Op[v] = O[v - 1];
 
-  if (d_out) {
-#pragma unroll
-    for (int v = 0; v < kWPer; ++v) {
-      const int i = lane * kWPer + v;
-      if (i < cnt) d_out[P0 + i] = O[v] > Op[v] ? (int32_t)Op[v] : (int32_t)n;
-    }
-  }
-  expand_wave(O, Op, O_lo, O_hi, P0, n, a_out, L->M, e_out);
+  if (claim) wave_claim_bits(O, Op, P0, claim);
+  expand_wave(O, Op, O_lo, O_hi, P0, n, a_out, L->M);
 }
 
 // ---------------------------------------------------------------- multinomial, one block per wave
@@ -909,13 +900,12 @@ __device__ __forceinline__ void emit_multi_wave(const T* __restrict__ w, int64_t
                                                 uint32_t offset, CEPtr CE, uint32_t nbe,
                                                 const uint64_t* __restrict__ evals,
                                                 int32_t* __restrict__ a_out, MultiWaveLds* L,
-                                                int32_t* __restrict__ d_out = nullptr,
-                                                int32_t* __restrict__ e_out = nullptr) {
+                                                uint32_t* __restrict__ claim = nullptr) {
   const int lane = (int)lane_id();
   const int cnt = (int)min((int64_t)kBlock, n - P0);
   BlockR R;
   block_r_wave(w, n, P0, rec, Cb, Cb1, gscale, Q, R, L->M);
-  if (!(R.hi > R.lo) && !d_out) return;  // an empty range has no outputs
+  if (!(R.hi > R.lo) && !claim) return;  // an empty range has no outputs
   const RMap em = make_rmap(CE[nbe], n);
   const double ce = em.Nd * em.invQ;
   const uint32_t e_first = (uint32_t)__builtin_amdgcn_readfirstlane(exp_block_of(R.lo, n, CE, nbe, em));
@@ -1004,14 +994,8 @@ __device__ __forceinline__ void emit_multi_wave(const T* __restrict__ w, int64_t
   Op[0] = wave_shift_up_u32(O[kWPer - 1], O_lo);
 #pragma unroll
   for (int v = 1; v < kWPer; ++v) Op[v] = O[v - 1];
-  if (d_out) {  // the ancestry is sorted: the sorted claim, as the strata schemes form it
-#pragma unroll
-    for (int v = 0; v < kWPer; ++v) {
-      const int i = lane * kWPer + v;
-      if (i < cnt) d_out[P0 + i] = O[v] > Op[v] ? (int32_t)Op[v] : (int32_t)n;
-    }
-  }
-  expand_wave(O, Op, O_lo, O_hi, P0, n, a_out, L->M, e_out);
+  if (claim) wave_claim_bits(O, Op, P0, claim);
+  expand_wave(O, Op, O_lo, O_hi, P0, n, a_out, L->M);
 }
 
 // Weight records, one block per wave (blockIdx.x < wgs_b), and for the
@@ -1043,49 +1027,410 @@ __global__ __launch_bounds__(kT) void k_scan_records_w(const T* __restrict__ w, 
   }
 }
 
-// Direct carries of block b by its own wave: the global scale, the block's
-// exact carry and the total from all nb records, read by the wave in two
-// lane-strided passes and summed by DPP scans, with no workgroup barrier and
-// no LDS.  Every record is converted straight to the global scale (the
-// carries pass converts a group's sums to the group's scale first, which
-// gives the same values when there is one group of 1024 blocks).
-struct DirectW {
+// ---------------------------------------------------------------- one block per workgroup
+// The emission of a single vector with one 1024-weight block per workgroup of
+// four waves, four weights per thread.  At up to about a thousand blocks the
+// wave form above leaves one wave per SIMD, whose serial latency (16 weights a
+// lane, and some 20 KB of straight-line code fetched once) is the call; here
+// the chain is a quarter as long, and its code is fetched for four times the
+// waves.  Kernel time, systematic, 2^16 / 2^18 / 2^20 weights: 8.7 / 10.9 / 13.1
+// (with the carries pass) -> 5.8 / 6.4 / 9.9 us; from 2^21 on the wave form is
+// faster (2^21 10.6 against 13.6 us, 2^24 38 against 70 us: fewer barriers).
+//
+// Carries.  Up to kGrp blocks each workgroup reduces all records itself, four
+// per thread (DIRECT); beyond, the group pass leaves every block's prefix
+// inside its group and the groups' totals, and the workgroup reduces the
+// groups (at most 2048).  Either way the values are those of the carries pass.
+struct WgCarry {
   u128 Cb, Cb1, Q;
   int32_t gscale;
   uint32_t status;
 };
 
-__device__ DirectW wave_direct_carries(uint32_t nb, uint32_t b,
-                                       const BlockRec* __restrict__ recs) {
-  const uint32_t lane = lane_id();
-  uint32_t bad = 0, key = 0xFFFFFFFFu;
-  for (uint32_t j = lane; j < nb; j += kWave) {
-    const BlockRec r = recs[j];
-    bad |= r.bad;
-    if (r.sum) key = min(key, (uint32_t)r.scale ^ 0x80000000u);
+struct CarryScratch {
+  uint32_t key[kNW], bad[kNW];
+  u128 before[kNW], all[kNW];
+};
+
+// min over the workgroup of the scale keys and or of the bad flags, in
+// registers of every thread after the barrier inside.
+__device__ __forceinline__ void wg_key_bad(uint32_t& key, uint32_t& bad, CarryScratch* s) {
+  const int wave = (int)threadIdx.x / kWave;
+  key = ~wave_max_u32(~key);
+  bad = ballot(bad != 0) ? FLAG_BAD_WEIGHTS : 0u;
+  if (lane_id() == 0) {
+    s->key[wave] = key;
+    s->bad[wave] = bad;
   }
-  bad = wave_reduce(bad, OpOr());
-  key = wave_reduce(key, OpMin());
-  DirectW d;
-  d.gscale = key == 0xFFFFFFFFu
-                 ? 0
-                 : (int32_t)(key ^ 0x80000000u) + (kCarryBits - 63) - ceil_log2(nb);
-  u128 before = 0, all = 0, own = 0;
-  for (uint32_t j = lane; j < nb; j += kWave) {
-    const u128 v = conv_rec(recs[j], d.gscale);
-    all += v;
-    before += j < b ? v : (u128)0;
-    own += j == b ? v : (u128)0;
+  __syncthreads();
+#pragma unroll
+  for (int w2 = 0; w2 < kNW; ++w2) {
+    key = min(key, s->key[w2]);
+    bad |= s->bad[w2];
   }
-  d.Q = readlane(wave_incl_add_u128(all), kWave - 1);
-  d.Cb = readlane(wave_incl_add_u128(before), kWave - 1);
-  d.Cb1 = d.Cb + readlane(wave_incl_add_u128(own), kWave - 1);
-  d.status = bad;
-  if (!bad && d.Q == 0) d.status |= FLAG_ZERO_TOTAL;
-  return d;
+}
+// Workgroup sums of two 128-bit values.
+__device__ __forceinline__ void wg_sum2(u128& x, u128& y, CarryScratch* s) {
+  const int wave = (int)threadIdx.x / kWave;
+  x = wave_incl_add_u128(x);
+  y = wave_incl_add_u128(y);
+  if (lane_id() == kWave - 1) {
+    s->before[wave] = x;
+    s->all[wave] = y;
+  }
+  __syncthreads();
+  x = y = 0;
+#pragma unroll
+  for (int w2 = 0; w2 < kNW; ++w2) {
+    x += s->before[w2];
+    y += s->all[w2];
+  }
 }
 
+// Blocks up to which the records are converted straight to the global scale;
+// beyond, up to one group, they go through the group's scale, as in the
+// carries pass (the two differ, by truncation, only for blocks 2^27 times
+// lighter than the heaviest).
+constexpr uint32_t kStraight = 256;
+
+__device__ __forceinline__ WgCarry direct_carries(uint32_t nb, uint32_t b,
+                                                  const BlockRec* __restrict__ recs,
+                                                  const BlockRec& own, CarryScratch* s) {
+  // record j = r kT + thread, so that a load covers consecutive records
+  constexpr int kR = (int)(kDirectMax / kT);
+  uint32_t key = 0xFFFFFFFFu, bad = 0;
+  u128 before = 0, all = 0;
+  if (nb <= kGrp) {
+    BlockRec r[kGPer];
+#pragma unroll
+    for (int k = 0; k < kGPer; ++k) {
+      const uint32_t j = (uint32_t)k * kT + threadIdx.x;
+      if (j < nb) r[k] = recs[j];
+      else r[k].sum = 0, r[k].scale = 0, r[k].bad = 0;
+    }
+#pragma unroll
+    for (int k = 0; k < kGPer; ++k) {
+      bad |= r[k].bad;
+      if (r[k].sum) key = min(key, (uint32_t)r[k].scale ^ 0x80000000u);
+    }
+    wg_key_bad(key, bad, s);
+    const bool none = key == 0xFFFFFFFFu;
+    const int32_t top = (int32_t)(key ^ 0x80000000u) + (kCarryBits - 63);
+    const int32_t gscale = none ? 0 : top - ceil_log2(nb);
+    const int32_t via = none ? 0 : nb <= kStraight ? gscale : top - kGrpLog;
+#pragma unroll
+    for (int k = 0; k < kGPer; ++k) {
+      const uint32_t j = (uint32_t)k * kT + threadIdx.x;
+      const u128 v = conv_rec_fast(r[k], via);
+      all += v;
+      before += j < b ? v : (u128)0;
+    }
+    wg_sum2(before, all, s);
+    WgCarry c;
+    c.gscale = gscale;
+    c.Cb = shift_u128(before, gscale - via);
+    c.Cb1 = shift_u128(before + conv_rec_fast(own, via), gscale - via);
+    c.Q = shift_u128(all, gscale - via);
+    c.status = bad | (!bad && c.Q == 0 ? FLAG_ZERO_TOTAL : 0u);
+    return c;
+  }
+  for (int k = 0; k < kR; ++k) {
+    const uint32_t j = (uint32_t)k * kT + threadIdx.x;
+    if (j < nb) {
+      const BlockRec r = recs[j];
+      bad |= r.bad;
+      if (r.sum) key = min(key, (uint32_t)r.scale ^ 0x80000000u);
+    }
+  }
+  wg_key_bad(key, bad, s);
+  const int32_t gscale = key == 0xFFFFFFFFu ? 0
+                                            : (int32_t)(key ^ 0x80000000u) + (kCarryBits - 63) -
+                                                  ceil_log2(nb);
+  for (int k = 0; k < kR; ++k) {
+    const uint32_t j = (uint32_t)k * kT + threadIdx.x;
+    if (j < nb) {
+      const u128 v = conv_rec_fast(recs[j], gscale);
+      all += v;
+      before += j < b ? v : (u128)0;
+    }
+  }
+  wg_sum2(before, all, s);
+  WgCarry c;
+  c.gscale = gscale;
+  c.Cb = before;
+  c.Cb1 = before + conv_rec_fast(own, gscale);
+  c.Q = all;
+  c.status = bad | (!bad && c.Q == 0 ? FLAG_ZERO_TOTAL : 0u);
+  return c;
+}
+
+// From the group pass: the top level over the G groups, by every workgroup.
+__device__ __forceinline__ WgCarry group_carries(uint32_t nb, uint32_t b, const Carries& C,
+                                                 CarryScratch* s) {
+  const uint32_t G = C.G, g0 = b >> kGrpLog, g1 = (b + 1) >> kGrpLog;
+  const u128 P0 = C.P[b];
+  const u128 P1 = b + 1 < nb ? C.P[b + 1] : (u128)0;
+  const int32_t gs0 = C.grp[g0].gs, gs1 = b + 1 < nb ? C.grp[g1].gs : 0;
+  uint32_t key = 0xFFFFFFFFu, bad = 0;
+  for (uint32_t g = threadIdx.x; g < G; g += kT) {
+    bad |= C.grp[g].bad;
+    key = min(key, C.grp[g].key);
+  }
+  wg_key_bad(key, bad, s);
+  const int32_t gscale = key == 0xFFFFFFFFu ? 0
+                                            : (int32_t)(key ^ 0x80000000u) + (kCarryBits - 63) -
+                                                  ceil_log2(nb);
+  u128 before = 0, all = 0;
+  for (uint32_t g = threadIdx.x; g < G; g += kT) {
+    const u128 v = shift_u128(C.grp[g].T, gscale - C.grp[g].gs);
+    all += v;
+    before += g < g0 ? v : (u128)0;
+  }
+  const u128 T0 = shift_u128(C.grp[g0].T, gscale - gs0);
+  wg_sum2(before, all, s);
+  WgCarry c;
+  c.gscale = gscale;
+  c.Q = all;
+  c.Cb = before + shift_u128(P0, gscale - gs0);
+  c.Cb1 = b + 1 >= nb ? all : (g1 == g0 ? before : before + T0) + shift_u128(P1, gscale - gs1);
+  c.status = bad | (!bad && c.Q == 0 ? FLAG_ZERO_TOTAL : 0u);
+  return c;
+}
+
+// Four consecutive weights of the block (zeros past the end); the vector
+// starts anywhere, so the wide load is aligned to one weight only.
+template <typename T>
+__device__ __forceinline__ void load4_any(const T* __restrict__ w, int64_t n, int64_t base,
+                                          T (&x)[kPer]) {
+  const int64_t idx = base + (int64_t)threadIdx.x * kPer;
+  if (idx + kPer <= n) {
+    typedef T V __attribute__((ext_vector_type(4), aligned(sizeof(T))));
+    const V t = *reinterpret_cast<const V*>(w + idx);
+    x[0] = t.x; x[1] = t.y; x[2] = t.z; x[3] = t.w;
+  } else {
+#pragma unroll
+    for (int v = 0; v < kPer; ++v) x[v] = (idx + v < n) ? w[idx + v] : (T)0;
+  }
+}
+
+// r of the thread's four particles and of the particle before them (the
+// formula of block_r_wave; the block's lower end before its first particle).
+struct WgR {
+  double r[kPer], prev, lo, hi;
+};
+struct PrefixScratch {
+  uint64_t sum[kNW];
+};
+// The thread's quantised weights as inclusive prefixes inside the thread, and
+// their sum, which goes to the scratch per wave (a barrier must follow).
+template <typename T>
+__device__ __forceinline__ uint64_t wg_quantize(const T (&x)[kPer], int32_t scale,
+                                                uint64_t (&q)[kPer], PrefixScratch* s) {
+  uint64_t acc = 0;
+#pragma unroll
+  for (int v = 0; v < kPer; ++v) {
+    acc += quantize_nb(x[v], scale);
+    q[v] = acc;
+  }
+  const uint64_t incl = wave_incl_add_u64(acc);
+  if (lane_id() == kWave - 1) s->sum[threadIdx.x / kWave] = incl;
+  return incl - acc;  // exclusive inside the wave
+}
+__device__ __forceinline__ void wg_block_r(const uint64_t (&q)[kPer], uint64_t off,
+                                           const PrefixScratch* s, int32_t scale,
+                                           const WgCarry& C, int64_t n, WgR& R) {
+  const int wave = (int)threadIdx.x / kWave;
+  uint64_t total = 0;
+#pragma unroll
+  for (int w2 = 0; w2 < kNW; ++w2) {
+    off += w2 < wave ? s->sum[w2] : 0ull;
+    total += s->sum[w2];
+  }
+  const RMap rm = make_rmap(C.Q, n);
+  R.lo = rm(C.Cb);
+  R.hi = rm(C.Cb1);
+  const double c = ldexp(rm.Nd * rm.invQ, C.gscale - scale);
+  auto r_of = [&](uint64_t L) -> double {
+    const double rv = __fma_rn(u64_to_f64(L), c, R.lo);
+    return (L == total || rv > R.hi) ? R.hi : rv;
+  };
+  R.prev = off ? r_of(off) : R.lo;  // (no weight before: the block's lower end)
+#pragma unroll
+  for (int v = 0; v < kPer; ++v) R.r[v] = r_of(off + q[v]);
+}
+
+// Expansion of cumulative offspring into ancestors, as expand_wave: 2048
+// outputs a round, eight consecutive ones per thread, 16-byte stores.
+constexpr int kOut = 8;  // outputs per thread and round
+struct ExpandLds {
+  alignas(16) int32_t M[kT * kOut + 4];
+  int32_t top[kNW];
+};
+__device__ __forceinline__ void wg_markers_clear(ExpandLds* L) {
+  int4* M4 = reinterpret_cast<int4*>(L->M) + threadIdx.x * (kOut / 4);
+#pragma unroll
+  for (int k = 0; k < kOut / 4; ++k) M4[k] = make_int4(-1, -1, -1, -1);
+}
+typedef int32_t OutQuad __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ void store_quad(int32_t* __restrict__ p, uint32_t i, uint32_t len,
+                                           int32_t v0, int32_t v1, int32_t v2, int32_t v3) {
+  if (i + 4 <= len) {
+    OutQuad q;
+    q.x = v0; q.y = v1; q.z = v2; q.w = v3;
+    *reinterpret_cast<OutQuad*>(p + i) = q;
+  } else {
+    if (i < len) p[i] = v0;
+    if (i + 1 < len) p[i + 1] = v1;
+    if (i + 2 < len) p[i + 2] = v2;
+  }
+}
+// The markers are cleared (with a barrier behind it) before the first call.
+__device__ __forceinline__ void wg_expand(const uint32_t (&O)[kPer], uint32_t Oprev,
+                                          uint32_t O_lo, uint32_t O_hi, int32_t P0, int64_t n,
+                                          int32_t* __restrict__ a_out, ExpandLds* L) {
+  constexpr uint32_t kRound = kT * kOut;
+  const int tid = (int)threadIdx.x, wave = tid / kWave;
+  O_hi = min(O_hi, (uint32_t)n);  // (never binds: every O is at most n)
+  int32_t carry = -1;             // particle covering the first output of the round
+  for (uint32_t cs = O_lo; cs < O_hi; cs += kRound) {
+    const uint32_t len = min(kRound, O_hi - cs);
+    if (cs != O_lo) {
+      __syncthreads();  // the last round's markers and tops have been read
+      wg_markers_clear(L);
+      __syncthreads();
+    }
+    uint32_t p = Oprev;
+#pragma unroll
+    for (int v = 0; v < kPer; ++v) {
+      const uint32_t pos = p - cs;
+      if (O[v] > p && pos < len) L->M[pos] = tid * kPer + v;
+      p = O[v];
+    }
+    __syncthreads();
+    const int4* M4 = reinterpret_cast<const int4*>(L->M) + tid * (kOut / 4);
+    int32_t m[kOut];
+#pragma unroll
+    for (int k = 0; k < kOut / 4; ++k) {
+      const int4 t = M4[k];
+      m[4 * k] = t.x; m[4 * k + 1] = t.y; m[4 * k + 2] = t.z; m[4 * k + 3] = t.w;
+    }
+#pragma unroll
+    for (int k = 1; k < kOut; ++k) m[k] = max(m[k], m[k - 1]);
+    const int32_t incl = wave_incl_max_i32(m[kOut - 1]);
+    if (lane_id() == kWave - 1) L->top[wave] = incl;
+    __syncthreads();
+    int32_t before = (int32_t)wave_shift_up_u32((uint32_t)incl, 0xFFFFFFFFu);
+    before = max(before, carry);
+#pragma unroll
+    for (int w2 = 0; w2 < kNW; ++w2) {
+      const int32_t t = L->top[w2];
+      before = w2 < wave ? max(before, t) : before;
+      carry = max(carry, t);
+    }
+#pragma unroll
+    for (int k = 0; k < kOut; ++k) m[k] = P0 + max(m[k], before);
+    const uint32_t i = (uint32_t)tid * kOut;
+    int32_t* __restrict__ ap = a_out + cs;
+#pragma unroll
+    for (int k = 0; k < kOut; k += 4)
+      store_quad(ap, i + k, len, m[k], m[k + 1], m[k + 2], m[k + 3]);
+  }
+}
+
+template <bool SYSTEMATIC>
+struct StrataWgLds {
+  ExpandLds ex;
+  CarryScratch cs;
+  PrefixScratch ps;
+  uint32_t u[SYSTEMATIC ? 1 : kUTabW];  // offset words of strata [m_lo, m_lo + kUTabW)
+};
+
 template <typename T, int SCHEME, bool DIRECT>
+__global__ __launch_bounds__(kT) void k_scan_emit_b(const T* __restrict__ w, int64_t n,
+                                                    uint32_t nb, Key key, uint32_t offset,
+                                                    uint32_t filter,
+                                                    const BlockRec* __restrict__ recs,
+                                                    Carries C, int32_t* __restrict__ a,
+                                                    uint32_t* __restrict__ flags,
+                                                    uint32_t* __restrict__ claim) {
+  static_assert(SCHEME != SCHEME_MULTINOMIAL, "strata schemes only");
+  constexpr bool SYSTEMATIC = SCHEME == SCHEME_SYSTEMATIC;
+  __shared__ StrataWgLds<SYSTEMATIC> L;
+  const uint32_t b = blockIdx.x;
+  const int tid = (int)threadIdx.x;
+  const int64_t P0 = (int64_t)b * kBlock;
+  T x[kPer];
+  load4_any(w, n, P0, x);
+  const BlockRec rec = recs[b];
+  offset = counter_offset(key, offset);
+  wg_markers_clear(&L.ex);
+  const WgCarry c = DIRECT ? direct_carries(nb, b, recs, rec, &L.cs)
+                           : group_carries(nb, b, C, &L.cs);
+  if (flags && b == 0 && tid == 0 && c.status) atomicOr(flags, c.status);
+  if (c.status & (FLAG_BAD_WEIGHTS | FLAG_ZERO_TOTAL)) {
+    block_identity(P0, n, tid, kT, a, claim);
+    return;
+  }
+  uint64_t q[kPer];
+  const uint64_t off = wg_quantize(x, rec.scale, q, &L.ps);
+  __syncthreads();
+  WgR R;
+  wg_block_r(q, off, &L.ps, rec.scale, c, n, R);
+  if (!(R.hi > R.lo) && !claim) return;  // an empty range has no outputs
+
+  // O(r) = #{s : s + 1 - u_s <= r}, exactly: m = floor(r), frac(r) >= 1 - u_m
+  // (0 <= r <= n < 2^31, so m converts exactly to 32 bits)
+  const int32_t n32 = (int32_t)n;
+  const int32_t m_lo = (int32_t)floor(R.lo);
+  const int32_t m_hi = min(n32 - 1, (int32_t)floor(R.hi));
+  const bool table = !SYSTEMATIC && m_hi - m_lo + 1 <= kUTabW;
+  const double t_sys =
+      SYSTEMATIC ? 1.0 - u_offset(draw_uniform(key, 0, DOM_STRATA, 0, filter, offset).x) : 0.0;
+  if (!SYSTEMATIC) {
+    if (table) {
+      for (int32_t cc = (m_lo >> 2) + tid; cc <= (m_hi >> 2); cc += kT) {
+        const uint4 xw = draw(key, (uint32_t)cc, DOM_STRATA, 0, filter, offset);
+        const uint32_t xs[4] = {xw.x, xw.y, xw.z, xw.w};
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int32_t m = cc * 4 + v;
+          if (m >= m_lo && m <= m_hi) L.u[m - m_lo] = xs[v];
+        }
+      }
+    }
+    __syncthreads();
+  }
+  auto cum = [&](double rv) -> uint32_t {
+    const double mf = floor(rv);
+    const int32_t m = (int32_t)mf;
+    if (m >= n32) return (uint32_t)n32;
+    const double t = SYSTEMATIC ? t_sys
+                     : table    ? 1.0 - u_offset(L.u[m - m_lo])
+                                : 1.0 - u_offset(stratum_word(key, filter, offset, m));
+    return (uint32_t)m + ((rv - mf) >= t ? 1u : 0u);
+  };
+  uint32_t O[kPer];
+  const uint32_t Oprev = cum(R.prev);
+#pragma unroll
+  for (int v = 0; v < kPer; ++v) O[v] = cum(R.r[v]);
+  const uint32_t O_lo = uniform_u32(cum(R.lo)), O_hi = uniform_u32(cum(R.hi));
+  if (claim) {  // the nibbles of eight lanes make a word
+    uint32_t p = Oprev, bits = 0;
+#pragma unroll
+    for (int v = 0; v < kPer; ++v) {
+      bits |= (O[v] > p ? 1u : 0u) << v;
+      p = O[v];
+    }
+    bits <<= 4 * (tid & 7);
+    bits |= dpp_u32<kDppXor1>(0u, bits);
+    bits |= dpp_u32<kDppXor2>(0u, bits);
+    bits |= dpp_u32<kDppHalfMirror>(0u, bits);
+    if ((tid & 7) == 0) claim[(P0 >> 5) + (tid >> 3)] = bits;
+  }
+  wg_expand(O, Oprev, O_lo, O_hi, (int32_t)P0, n, a, &L.ex);
+}
+
+template <typename T, int SCHEME>
 __global__ __launch_bounds__(kT) void k_scan_emit_w(const T* __restrict__ w, int64_t n,
                                                     uint32_t nb, Key key, uint32_t offset,
                                                     uint32_t filter,
@@ -1093,54 +1438,30 @@ __global__ __launch_bounds__(kT) void k_scan_emit_w(const T* __restrict__ w, int
                                                     const BlockRec* __restrict__ recs,
                                                     Carries C, int32_t* __restrict__ a,
                                                     uint32_t* __restrict__ flags,
-                                                    int32_t* __restrict__ d_out,
-                                                    int32_t* __restrict__ e_out) {
+                                                    uint32_t* __restrict__ claim) {
   static_assert(SCHEME != SCHEME_MULTINOMIAL, "strata schemes only");
   offset = counter_offset(key, offset);
   __shared__ StrataWaveLds<SCHEME == SCHEME_SYSTEMATIC> L[kWavesPerWG];
   const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const uint32_t b = blockIdx.x * kWavesPerWG + wave;
-  uint32_t status;
-  u128 Cb, Cb1, Q;
-  int32_t gscale;
-  if (DIRECT) {
-    if (b >= nb) return;
-    const DirectW d = wave_direct_carries(nb, b, recs);
-    status = d.status;
-    Cb = d.Cb;
-    Cb1 = d.Cb1;
-    Q = d.Q;
-    gscale = d.gscale;
-  } else {
-    if (b >= nb) return;
-    status = hdr->status;
-    gscale = hdr->gscale;
-    C.gscale = gscale;
-    Cb = C[b];
-    Cb1 = C[b + 1];
-    Q = hdr->Q;
-  }
   if (b >= nb) return;
+  const uint32_t status = hdr->status;
+  const int32_t gscale = hdr->gscale;
+  C.gscale = gscale;
+  const u128 Cb = C[b], Cb1 = C[b + 1], Q = hdr->Q;
   if (flags && b == 0 && threadIdx.x == 0 && status) atomicOr(flags, status);
   const int64_t P0 = (int64_t)b * kBlock;
   if (status & (FLAG_BAD_WEIGHTS | FLAG_ZERO_TOTAL)) {
-    // identity: every position claims its own slot
-    for (int64_t i = P0 + lane_id(); i < min(P0 + kBlock, n); i += kWave) {
-      a[i] = (int32_t)i;
-      if (d_out) {
-        d_out[i] = (int32_t)i;
-        e_out[i] = (int32_t)i;
-      }
-    }
+    block_identity(P0, n, (int)lane_id(), kWave, a, claim);
     return;
   }
   emit_block_wave<T, SCHEME == SCHEME_SYSTEMATIC>(w, n, P0, recs[b], Cb, Cb1, gscale, Q, key,
-                                                   filter, offset, a, &L[wave], d_out, e_out);
+                                                   filter, offset, a, &L[wave], claim);
 }
 
 // Multinomial emission, one weight block per wave (after the carries); with
-// d_out and e_out also the claim vector and the marked ancestry of Code 10's
-// Prepermute (the multinomial ancestry is sorted, as the strata schemes' is).
+// claim also the claimed slots (the multinomial ancestry is sorted, as the
+// strata schemes' is).
 template <typename T>
 __global__ __launch_bounds__(kT) void k_scan_emit_mw(const T* __restrict__ w, int64_t n,
                                                      uint32_t nb, uint32_t nbe, Key key,
@@ -1151,8 +1472,7 @@ __global__ __launch_bounds__(kT) void k_scan_emit_mw(const T* __restrict__ w, in
                                                      const uint64_t* __restrict__ evals,
                                                      int32_t* __restrict__ a,
                                                      uint32_t* __restrict__ flags,
-                                                     int32_t* __restrict__ d_out,
-                                                     int32_t* __restrict__ e_out) {
+                                                     uint32_t* __restrict__ claim) {
   offset = counter_offset(key, offset);
   __shared__ MultiWaveLds L[kWavesPerWG];
   const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -1162,18 +1482,208 @@ __global__ __launch_bounds__(kT) void k_scan_emit_mw(const T* __restrict__ w, in
   if (flags && b == 0 && threadIdx.x == 0 && status) atomicOr(flags, status);
   const int64_t P0 = (int64_t)b * kBlock;
   if (status & (FLAG_BAD_WEIGHTS | FLAG_ZERO_TOTAL)) {
-    for (int64_t i = P0 + lane_id(); i < min(P0 + kBlock, n); i += kWave) {
-      a[i] = (int32_t)i;
-      if (d_out) {
-        d_out[i] = (int32_t)i;
-        e_out[i] = (int32_t)i;
-      }
-    }
+    block_identity(P0, n, (int)lane_id(), kWave, a, claim);
     return;
   }
   C.gscale = hdr->gscale;
   emit_multi_wave<T, true>(w, n, P0, recs[b], C[b], C[b + 1], C.gscale, hdr->Q, key, filter,
-                           offset, CE, nbe, evals, a, &L[wave], d_out, e_out);
+                           offset, CE, nbe, evals, a, &L[wave], claim);
+}
+
+// ---------------------------------------------------------------- whole vector in one workgroup
+// Stratified / systematic resampling of a vector (or of every short segment of
+// a batch) of at most NB blocks by one workgroup in one launch: the weights
+// are read once and stay quantised in registers from the records to the
+// emission.  Thread t takes the quads of four weights t, t + THREADS, ...; a
+// block is four waves of one round.  All outputs fit one marker pass, since
+// there are as many as particles.  Records, scale, carries and r are those of
+// the block-parallel kernels.  Bound by the latency of its phases.  Per call (captured), systematic:
+// n = 1000 8.3 -> 3.9 us, 4096 9.4 -> 5.8 us (from 256 threads with 16 weights
+// a lane); 65536 segments of 256 535 -> 185 us and 1024 of 16384 61 -> 46 us
+// (from records, carries and emission).
+template <int NB>
+struct OneWg {
+  static constexpr int kThreads = NB >= 4 ? 1024 : 256 * NB;
+  static constexpr int kW = kThreads / kWave;               // waves
+  static constexpr int kR = NB * kBlock / (4 * kThreads);   // quads per thread
+  static constexpr int kParts = NB * 4;                     // waves' shares of blocks
+  static_assert(kParts <= kWave, "a wave holds one entry per share");
+};
+
+template <typename T, int SCHEME, int NB>
+__global__ __launch_bounds__(OneWg<NB>::kThreads,
+                             NB == 16 && sizeof(T) == 4 ? 8 : 1) void k_scan_one(
+    const T* __restrict__ w_all, int64_t n_total, const int64_t* __restrict__ offsets,
+    int64_t above, Key key, uint32_t offset, uint32_t filter_base, int32_t* __restrict__ a_all,
+    uint32_t* __restrict__ flags) {
+  typedef OneWg<NB> G;
+  constexpr bool SYSTEMATIC = SCHEME == SCHEME_SYSTEMATIC;
+  static_assert(SCHEME != SCHEME_MULTINOMIAL, "strata schemes only");
+  __shared__ __align__(16) int32_t M[NB * kBlock];
+  __shared__ __align__(16) uint32_t u[SYSTEMATIC ? 4 : NB * kBlock];
+  __shared__ uint32_t s_key[G::kParts];
+  __shared__ uint64_t s_sum[G::kParts];
+  __shared__ int32_t s_top[G::kParts];
+  const uint32_t f = blockIdx.x;
+  const int64_t base = offsets ? offsets[f] : 0;
+  const int64_t n = offsets ? offsets[f + 1] - base : n_total;
+  if (n <= above || n > (int64_t)NB * kBlock) return;  // another launch's segment
+  const T* __restrict__ w = w_all + base;
+  int32_t* __restrict__ a = a_all + base;
+  const uint32_t filter = filter_base + f;
+  offset = counter_offset(key, offset);
+  const int tid = (int)threadIdx.x, wave = (int)uniform_u32((uint32_t)tid / kWave);
+  const int lane = (int)lane_id();
+  const int32_t n32 = (int32_t)n;
+  const uint32_t nb = ((uint32_t)n + kBlock - 1) / kBlock;
+
+  // records: reference exponents
+  T x[G::kR][4];
+#pragma unroll
+  for (int r = 0; r < G::kR; ++r) {
+    const int32_t i = r * 4 * G::kThreads + 4 * tid;
+    if (i + 4 <= n32) {
+      typedef T V __attribute__((ext_vector_type(4), aligned(sizeof(T))));
+      const V t = *reinterpret_cast<const V*>(w + i);
+      x[r][0] = t.x; x[r][1] = t.y; x[r][2] = t.z; x[r][3] = t.w;
+    } else {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) x[r][v] = i + v < n32 ? w[i + v] : (T)0;
+    }
+    reinterpret_cast<int4*>(M)[r * G::kThreads + tid] = make_int4(-1, -1, -1, -1);
+  }
+  if (!SYSTEMATIC) {
+    for (int32_t cc = tid; cc < (n32 + 3) / 4; cc += G::kThreads)
+      reinterpret_cast<uint4*>(u)[cc] = draw(key, (uint32_t)cc, DOM_STRATA, 0, filter, offset);
+  }
+#pragma unroll
+  for (int r = 0; r < G::kR; ++r) {
+    uint32_t k = 1;
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+      k = max(k, weight_ok(x[r][v]) ? (uint32_t)exp_field(x[r][v]) : FLAG_BAD_WEIGHTS << 16);
+    k = wave_max_u32(k);
+    if (lane == 0) s_key[r * G::kW + wave] = k;
+  }
+  __syncthreads();
+  // quantised prefixes inside the waves.  With sixteen weights a thread they
+  // are formed again from the weights in the emission: 64 registers instead of
+  // 86, and two workgroups to a CU (systematic, 1024 segments of 16384: 64 ->
+  // 46 us)
+  constexpr bool kAgain = G::kR > 1 && sizeof(T) == 4;
+  uint64_t q[kAgain ? 1 : G::kR][4], off[G::kR];
+  int32_t scale[G::kR];
+#pragma unroll
+  for (int r = 0; r < G::kR; ++r) {
+    const uint32_t* k4 = s_key + ((r * G::kW + wave) & ~3);
+    scale[r] = scale_of<T>((int)(max(max(k4[0], k4[1]), max(k4[2], k4[3])) & 0xFFFFu));
+    uint64_t acc = 0;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      acc += quantize_nb(x[r][v], scale[r]);
+      if (!kAgain) q[kAgain ? 0 : r][v] = acc;
+    }
+    const uint64_t incl = wave_incl_add_u64(acc);
+    if (lane == kWave - 1) s_sum[r * G::kW + wave] = incl;
+    off[r] = incl - acc;
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  __syncthreads();
+  // carries, by every wave: lane l holds block l
+  uint64_t sum = 0;
+  uint32_t bkey = 0;
+  if ((uint32_t)lane < nb) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      sum += s_sum[4 * lane + k];
+      bkey = max(bkey, s_key[4 * lane + k]);
+    }
+  }
+  BlockRec rec;
+  rec.sum = sum;
+  rec.scale = scale_of<T>((int)(bkey & 0xFFFFu));
+  rec.bad = bkey >> 16;
+  const uint32_t bad = ballot(rec.bad != 0) ? FLAG_BAD_WEIGHTS : 0u;
+  const uint32_t skey = ~wave_max_u32(sum ? ~((uint32_t)rec.scale ^ 0x80000000u) : 0u);
+  const int32_t gscale = skey == 0xFFFFFFFFu ? 0
+                                             : (int32_t)(skey ^ 0x80000000u) + (kCarryBits - 63) -
+                                                   ceil_log2(nb);
+  const u128 val = sum ? conv_rec(rec, gscale) : (u128)0;
+  const u128 inc = wave_incl_add_u128(val);
+  const u128 Q = readlane(inc, kWave - 1);
+  const uint32_t status = bad | (!bad && Q == 0 ? FLAG_ZERO_TOTAL : 0u);
+  if (flags && tid == 0 && status) atomicOr(flags, status);
+  if (status) {
+    for (int32_t i = tid; i < n32; i += G::kThreads) a[i] = i;
+    return;
+  }
+  const RMap rm = make_rmap(Q, n);
+  const double lo_l = rm(inc - val), hi_l = rm(inc), slope = rm.Nd * rm.invQ;
+  const double t_sys =
+      SYSTEMATIC ? 1.0 - u_offset(draw_uniform(key, 0, DOM_STRATA, 0, filter, offset).x) : 0.0;
+  auto cum = [&](double rv) -> int32_t {
+    const double mf = floor(rv);
+    const int32_t m = (int32_t)mf;
+    const double t = SYSTEMATIC ? t_sys : 1.0 - u_offset(u[m >= n32 ? 0 : m]);
+    return m >= n32 ? n32 : m + ((rv - mf) >= t ? 1 : 0);
+  };
+#pragma unroll
+  for (int r = 0; r < G::kR; ++r) {
+    const int part = r * G::kW + wave, blk = part >> 2;
+    if ((uint32_t)blk >= nb) break;  // the same on every lane of the wave
+    const double lo = readlane(lo_l, blk), hi = readlane(hi_l, blk);
+    const double c = ldexp(slope, gscale - scale[r]);
+    uint64_t total = 0, o = off[r];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const uint64_t sk = s_sum[4 * blk + k];
+      o += k < (part & 3) ? sk : 0ull;
+      total += sk;
+    }
+    auto r_of = [&](uint64_t L) -> double {
+      const double rv = __fma_rn(u64_to_f64(L), c, lo);
+      return (L == total || rv > hi) ? hi : rv;
+    };
+    int32_t p = cum(o ? r_of(o) : lo);
+    const int32_t i = r * 4 * G::kThreads + 4 * tid;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      if (kAgain) {
+        asm("" : "+v"(x[r][v]));  // or the compiler keeps the earlier values instead
+        o += quantize_nb(x[r][v], scale[r]);
+      }
+      const int32_t O = cum(r_of(kAgain ? o : o + q[kAgain ? 0 : r][v]));
+      if (O > p && i + v < n32) M[p] = i + v;
+      p = O;
+    }
+    __builtin_amdgcn_sched_barrier(0);  // one round's values in registers at a time
+  }
+  __syncthreads();
+  // expansion: the running maximum of the markers
+  int32_t m[G::kR][4], in[G::kR];
+#pragma unroll
+  for (int r = 0; r < G::kR; ++r) {
+    const int4 t = reinterpret_cast<const int4*>(M)[r * G::kThreads + tid];
+    m[r][0] = t.x;
+    m[r][1] = max(t.y, m[r][0]);
+    m[r][2] = max(t.z, m[r][1]);
+    m[r][3] = max(t.w, m[r][2]);
+    in[r] = wave_incl_max_i32(m[r][3]);
+    if (lane == kWave - 1) s_top[r * G::kW + wave] = in[r];
+  }
+  __syncthreads();
+  const int32_t tops = wave_incl_max_i32(lane < G::kParts ? s_top[lane] : -1);
+#pragma unroll
+  for (int r = 0; r < G::kR; ++r) {
+    const int part = r * G::kW + wave;
+    const int32_t upto =
+        part > 0 ? (int32_t)__builtin_amdgcn_readlane(tops, part - 1) : -1;
+    const int32_t before = max(upto, (int32_t)wave_shift_up_u32((uint32_t)in[r], 0xFFFFFFFFu));
+    const uint32_t i = (uint32_t)(r * 4 * G::kThreads + 4 * tid);
+    if (i < (uint32_t)n32)
+      store_quad(a, i, (uint32_t)n32, max(m[r][0], before), max(m[r][1], before),
+                 max(m[r][2], before), max(m[r][3], before));
+  }
 }
 
 // ---------------------------------------------------------------- Code 5
@@ -1269,8 +1779,9 @@ struct BatchLds {
 template <typename T, int SCHEME>
 __global__ __launch_bounds__(kT) void k_scan_batched(const T* __restrict__ w, int64_t n_total,
                                                      const int64_t* __restrict__ offsets,
-                                                     uint32_t n_filters, Key key, uint32_t offset,
-                                                     uint32_t filter_base, int32_t* __restrict__ a,
+                                                     uint32_t n_filters, int64_t above, Key key,
+                                                     uint32_t offset, uint32_t filter_base,
+                                                     int32_t* __restrict__ a,
                                                      uint32_t* __restrict__ flags) {
   offset = counter_offset(key, offset);
   __shared__ BatchLds B;
@@ -1280,7 +1791,7 @@ __global__ __launch_bounds__(kT) void k_scan_batched(const T* __restrict__ w, in
   const int tid = (int)threadIdx.x;
   const int64_t base = offsets ? offsets[f] : 0;
   const int64_t n = offsets ? offsets[f + 1] - base : n_total;
-  if (n <= 0) return;
+  if (n <= above) return;  // empty, or another launch's segment
   const T* __restrict__ ws = w + base;
   int32_t* __restrict__ as = a + base;
   const uint32_t filt = filter_base + f;
@@ -1323,8 +1834,7 @@ __global__ __launch_bounds__(kT) void k_scan_batched(const T* __restrict__ w, in
     for (uint32_t b = wave; b < nb; b += kWavesPerWG)
       emit_block_wave<T, SCHEME == SCHEME_SYSTEMATIC>(ws, n, (int64_t)b * kBlock, B.recs[b],
                                                        B.C[b], B.C[b + 1], t.gscale, t.Q, key,
-                                                       filt, offset, as, &L[wave], nullptr,
-                                                       nullptr);
+                                                       filt, offset, as, &L[wave], nullptr);
   }
 }
 
@@ -1490,7 +2000,7 @@ __global__ __launch_bounds__(kT) void k_seg_emit_w(
   const u128* Cs = C + bstart[f] + f;
   emit_block_wave<T, SCHEME == SCHEME_SYSTEMATIC>(w + base, n, P0, recs[g], Cs[b], Cs[b + 1],
                                                    hdr[f].gscale, hdr[f].Q, key, filter_base + f,
-                                                   offset, as, &L[wave], nullptr, nullptr);
+                                                   offset, as, &L[wave], nullptr);
 }
 
 // Multinomial emission of the segmented batch, one block per wave.
@@ -1558,7 +2068,7 @@ hipError_t launch_carries(const CarrySet& c, ScanHeader* hdr, const BlockRec* re
 template <typename T, int SCHEME>
 hipError_t launch_scan_t(const void* wv, int64_t n, Key key, uint32_t offset, uint32_t filter,
                          int32_t* a, void* ws, uint32_t* flags, hipStream_t stream,
-                         int32_t* d_out = nullptr, int32_t* e_out = nullptr) {
+                         uint32_t* claim = nullptr) {
   const T* w = (const T*)wv;
   constexpr bool multi = SCHEME == SCHEME_MULTINOMIAL;
   const ScanLayout L = scan_layout(n, multi);
@@ -1577,8 +2087,8 @@ hipError_t launch_scan_t(const void* wv, int64_t n, Key key, uint32_t offset, ui
   if (e != hipSuccess) return e;
   if constexpr (!multi) {
     if (nb <= (uint32_t)tuning().direct_max_blocks && nb <= kDirectMax) {
-      hipLaunchKernelGGL((k_scan_emit_w<T, SCHEME, true>), dim3(wgs_b), dim3(kT), 0, stream, w,
-                         n, nb, key, offset, filter, hdr, recs, cs.C, a, flags, d_out, e_out);
+      hipLaunchKernelGGL((k_scan_emit_b<T, SCHEME, true>), dim3(nb), dim3(kT), 0, stream, w, n,
+                         nb, key, offset, filter, recs, cs.C, a, flags, claim);
       return hipGetLastError();
     }
   }
@@ -1587,10 +2097,10 @@ hipError_t launch_scan_t(const void* wv, int64_t n, Key key, uint32_t offset, ui
   if constexpr (multi) {
     hipLaunchKernelGGL((k_scan_emit_mw<T>), dim3(wgs_b), dim3(kT), 0, stream, w, n, nb, nbe, key,
                        offset, filter, hdr, recs, cs.C, cs.CE, (const uint64_t*)evals, a, flags,
-                       d_out, e_out);
+                       claim);
   } else {
-    hipLaunchKernelGGL((k_scan_emit_w<T, SCHEME, false>), dim3(wgs_b), dim3(kT), 0, stream, w,
-                       n, nb, key, offset, filter, hdr, recs, cs.C, a, flags, d_out, e_out);
+    hipLaunchKernelGGL((k_scan_emit_w<T, SCHEME>), dim3(wgs_b), dim3(kT), 0, stream, w,
+                       n, nb, key, offset, filter, hdr, recs, cs.C, a, flags, claim);
   }
   return hipGetLastError();
 }
@@ -1609,30 +2119,56 @@ hipError_t launch_scan_scheme(int scheme, const void* w, int64_t n, Key key, uin
   }
 }
 
+// One workgroup per segment (or for one vector): the strata schemes in tiers
+// of segment length, the multinomial scheme and longer segments through
+// k_scan_batched.  max_len: longest segment (0 = unknown).
+template <typename T, int SCHEME>
+hipError_t launch_batched_t(const T* w, int64_t n_total, const int64_t* offsets,
+                            uint32_t n_filters, int64_t max_len, Key key, uint32_t offset,
+                            uint32_t filter_base, int32_t* a, uint32_t* flags,
+                            hipStream_t stream) {
+  int64_t above = 0;
+  if constexpr (SCHEME != SCHEME_MULTINOMIAL) {
+    if (!offsets) max_len = n_total;
+    const bool equal = max_len > 0 && max_len * (int64_t)n_filters == n_total;
+    auto tier = [&](auto kernel, int threads, int64_t upto) {
+      // a tier is left to the next one where every segment is longer, or where
+      // few segments would only add launches
+      if (max_len > 0 && above >= max_len) return;
+      if ((max_len <= 0 || max_len > upto) && (equal || (upto < kOneWgMax && n_filters <= 256)))
+        return;
+      hipLaunchKernelGGL(kernel, dim3(n_filters), dim3(threads), 0, stream, w, n_total, offsets,
+                         above, key, offset, filter_base, a, flags);
+      above = upto;
+    };
+    tier(k_scan_one<T, SCHEME, 1>, OneWg<1>::kThreads, 1024);
+    tier(k_scan_one<T, SCHEME, 4>, OneWg<4>::kThreads, 4096);
+    tier(k_scan_one<T, SCHEME, 16>, OneWg<16>::kThreads, kOneWgMax);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || (max_len > 0 && max_len <= kOneWgMax)) return e;
+  }
+  hipLaunchKernelGGL((k_scan_batched<T, SCHEME>), dim3(n_filters), dim3(kT), 0, stream, w, n_total,
+                     offsets, n_filters, above, key, offset, filter_base, a, flags);
+  return hipGetLastError();
+}
+
 template <typename T>
 hipError_t launch_batched_scheme(int scheme, const void* w, int64_t n_total,
-                                 const int64_t* offsets, uint32_t n_filters, Key key,
-                                 uint32_t offset, uint32_t filter_base, int32_t* a,
+                                 const int64_t* offsets, uint32_t n_filters, int64_t max_len,
+                                 Key key, uint32_t offset, uint32_t filter_base, int32_t* a,
                                  uint32_t* flags, hipStream_t stream) {
   const T* wt = (const T*)w;
   switch (scheme) {
     case SCHEME_MULTINOMIAL:
-      hipLaunchKernelGGL((k_scan_batched<T, SCHEME_MULTINOMIAL>), dim3(n_filters), dim3(kT), 0,
-                         stream, wt, n_total, offsets, n_filters, key, offset, filter_base, a,
-                         flags);
-      break;
+      return launch_batched_t<T, SCHEME_MULTINOMIAL>(wt, n_total, offsets, n_filters, max_len, key,
+                                                     offset, filter_base, a, flags, stream);
     case SCHEME_STRATIFIED:
-      hipLaunchKernelGGL((k_scan_batched<T, SCHEME_STRATIFIED>), dim3(n_filters), dim3(kT), 0,
-                         stream, wt, n_total, offsets, n_filters, key, offset, filter_base, a,
-                         flags);
-      break;
+      return launch_batched_t<T, SCHEME_STRATIFIED>(wt, n_total, offsets, n_filters, max_len, key,
+                                                    offset, filter_base, a, flags, stream);
     default:
-      hipLaunchKernelGGL((k_scan_batched<T, SCHEME_SYSTEMATIC>), dim3(n_filters), dim3(kT), 0,
-                         stream, wt, n_total, offsets, n_filters, key, offset, filter_base, a,
-                         flags);
-      break;
+      return launch_batched_t<T, SCHEME_SYSTEMATIC>(wt, n_total, offsets, n_filters, max_len, key,
+                                                    offset, filter_base, a, flags, stream);
   }
-  return hipGetLastError();
 }
 
 template <typename T, int SCHEME>
@@ -1831,33 +2367,33 @@ hipError_t launch_multinomial_iid(bool f64, const void* w, int64_t n, Key key, u
 
 hipError_t launch_scan_claimed(int scheme, bool f64, const void* w, int64_t n, Key key,
                                uint32_t offset, uint32_t filter, int32_t* a, void* ws,
-                               uint32_t* flags, int32_t* d, int32_t* e, hipStream_t stream) {
+                               uint32_t* flags, uint32_t* claim, hipStream_t stream) {
   if (scheme == SCHEME_MULTINOMIAL)
     return f64 ? launch_scan_t<double, SCHEME_MULTINOMIAL>(w, n, key, offset, filter, a, ws,
-                                                           flags, stream, d, e)
+                                                           flags, stream, claim)
                : launch_scan_t<float, SCHEME_MULTINOMIAL>(w, n, key, offset, filter, a, ws, flags,
-                                                          stream, d, e);
+                                                          stream, claim);
   if (scheme == SCHEME_STRATIFIED)
     return f64 ? launch_scan_t<double, SCHEME_STRATIFIED>(w, n, key, offset, filter, a, ws, flags,
-                                                          stream, d, e)
+                                                          stream, claim)
                : launch_scan_t<float, SCHEME_STRATIFIED>(w, n, key, offset, filter, a, ws, flags,
-                                                         stream, d, e);
+                                                         stream, claim);
   if (scheme == SCHEME_SYSTEMATIC)
     return f64 ? launch_scan_t<double, SCHEME_SYSTEMATIC>(w, n, key, offset, filter, a, ws, flags,
-                                                          stream, d, e)
+                                                          stream, claim)
                : launch_scan_t<float, SCHEME_SYSTEMATIC>(w, n, key, offset, filter, a, ws, flags,
-                                                         stream, d, e);
+                                                         stream, claim);
   return hipErrorInvalidValue;
 }
 
 hipError_t launch_scan_batched(int scheme, bool f64, const void* w, int64_t n_total,
-                               const int64_t* offsets, uint32_t n_filters, Key key,
-                               uint32_t offset, uint32_t filter_base, int32_t* a, uint32_t* flags,
-                               hipStream_t stream) {
-  return f64 ? launch_batched_scheme<double>(scheme, w, n_total, offsets, n_filters, key, offset,
-                                             filter_base, a, flags, stream)
-             : launch_batched_scheme<float>(scheme, w, n_total, offsets, n_filters, key, offset,
-                                            filter_base, a, flags, stream);
+                               const int64_t* offsets, uint32_t n_filters, int64_t max_len,
+                               Key key, uint32_t offset, uint32_t filter_base, int32_t* a,
+                               uint32_t* flags, hipStream_t stream) {
+  return f64 ? launch_batched_scheme<double>(scheme, w, n_total, offsets, n_filters, max_len, key,
+                                             offset, filter_base, a, flags, stream)
+             : launch_batched_scheme<float>(scheme, w, n_total, offsets, n_filters, max_len, key,
+                                            offset, filter_base, a, flags, stream);
 }
 
 }  // namespace pfr

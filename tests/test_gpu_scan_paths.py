@@ -1,0 +1,112 @@
+"""The paths of the stratified and systematic schemes give the same bits: one
+workgroup per vector or segment (up to 1024, 4096 and 16384 weights), one block
+per workgroup with its own carries, and records, carries and one block per
+wave, at the edges of their ranges; and the resolve pass over a sorted
+ancestry, inside and outside its LDS window, is Code 10."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1301_4019_amd import inputs
+from test_gpu_parity import dev, host, new_flags, pfr
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+SCHEMES = ("stratified", "systematic")
+GENERAL = {"single_wg_max": 0, "direct_max_blocks": 0, "batch_scan_wg_max_len": 0}
+
+
+def general(scheme, w, **kw):
+    """The result of records, carries and one block per wave."""
+    m = pfr()
+    saved = m.get_tuning()
+    try:
+        m.set_tuning(**GENERAL)
+        return host(getattr(m, "resample_" + scheme)(w, **kw))
+    finally:
+        m.set_tuning(**saved)
+
+
+def weights(kind, n, dtype):
+    g = np.random.default_rng(n)
+    if kind == "wide":  # blocks 2^40 apart, zeros, a run of zero blocks
+        w = np.ldexp(g.random(n) + 0.5, g.integers(-20, 20, n))
+        w *= np.ldexp(1.0, g.integers(-20, 20, (n + 1023) // 1024)).repeat(1024)[:n]
+        w[g.random(n) < 0.3] = 0
+        w[n // 3:n // 2] = 0
+        if not w.any():
+            w[0] = 1
+        return w.astype(dtype)
+    if kind == "one":  # all the mass on one weight
+        w = np.zeros(n, dtype)
+        w[n // 2] = 3
+        return w
+    return inputs.weights(n, kind, seed=n, dtype=dtype)
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("n", [1, 5, 1023, 1024, 1025, 4095, 4096, 4097, 70001, 262144, 262145,
+                               524289, 1048575, 1048576, 1048577])
+def test_single_vector_paths_agree(n, dtype):
+    for kind in (0.0, 4.0, "wide", "one"):
+        w = dev(weights(kind, n, dtype))
+        for s in SCHEMES:
+            a = host(getattr(pfr(), "resample_" + s)(w, seed=7, offset=n & 3, filter_base=2))
+            ref = general(s, w, seed=7, offset=n & 3, filter_base=2)
+            assert np.array_equal(a, ref), (kind, s)
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("filters", [3, 40])
+@pytest.mark.parametrize("with_max_len", [True, False])
+def test_segment_tiers_agree_with_single_calls(filters, dtype, with_max_len):
+    sizes = ([1, 0, 1024, 1025, 3, 4096, 4097, 16384, 1000, 16383, 2049] * 4)[:filters]
+    if filters == 40:
+        sizes += [1] * 300  # more segments than one round of workgroups
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    kinds = [0.0, 4.0, "wide", "one", 2.0]
+    w = np.concatenate([weights(kinds[f % 5], n, dtype) if n else np.zeros(0, dtype)
+                        for f, n in enumerate(sizes)])
+    for s in SCHEMES:
+        a = host(getattr(pfr(), "resample_" + s)(dev(w), seed=3, filter_base=1, offsets=dev(off),
+                                                 max_len=max(sizes) if with_max_len else None))
+        for f, n in enumerate(sizes):
+            if n:
+                ref = general(s, dev(w[off[f]:off[f + 1]]), seed=3, filter_base=1 + f)
+                assert np.array_equal(a[off[f]:off[f + 1]], ref), (s, f, n)
+
+
+def test_bad_and_zero_segments_give_the_identity():
+    sizes = [1000, 4000, 16000, 300, 5000]
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    w = np.concatenate([weights(1.0, n, np.float32) for n in sizes])
+    w[10] = np.nan
+    w[off[1]:off[2]] = 0
+    w[off[3] - 1] = -1
+    for s in SCHEMES:
+        fl = new_flags()
+        a = host(getattr(pfr(), "resample_" + s)(dev(w), offsets=dev(off), max_len=16000, flags=fl))
+        for f in (0, 1, 2):
+            assert np.array_equal(a[off[f]:off[f + 1]], np.arange(sizes[f])), f
+        for f in (3, 4):
+            ref = general(s, dev(w[off[f]:off[f + 1]]), filter_base=f)
+            assert np.array_equal(a[off[f]:off[f + 1]], ref), f
+        m = pfr()
+        assert int(host(fl)[0]) == m.FLAG_BAD_WEIGHTS | m.FLAG_ZERO_TOTAL
+
+
+@pytest.mark.parametrize("scheme", ["stratified", "systematic", "multinomial"])
+@pytest.mark.parametrize("n", [4097, 8191, 8192, 65537, 1 << 20, (1 << 21) - 1, 1 << 21,
+                               (1 << 21) + 1])
+def test_resolve_of_the_fused_claim(scheme, n):
+    """The fused permutation of sorted ancestries whose chains stay near their
+    start, drift out of the window, or do not move."""
+    g = np.random.default_rng(3)
+    half = np.where(np.arange(n) < n // 2, 0.01, 1.0)  # drifts by n / 2
+    for w in (inputs.weights(n, 0.0, seed=1), inputs.weights(n, 3.0, seed=2),
+              (half * (g.random(n) + 0.5)).astype(np.float32), np.ones(n, np.float32),
+              np.zeros(n, np.float32)):
+        a, c = pfr().resample_permuted(scheme, dev(w), seed=5)
+        a, c = host(a), host(c)
+        assert np.array_equal(c, oracle.permute(a)[0])
