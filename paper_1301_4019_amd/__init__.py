@@ -15,6 +15,7 @@ from __future__ import annotations
 
 import collections
 import ctypes
+import functools
 import os
 
 from . import _lib
@@ -35,9 +36,17 @@ __all__ = [
 ]
 
 
+_TORCH = None
+
+
 def _torch():
-    import torch
-    return torch
+    """torch, imported by the first call that needs it (an import statement in
+    every call would cost as much as a small kernel)."""
+    global _TORCH
+    if _TORCH is None:
+        import torch
+        _TORCH = torch
+    return _TORCH
 
 
 def version() -> str:
@@ -87,11 +96,17 @@ def default_tuning() -> dict:
 
 
 def _stream():
-    return ctypes.c_void_p(_torch().cuda.current_stream().cuda_stream)
+    """The current stream of the current device, as the address the library
+    takes (without building torch's Stream object where torch offers that)."""
+    c = _torch()._C
+    raw = getattr(c, "_cuda_getCurrentRawStream", None)
+    if raw is None:
+        return _torch().cuda.current_stream().cuda_stream
+    return raw(c._cuda_getDevice())
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _dtype_code(w):
@@ -109,9 +124,15 @@ def _require_cuda(*ts):
             raise ValueError("tensors must be contiguous GPU tensors")
 
 
+@functools.lru_cache(maxsize=1024)
+def _one_segment(n_total):
+    """One vector of n_total particles (never written after it is built)."""
+    return _lib.Segments(n_total, 1, None, n_total)
+
+
 def _segments(n_total, offsets=None, max_len=None):
     if offsets is None:
-        return _lib.Segments(int(n_total), 1, None, int(n_total))
+        return _one_segment(int(n_total))
     _require_cuda(offsets)
     torch = _torch()
     if offsets.dtype != torch.int64:
@@ -173,10 +194,6 @@ class _WorkspaceCache:
 _WS_CACHE = _WorkspaceCache(int(os.environ.get("PFR_WS_CACHE_BYTES", 4 << 30)))
 
 
-def _stream_key():
-    return _torch().cuda.current_stream().cuda_stream
-
-
 def workspace_bytes(op: int, n_total: int, offsets=None, max_len=None, dtype_code=0) -> int:
     seg = _segments(n_total, offsets, max_len)
     return int(_lib.load().pfr_workspace_bytes(op, ctypes.byref(seg), dtype_code))
@@ -191,18 +208,20 @@ def new_workspace(nbytes: int, device=None):
     return ws
 
 
-def _workspace(op, seg, dtype_code, device, ws):
-    need = int(_lib.load().pfr_workspace_bytes(op, ctypes.byref(seg), dtype_code))
+def _workspace(op, seg, dtype_code, device, ws, stream):
+    """(workspace, its bytes): the caller's, or the cached one of this device,
+    stream (the current one), operation and size."""
     if ws is not None:
-        return ws, need
+        return ws, ws.numel()
+    need = _lib.load().pfr_workspace_bytes(op, ctypes.byref(seg), dtype_code)
     if need == 0:
         return None, 0
-    key = (str(device), _stream_key(), op, need)
+    key = (device, stream, op, need)
     cached = _WS_CACHE.get(key)
     if cached is None:
         cached = new_workspace(need, device)
         _WS_CACHE.put(key, cached)
-    return cached, need
+    return cached, cached.numel()
 
 
 def _out_like(n, device, out):
@@ -221,10 +240,11 @@ def _collective(fn_name, op, w, seed, offset, filter_base, precision, offsets, m
     dt = _dtype_code(w)
     seg = _segments(w.numel(), offsets, max_len)
     a = _out_like(w.numel(), w.device, out)
-    ws, _ = _workspace(op, seg, dt, w.device, workspace)
+    stream = _stream()
+    ws, ws_bytes = _workspace(op, seg, dt, w.device, workspace, stream)
     fn = getattr(_lib.load(), fn_name)
     rc = fn(_ptr(w), dt, ctypes.byref(seg), int(precision), _rng(seed, offset, filter_base),
-            _ptr(a), _ptr(ws), 0 if ws is None else ws.numel(), _ptr(flags), _stream())
+            _ptr(a), _ptr(ws), ws_bytes, _ptr(flags), stream)
     _lib.check(rc, fn_name)
     return a
 
@@ -244,11 +264,12 @@ def resample_multinomial_iid(w, seed=0, offset=0, filter_base=0, out=None, flags
     dt = _dtype_code(w)
     seg = _segments(w.numel())
     a = _out_like(w.numel(), w.device, out)
-    ws, _ = _workspace(_lib.OP_MULTINOMIAL_IID, seg, dt, w.device, workspace)
+    stream = _stream()
+    ws, ws_bytes = _workspace(_lib.OP_MULTINOMIAL_IID, seg, dt, w.device, workspace, stream)
     rc = _lib.load().resample_multinomial_iid(_ptr(w), dt, ctypes.byref(seg),
                                               _rng(seed, offset, filter_base), _ptr(a), _ptr(ws),
-                                              0 if ws is None else ws.numel(), _ptr(flags),
-                                              _stream())
+                                              ws_bytes, _ptr(flags),
+                                              stream)
     _lib.check(rc, "resample_multinomial_iid")
     return a
 
@@ -275,11 +296,12 @@ def resample_metropolis(w, B, seed=0, offset=0, filter_base=0, B_per_filter=None
     seg = _segments(w.numel(), offsets, max_len)
     _per_segment(B_per_filter, "int32", seg, "B_per_filter")
     a = _out_like(w.numel(), w.device, out)
-    ws, _ = _workspace(_lib.OP_METROPOLIS, seg, dt, w.device, workspace)
+    stream = _stream()
+    ws, ws_bytes = _workspace(_lib.OP_METROPOLIS, seg, dt, w.device, workspace, stream)
     rc = _lib.load().resample_metropolis(_ptr(w), dt, ctypes.byref(seg), int(B),
                                          _ptr(B_per_filter), _rng(seed, offset, filter_base),
-                                         _ptr(a), _ptr(ws), 0 if ws is None else ws.numel(),
-                                         _stream())
+                                         _ptr(a), _ptr(ws), ws_bytes,
+                                         stream)
     _lib.check(rc, "resample_metropolis")
     return a
 
@@ -293,12 +315,13 @@ def resample_rejection(w, w_max, seed=0, offset=0, filter_base=0, max_trials=1 <
     seg = _segments(w.numel(), offsets, max_len)
     _per_segment(w_max_per_filter, "float64", seg, "w_max_per_filter")
     a = _out_like(w.numel(), w.device, out)
-    ws, _ = _workspace(_lib.OP_REJECTION, seg, dt, w.device, workspace)
+    stream = _stream()
+    ws, ws_bytes = _workspace(_lib.OP_REJECTION, seg, dt, w.device, workspace, stream)
     rc = _lib.load().resample_rejection(_ptr(w), dt, ctypes.byref(seg), float(w_max),
                                         _ptr(w_max_per_filter), int(max_trials),
                                         _rng(seed, offset, filter_base), _ptr(a), _ptr(ws),
-                                        0 if ws is None else ws.numel(), _ptr(flags),
-                                        _stream())
+                                        ws_bytes, _ptr(flags),
+                                        stream)
     _lib.check(rc, "resample_rejection")
     return a
 
@@ -319,13 +342,14 @@ def resample_partial_rejection(w, v_max, seed=0, offset=0, filter_base=0, max_tr
         weights_out = torch.empty_like(w)
     elif weights_out.dtype != w.dtype or weights_out.numel() != w.numel():
         raise ValueError("weights_out must match the weights' type and size")
-    ws, _ = _workspace(_lib.OP_REJECTION, seg, dt, w.device, workspace)
+    stream = _stream()
+    ws, ws_bytes = _workspace(_lib.OP_REJECTION, seg, dt, w.device, workspace, stream)
     rc = _lib.load().resample_partial_rejection(_ptr(w), dt, ctypes.byref(seg), float(v_max),
                                                 _ptr(v_max_per_filter), int(max_trials),
                                                 _rng(seed, offset, filter_base), _ptr(a),
                                                 _ptr(weights_out), _ptr(ws),
-                                                0 if ws is None else ws.numel(), _ptr(flags),
-                                                _stream())
+                                                ws_bytes, _ptr(flags),
+                                                stream)
     _lib.check(rc, "resample_partial_rejection")
     return a, weights_out
 
@@ -348,8 +372,9 @@ def resample_permuted(scheme, w, seed=0, offset=0, filter_base=0, precision=SCAN
     c = _out_like(w.numel(), w.device, permuted)
     lib = _lib.load()
     need = int(lib.pfr_resample_permuted_workspace_bytes(op, ctypes.byref(seg), dt))
+    stream = _stream()
     if workspace is None:
-        key = (str(w.device), _stream_key(), "permuted", op, need)
+        key = (w.device, stream, "permuted", op, need)
         workspace = _WS_CACHE.get(key)
         if workspace is None:
             workspace = new_workspace(need, w.device)
@@ -360,7 +385,7 @@ def resample_permuted(scheme, w, seed=0, offset=0, filter_base=0, precision=SCAN
                                int(max_trials))
     rc = lib.resample_permuted(op, _ptr(w), dt, ctypes.byref(seg), ctypes.byref(params),
                                _rng(seed, offset, filter_base), _ptr(a), _ptr(c), _ptr(workspace),
-                               workspace.numel(), _ptr(flags), _stream())
+                               workspace.numel(), _ptr(flags), stream)
     _lib.check(rc, "resample_permuted")
     return a, c
 
@@ -373,10 +398,11 @@ def offspring_to_ancestors(o, offsets=None, max_len=None, out=None, flags=None, 
         raise TypeError("offspring must be int32")
     seg = _segments(o.numel(), offsets, max_len)
     a = _out_like(o.numel(), o.device, out)
-    ws, _ = _workspace(_lib.OP_OFFSPRING_TO_ANCESTORS, seg, 0, o.device, workspace)
+    stream = _stream()
+    ws, ws_bytes = _workspace(_lib.OP_OFFSPRING_TO_ANCESTORS, seg, 0, o.device, workspace, stream)
     rc = _lib.load().offspring_to_ancestors(_ptr(o), ctypes.byref(seg), _ptr(a), _ptr(ws),
-                                            0 if ws is None else ws.numel(), _ptr(flags),
-                                            _stream())
+                                            ws_bytes, _ptr(flags),
+                                            stream)
     _lib.check(rc, "offspring_to_ancestors")
     return a
 
@@ -390,10 +416,11 @@ def permute_ancestors(a, sorted_hint=False, offsets=None, max_len=None, out=None
         raise TypeError("ancestors must be int32")
     seg = _segments(a.numel(), offsets, max_len)
     c = _out_like(a.numel(), a.device, out)
-    ws, _ = _workspace(_lib.OP_PERMUTE, seg, 0, a.device, workspace)
+    stream = _stream()
+    ws, ws_bytes = _workspace(_lib.OP_PERMUTE, seg, 0, a.device, workspace, stream)
     rc = _lib.load().permute_ancestors(_ptr(a), ctypes.byref(seg), 1 if sorted_hint else 0,
-                                       _ptr(c), _ptr(ws), 0 if ws is None else ws.numel(),
-                                       _ptr(flags), _stream())
+                                       _ptr(c), _ptr(ws), ws_bytes,
+                                       _ptr(flags), stream)
     _lib.check(rc, "permute_ancestors")
     return c
 
@@ -427,10 +454,11 @@ def scaled_prefix(w, precision=SCAN_EXACT, out=None, flags=None, workspace=None)
     if r.dtype != torch.float64 or r.numel() != w.numel():
         raise ValueError("out must be a float64 tensor with one entry per particle")
     _require_cuda(r)
-    ws, _ = _workspace(_lib.OP_SCALED_PREFIX, seg, dt, w.device, workspace)
+    stream = _stream()
+    ws, ws_bytes = _workspace(_lib.OP_SCALED_PREFIX, seg, dt, w.device, workspace, stream)
     rc = _lib.load().pfr_scaled_prefix(_ptr(w), dt, ctypes.byref(seg), int(precision), _ptr(r),
-                                       _ptr(ws), 0 if ws is None else ws.numel(), _ptr(flags),
-                                       _stream())
+                                       _ptr(ws), ws_bytes, _ptr(flags),
+                                       stream)
     _lib.check(rc, "pfr_scaled_prefix")
     return r
 
@@ -462,10 +490,11 @@ def effective_sample_size(w, offsets=None, max_len=None, out=None, flags=None, w
         out = torch.empty(nf, dtype=torch.float64, device=w.device)
     elif out.dtype != torch.float64 or out.numel() != nf:
         raise ValueError("out must be a float64 tensor with one entry per segment")
-    ws, _ = _workspace(_lib.OP_ESS, seg, dt, w.device, workspace)
+    stream = _stream()
+    ws, ws_bytes = _workspace(_lib.OP_ESS, seg, dt, w.device, workspace, stream)
     rc = _lib.load().effective_sample_size(_ptr(w), dt, ctypes.byref(seg), _ptr(out), _ptr(ws),
-                                           0 if ws is None else ws.numel(), _ptr(flags),
-                                           _stream())
+                                           ws_bytes, _ptr(flags),
+                                           stream)
     _lib.check(rc, "effective_sample_size")
     return out
 
