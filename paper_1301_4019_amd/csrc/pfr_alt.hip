@@ -196,6 +196,7 @@ __global__ __launch_bounds__(kCodeThreads) void k_bound_codes(const T* __restric
 }
 
 struct BoundTable {
+  static constexpr bool kUsed = true;
   const uint8_t* nib;  // LDS, two 4-bit codes per byte
   int shift;
   // high word of the binary64 bound 2^(cM - 127) of the largest bucket, or
@@ -328,6 +329,7 @@ __device__ __forceinline__ uint32_t bound16(double v) {
 
 template <typename T>
 struct CodeTable {
+  static constexpr bool kUsed = true;
   const uint16_t* code;  // LDS
   uint32_t shift;        // particle j's bound is code[j >> shift]
   // True when p = fl(u w_k) shows u w_k > w_j: the high word of p (as a signed
@@ -617,224 +619,193 @@ __global__ __launch_bounds__(THREADS) void k_metropolis_staged(
 // rejections the particle keeps a_i = i and FLAG_TRIAL_CAP is raised.
 //
 // Scheduling (the variable task-length problem of the paper's section 2.2):
-// every wave owns a contiguous range of particles.  While the range lasts, a
-// lane that finishes takes the next particle of the range (ballot + prefix
-// count, no atomics).  When the range is used up, the particles still running
-// share all 64 lanes: each gets 64/m lanes (m = particles left) that try
-// consecutive trials of it at once, and the lowest accepting trial wins.
+// the waves of a workgroup hand out its particles among themselves through an
+// LDS counter, a wave taking as many as it has free lanes, so that none runs
+// out of work while another still holds a long range.  When the particles are
+// used up, those still running in a wave share all its lanes: compacted to the
+// first m lanes, each gets 64 / m lanes (shares that differ by at most one) that
+// try consecutive trials of it at once, and the lowest accepting trial wins.
 // That is the same answer as trying the trials one by one, so the output does
-// not depend on the schedule, and the slowest particle of a wave no longer
-// runs alone on one lane.
+// not depend on the schedule, and the slowest particle of a wave does not run
+// alone on one lane.
+constexpr int kRejBatch = 4;  // trials per lane and pass while acceptance is rare
+constexpr uint32_t kNoParticle = 0xFFFFFFFFu;
 
-// position of the q-th set bit (0-based) of mask, which has more than q bits
-__device__ __forceinline__ int nth_set_bit(uint64_t mask, int q) {
-  int pos = 0;
+// No bound table: every weight is read (from LDS, or from global memory).
+struct NoTable {
+  static constexpr bool kUsed = false;
+};
+
+// Trials t .. t + NQ - 1 of particle i: true when one accepts, j the lowest
+// accepting one's proposal.  The draws, then the table checks, then the weight
+// loads together, then the decisions: one wait per pass.  With a table, a
+// trial that needs no load reads nothing (an out-of-range buffer offset).
+// TINY: the bound may lie below 2^-900, where a difference can round to zero
+// (accept_exact); elsewhere one fused multiply-add decides.
+template <int NQ, bool TINY, typename T, typename Table>
+__device__ __forceinline__ bool rejection_try(const T* ws, __amdgpu_buffer_rsrc_t wv, uint32_t i,
+                                              uint32_t t, uint32_t n, uint32_t filt, double wmax,
+                                              uint32_t max_trials, Key key, uint32_t offset,
+                                              const Table& tab, uint32_t& j) {
+  const uint32_t left = t < max_trials ? max_trials - t : 0u;
+  uint32_t jq[NQ];
+  double uq[NQ], vq[NQ];
+  bool live[NQ];
 #pragma unroll
-  for (int width = 32; width >= 1; width >>= 1) {
-    const uint64_t low = mask & ((1ull << width) - 1ull);
-    const int cnt = __popcll(low);
-    if (q >= cnt) {
-      q -= cnt;
-      mask >>= width;
-      pos += width;
-    }
+  for (int q = 0; q < NQ; ++q) {
+    const uint4 x = draw(key, i, DOM_TRIAL, t + (uint32_t)q, filt, offset);
+    jq[q] = index_draw(x.x, x.y, n);
+    if (q == 0) jq[q] = t == 0 ? i : jq[q];
+    uq[q] = u_accept(x.z);
+    live[q] = (uint32_t)q < left;
+    if constexpr (Table::kUsed) live[q] = live[q] & !tab.rejects(uq[q], wmax, jq[q]);
   }
-  return pos;
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+    if constexpr (Table::kUsed)
+      vq[q] = (double)buffer_gather<T>(wv, live[q] ? jq[q] * (uint32_t)sizeof(T) : kNoLoad);
+    else
+      vq[q] = (double)ws[jq[q]];
+  }
+  bool any = false;
+#pragma unroll
+  for (int q = NQ - 1; q >= 0; --q) {
+    const bool acc =
+        live[q] & (TINY ? accept_exact<double>(uq[q], wmax, vq[q])
+                        : __fma_rn(uq[q], wmax, -vq[q]) <= 0.0);
+    j = acc ? jq[q] : j;
+    any |= acc;
+  }
+  return any;
 }
 
-// One wave works through the particles [r0, r1) (global indices) of one
-// segment (weights ws, length n, filter id filt).  With a queue (an LDS
-// counter shared by the workgroup's waves, starting at 0) the waves hand out
-// the particles of [r0, r1) among themselves, so that none runs out of work
-// while another still holds a long range: a wave takes as many particles as
-// it has free lanes.  (Pieces of about four passes' worth, to wait on the
-// counter less often, were slower: the waves then ran out unevenly.)
-// With TABLE, a trial whose u * w_max exceeds the bucket bound of j is
-// rejected without loading w_j.
-constexpr int kRejBatch = 4;  // trials per lane and pass (past the first pass)
-template <bool TABLE, typename T>
-__device__ void rejection_wave_range(const T* ws, int64_t base, uint32_t n, uint32_t filt,
-                                     double wmax, int64_t r0, int64_t r1, uint32_t max_trials,
-                                     Key key, uint32_t offset, int32_t* __restrict__ a,
-                                     uint32_t& my_flags, const BoundTable& tab,
-                                     uint32_t* queue = nullptr) {
-  const uint32_t lane = lane_id();
-  // table kernels: ws is a global vector of n * sizeof(T) < 2^31 bytes
-  const __amdgpu_buffer_rsrc_t wv = buffer_view(ws, TABLE ? n * (uint32_t)sizeof(T) : 0u);
-  int64_t next = r0;  // wave-uniform: next particle of the range to hand out
-  int64_t cur = -1;   // particle (global index) this lane works on
-  uint32_t t = 0;     // its next trial
+// floor(x / m) = x kShareMagic[m] >> 18 for x <= 4095, m <= 64 (x m < 2^18)
+struct ShareMagic {
+  uint32_t v[kWave + 1];
+};
+constexpr ShareMagic share_magic() {
+  ShareMagic s{};
+  for (uint32_t m = 1; m <= kWave; ++m) s.v[m] = (1u << 18) / m + 1u;
+  return s;
+}
+static __constant__ const ShareMagic kShare = share_magic();
 
-  // main phase: each pass tries trials t .. t + nq - 1 of every lane's
-  // particle, of which the lowest accepting one counts (as if they ran one by
-  // one).  nq is the same on every lane, so the wave never runs two code
-  // paths in one pass (a particle's trial 0 proposes j = i): 4 while the
-  // wave's acceptance rate so far is below 1/2 (long runs of rejections,
-  // where four trials share one pass's overhead), else 1 (acceptance is
-  // likely and further trials would be wasted draws and loads).
-  uint64_t tried = 0, accepted = 0;  // wave-uniform counts of this range
+// One wave works through the particles [i0, i1) (local indices) of one segment
+// (weights ws, length n, filter id filt, output as) together with the other
+// waves of its workgroup (queue: the LDS counter, 0 at the start).  VALU bound,
+// mostly by Philox, where acceptance is rare: 1024 vectors of 16000 binary32
+// weights at 1.8 % acceptance 621 G trials/s (2.04 ms), 467 with per-trial
+// conditions on the pass's length, the exact test's underflow branch and
+// 64-bit particle indices; at 70 %, where a pass is one trial and the queue,
+// 94 us against 176.  Even lane shares in the tail (64 / m, not its floor, and
+// no search for the m-th running lane) took 4096 vectors of 4000 from 3.16 to
+// 2.26 ms.
+template <bool TINY, typename T, typename Table>
+__device__ void rejection_wave_range(const T* ws, __amdgpu_buffer_rsrc_t wv, uint32_t n,
+                                     uint32_t filt, double wmax, uint32_t i0, uint32_t i1,
+                                     uint32_t max_trials, Key key, uint32_t offset,
+                                     int32_t* __restrict__ as, uint32_t& my_flags,
+                                     const Table& tab, uint32_t* queue) {
+  const uint32_t lane = lane_id();
+  const uint32_t len = i1 - i0;
+  uint32_t cur = kNoParticle;  // the particle this lane works on
+  uint32_t t = 0;              // its next trial
+  uint64_t tried = 0, accepted = 0;  // wave-uniform counts
+  auto rank_in = [](uint64_t mask) -> uint32_t {  // set bits below this lane
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
+                                     __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+  };
+  auto give_up = [&]() {  // the trial cap: the particle keeps its own index
+    as[cur] = (int32_t)cur;
+    my_flags |= FLAG_TRIAL_CAP;
+    cur = kNoParticle;
+  };
+
+  // main phase.  Each pass tries NQ trials of every lane's particle: 4 while
+  // the wave's acceptance rate so far is below 1/2 (long runs of rejections,
+  // where four trials share one pass's overhead), else 1 (further trials would
+  // be wasted draws and loads).  The results do not depend on it.
   while (true) {
-    const uint64_t freem = ballot(cur < 0);
-    if (freem != 0 && next < r1) {
-      const int64_t nfree = __popcll(freem);
-      if (queue) {  // the next nfree particles of the workgroup's range
-        uint32_t old = 0;
-        if (lane == 0) old = atomicAdd(queue, (uint32_t)nfree);
-        next = r0 + (int64_t)shfl(old, 0);
-      }
-      const int64_t avail = r1 - next > 0 ? r1 - next : 0;
-      const int64_t take = nfree < avail ? nfree : avail;
-      const int64_t rank = __popcll(freem & lanemask_lt());
-      if (cur < 0 && rank < take) {
-        cur = next + rank;
+    const uint64_t freem = ballot(cur == kNoParticle);
+    if (freem != 0) {
+      uint32_t old = 0;
+      if (lane == 0) old = atomicAdd(queue, (uint32_t)__popcll(freem));
+      const uint32_t next = uniform_u32(old);
+      const uint32_t mine = next + rank_in(freem);
+      if (cur == kNoParticle && mine < len) {
+        cur = i0 + mine;
         t = 0;
       }
-      // past the range: the queue is used up for every wave
-      next += queue ? nfree : take;
+      if (next + (uint32_t)__popcll(freem) >= len) break;  // used up for every wave
     }
-    if (next >= r1) break;
-    const int nq = accepted * 2u < tried ? kRejBatch : 1;  // (results do not depend on nq)
-    const uint64_t busy = ballot(cur >= 0);
     bool won = false;
-    if (cur >= 0) {
-      const uint32_t i = (uint32_t)(cur - base);
-      // the trials' draws, then their table checks, then their weight loads
-      // issued together, then the decisions: one wait per pass instead of one
-      // per trial.  A trial that needs no load reads nothing (table kernel: an
-      // out-of-range buffer offset) or re-reads the particle's own weight
-      // (staged kernels: an LDS read)
-      uint32_t jq[kRejBatch];
-      double uq[kRejBatch];
-      bool live[kRejBatch];
-#pragma unroll
-      for (int q = 0; q < kRejBatch; ++q) {
-        live[q] = false;
-        jq[q] = i;
-        uq[q] = 1.0;
-        if (q < nq) {
-          const uint4 x = draw(key, i, DOM_TRIAL, t + (uint32_t)q, filt, offset);
-          jq[q] = (q == 0 && t == 0) ? i : index_draw(x.x, x.y, n);
-          uq[q] = u_accept(x.z);
-          live[q] = (t + (uint32_t)q < max_trials) & !(TABLE && tab.rejects(uq[q], wmax, jq[q]));
-        }
-      }
-      double vq[kRejBatch];
-#pragma unroll
-      for (int q = 0; q < kRejBatch; ++q) {
-        if constexpr (TABLE)
-          vq[q] = (double)buffer_gather<T>(wv, live[q] ? jq[q] * (uint32_t)sizeof(T) : kNoLoad);
-        else
-          vq[q] = (double)ws[live[q] ? jq[q] : i];
-      }
-      bool accq[kRejBatch];
-#pragma unroll
-      for (int q = 0; q < kRejBatch; ++q) accq[q] = live[q] & accept_exact<double>(uq[q], wmax, vq[q]);
-      int first = -1;
-#pragma unroll
-      for (int q = kRejBatch - 1; q >= 0; --q)
-        if (accq[q]) first = q;
-      if (first >= 0) {
-        uint32_t jsel = jq[0];
-#pragma unroll
-        for (int q = 1; q < kRejBatch; ++q)
-          if (q == first) jsel = jq[q];
-        a[cur] = (int32_t)jsel;
-        cur = -1;
-        won = true;
-      } else {
-        t += (uint32_t)nq;
-        if (t >= max_trials) {
-          a[cur] = (int32_t)i;
-          my_flags |= FLAG_TRIAL_CAP;
-          cur = -1;
-        }
-      }
+    if (accepted * 2u < tried) {
+      uint32_t j = 0;
+      won = rejection_try<kRejBatch, TINY>(ws, wv, cur, t, n, filt, wmax, max_trials, key, offset,
+                                           tab, j);
+      if (won) as[cur] = (int32_t)j;
+      t += kRejBatch;
+      tried += (uint64_t)kRejBatch * kWave;
+    } else {
+      uint32_t j = 0;
+      won = rejection_try<1, TINY>(ws, wv, cur, t, n, filt, wmax, max_trials, key, offset, tab, j);
+      if (won) as[cur] = (int32_t)j;
+      t += 1;
+      tried += kWave;
     }
-    tried += (uint64_t)nq * (uint64_t)__popcll(busy);
     accepted += (uint64_t)__popcll(ballot(won));
+    if (won) cur = kNoParticle;
+    else if (t >= max_trials) give_up();
   }
 
-  // tail phase: the remaining particles share the wave's lanes.  Each gets
-  // slot = 64 / m lanes (m = particles left); lane r of a particle's group
-  // tries its trials t + tb r .. t + tb r + tb - 1, so a pass covers trials
-  // t .. t + slot tb - 1 of every particle, and the lowest accepting one wins
-  // (the lowest lane of the group with an acceptance, and its lowest trial).
-  // tb follows the wave's acceptance rate as nq does (the counts go on in
-  // the tail, which is all there is when the range is shorter than a wave).
+  // tail phase (the counts go on: the tail is all there is when the range is
+  // shorter than a wave)
   while (true) {
-    const uint64_t act = ballot(cur >= 0);
+    const uint64_t act = ballot(cur != kNoParticle);
     if (act == 0) break;
-    const int tb = accepted * 2u < tried ? kRejBatch : 1;
-    const int m = __popcll(act);
-    const int slot = kWave / m;  // lanes per particle
-    const int grp = (int)lane / slot;
-    const bool helper = grp < m;
-    const int owner = helper ? nth_set_bit(act, grp) : (int)lane;
-    const int64_t o_cur = shfl(cur, owner);
-    const uint32_t o_t = shfl(t, owner);
-    const uint32_t t0 = o_t + (uint32_t)tb * (lane - (uint32_t)(grp * slot));
-    bool acc = false;
-    uint32_t jj = 0;
-    if (helper) {
-      const uint32_t i = (uint32_t)(o_cur - base);
-      uint32_t jb[kRejBatch];
-      double ub[kRejBatch];
-      bool live[kRejBatch];
-#pragma unroll
-      for (int b = 0; b < kRejBatch; ++b) {
-        live[b] = false;
-        jb[b] = i;
-        ub[b] = 1.0;
-        if (b < tb) {
-          const uint32_t tt = t0 + (uint32_t)b;  // < 2^28 + 256: no wrap
-          const uint4 x = draw(key, i, DOM_TRIAL, tt, filt, offset);
-          jb[b] = (tt == 0) ? i : index_draw(x.x, x.y, n);
-          ub[b] = u_accept(x.z);
-          live[b] = (tt < max_trials) & !(TABLE && tab.rejects(ub[b], wmax, jb[b]));
-        }
-      }
-      double vb[kRejBatch];
-#pragma unroll
-      for (int b = 0; b < kRejBatch; ++b) {
-        if constexpr (TABLE)
-          vb[b] = (double)buffer_gather<T>(wv, live[b] ? jb[b] * (uint32_t)sizeof(T) : kNoLoad);
-        else
-          vb[b] = (double)ws[live[b] ? jb[b] : i];
-      }
-#pragma unroll
-      for (int b = kRejBatch - 1; b >= 0; --b) {
-        if (live[b] & accept_exact<double>(ub[b], wmax, vb[b])) {
-          acc = true;
-          jj = jb[b];
-        }
-      }
+    const uint32_t m = (uint32_t)__popcll(act);
+    // the particles left move to lanes 0 .. m - 1
+    const uint32_t rank = rank_in(act);
+    const uint32_t to = cur != kNoParticle ? rank : m + (lane - rank);
+    cur = (uint32_t)__builtin_amdgcn_ds_permute((int)(to << 2), (int)cur);
+    t = (uint32_t)__builtin_amdgcn_ds_permute((int)(to << 2), (int)t);
+    // lane l helps particle g = floor(l m / 64); particle g's helpers start at
+    // ceil(64 g / m)
+    const uint32_t magic = kShare.v[m];
+    auto start = [&](uint32_t g) -> uint32_t {
+      return g >= m ? (uint32_t)kWave : ((64u * g + m - 1u) * magic) >> 18;
+    };
+    const uint32_t g = (lane * m) >> 6;
+    const uint32_t oi = shfl_u32(cur, (int)g), ot = shfl_u32(t, (int)g);
+    const uint32_t s_own = start(lane), e_own = start(lane + 1u);
+    const uint32_t r = lane - start(g);
+    uint32_t j = 0, batch;
+    bool acc;
+    if (accepted * 2u < tried) {
+      batch = kRejBatch;
+      acc = rejection_try<kRejBatch, TINY>(ws, wv, oi, ot + batch * r, n, filt, wmax, max_trials,
+                                           key, offset, tab, j);
+    } else {
+      batch = 1;
+      acc = rejection_try<1, TINY>(ws, wv, oi, ot + r, n, filt, wmax, max_trials, key, offset,
+                                   tab, j);
     }
     const uint64_t accm = ballot(acc);
-    int src = (int)lane;
-    uint64_t g = 0;
-    if (cur >= 0) {
-      const int rank = __popcll(act & lanemask_lt());
-      const uint64_t gm = (slot >= kWave ? ~0ull : ((1ull << slot) - 1ull)) << (rank * slot);
-      g = accm & gm;
-      if (g) src = __ffsll((long long)g) - 1;
+    const uint32_t size = e_own - s_own;  // helpers of this lane's own particle
+    uint64_t mine = 0;
+    if (cur != kNoParticle)
+      mine = accm & ((size >= kWave ? ~0ull : ((1ull << size) - 1ull)) << s_own);
+    const int src = mine ? __ffsll((long long)mine) - 1 : (int)lane;
+    const uint32_t jw = shfl_u32(j, src);
+    const bool won = mine != 0;
+    if (won) {
+      as[cur] = (int32_t)jw;
+      cur = kNoParticle;
+    } else if (cur != kNoParticle) {
+      t += batch * size;
+      if (t >= max_trials) give_up();
     }
-    const uint32_t jsel = shfl(jj, src);
-    bool won = false;
-    if (cur >= 0) {
-      if (g) {
-        a[cur] = (int32_t)jsel;
-        cur = -1;
-        won = true;
-      } else {
-        t += (uint32_t)(slot * tb);
-        if (t >= max_trials) {
-          a[cur] = (int32_t)(cur - base);
-          my_flags |= FLAG_TRIAL_CAP;
-          cur = -1;
-        }
-      }
-    }
-    tried += (uint64_t)(m * slot * tb);
+    tried += (uint64_t)batch * kWave;
     accepted += (uint64_t)__popcll(ballot(won));
   }
 }
@@ -842,20 +813,24 @@ __device__ void rejection_wave_range(const T* ws, int64_t base, uint32_t n, uint
 // A workgroup takes the particles [p0, p1) and walks the segments that overlap
 // them; the waves hand out each segment part among themselves (an LDS
 // counter reset between the part's barriers).  A segment of at most CAP
-// weights is first copied into LDS.
+// weights is first copied into LDS, of a longer one its bound codes (256
+// vectors of 60000 binary32 weights at 1.8 % acceptance: 9.2 ms with gathers
+// from global memory, 2.2 ms with codes).  The chunks go to the XCDs in runs
+// that share a segment (xcd_chunk).
 template <typename T, int CAP, int THREADS>
 __global__ __launch_bounds__(THREADS) void k_rejection(
     const T* __restrict__ w, int64_t n_total, const int64_t* __restrict__ offsets,
     uint32_t n_filters, double w_max, const double* __restrict__ w_max_dev, uint32_t max_trials,
     Key key, uint32_t offset, uint32_t filter_base, int32_t* __restrict__ a,
     uint32_t* __restrict__ flags, int64_t chunk) {
-  __shared__ T sw[CAP > 0 ? CAP : 1];
+  constexpr bool kCoded = CAP * sizeof(T) == 2 * kCodes;
+  __shared__ __align__(16) T sw[CAP > 0 ? CAP : 1];
   __shared__ uint32_t queue;  // particles of the segment part handed out so far
   offset = counter_offset(key, offset);
-  const int64_t p0 = (int64_t)blockIdx.x * chunk;
+  const int64_t p0 = (offsets ? xcd_chunk(chunk) : (int64_t)blockIdx.x) * chunk;
   const int64_t p1 = p0 + chunk < n_total ? p0 + chunk : n_total;
   uint32_t my_flags = 0;
-  uint32_t f = offsets ? find_segment(offsets, n_filters, p0) : 0u;
+  uint32_t f = offsets ? wave_find_segment(offsets, n_filters, p0) : 0u;
   for (int64_t g0 = p0; g0 < p1; ++f) {
     const int64_t base = offsets ? offsets[f] : 0;
     const int64_t end = offsets ? offsets[f + 1] : n_total;
@@ -863,17 +838,34 @@ __global__ __launch_bounds__(THREADS) void k_rejection(
     if (q1 <= g0) continue;  // empty segment
     const uint32_t n = (uint32_t)(end - base);
     const double wmax = w_max_dev ? w_max_dev[f] : w_max;
-    const bool staged = CAP > 0 && n <= (uint32_t)CAP;
+    const bool tiny = !(wmax >= 0x1p-900);
+    const uint32_t i0 = (uint32_t)(g0 - base), i1 = (uint32_t)(q1 - base);
+    const T* __restrict__ wf = w + base;
+    int32_t* __restrict__ af = a + base;
+    const uint32_t filt = filter_base + f;
+    const __amdgpu_buffer_rsrc_t none = buffer_view(wf, 0u);
     __syncthreads();  // the previous part's trials are done with sw and the queue
     if (threadIdx.x == 0) queue = 0;
-    if (staged) stage_weights(w + base, n, sw);
-    __syncthreads();
-    if (staged)
-      rejection_wave_range<false>(sw, base, n, filter_base + f, wmax, g0, q1, max_trials, key,
-                                  offset, a, my_flags, BoundTable{}, &queue);
-    else
-      rejection_wave_range<false>(w + base, base, n, filter_base + f, wmax, g0, q1, max_trials,
-                                  key, offset, a, my_flags, BoundTable{}, &queue);
+    if (CAP > 0 && !tiny && n <= (uint32_t)CAP) {
+      stage_weights(wf, n, sw);
+      __syncthreads();
+      rejection_wave_range<false>((const T*)sw, none, n, filt, wmax, i0, i1, max_trials, key,
+                                  offset, af, my_flags, NoTable{}, &queue);
+    } else if (kCoded && !tiny && wmax <= 0x1p127 && n <= kCodes << kCodesMaxShift) {
+      // (a product beyond binary32's range could exceed the code of an infinity)
+      const CodeTable<T> tab = stage_codes(wf, n, reinterpret_cast<uint16_t*>(sw));
+      __syncthreads();
+      rejection_wave_range<false>(wf, buffer_view(wf, n * (uint32_t)sizeof(T)), n, filt, wmax, i0,
+                                  i1, max_trials, key, offset, af, my_flags, tab, &queue);
+    } else if (CAP == 0 && !tiny) {
+      __syncthreads();
+      rejection_wave_range<false>(wf, none, n, filt, wmax, i0, i1, max_trials, key, offset, af,
+                                  my_flags, NoTable{}, &queue);
+    } else {
+      __syncthreads();
+      rejection_wave_range<true>(wf, none, n, filt, wmax, i0, i1, max_trials, key, offset, af,
+                                 my_flags, NoTable{}, &queue);
+    }
     g0 = q1;
   }
   if (flags) {
@@ -883,7 +875,7 @@ __global__ __launch_bounds__(THREADS) void k_rejection(
 }
 
 // One vector with the LDS bound table; the workgroup's waves hand out its
-// chunk among themselves.
+// chunk among themselves.  (w_max at least 2^-900: checked by the launcher.)
 template <typename T>
 __global__ __launch_bounds__(kTableThreads) void k_rejection_table(
     const T* __restrict__ w, int64_t n, double w_max, uint32_t max_trials, Key key,
@@ -898,9 +890,11 @@ __global__ __launch_bounds__(kTableThreads) void k_rejection_table(
   const int64_t p0 = (int64_t)blockIdx.x * chunk;
   const int64_t p1 = p0 + chunk < n ? p0 + chunk : n;
   uint32_t my_flags = 0;
+  // n * sizeof(T) < 2^31 (checked by the launcher)
   if (p0 < p1)
-    rejection_wave_range<true>(w, 0, (uint32_t)n, filter, w_max, p0, p1, max_trials, key,
-                               offset, a, my_flags, tab, &queue);
+    rejection_wave_range<false>(w, buffer_view(w, (uint32_t)(n * (int64_t)sizeof(T))),
+                                (uint32_t)n, filter, w_max, (uint32_t)p0, (uint32_t)p1,
+                                max_trials, key, offset, a, my_flags, tab, &queue);
   if (flags) {
     const uint32_t wf = wave_reduce(my_flags, OpOr());
     if (lane_id() == 0 && wf) atomicOr(flags, wf);
@@ -1183,7 +1177,32 @@ hipError_t launch_rejection_t(const void* wv, int64_t n_total, const int64_t* of
                          filter_base, a, flags, chunk1);
     return hipGetLastError();
   }
-  const int64_t chunk = (int64_t)tuning().batch_rejection_per_wave * 16;
+  if (n_total <= 256 * 256) {
+    // a small batch: 256 particles per 256-thread workgroup, as for one short
+    // vector, so that long trial sequences spread over the chip: 16 vectors of
+    // 4000 at 1.8 % acceptance 45 us, in chunks of 16384 it was 798.  Up to 256
+    // workgroups; with more of them the staging repeated in each costs more
+    // (every workgroup copies all of its segment).
+    const dim3 grid1((unsigned)((n_total + 255) / 256));
+    if (cap == 16 * per_kb)
+      hipLaunchKernelGGL((k_rejection<T, 16 * per_kb, 256>), grid1, dim3(256), 0, stream, w,
+                         n_total, offsets, n_filters, w_max, w_max_dev, max_trials, key, offset,
+                         filter_base, a, flags, (int64_t)256);
+    else if (cap == 64 * per_kb)
+      hipLaunchKernelGGL((k_rejection<T, 64 * per_kb, 256>), grid1, dim3(256), 0, stream, w,
+                         n_total, offsets, n_filters, w_max, w_max_dev, max_trials, key, offset,
+                         filter_base, a, flags, (int64_t)256);
+    else
+      hipLaunchKernelGGL((k_rejection<T, 128 * per_kb, 256>), grid1, dim3(256), 0, stream, w,
+                         n_total, offsets, n_filters, w_max, w_max_dev, max_trials, key, offset,
+                         filter_base, a, flags, (int64_t)256);
+    return hipGetLastError();
+  }
+  // the tuned chunk, less where it would leave CUs idle (64 vectors of 4000 at
+  // 1.8 % acceptance: 85 us against 818; 64 of 30000: 312 against 716)
+  int64_t chunk = (n_total / 512 + 1023) / 1024 * 1024;
+  if (chunk > (int64_t)tuning().batch_rejection_per_wave * 16)
+    chunk = (int64_t)tuning().batch_rejection_per_wave * 16;
   const dim3 grid((unsigned)((n_total + chunk - 1) / chunk));
   if (cap == 16 * per_kb)
     hipLaunchKernelGGL((k_rejection<T, 16 * per_kb, 1024>), grid, dim3(1024), 0, stream, w,
@@ -1226,7 +1245,8 @@ hipError_t launch_rejection(bool f64, const void* w, int64_t n_total, const int6
                             uint32_t offset, uint32_t filter_base, int32_t* a, uint32_t* flags,
                             void* ws, size_t ws_bytes, hipStream_t stream) {
   // below 2^20 particles the plain kernel was faster at every y measured (0..4)
-  if (ws && !w_max_dev && tuning().rejection_table && n_total >= (1 << 20) &&
+  if (ws && !w_max_dev && w_max >= 0x1p-900 && tuning().rejection_table &&
+      n_total >= (1 << 20) &&
       ws_bytes >= alt_workspace_bytes(f64, n_total, n_filters, max_len) &&
       (f64 ? use_table<double>(n_total, n_filters, max_len)
            : use_table<float>(n_total, n_filters, max_len)))
