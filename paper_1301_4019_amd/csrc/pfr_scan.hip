@@ -356,7 +356,7 @@ __device__ void carry_group(bool weights, uint32_t g, uint32_t m,
 // 9.7 us, is slower than three in parallel with the count, 8.8 us).
 constexpr uint32_t kFewGroups = 1;
 
-template <bool MULTI, bool TOP = true>
+template <bool MULTI>
 __global__ __launch_bounds__(kT) void k_carry_groups(uint32_t nb, uint32_t nbe, uint32_t G,
                                                      const BlockRec* __restrict__ recs,
                                                      const uint64_t* __restrict__ esums,
@@ -369,7 +369,7 @@ __global__ __launch_bounds__(kT) void k_carry_groups(uint32_t nb, uint32_t nbe, 
   __shared__ u128 s_w[kNW];
   __shared__ uint32_t s_u[2 * kNW];
   __shared__ uint32_t s_last;
-  if (TOP && G + (MULTI ? Ge : 0u) <= kFewGroups) {
+  if (G + (MULTI ? Ge : 0u) <= kFewGroups) {
     for (uint32_t g = 0; g < G; ++g) {
       carry_group(true, g, nb, recs, esums, P, groups, s_w, s_u);
       __syncthreads();  // the scratch is reused; the group records are read by all
@@ -388,7 +388,6 @@ __global__ __launch_bounds__(kT) void k_carry_groups(uint32_t nb, uint32_t nbe, 
   const uint32_t g = weights ? blockIdx.x : blockIdx.x - G;
   carry_group(weights, g, weights ? nb : nbe, recs, esums, weights ? P : PE,
               weights ? groups : egroups, s_w, s_u);
-  if (!TOP) return;
   if (threadIdx.x == 0) {
     // the last group to finish (the records pass zeroed the count) runs the
     // top level: release this group's record, count it, acquire the others
@@ -1037,10 +1036,8 @@ __global__ __launch_bounds__(kT) void k_scan_records_w(const T* __restrict__ w, 
 // (with the carries pass) -> 5.8 / 6.4 / 9.9 us; from 2^21 on the wave form is
 // faster (2^21 10.6 against 13.6 us, 2^24 38 against 70 us: fewer barriers).
 //
-// Carries.  Up to kGrp blocks each workgroup reduces all records itself, four
-// per thread (DIRECT); beyond, the group pass leaves every block's prefix
-// inside its group and the groups' totals, and the workgroup reduces the
-// groups (at most 2048).  Either way the values are those of the carries pass.
+// Carries.  Each workgroup reduces all records itself, up to kGrp blocks four
+// per thread; the values are those of the carries pass.
 struct WgCarry {
   u128 Cb, Cb1, Q;
   int32_t gscale;
@@ -1095,7 +1092,8 @@ constexpr uint32_t kStraight = 256;
 
 __device__ __forceinline__ WgCarry direct_carries(uint32_t nb, uint32_t b,
                                                   const BlockRec* __restrict__ recs,
-                                                  const BlockRec& own, CarryScratch* s) {
+                                                  const BlockRec& own, CarryScratch* s,
+                                                  uint32_t straight = kStraight) {
   // record j = r kT + thread, so that a load covers consecutive records
   constexpr int kR = (int)(kDirectMax / kT);
   uint32_t key = 0xFFFFFFFFu, bad = 0;
@@ -1117,7 +1115,7 @@ __device__ __forceinline__ WgCarry direct_carries(uint32_t nb, uint32_t b,
     const bool none = key == 0xFFFFFFFFu;
     const int32_t top = (int32_t)(key ^ 0x80000000u) + (kCarryBits - 63);
     const int32_t gscale = none ? 0 : top - ceil_log2(nb);
-    const int32_t via = none ? 0 : nb <= kStraight ? gscale : top - kGrpLog;
+    const int32_t via = none ? 0 : nb <= straight ? gscale : top - kGrpLog;
 #pragma unroll
     for (int k = 0; k < kGPer; ++k) {
       const uint32_t j = (uint32_t)k * kT + threadIdx.x;
@@ -1160,39 +1158,6 @@ __device__ __forceinline__ WgCarry direct_carries(uint32_t nb, uint32_t b,
   c.Cb = before;
   c.Cb1 = before + conv_rec_fast(own, gscale);
   c.Q = all;
-  c.status = bad | (!bad && c.Q == 0 ? FLAG_ZERO_TOTAL : 0u);
-  return c;
-}
-
-// From the group pass: the top level over the G groups, by every workgroup.
-__device__ __forceinline__ WgCarry group_carries(uint32_t nb, uint32_t b, const Carries& C,
-                                                 CarryScratch* s) {
-  const uint32_t G = C.G, g0 = b >> kGrpLog, g1 = (b + 1) >> kGrpLog;
-  const u128 P0 = C.P[b];
-  const u128 P1 = b + 1 < nb ? C.P[b + 1] : (u128)0;
-  const int32_t gs0 = C.grp[g0].gs, gs1 = b + 1 < nb ? C.grp[g1].gs : 0;
-  uint32_t key = 0xFFFFFFFFu, bad = 0;
-  for (uint32_t g = threadIdx.x; g < G; g += kT) {
-    bad |= C.grp[g].bad;
-    key = min(key, C.grp[g].key);
-  }
-  wg_key_bad(key, bad, s);
-  const int32_t gscale = key == 0xFFFFFFFFu ? 0
-                                            : (int32_t)(key ^ 0x80000000u) + (kCarryBits - 63) -
-                                                  ceil_log2(nb);
-  u128 before = 0, all = 0;
-  for (uint32_t g = threadIdx.x; g < G; g += kT) {
-    const u128 v = shift_u128(C.grp[g].T, gscale - C.grp[g].gs);
-    all += v;
-    before += g < g0 ? v : (u128)0;
-  }
-  const u128 T0 = shift_u128(C.grp[g0].T, gscale - gs0);
-  wg_sum2(before, all, s);
-  WgCarry c;
-  c.gscale = gscale;
-  c.Q = all;
-  c.Cb = before + shift_u128(P0, gscale - gs0);
-  c.Cb1 = b + 1 >= nb ? all : (g1 == g0 ? before : before + T0) + shift_u128(P1, gscale - gs1);
   c.status = bad | (!bad && c.Q == 0 ? FLAG_ZERO_TOTAL : 0u);
   return c;
 }
@@ -1337,6 +1302,24 @@ __device__ __forceinline__ void wg_expand(const uint32_t (&O)[kPer], uint32_t Op
   }
 }
 
+// The claim bits of the thread's particles (1: it has outputs); the nibbles of
+// eight lanes make a word.
+__device__ __forceinline__ void wg_claim_bits(const uint32_t (&O)[kPer], uint32_t Oprev,
+                                              int64_t P0, uint32_t* __restrict__ claim) {
+  const int tid = (int)threadIdx.x;
+  uint32_t p = Oprev, bits = 0;
+#pragma unroll
+  for (int v = 0; v < kPer; ++v) {
+    bits |= (O[v] > p ? 1u : 0u) << v;
+    p = O[v];
+  }
+  bits <<= 4 * (tid & 7);
+  bits |= dpp_u32<kDppXor1>(0u, bits);
+  bits |= dpp_u32<kDppXor2>(0u, bits);
+  bits |= dpp_u32<kDppHalfMirror>(0u, bits);
+  if ((tid & 7) == 0) claim[(P0 >> 5) + (tid >> 3)] = bits;
+}
+
 template <bool SYSTEMATIC>
 struct StrataWgLds {
   ExpandLds ex;
@@ -1345,12 +1328,12 @@ struct StrataWgLds {
   uint32_t u[SYSTEMATIC ? 1 : kUTabW];  // offset words of strata [m_lo, m_lo + kUTabW)
 };
 
-template <typename T, int SCHEME, bool DIRECT>
+template <typename T, int SCHEME>
 __global__ __launch_bounds__(kT) void k_scan_emit_b(const T* __restrict__ w, int64_t n,
                                                     uint32_t nb, Key key, uint32_t offset,
                                                     uint32_t filter,
                                                     const BlockRec* __restrict__ recs,
-                                                    Carries C, int32_t* __restrict__ a,
+                                                    int32_t* __restrict__ a,
                                                     uint32_t* __restrict__ flags,
                                                     uint32_t* __restrict__ claim) {
   static_assert(SCHEME != SCHEME_MULTINOMIAL, "strata schemes only");
@@ -1364,8 +1347,7 @@ __global__ __launch_bounds__(kT) void k_scan_emit_b(const T* __restrict__ w, int
   const BlockRec rec = recs[b];
   offset = counter_offset(key, offset);
   wg_markers_clear(&L.ex);
-  const WgCarry c = DIRECT ? direct_carries(nb, b, recs, rec, &L.cs)
-                           : group_carries(nb, b, C, &L.cs);
+  const WgCarry c = direct_carries(nb, b, recs, rec, &L.cs);
   if (flags && b == 0 && tid == 0 && c.status) atomicOr(flags, c.status);
   if (c.status & (FLAG_BAD_WEIGHTS | FLAG_ZERO_TOTAL)) {
     block_identity(P0, n, tid, kT, a, claim);
@@ -1414,19 +1396,7 @@ __global__ __launch_bounds__(kT) void k_scan_emit_b(const T* __restrict__ w, int
 #pragma unroll
   for (int v = 0; v < kPer; ++v) O[v] = cum(R.r[v]);
   const uint32_t O_lo = uniform_u32(cum(R.lo)), O_hi = uniform_u32(cum(R.hi));
-  if (claim) {  // the nibbles of eight lanes make a word
-    uint32_t p = Oprev, bits = 0;
-#pragma unroll
-    for (int v = 0; v < kPer; ++v) {
-      bits |= (O[v] > p ? 1u : 0u) << v;
-      p = O[v];
-    }
-    bits <<= 4 * (tid & 7);
-    bits |= dpp_u32<kDppXor1>(0u, bits);
-    bits |= dpp_u32<kDppXor2>(0u, bits);
-    bits |= dpp_u32<kDppHalfMirror>(0u, bits);
-    if ((tid & 7) == 0) claim[(P0 >> 5) + (tid >> 3)] = bits;
-  }
+  if (claim) wg_claim_bits(O, Oprev, P0, claim);
   wg_expand(O, Oprev, O_lo, O_hi, (int32_t)P0, n, a, &L.ex);
 }
 
@@ -1488,6 +1458,185 @@ __global__ __launch_bounds__(kT) void k_scan_emit_mw(const T* __restrict__ w, in
   C.gscale = hdr->gscale;
   emit_multi_wave<T, true>(w, n, P0, recs[b], C[b], C[b + 1], C.gscale, hdr->Q, key, filter,
                            offset, CE, nbe, evals, a, &L[wave], claim);
+}
+
+// The multinomial emission with one block per workgroup (at most kGrp blocks,
+// whose carries go through the group's scale as in the carries pass, and
+// kDirectMulti exponential blocks).  The workgroup forms its own weight carries from the
+// records and, in the same two barriers, the prefix of the exponential block
+// sums, kept in LDS as the last point of every block.  Each particle finds the
+// exponential block of its r there (a few steps between the first and the last
+// block that the workgroup's range touches), and only blocks that hold the r
+// of some particle are rebuilt from their stored spacings and searched, which
+// matters where one weight covers many of them.  r, points and comparisons
+// are those of emit_multi_wave.  Bound by the serial chain (carries, prefix,
+// ten LDS steps per searched block, expansion); four workgroups per CU at 2^20
+// weights.  MULTI_NUM
+constexpr uint32_t kDirectMulti = 5 * kT;
+struct MultiWgLds {
+  double top[kDirectMulti + 1];  // top[e]: point of the exponential prefix up to block e
+  double P[kBlock];              // the points of one exponential block
+  ExpandLds ex;
+  CarryScratch cs;
+  PrefixScratch ps;
+  u128 esum[kNW];
+  uint64_t wsum[kNW];
+  uint32_t used[kDirectMulti / 32];  // exponential blocks that hold some r
+  uint32_t O_lo, O_hi;
+};
+
+template <typename T>
+__global__ __launch_bounds__(kT) void k_scan_emit_mb(const T* __restrict__ w, int64_t n,
+                                                     uint32_t nb, uint32_t nbe, Key key,
+                                                     uint32_t offset, uint32_t filter,
+                                                     const BlockRec* __restrict__ recs,
+                                                     const uint64_t* __restrict__ esums,
+                                                     const uint64_t* __restrict__ evals,
+                                                     int32_t* __restrict__ a,
+                                                     uint32_t* __restrict__ flags,
+                                                     uint32_t* __restrict__ claim) {
+  constexpr int kE = (int)(kDirectMulti / kT);  // exponential blocks per thread
+  __shared__ MultiWgLds L;
+  const uint32_t b = blockIdx.x;
+  const int tid = (int)threadIdx.x, wave = (int)uniform_u32((uint32_t)tid / kWave);
+  const int64_t P0 = (int64_t)b * kBlock;
+  T x[kPer];
+  load4_any(w, n, P0, x);
+  const BlockRec rec = recs[b];
+  u128 ee[kE];  // inclusive prefixes of the thread's exponential block sums
+  {
+    u128 run = 0;
+#pragma unroll
+    for (int k = 0; k < kE; ++k) {
+      const uint32_t e = (uint32_t)tid * kE + (uint32_t)k;
+      run += e < nbe ? (u128)esums[e] : (u128)0;
+      ee[k] = run;
+    }
+    const u128 inc = wave_incl_add_u128(run);
+    if (lane_id() == kWave - 1) L.esum[wave] = inc;
+#pragma unroll
+    for (int k = 0; k < kE; ++k) ee[k] += inc - run;
+  }
+  wg_markers_clear(&L.ex);
+  if (tid < (int)(kDirectMulti / 32)) L.used[tid] = 0;
+  const WgCarry c = direct_carries(nb, b, recs, rec, &L.cs, 0u);
+  if (flags && b == 0 && tid == 0 && c.status) atomicOr(flags, c.status);
+  if (c.status & (FLAG_BAD_WEIGHTS | FLAG_ZERO_TOTAL)) {
+    block_identity(P0, n, tid, kT, a, claim);
+    return;
+  }
+  u128 ebefore = 0, S = 0;
+#pragma unroll
+  for (int w2 = 0; w2 < kNW; ++w2) {
+    const u128 t = L.esum[w2];
+    ebefore += w2 < wave ? t : (u128)0;
+    S += t;
+  }
+  const RMap em = make_rmap(S, n);
+  if (tid == 0) L.top[0] = em((u128)0);
+#pragma unroll
+  for (int k = 0; k < kE; ++k) L.top[tid * kE + k + 1] = em(ebefore + ee[k]);
+  uint64_t q[kPer];
+  const uint64_t off = wg_quantize(x, rec.scale, q, &L.ps);
+  __syncthreads();
+  WgR R;
+  wg_block_r(q, off, &L.ps, rec.scale, c, n, R);
+  if (!(R.hi > R.lo)) {  // an empty range has no outputs
+    if (claim && (tid & 7) == 0) claim[(P0 >> 5) + (tid >> 3)] = 0;
+    return;
+  }
+
+  // exponential block of a value: the blocks whose last point lies below it
+  auto block_between = [&](double rv, uint32_t lo, uint32_t hi) -> uint32_t {
+    while (lo < hi) {
+      const uint32_t mid = (lo + hi) >> 1;
+      if (L.top[mid + 1] < rv) lo = mid + 1;
+      else hi = mid;
+    }
+    return lo;
+  };
+  // the ends of the range: one probe of 64 blocks around the expected one
+  // (the boundaries scatter by half a block at 2^20 points), else a bisection
+  auto block_of = [&](double rv) -> uint32_t {
+    const double per_block = (double)kBlock * (double)n / (double)(n + 1);
+    const uint32_t last = nbe - 1;
+    uint32_t e0 = (uint32_t)(rv / per_block);
+    e0 = e0 > 32u ? e0 - 32u : 0u;
+    e0 = min(e0, last);
+    const uint32_t e = e0 + lane_id();
+    const uint32_t below =
+        (uint32_t)__popcll(ballot(e < last && L.top[e < last ? e + 1 : 0] < rv));
+    const bool ok = (e0 == 0 || below > 0) && (e0 + kWave >= last || below < kWave);
+    return uniform_u32(ok ? e0 + below : block_between(rv, 0u, last));
+  };
+  const uint32_t e_first = block_of(R.lo), e_last = block_of(R.hi);
+  double rr[kPer + 1];
+  uint32_t re[kPer + 1], O[kPer + 1];
+  rr[0] = R.prev;
+#pragma unroll
+  for (int v = 0; v < kPer; ++v) rr[v + 1] = R.r[v];
+#pragma unroll
+  for (int v = 0; v <= kPer; ++v) {
+    O[v] = 0;
+    re[v] = block_between(rr[v], e_first, e_last);
+    if (v == 0 || re[v] != re[v - 1]) atomicOr(&L.used[re[v] >> 5], 1u << (re[v] & 31u));
+  }
+  __syncthreads();
+  const double ce = em.Nd * em.invQ;
+  for (uint32_t word = e_first >> 5; word <= e_last >> 5; ++word) {
+    uint32_t bits = uniform_u32(L.used[word]);
+    while (bits) {
+      const uint32_t e = word * 32u + (uint32_t)__ffs((int)bits) - 1u;
+      bits &= bits - 1u;
+      uint64_t p[kPer];
+      load_exp_values(evals, e, p);
+#pragma unroll
+      for (int v = 1; v < kPer; ++v) p[v] += p[v - 1];
+      const uint64_t incl = wave_incl_add_u64(p[kPer - 1]);
+      if (lane_id() == kWave - 1) L.wsum[wave] = incl;
+      __syncthreads();
+      uint64_t before = incl - p[kPer - 1], total = 0;
+#pragma unroll
+      for (int w2 = 0; w2 < kNW; ++w2) {
+        before += w2 < wave ? L.wsum[w2] : 0ull;
+        total += L.wsum[w2];
+      }
+      const double p_base = L.top[e], p_top = L.top[e + 1];
+      double pv[kPer];
+#pragma unroll
+      for (int v = 0; v < kPer; ++v) {
+        const uint64_t Lv = before + p[v];
+        const double t = __fma_rn(u64_to_f64(Lv), ce, p_base);
+        pv[v] = (Lv == total || t > p_top) ? p_top : t;
+      }
+      double2* P2 = reinterpret_cast<double2*>(L.P) + tid * (kPer / 2);
+      P2[0] = make_double2(pv[0], pv[1]);
+      P2[1] = make_double2(pv[2], pv[3]);
+      __syncthreads();
+      bool any = false;
+#pragma unroll
+      for (int v = 0; v <= kPer; ++v) any |= re[v] == e;
+      if (any) {
+        // points below r: at most 1023, as r is at most the last one
+        uint32_t pos[kPer + 1];
+#pragma unroll
+        for (int v = 0; v <= kPer; ++v) pos[v] = 0;
+#pragma unroll
+        for (uint32_t st = kBlock / 2; st > 0; st >>= 1) {
+#pragma unroll
+          for (int v = 0; v <= kPer; ++v) pos[v] += (L.P[pos[v] + st - 1] < rr[v]) ? st : 0u;
+        }
+#pragma unroll
+        for (int v = 0; v <= kPer; ++v) O[v] = re[v] == e ? e * (uint32_t)kBlock + pos[v] : O[v];
+      }
+    }
+  }
+  if (tid == 0) L.O_lo = O[0];
+  if (tid == kT - 1) L.O_hi = O[kPer];  // its r is the range's upper end
+  __syncthreads();
+  const uint32_t Ov[kPer] = {O[1], O[2], O[3], O[4]};
+  if (claim) wg_claim_bits(Ov, O[0], P0, claim);
+  wg_expand(Ov, O[0], uniform_u32(L.O_lo), uniform_u32(L.O_hi), (int32_t)P0, n, a, &L.ex);
 }
 
 // ---------------------------------------------------------------- whole vector in one workgroup
@@ -2087,8 +2236,15 @@ hipError_t launch_scan_t(const void* wv, int64_t n, Key key, uint32_t offset, ui
   if (e != hipSuccess) return e;
   if constexpr (!multi) {
     if (nb <= (uint32_t)tuning().direct_max_blocks && nb <= kDirectMax) {
-      hipLaunchKernelGGL((k_scan_emit_b<T, SCHEME, true>), dim3(nb), dim3(kT), 0, stream, w, n,
-                         nb, key, offset, filter, recs, cs.C, a, flags, claim);
+      hipLaunchKernelGGL((k_scan_emit_b<T, SCHEME>), dim3(nb), dim3(kT), 0, stream, w, n, nb,
+                         key, offset, filter, recs, a, flags, claim);
+      return hipGetLastError();
+    }
+  }
+  if constexpr (multi) {
+    if (nb <= (uint32_t)tuning().direct_max_blocks && nb <= kGrp && nbe <= kDirectMulti) {
+      hipLaunchKernelGGL((k_scan_emit_mb<T>), dim3(nb), dim3(kT), 0, stream, w, n, nb, nbe, key,
+                         offset, filter, recs, esums, (const uint64_t*)evals, a, flags, claim);
       return hipGetLastError();
     }
   }

@@ -58,6 +58,27 @@ def test_single_vector_paths_agree(n, dtype):
 
 
 @pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("n", [1, 5, 1022, 1023, 1024, 1025, 2047, 2048, 4097, 70001, 262143,
+                               524289, 1048575, 1048576, 1048577])
+def test_multinomial_paths_agree(n, dtype):
+    """One block per workgroup (up to 1024 blocks) against records, carries and
+    one block per wave: one weight over every exponential block, blocks without
+    weight, ranges within one exponential block."""
+    m = pfr()
+    saved = m.get_tuning()
+    for kind in (0.0, 4.0, "wide", "one"):
+        w = dev(weights(kind, n, dtype))
+        ref = general("multinomial", w, seed=7, offset=n & 3, filter_base=2)
+        try:
+            m.set_tuning(single_wg_max=0, direct_max_blocks=1024)
+            a = host(m.resample_multinomial(w, seed=7, offset=n & 3, filter_base=2))
+            b = host(m.resample_permuted("multinomial", w, seed=7, offset=n & 3, filter_base=2)[0])
+        finally:
+            m.set_tuning(**saved)
+        assert np.array_equal(a, ref) and np.array_equal(b, ref), kind
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
 @pytest.mark.parametrize("filters", [3, 40])
 @pytest.mark.parametrize("with_max_len", [True, False])
 def test_segment_tiers_agree_with_single_calls(filters, dtype, with_max_len):
