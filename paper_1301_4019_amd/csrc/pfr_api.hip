@@ -118,9 +118,20 @@ bool uses_scan_workspace(const SegInfo& s) {
   return s.n_filters == 1 && s.n_total > tuning().single_wg_max;
 }
 
+// A batch with a workspace runs block-parallel, without one (or when its
+// longest segment is short) in one workgroup per segment; the results are the
+// same.  (Short segments of the strata schemes always: one launch that reads
+// the weights once, 65536 segments of 256 186 against 535 us.)
+bool block_parallel_batch(int scheme, const SegInfo& s) {
+  const int64_t one_wg = scheme == SCHEME_MULTINOMIAL
+                             ? tuning().batch_scan_wg_max_len
+                             : std::max<int64_t>(kOneWgMax, tuning().batch_scan_wg_max_len);
+  return s.n_filters > 1 && !(s.max_len > 0 && s.max_len <= one_wg);
+}
+
 int collective(int scheme, const void* w, pfr_dtype dtype, const pfr_segments* seg,
                pfr_precision precision, pfr_rng rng, int32_t* a, void* ws, size_t ws_bytes,
-               uint32_t* dev_flags, void* stream) {
+               uint32_t* dev_flags, void* stream, const SegClaim& sc = SegClaim()) {
   SegInfo s;
   int rc = check_segments(seg, &s);
   if (rc) return rc;
@@ -138,21 +149,14 @@ int collective(int scheme, const void* w, pfr_dtype dtype, const pfr_segments* s
       return launch_result(launch_fscan_batched(scheme, (int)precision, dtype == PFR_F64, w,
                                                 s.n_total, s.offsets, s.n_filters, key,
                                                 rng.offset, rng.filter_base, a, dev_flags, st));
-    // a batch with a workspace runs block-parallel, without one (or when
-    // its longest segment is short) in one workgroup per segment; the
-    // results are the same
-    // (short segments of the strata schemes always: one launch that reads the
-    // weights once, 65536 segments of 256 186 against 535 us)
-    const int64_t one_wg = scheme == SCHEME_MULTINOMIAL
-                               ? tuning().batch_scan_wg_max_len
-                               : std::max<int64_t>(kOneWgMax, tuning().batch_scan_wg_max_len);
-    if (s.n_filters > 1 && ws && !(s.max_len > 0 && s.max_len <= one_wg)) {
+    if (ws && block_parallel_batch(scheme, s)) {
       const SegLayout SL = seg_layout(s.n_total, s.n_filters, scheme == SCHEME_MULTINOMIAL);
       if (ws_bytes < SL.total || !aligned256(ws)) return PFR_EWORKSPACE;
       if (overlaps(ws, SL.total, a, (size_t)s.n_total * 4)) return PFR_EINVAL;
       return launch_result(launch_scan_segmented(scheme, dtype == PFR_F64, w, s.n_total,
                                                  s.offsets, s.n_filters, key, rng.offset,
-                                                 rng.filter_base, a, ws, dev_flags, st));
+                                                 rng.filter_base, a, ws, dev_flags, st, nullptr,
+                                                 nullptr, sc));
     }
     return launch_result(launch_scan_batched(scheme, dtype == PFR_F64, w, s.n_total, s.offsets,
                                              s.n_filters, s.max_len, key, rng.offset,
@@ -562,31 +566,43 @@ int resample_permuted(pfr_op scheme, const void* w, pfr_dtype dtype, const pfr_s
   const size_t rbytes = ws_bytes - perm;
   const bool sorted_out = scheme <= PFR_OP_SYSTEMATIC;  // collective schemes
   const hipStream_t st = (hipStream_t)stream;
-  // the claim fused into the emission: long single vectors of the exact
-  // collective schemes, whose ancestries are sorted (shorter ones are
-  // permuted in LDS)
-  if (s.n_filters == 1 && sorted_out && params->precision == PFR_SCAN_EXACT &&
-      uses_scan_workspace(s) && s.n_total > 1024) {
-    rc = launch_result(launch_scan_claimed(scheme == PFR_OP_MULTINOMIAL   ? SCHEME_MULTINOMIAL
-                                           : scheme == PFR_OP_STRATIFIED ? SCHEME_STRATIFIED
-                                                                         : SCHEME_SYSTEMATIC,
-                                           dtype == PFR_F64, w, s.n_total, make_key(rng),
-                                           rng.offset, rng.filter_base, ancestors, rws, dev_flags,
-                                           (uint32_t*)ws, st));
-    if (rc) return rc;
-    return launch_result(
-        launch_resolve_sorted(ancestors, s.n_total, (const uint32_t*)ws, permuted, st));
+  const int cscheme = scheme == PFR_OP_MULTINOMIAL   ? SCHEME_MULTINOMIAL
+                      : scheme == PFR_OP_STRATIFIED ? SCHEME_STRATIFIED
+                                                    : SCHEME_SYSTEMATIC;
+  // the claim fused into the emission: long single vectors and block-parallel
+  // batches of the exact collective schemes, whose ancestries are sorted.
+  // Shorter ones are permuted in LDS, as are batches whose segments average so
+  // few particles that the claims' whole tiles outgrow the workspace, and a
+  // few short segments, which one small launch permutes (multinomial, 16 of
+  // 300: 28.0 us in LDS, 29.7 fused; 256 of 2048 45.7 and 45.5; 4096 of 300
+  // 104.8 and 98.9; systematic without max_len, 4096 of 4096, 345 and 113)
+  if (sorted_out && params->precision == PFR_SCAN_EXACT) {
+    if (s.n_filters == 1 && uses_scan_workspace(s) && s.n_total > 1024) {
+      rc = launch_result(launch_scan_claimed(cscheme, dtype == PFR_F64, w, s.n_total,
+                                             make_key(rng), rng.offset, rng.filter_base, ancestors,
+                                             rws, dev_flags, (uint32_t*)ws, st));
+      if (rc) return rc;
+      return launch_result(
+          launch_resolve_sorted(ancestors, s.n_total, (const uint32_t*)ws, permuted, st));
+    }
+    const bool few = s.max_len > 0 && s.max_len <= 2048 && s.n_filters < 256;
+    if (block_parallel_batch(cscheme, s) && !few &&
+        seg_claim_bytes(s.n_total, s.n_filters) <= perm) {
+      const SegClaim sc = seg_claim_in(ws, s.n_total, s.n_filters);
+      rc = collective(cscheme, w, dtype, seg, params->precision, rng, ancestors, rws, rbytes,
+                      dev_flags, stream, sc);
+      if (rc) return rc;
+      return launch_result(launch_resolve_segments(ancestors, s.n_total, s.offsets, s.n_filters,
+                                                   sc, permuted, st));
+    }
   }
   // the two steps one after the other
   switch (scheme) {
     case PFR_OP_MULTINOMIAL:
     case PFR_OP_STRATIFIED:
     case PFR_OP_SYSTEMATIC:
-      rc = collective(scheme == PFR_OP_MULTINOMIAL   ? SCHEME_MULTINOMIAL
-                      : scheme == PFR_OP_STRATIFIED ? SCHEME_STRATIFIED
-                                                    : SCHEME_SYSTEMATIC,
-                      w, dtype, seg, params->precision, rng, ancestors, rws, rbytes, dev_flags,
-                      stream);
+      rc = collective(cscheme, w, dtype, seg, params->precision, rng, ancestors, rws, rbytes,
+                      dev_flags, stream);
       break;
     case PFR_OP_METROPOLIS:
       rc = resample_metropolis(w, dtype, seg, params->B, params->B_dev, rng, ancestors, rws,

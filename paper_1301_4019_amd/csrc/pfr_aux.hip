@@ -1162,16 +1162,11 @@ __global__ __launch_bounds__(kClaimThreads) void k_bucket_claim(
 // is written and read.  A chain moves by the ancestry's drift, of the order of
 // sqrt(n), per step.  Up to kWindowMax particles a workgroup therefore holds
 // the ancestry around its tile of slots in LDS, where most chains stay (a step
-// costs an LDS read instead of one beyond the L2): kWinSteps steps for the four
+// costs an LDS read instead of one beyond the L2): a few steps for the four
 // chains of a quad together, then the longer ones from a list, one a lane.
 // Chains that leave the window go on in global memory, as do all of them in
 // longer vectors.
 constexpr int kWinThreads = 512;
-constexpr uint32_t kWinTile = 4 * kWinThreads;     // slots
-constexpr uint32_t kWinHalo = 3072;                // positions on either side
-constexpr uint32_t kWinSpan = kWinTile + 2 * kWinHalo;
-constexpr int kWinSteps = 8;
-constexpr uint32_t kWinSlow = 1024;                // entries of the list
 constexpr int64_t kWindowMax = 1 << 21;
 constexpr uint32_t kWon = 0x80000000u;
 
@@ -1182,22 +1177,38 @@ __device__ __forceinline__ uint32_t marked_at(const int32_t* __restrict__ a, uin
   return v != p ? v | kWon : v;
 }
 
-__global__ __launch_bounds__(kWinThreads) void k_resolve_window(const int32_t* __restrict__ a,
-                                                                uint32_t n,
-                                                                const uint32_t* __restrict__ claim,
-                                                                int32_t* __restrict__ c) {
-  __shared__ __align__(16) uint32_t win[kWinSpan];
-  __shared__ uint2 slow[kWinSlow];
-  __shared__ uint32_t n_slow;
+template <uint32_t TILE, uint32_t HALO, int STEPS>
+struct WindowLds {
+  static constexpr uint32_t kTile = TILE, kHalo = HALO, kSpan = TILE + 2 * HALO;
+  static constexpr int kSteps = STEPS;
+  static constexpr uint32_t kSlow = 1024;  // entries of the list
+  alignas(16) uint32_t win[kSpan];
+  uint2 slow[kSlow];
+  uint32_t n_slow;
+};
+
+// The slots [t0, t0 + kTile) of a vector (or segment) of n particles.
+template <typename Lds>
+__device__ __forceinline__ void resolve_window(const int32_t* __restrict__ a, uint32_t n,
+                                               uint32_t t0, const uint32_t* __restrict__ claim,
+                                               int32_t* __restrict__ c, Lds* L) {
+  constexpr uint32_t kQuads = Lds::kTile / (4 * kWinThreads);  // of a thread
+  static_assert(Lds::kTile % (4 * kWinThreads) == 0 && Lds::kSpan % (4 * kWinThreads) == 0,
+                "whole rounds");
+  uint32_t* const win = L->win;
   const uint32_t tid = threadIdx.x, lane = lane_id();
-  const uint32_t t0 = blockIdx.x * kWinTile;
-  const uint32_t lo = t0 > kWinHalo ? t0 - kWinHalo : 0u;
-  const uint32_t hi = min(n, t0 + kWinTile + kWinHalo), span = hi - lo;
-  if (tid == 0) n_slow = 0;
-  const uint32_t j = t0 + 4 * tid;
-  const uint32_t cl = j < n ? (claim[j >> 5] >> (j & 31u)) & 15u : 0u;
+  const uint32_t lo = t0 > Lds::kHalo ? t0 - Lds::kHalo : 0u;
+  const uint32_t hi = min(n, t0 + Lds::kTile + Lds::kHalo), span = hi - lo;
+  if (tid == 0) L->n_slow = 0;
+  uint32_t cl[kQuads];
 #pragma unroll
-  for (uint32_t r = 0; r < kWinSpan / kWinTile; ++r) {
+  for (uint32_t g = 0; g < kQuads; ++g) {
+    const uint32_t j = t0 + 4 * (g * kWinThreads + tid);
+    cl[g] = j < n ? (claim[j >> 5] >> (j & 31u)) & 15u : 0u;
+  }
+#pragma unroll
+  for (uint32_t r = 0; r < Lds::kSpan / (4 * kWinThreads); ++r) {
+    if (r * 4 * kWinThreads >= span) break;
     const uint32_t q = r * kWinThreads + tid;  // whole waves: the shift below reads lane - 1
     int32_t x[4];
     load_quad(a + lo, q, span, x);
@@ -1221,13 +1232,16 @@ __global__ __launch_bounds__(kWinThreads) void k_resolve_window(const int32_t* _
       y = m & ~kWon;
     }
   };
-  if (j < n) {
+#pragma unroll
+  for (uint32_t g = 0; g < kQuads; ++g) {
+    const uint32_t j = t0 + 4 * (g * kWinThreads + tid);
+    if (j >= n) continue;
     const uint4 t = reinterpret_cast<const uint4*>(win)[(j - lo) / 4];
     uint32_t y[4] = {t.x, t.y, t.z, t.w};
 #pragma unroll
     for (int k = 0; k < 4; ++k)
-      if ((cl >> k) & 1u || j + k >= n) y[k] = j + k;
-    for (int s = 0; s < kWinSteps && ((y[0] | y[1] | y[2] | y[3]) & kWon); ++s) {
+      if ((cl[g] >> k) & 1u || j + k >= n) y[k] = j + k;
+    for (int s = 0; s < Lds::kSteps && ((y[0] | y[1] | y[2] | y[3]) & kWon); ++s) {
       uint32_t z[4];
       bool in[4];
 #pragma unroll
@@ -1242,8 +1256,8 @@ __global__ __launch_bounds__(kWinThreads) void k_resolve_window(const int32_t* _
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       if (y[k] & kWon) {
-        const uint32_t at = atomicAdd(&n_slow, 1u);
-        if (at < kWinSlow) slow[at] = make_uint2(j + k, y[k] & ~kWon);
+        const uint32_t at = atomicAdd(&L->n_slow, 1u);
+        if (at < Lds::kSlow) L->slow[at] = make_uint2(j + k, y[k] & ~kWon);
         else y[k] = walk(y[k] & ~kWon);
       }
     }
@@ -1258,12 +1272,44 @@ __global__ __launch_bounds__(kWinThreads) void k_resolve_window(const int32_t* _
     }
   }
   __syncthreads();  // also orders the chains' slots after the quads stored above
-  const uint32_t ns = min(n_slow, kWinSlow);
+  const uint32_t ns = min(L->n_slow, Lds::kSlow);
   for (uint32_t t = tid; t < ns; t += kWinThreads) {
-    const uint2 e = slow[t];
+    const uint2 e = L->slow[t];
     c[e.x] = (int32_t)walk(e.y);
   }
 }
+
+typedef WindowLds<2048, 3072, 8> VectorWindow;
+__global__ __launch_bounds__(kWinThreads) void k_resolve_window(const int32_t* __restrict__ a,
+                                                                uint32_t n,
+                                                                const uint32_t* __restrict__ claim,
+                                                                int32_t* __restrict__ c) {
+  __shared__ VectorWindow L;
+  resolve_window(a, n, blockIdx.x * VectorWindow::kTile, claim, c, &L);
+}
+
+// The same over the segments of a batch, a workgroup per tile.  There are
+// tiles enough to fill the chip, so they are larger against their margins (a
+// chain moves less in a segment of 2^16 than in a vector of 2^20), and four
+// workgroups fit a CU.  Bound by the LDS reads of the chains.  Segments in LDS
+// whole (k_permute_lds) leave one workgroup per CU on those of 2^16, and a last
+// round that is nearly empty: 4096 ragged segments of 2^8 .. 2^16, 48 M
+// particles, 386 -> 155 us, the call 571 -> 342 us.  After three steps half
+// the lanes have nothing to do: the list takes the rest (8 steps: 349 us; 16:
+// 365; margins of 2048: 354).
+typedef WindowLds<(uint32_t)kSegTile, 1024, 3> SegWindow;
+__global__ __launch_bounds__(kWinThreads) void k_resolve_segments(
+    const int32_t* __restrict__ a, const int64_t* __restrict__ offsets, uint32_t n_filters,
+    SegClaim sc, int32_t* __restrict__ c) {
+  __shared__ SegWindow L;
+  const uint32_t t = blockIdx.x;
+  if (t >= sc.tstart[n_filters]) return;
+  const uint32_t f = wave_find_segment<uint32_t>(sc.tstart, n_filters, t), t0 = sc.tstart[f];
+  const int64_t base = offsets[f];
+  resolve_window(a + base, (uint32_t)(offsets[f + 1] - base), (t - t0) * SegWindow::kTile,
+                 sc.claim + (size_t)t0 * (kSegTile / 32), c + base, &L);
+}
+
 
 __global__ __launch_bounds__(256) void k_resolve_sorted(const int32_t* __restrict__ a, int64_t n,
                                                         const uint32_t* __restrict__ claim,
@@ -1425,10 +1471,34 @@ hipError_t launch_permute(const int32_t* a, int64_t n_total, const int64_t* offs
 hipError_t launch_resolve_sorted(const int32_t* a, int64_t n, const uint32_t* claim, int32_t* c,
                                  hipStream_t stream) {
   if (n <= kWindowMax)
-    hipLaunchKernelGGL(k_resolve_window, dim3((unsigned)((n + kWinTile - 1) / kWinTile)),
+    hipLaunchKernelGGL(k_resolve_window, dim3((unsigned)((n + VectorWindow::kTile - 1) / VectorWindow::kTile)),
                        dim3(kWinThreads), 0, stream, a, (uint32_t)n, claim, c);
   else
     hipLaunchKernelGGL(k_resolve_sorted, dim3(grid_for(n)), dim3(256), 0, stream, a, n, claim, c);
+  return hipGetLastError();
+}
+
+// whole tiles: each segment adds at most one partial one
+static size_t seg_claim_words(int64_t n_total, uint32_t n_filters) {
+  return (size_t)(n_total / kSegTile + n_filters) * (kSegTile / 32);
+}
+size_t seg_claim_bytes(int64_t n_total, uint32_t n_filters) {
+  return align256(seg_claim_words(n_total, n_filters) * sizeof(uint32_t)) +
+         align256(((size_t)n_filters + 1) * sizeof(uint32_t));
+}
+SegClaim seg_claim_in(void* ws, int64_t n_total, uint32_t n_filters) {
+  SegClaim sc;
+  sc.claim = (uint32_t*)ws;
+  sc.tstart = (uint32_t*)((char*)ws +
+                          align256(seg_claim_words(n_total, n_filters) * sizeof(uint32_t)));
+  return sc;
+}
+
+hipError_t launch_resolve_segments(const int32_t* a, int64_t n_total, const int64_t* offsets,
+                                   uint32_t n_filters, const SegClaim& sc, int32_t* c,
+                                   hipStream_t stream) {
+  hipLaunchKernelGGL(k_resolve_segments, dim3((unsigned)(n_total / kSegTile + n_filters)),
+                     dim3(kWinThreads), 0, stream, a, offsets, n_filters, sc, c);
   return hipGetLastError();
 }
 

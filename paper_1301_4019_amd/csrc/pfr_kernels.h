@@ -73,11 +73,22 @@ struct SegLayout {
   size_t bstart, estart, recs, esums, carries, ecarries, hdr, evals, total;
 };
 SegLayout seg_layout(int64_t n_total, uint32_t n_filters, bool multinomial);
+// The claims of the fused permutation of such a batch: a bit per slot, in whole
+// tiles of kSegTile slots, and the tiles' prefix over the segments (both in
+// workspace; null without the permutation).
+constexpr int64_t kSegTile = 4096;
+struct SegClaim {
+  uint32_t* claim = nullptr;
+  uint32_t* tstart = nullptr;
+};
+size_t seg_claim_bytes(int64_t n_total, uint32_t n_filters);
+SegClaim seg_claim_in(void* ws, int64_t n_total, uint32_t n_filters);
 hipError_t launch_scan_segmented(int scheme, bool f64, const void* w, int64_t n_total,
                                  const int64_t* offsets, uint32_t n_filters, Key key,
                                  uint32_t offset, uint32_t filter_base, int32_t* a, void* ws,
                                  uint32_t* flags, hipStream_t stream,
-                                 uint32_t* bstart = nullptr, uint32_t* estart = nullptr);
+                                 uint32_t* bstart = nullptr, uint32_t* estart = nullptr,
+                                 const SegClaim& sc = SegClaim());
 size_t batch_scan_lds_bytes();
 
 hipError_t launch_scan(int scheme, bool f64, const void* w, int64_t n, Key key, uint32_t offset,
@@ -138,6 +149,9 @@ size_t permute_workspace_min_bytes(int64_t n_total);
 // resolve pass over the sorted ancestry of a single vector.
 hipError_t launch_resolve_sorted(const int32_t* a, int64_t n, const uint32_t* claim, int32_t* c,
                                  hipStream_t stream);
+hipError_t launch_resolve_segments(const int32_t* a, int64_t n_total, const int64_t* offsets,
+                                   uint32_t n_filters, const SegClaim& sc, int32_t* c,
+                                   hipStream_t stream);
 hipError_t launch_scan_claimed(int scheme, bool f64, const void* w, int64_t n, Key key,
                                uint32_t offset, uint32_t filter, int32_t* a, void* ws,
                                uint32_t* flags, uint32_t* claim, hipStream_t stream);

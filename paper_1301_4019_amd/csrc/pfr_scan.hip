@@ -1471,7 +1471,8 @@ __global__ __launch_bounds__(kT) void k_scan_emit_mw(const T* __restrict__ w, in
 // matters where one weight covers many of them.  r, points and comparisons
 // are those of emit_multi_wave.  Bound by the serial chain (carries, prefix,
 // ten LDS steps per searched block, expansion); four workgroups per CU at 2^20
-// weights.  MULTI_NUM
+// weights: 23 us, where carries and one block per wave took 9 and 29 (a wave
+// per SIMD).  About half of it is instruction issue, a quarter the carries.
 constexpr uint32_t kDirectMulti = 5 * kT;
 struct MultiWgLds {
   double top[kDirectMulti + 1];  // top[e]: point of the exponential prefix up to block e
@@ -1995,48 +1996,80 @@ __global__ __launch_bounds__(kT) void k_scan_batched(const T* __restrict__ w, in
 // and one workgroup per segment forms the segment's exact carries, so the
 // result is that of one call per segment.
 
-// Exclusive block prefixes over the segments: bstart[f] (weight blocks) and,
-// for the multinomial scheme, estart[f] (exponential blocks).  One workgroup.
-__global__ __launch_bounds__(kT) void k_seg_prefix(const int64_t* __restrict__ offsets,
-                                                   uint32_t n_filters,
-                                                   uint32_t* __restrict__ bstart,
-                                                   uint32_t* __restrict__ estart) {
-  __shared__ WgScratch s;
-  uint64_t carry_b = 0, carry_e = 0;
-  for (uint32_t base = 0; base < n_filters; base += kT) {
-    const uint32_t f = base + threadIdx.x;
-    uint64_t nb = 0, ne = 0;
-    if (f < n_filters) {
-      const int64_t n = offsets[f + 1] - offsets[f];
-      nb = n > 0 ? (uint64_t)((n + kBlock - 1) / kBlock) : 0;
-      ne = n > 0 ? (uint64_t)((n + 1 + kBlock - 1) / kBlock) : 0;
+// Exclusive prefixes over the segments: bstart[f] (weight blocks) and, when
+// given, estart[f] (exponential blocks) and tstart[f] (tiles of kSegTile slots
+// of the fused permutation).  One workgroup, four segments per thread and
+// round; bound by the latency of its rounds (4096 segments 5.7 us; one segment
+// per thread of 256, 19.6).
+constexpr int kPrefixThreads = 1024;
+__global__ __launch_bounds__(kPrefixThreads) void k_seg_prefix(const int64_t* __restrict__ offsets,
+                                                               uint32_t n_filters,
+                                                               uint32_t* __restrict__ bstart,
+                                                               uint32_t* __restrict__ estart,
+                                                               uint32_t* __restrict__ tstart) {
+  constexpr int kF = 4, kW = kPrefixThreads / kWave;
+  __shared__ uint32_t s_b[kW], s_e[kW], s_t[kW];
+  const uint32_t tid = threadIdx.x, wave = tid / kWave;
+  uint32_t cb = 0, ce = 0, ct = 0;  // totals of the rounds before (below 2^32, as the layouts' are)
+  for (uint32_t base = 0; base < n_filters; base += kF * kPrefixThreads) {
+    const uint32_t f0 = base + kF * tid;
+    int64_t o[kF + 1];
+#pragma unroll
+    for (int k = 0; k <= kF; ++k) o[k] = offsets[min(f0 + k, n_filters)];
+    uint32_t nb[kF], ne[kF], nt[kF], tb = 0, te = 0, tt = 0;
+#pragma unroll
+    for (int k = 0; k < kF; ++k) {
+      const int64_t n = o[k + 1] - o[k];
+      nb[k] = n > 0 ? (uint32_t)((n + kBlock - 1) / kBlock) : 0u;
+      ne[k] = n > 0 ? (uint32_t)((n + 1 + kBlock - 1) / kBlock) : 0u;
+      nt[k] = n > 0 ? (uint32_t)((n + kSegTile - 1) / kSegTile) : 0u;
+      tb += nb[k];
+      te += ne[k];
+      tt += nt[k];
     }
-    uint64_t tb, te;
-    const uint64_t xb = wg_exclusive(nb, s.u, &tb);
-    const uint64_t xe = wg_exclusive(ne, s.u, &te);
-    if (f < n_filters) {
-      bstart[f] = (uint32_t)(carry_b + xb);
-      if (estart) estart[f] = (uint32_t)(carry_e + xe);
+    const uint32_t ib = wave_inclusive_scan(tb, OpAdd()), ie = wave_inclusive_scan(te, OpAdd()),
+                   it = wave_inclusive_scan(tt, OpAdd());
+    __syncthreads();  // the round before has read the totals
+    if (lane_id() == kWave - 1) {
+      s_b[wave] = ib;
+      s_e[wave] = ie;
+      s_t[wave] = it;
     }
-    carry_b += tb;
-    carry_e += te;
+    __syncthreads();
+    uint32_t b = cb + ib - tb, e = ce + ie - te, t = ct + it - tt;
+#pragma unroll
+    for (uint32_t w2 = 0; w2 < (uint32_t)kW; ++w2) {
+      const uint32_t vb = s_b[w2], ve = s_e[w2], vt = s_t[w2];
+      b += w2 < wave ? vb : 0u;
+      e += w2 < wave ? ve : 0u;
+      t += w2 < wave ? vt : 0u;
+      cb += vb;
+      ce += ve;
+      ct += vt;
+    }
+#pragma unroll
+    for (int k = 0; k < kF; ++k) {
+      const uint32_t f = f0 + (uint32_t)k;
+      if (f < n_filters) {
+        bstart[f] = b;
+        if (estart) estart[f] = e;
+        if (tstart) tstart[f] = t;
+      }
+      b += nb[k];
+      e += ne[k];
+      t += nt[k];
+    }
   }
-  if (threadIdx.x == 0) {
-    bstart[n_filters] = (uint32_t)carry_b;
-    if (estart) estart[n_filters] = (uint32_t)carry_e;
+  if (tid == 0) {
+    bstart[n_filters] = cb;
+    if (estart) estart[n_filters] = ce;
+    if (tstart) tstart[n_filters] = ct;
   }
 }
 
-// segment f of global block g: the last f with start[f] <= g (start non-decreasing)
-__device__ __forceinline__ uint32_t seg_of_block(const uint32_t* __restrict__ start,
-                                                 uint32_t n_filters, uint32_t g) {
-  uint32_t lo = 0, hi = n_filters;
-  while (hi - lo > 1) {
-    const uint32_t mid = (lo + hi) >> 1;
-    if (start[mid] <= g) lo = mid;
-    else hi = mid;
-  }
-  return lo;
+// The claim words of segment f, when the emission writes them: whole tiles.
+__device__ __forceinline__ uint32_t* seg_claim(const SegClaim& c, uint32_t f) {
+  return c.claim ? c.claim + (size_t)c.tstart[f] * (kSegTile / 32) : nullptr;
 }
 
 template <typename T, bool MULTI>
@@ -2050,7 +2083,7 @@ __global__ __launch_bounds__(kT) void k_seg_records(
   if (blockIdx.x < grid_b) {
     const uint32_t g = blockIdx.x;
     if (g >= bstart[n_filters]) return;
-    const uint32_t f = seg_of_block(bstart, n_filters, g);
+    const uint32_t f = wave_find_segment<uint32_t>(bstart, n_filters, g);
     const int64_t base = offsets[f];
     const int64_t n = offsets[f + 1] - base;
     const BlockRec r = block_record(w + base, n, (int64_t)(g - bstart[f]) * kBlock, &s);
@@ -2058,7 +2091,7 @@ __global__ __launch_bounds__(kT) void k_seg_records(
   } else if (MULTI) {
     const uint32_t g = blockIdx.x - grid_b;
     if (g >= estart[n_filters]) return;
-    const uint32_t f = seg_of_block(estart, n_filters, g);
+    const uint32_t f = wave_find_segment<uint32_t>(estart, n_filters, g);
     const int64_t n = offsets[f + 1] - offsets[f];
     uint64_t q[kPer];
     exp_values(key, filter_base + f, offset, n, g - estart[f], q);
@@ -2079,7 +2112,7 @@ __global__ __launch_bounds__(kT) void k_seg_records_w(const T* __restrict__ w,
   const uint32_t g = blockIdx.x * kWavesPerWG +
                      (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   if (g >= bstart[n_filters]) return;
-  const uint32_t f = seg_of_block(bstart, n_filters, g);
+  const uint32_t f = wave_find_segment<uint32_t>(bstart, n_filters, g);
   const int64_t base = offsets[f];
   const int64_t n = offsets[f + 1] - base;
   const BlockRec r = wave_block_record(w + base, n, (int64_t)(g - bstart[f]) * kBlock);
@@ -2127,14 +2160,15 @@ __global__ __launch_bounds__(kT) void k_seg_emit_w(
     const T* __restrict__ w, const int64_t* __restrict__ offsets, uint32_t n_filters, Key key,
     uint32_t offset, uint32_t filter_base, const uint32_t* __restrict__ bstart,
     const BlockRec* __restrict__ recs, const u128* __restrict__ C,
-    const SegHdr* __restrict__ hdr, int32_t* __restrict__ a, uint32_t* __restrict__ flags) {
+    const SegHdr* __restrict__ hdr, int32_t* __restrict__ a, uint32_t* __restrict__ flags,
+    SegClaim sc) {
   static_assert(SCHEME != SCHEME_MULTINOMIAL, "strata schemes only");
   __shared__ StrataWaveLds<SCHEME == SCHEME_SYSTEMATIC> L[kWavesPerWG];
   offset = counter_offset(key, offset);
   const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const uint32_t g = blockIdx.x * kWavesPerWG + wave;
   if (g >= bstart[n_filters]) return;
-  const uint32_t f = seg_of_block(bstart, n_filters, g);
+  const uint32_t f = wave_find_segment<uint32_t>(bstart, n_filters, g);
   const int64_t base = offsets[f];
   const int64_t n = offsets[f + 1] - base;
   const uint32_t b = g - bstart[f];
@@ -2143,13 +2177,13 @@ __global__ __launch_bounds__(kT) void k_seg_emit_w(
   if (flags && b == 0 && lane_id() == 0 && status) atomicOr(flags, status);
   const int64_t P0 = (int64_t)b * kBlock;
   if (status & (FLAG_BAD_WEIGHTS | FLAG_ZERO_TOTAL)) {
-    for (int64_t i = P0 + lane_id(); i < min(P0 + kBlock, n); i += kWave) as[i] = (int32_t)i;
+    block_identity(P0, n, (int)lane_id(), kWave, as, seg_claim(sc, f));
     return;
   }
   const u128* Cs = C + bstart[f] + f;
   emit_block_wave<T, SCHEME == SCHEME_SYSTEMATIC>(w + base, n, P0, recs[g], Cs[b], Cs[b + 1],
                                                    hdr[f].gscale, hdr[f].Q, key, filter_base + f,
-                                                   offset, as, &L[wave], nullptr);
+                                                   offset, as, &L[wave], seg_claim(sc, f));
 }
 
 // Multinomial emission of the segmented batch, one block per wave.
@@ -2159,13 +2193,14 @@ __global__ __launch_bounds__(kT) void k_seg_emit_mw(
     uint32_t offset, uint32_t filter_base, const uint32_t* __restrict__ bstart,
     const uint32_t* __restrict__ estart, const BlockRec* __restrict__ recs,
     const u128* __restrict__ C, const u128* __restrict__ CE, const SegHdr* __restrict__ hdr,
-    int32_t* __restrict__ a, uint32_t* __restrict__ flags, const uint64_t* __restrict__ evals) {
+    int32_t* __restrict__ a, uint32_t* __restrict__ flags, const uint64_t* __restrict__ evals,
+    SegClaim sc) {
   __shared__ MultiWaveLds L[kWavesPerWG];
   offset = counter_offset(key, offset);
   const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const uint32_t g = blockIdx.x * kWavesPerWG + wave;
   if (g >= bstart[n_filters]) return;
-  const uint32_t f = seg_of_block(bstart, n_filters, g);
+  const uint32_t f = wave_find_segment<uint32_t>(bstart, n_filters, g);
   const int64_t base = offsets[f];
   const int64_t n = offsets[f + 1] - base;
   const uint32_t b = g - bstart[f];
@@ -2174,14 +2209,14 @@ __global__ __launch_bounds__(kT) void k_seg_emit_mw(
   if (flags && b == 0 && lane_id() == 0 && status) atomicOr(flags, status);
   const int64_t P0 = (int64_t)b * kBlock;
   if (status & (FLAG_BAD_WEIGHTS | FLAG_ZERO_TOTAL)) {
-    for (int64_t i = P0 + lane_id(); i < min(P0 + kBlock, n); i += kWave) as[i] = (int32_t)i;
+    block_identity(P0, n, (int)lane_id(), kWave, as, seg_claim(sc, f));
     return;
   }
   const u128* Cs = C + bstart[f] + f;
   const uint32_t nbe = estart[f + 1] - estart[f];
   emit_multi_wave<T, true>(w + base, n, P0, recs[g], Cs[b], Cs[b + 1], hdr[f].gscale, hdr[f].Q,
                            key, filter_base + f, offset, CE + estart[f] + f, nbe,
-                           evals + (size_t)estart[f] * kBlock, as, &L[wave]);
+                           evals + (size_t)estart[f] * kBlock, as, &L[wave], seg_claim(sc, f));
 }
 
 // The two-level carries of a single vector in its workspace.
@@ -2331,7 +2366,7 @@ template <typename T, int SCHEME>
 hipError_t launch_segmented_t(const T* w, int64_t n_total, const int64_t* offsets,
                               uint32_t n_filters, Key key, uint32_t offset, uint32_t filter_base,
                               int32_t* a, void* ws, uint32_t* flags, uint32_t* bstart,
-                              uint32_t* estart, hipStream_t stream) {
+                              uint32_t* estart, const SegClaim& sc, hipStream_t stream) {
   constexpr bool multi = SCHEME == SCHEME_MULTINOMIAL;
   const SegLayout L = seg_layout(n_total, n_filters, multi);
   char* base = (char*)ws;
@@ -2342,8 +2377,8 @@ hipError_t launch_segmented_t(const T* w, int64_t n_total, const int64_t* offset
   if (!bstart) {  // (else the caller keeps the block prefixes)
     bstart = (uint32_t*)(base + L.bstart);
     estart = multi ? (uint32_t*)(base + L.estart) : nullptr;
-    hipLaunchKernelGGL(k_seg_prefix, dim3(1), dim3(kT), 0, stream, offsets, n_filters, bstart,
-                       estart);
+    hipLaunchKernelGGL(k_seg_prefix, dim3(1), dim3(kPrefixThreads), 0, stream, offsets, n_filters,
+                       bstart, estart, sc.tstart);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
@@ -2367,10 +2402,10 @@ hipError_t launch_segmented_t(const T* w, int64_t n_total, const int64_t* offset
   if constexpr (multi)
     hipLaunchKernelGGL((k_seg_emit_mw<T>), dim3(wgs_b), dim3(kT), 0, stream, w, offsets,
                        n_filters, key, offset, filter_base, bstart, estart, recs, C, CE, hdr, a,
-                       flags, (const uint64_t*)evals);
+                       flags, (const uint64_t*)evals, sc);
   else
     hipLaunchKernelGGL((k_seg_emit_w<T, SCHEME>), dim3(wgs_b), dim3(kT), 0, stream, w, offsets,
-                       n_filters, key, offset, filter_base, bstart, recs, C, hdr, a, flags);
+                       n_filters, key, offset, filter_base, bstart, recs, C, hdr, a, flags, sc);
   return hipGetLastError();
 }
 
@@ -2379,21 +2414,21 @@ hipError_t launch_segmented_scheme(int scheme, const void* w, int64_t n_total,
                                    const int64_t* offsets, uint32_t n_filters, Key key,
                                    uint32_t offset, uint32_t filter_base, int32_t* a, void* ws,
                                    uint32_t* flags, uint32_t* bstart, uint32_t* estart,
-                                   hipStream_t stream) {
+                                   const SegClaim& sc, hipStream_t stream) {
   const T* wt = (const T*)w;
   switch (scheme) {
     case SCHEME_MULTINOMIAL:
       return launch_segmented_t<T, SCHEME_MULTINOMIAL>(wt, n_total, offsets, n_filters, key,
                                                        offset, filter_base, a, ws, flags, bstart,
-                                                       estart, stream);
+                                                       estart, sc, stream);
     case SCHEME_STRATIFIED:
       return launch_segmented_t<T, SCHEME_STRATIFIED>(wt, n_total, offsets, n_filters, key,
                                                       offset, filter_base, a, ws, flags, bstart,
-                                                       estart, stream);
+                                                       estart, sc, stream);
     default:
       return launch_segmented_t<T, SCHEME_SYSTEMATIC>(wt, n_total, offsets, n_filters, key,
                                                       offset, filter_base, a, ws, flags, bstart,
-                                                       estart, stream);
+                                                       estart, sc, stream);
   }
 }
 
@@ -2421,13 +2456,13 @@ hipError_t launch_scan_segmented(int scheme, bool f64, const void* w, int64_t n_
                                  const int64_t* offsets, uint32_t n_filters, Key key,
                                  uint32_t offset, uint32_t filter_base, int32_t* a, void* ws,
                                  uint32_t* flags, hipStream_t stream, uint32_t* bstart,
-                                 uint32_t* estart) {
+                                 uint32_t* estart, const SegClaim& sc) {
   return f64 ? launch_segmented_scheme<double>(scheme, w, n_total, offsets, n_filters, key,
                                                offset, filter_base, a, ws, flags, bstart, estart,
-                                               stream)
+                                               sc, stream)
              : launch_segmented_scheme<float>(scheme, w, n_total, offsets, n_filters, key,
                                               offset, filter_base, a, ws, flags, bstart, estart,
-                                               stream);
+                                               sc, stream);
 }
 
 ScanLayout scan_layout(int64_t n, bool multinomial) {

@@ -131,3 +131,35 @@ def test_resolve_of_the_fused_claim(scheme, n):
         a, c = pfr().resample_permuted(scheme, dev(w), seed=5)
         a, c = host(a), host(c)
         assert np.array_equal(c, oracle.permute(a)[0])
+
+
+@pytest.mark.parametrize("scheme", ["stratified", "systematic", "multinomial"])
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("short", [0, 6000])
+def test_permutation_fused_into_a_batch(scheme, dtype, short):
+    """Tiles of 4096 slots at their edges, empty segments, chains that leave
+    the window, invalid and zero segments; and (short) segments so small that
+    the claims do not fit, which are permuted after the emission as before."""
+    sizes = [0, 1, 4095, 4096, 4097, 0, 31, 8191, 8192, 8193, 16385, 65537, 200000, 3, 12288, 5000]
+    sizes += [1, 0, 2] * (short // 3) + [0]
+    kinds = [0.0, 4.0, "wide", "one", 2.0]
+    ws = [weights(kinds[f % 5], n, dtype) if n else np.zeros(0, dtype) for f, n in enumerate(sizes)]
+    g = np.random.default_rng(1)
+    ws[12] = (np.where(np.arange(200000) < 100000, 0.01, 1.0) * (g.random(200000) + 0.5)).astype(dtype)
+    ws[14][5] = np.nan
+    ws[15][:] = 0
+    if short:  # mostly tiny segments
+        for f in (11, 12):
+            sizes[f], ws[f] = 7, ws[f][:7]
+    w, off = np.concatenate(ws), np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    fl = new_flags()
+    kw = dict(seed=3, filter_base=1, offsets=dev(off))
+    a, c = pfr().resample_permuted(scheme, dev(w), flags=fl, **kw)
+    a, c = host(a), host(c)
+    assert np.array_equal(a, host(getattr(pfr(), "resample_" + scheme)(dev(w), **kw)))
+    for f, n in enumerate(sizes):
+        if n:
+            s = slice(off[f], off[f + 1])
+            assert np.array_equal(c[s], oracle.permute(a[s])[0]), (f, n)
+    m = pfr()
+    assert int(host(fl)[0]) == m.FLAG_BAD_WEIGHTS | m.FLAG_ZERO_TOTAL
