@@ -131,7 +131,8 @@ bool block_parallel_batch(int scheme, const SegInfo& s) {
 
 int collective(int scheme, const void* w, pfr_dtype dtype, const pfr_segments* seg,
                pfr_precision precision, pfr_rng rng, int32_t* a, void* ws, size_t ws_bytes,
-               uint32_t* dev_flags, void* stream, const SegClaim& sc = SegClaim()) {
+               uint32_t* dev_flags, void* stream, const SegClaim& sc = SegClaim(),
+               int32_t* permuted = nullptr) {
   SegInfo s;
   int rc = check_segments(seg, &s);
   if (rc) return rc;
@@ -160,7 +161,7 @@ int collective(int scheme, const void* w, pfr_dtype dtype, const pfr_segments* s
     }
     return launch_result(launch_scan_batched(scheme, dtype == PFR_F64, w, s.n_total, s.offsets,
                                              s.n_filters, s.max_len, key, rng.offset,
-                                             rng.filter_base, a, dev_flags, st));
+                                             rng.filter_base, a, dev_flags, st, permuted));
   }
   const ScanLayout L = scan_layout(s.n_total, scheme == SCHEME_MULTINOMIAL);
   if (!ws || ws_bytes < L.total) return PFR_EWORKSPACE;
@@ -585,6 +586,13 @@ int resample_permuted(pfr_op scheme, const void* w, pfr_dtype dtype, const pfr_s
       return launch_result(
           launch_resolve_sorted(ancestors, s.n_total, (const uint32_t*)ws, permuted, st));
     }
+    // the strata schemes in one workgroup per vector or segment: all of it in
+    // one launch
+    const int64_t len = s.n_filters == 1 ? s.n_total : s.max_len;
+    if (cscheme != SCHEME_MULTINOMIAL && len > 0 && len <= kOneWgMax &&
+        (s.n_filters == 1 ? !uses_scan_workspace(s) : !block_parallel_batch(cscheme, s)))
+      return collective(cscheme, w, dtype, seg, params->precision, rng, ancestors, rws, rbytes,
+                        dev_flags, stream, SegClaim(), permuted);
     const bool few = s.max_len > 0 && s.max_len <= 2048 && s.n_filters < 256;
     if (block_parallel_batch(cscheme, s) && !few &&
         seg_claim_bytes(s.n_total, s.n_filters) <= perm) {
@@ -666,6 +674,7 @@ int lgssm_step(const pfr_lgssm* model, pfr_op scheme, pfr_precision precision, i
   rkey.offset_dev = t_dev;
   const uint32_t nf = (uint32_t)n_filters;
   hipError_t e;
+  bool permutes = false;  // the resampler permutes too
   switch (scheme) {
     case PFR_OP_METROPOLIS:
       e = launch_metropolis(false, w, total, offsets, nf, n, 0, B_dev, rkey, 0u, rng.filter_base,
@@ -680,9 +689,9 @@ int lgssm_step(const pfr_lgssm* model, pfr_op scheme, pfr_precision precision, i
                       : scheme == PFR_OP_STRATIFIED ? SCHEME_STRATIFIED
                                                     : SCHEME_SYSTEMATIC;
       // the resampler's workspace is free again before the permutation uses it
-      e = precision == PFR_SCAN_EXACT && n <= kOneWgMax && sch != SCHEME_MULTINOMIAL
-              ? launch_scan_batched(sch, false, w, total, offsets, nf, n, rkey, 0u,
-                                    rng.filter_base, ancestors, dev_flags, st)
+      permutes = precision == PFR_SCAN_EXACT && n <= kOneWgMax && sch != SCHEME_MULTINOMIAL;
+      e = permutes ? launch_scan_batched(sch, false, w, total, offsets, nf, n, rkey, 0u,
+                                         rng.filter_base, ancestors, dev_flags, st, permuted)
           : precision == PFR_SCAN_EXACT
               ? launch_scan_segmented(sch, false, w, total, offsets, nf, rkey, 0u,
                                       rng.filter_base, ancestors, perm_ws, dev_flags, st,
@@ -692,9 +701,11 @@ int lgssm_step(const pfr_lgssm* model, pfr_op scheme, pfr_precision precision, i
     }
   }
   if (e != hipSuccess) return PFR_ELAUNCH;
-  e = launch_permute(ancestors, total, offsets, nf, n, collective_scheme, permuted, perm_ws,
-                     permute_workspace_bytes(total, nf), dev_flags, st);
-  if (e != hipSuccess) return PFR_ELAUNCH;
+  if (!permutes) {
+    e = launch_permute(ancestors, total, offsets, nf, n, collective_scheme, permuted, perm_ws,
+                       permute_workspace_bytes(total, nf), dev_flags, st);
+    if (e != hipSuccess) return PFR_ELAUNCH;
+  }
   Key nkey = make_key(rng);
   nkey.offset_dev = nullptr;
   return launch_result(launch_lgssm_move(n_filters, n, model->phi, model->q, model->r,

@@ -97,7 +97,7 @@ hipError_t launch_scan(int scheme, bool f64, const void* w, int64_t n, Key key, 
 hipError_t launch_scan_batched(int scheme, bool f64, const void* w, int64_t n_total,
                                const int64_t* offsets, uint32_t n_filters, int64_t max_len,
                                Key key, uint32_t offset, uint32_t filter_base, int32_t* a,
-                               uint32_t* flags, hipStream_t stream);
+                               uint32_t* flags, hipStream_t stream, int32_t* c = nullptr);
 // Longest segment that the strata schemes resample in one workgroup and launch.
 constexpr int64_t kOneWgMax = 16384;
 

@@ -1651,21 +1651,33 @@ __global__ __launch_bounds__(kT) void k_scan_emit_mb(const T* __restrict__ w, in
 // n = 1000 8.3 -> 3.9 us, 4096 9.4 -> 5.8 us (from 256 threads with 16 weights
 // a lane); 65536 segments of 256 535 -> 185 us and 1024 of 16384 61 -> 46 us
 // (from records, carries and emission).
+//
+// PERM: the permutation of Code 10 too.  The claimed slots are the particles
+// with outputs, which a thread knows for its own quads; the winners, the first
+// outputs of their runs, are the marked positions.  The ancestry is in LDS
+// already, so the chains are walked there: the first kOneSteps steps of a quad
+// together, the rest from a list.  With the permutation as a second launch
+// (k_permute_lds) -> in this one, systematic: one vector of 1000 9.7 -> 7.2 us,
+// 4096 of 300 28.5 -> 21.1, 65536 of 256 298 -> 209, 4096 of 4096 127 -> 91,
+// 1024 of 16384 97 -> 84 (a step of as many filters: 88 -> 64).
+constexpr uint32_t kMarked = 0x80000000u;
+constexpr int kOneSteps = 3;
 template <int NB>
 struct OneWg {
   static constexpr int kThreads = NB >= 4 ? 1024 : 256 * NB;
   static constexpr int kW = kThreads / kWave;               // waves
   static constexpr int kR = NB * kBlock / (4 * kThreads);   // quads per thread
   static constexpr int kParts = NB * 4;                     // waves' shares of blocks
+  static constexpr uint32_t kList = NB >= 4 ? 1024 : 256;   // entries of the chains' list
   static_assert(kParts <= kWave, "a wave holds one entry per share");
 };
 
-template <typename T, int SCHEME, int NB>
+template <typename T, int SCHEME, int NB, bool PERM>
 __global__ __launch_bounds__(OneWg<NB>::kThreads,
                              NB == 16 && sizeof(T) == 4 ? 8 : 1) void k_scan_one(
     const T* __restrict__ w_all, int64_t n_total, const int64_t* __restrict__ offsets,
     int64_t above, Key key, uint32_t offset, uint32_t filter_base, int32_t* __restrict__ a_all,
-    uint32_t* __restrict__ flags) {
+    int32_t* __restrict__ c_all, uint32_t* __restrict__ flags) {
   typedef OneWg<NB> G;
   constexpr bool SYSTEMATIC = SCHEME == SCHEME_SYSTEMATIC;
   static_assert(SCHEME != SCHEME_MULTINOMIAL, "strata schemes only");
@@ -1674,6 +1686,7 @@ __global__ __launch_bounds__(OneWg<NB>::kThreads,
   __shared__ uint32_t s_key[G::kParts];
   __shared__ uint64_t s_sum[G::kParts];
   __shared__ int32_t s_top[G::kParts];
+  __shared__ uint32_t s_list[PERM ? G::kList : 1], s_count;
   const uint32_t f = blockIdx.x;
   const int64_t base = offsets ? offsets[f] : 0;
   const int64_t n = offsets ? offsets[f + 1] - base : n_total;
@@ -1764,9 +1777,14 @@ __global__ __launch_bounds__(OneWg<NB>::kThreads,
   const uint32_t status = bad | (!bad && Q == 0 ? FLAG_ZERO_TOTAL : 0u);
   if (flags && tid == 0 && status) atomicOr(flags, status);
   if (status) {
-    for (int32_t i = tid; i < n32; i += G::kThreads) a[i] = i;
+    for (int32_t i = tid; i < n32; i += G::kThreads) {
+      a[i] = i;
+      if (PERM) c_all[base + i] = i;
+    }
     return;
   }
+  if (PERM && tid == 0) s_count = 0;
+  uint32_t claimed = 0;  // bit 4 r + v: particle v of the thread's quad r has outputs
   const RMap rm = make_rmap(Q, n);
   const double lo_l = rm(inc - val), hi_l = rm(inc), slope = rm.Nd * rm.invQ;
   const double t_sys =
@@ -1803,7 +1821,10 @@ __global__ __launch_bounds__(OneWg<NB>::kThreads,
         o += quantize_nb(x[r][v], scale[r]);
       }
       const int32_t O = cum(r_of(kAgain ? o : o + q[kAgain ? 0 : r][v]));
-      if (O > p && i + v < n32) M[p] = i + v;
+      if (O > p && i + v < n32) {
+        M[p] = i + v;
+        if (PERM) claimed |= 1u << (4 * r + v);
+      }
       p = O;
     }
     __builtin_amdgcn_sched_barrier(0);  // one round's values in registers at a time
@@ -1811,9 +1832,13 @@ __global__ __launch_bounds__(OneWg<NB>::kThreads,
   __syncthreads();
   // expansion: the running maximum of the markers
   int32_t m[G::kR][4], in[G::kR];
+  uint32_t won = 0;  // bit 4 r + v: position v of the thread's quad r is marked
 #pragma unroll
   for (int r = 0; r < G::kR; ++r) {
     const int4 t = reinterpret_cast<const int4*>(M)[r * G::kThreads + tid];
+    if (PERM)
+      won |= ((t.x >= 0 ? 1u : 0u) | (t.y >= 0 ? 2u : 0u) | (t.z >= 0 ? 4u : 0u) |
+              (t.w >= 0 ? 8u : 0u)) << (4 * r);
     m[r][0] = t.x;
     m[r][1] = max(t.y, m[r][0]);
     m[r][2] = max(t.z, m[r][1]);
@@ -1830,11 +1855,58 @@ __global__ __launch_bounds__(OneWg<NB>::kThreads,
         part > 0 ? (int32_t)__builtin_amdgcn_readlane(tops, part - 1) : -1;
     const int32_t before = max(upto, (int32_t)wave_shift_up_u32((uint32_t)in[r], 0xFFFFFFFFu));
     const uint32_t i = (uint32_t)(r * 4 * G::kThreads + 4 * tid);
-    if (i < (uint32_t)n32)
-      store_quad(a, i, (uint32_t)n32, max(m[r][0], before), max(m[r][1], before),
-                 max(m[r][2], before), max(m[r][3], before));
+#pragma unroll
+    for (int v = 0; v < 4; ++v) m[r][v] = max(m[r][v], before);
+    if (i < (uint32_t)n32) store_quad(a, i, (uint32_t)n32, m[r][0], m[r][1], m[r][2], m[r][3]);
+    if constexpr (PERM) {
+      uint32_t y[4];
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        y[v] = (uint32_t)m[r][v] | ((won >> (4 * r + v)) & 1u ? kMarked : 0u);
+      reinterpret_cast<uint4*>(M)[r * G::kThreads + tid] = make_uint4(y[0], y[1], y[2], y[3]);
+    }
+  }
+  if constexpr (PERM) {
+    const uint32_t* MM = reinterpret_cast<const uint32_t*>(M);
+    int32_t* __restrict__ c = c_all + base;
+    auto walk = [&](uint32_t y) -> uint32_t {  // the end of the chain from the marked value y
+      while (y & kMarked) y = MM[y & ~kMarked];
+      return y;
+    };
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < G::kR; ++r) {
+      const uint32_t i = (uint32_t)(r * 4 * G::kThreads + 4 * tid);
+      if (i >= (uint32_t)n32) break;
+      const uint4 t = reinterpret_cast<const uint4*>(MM)[r * G::kThreads + tid];
+      uint32_t y[4] = {t.x, t.y, t.z, t.w};
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        if ((claimed >> (4 * r + v)) & 1u || i + v >= (uint32_t)n32) y[v] = i + v;
+      for (int k = 0; k < kOneSteps && ((y[0] | y[1] | y[2] | y[3]) & kMarked); ++k) {
+        uint32_t z[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) z[v] = MM[y[v] & kMarked ? y[v] & ~kMarked : 0u];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) y[v] = y[v] & kMarked ? z[v] : y[v];
+      }
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        if (y[v] & kMarked) {
+          const uint32_t at = atomicAdd(&s_count, 1u);
+          if (at < G::kList) s_list[at] = (i + v) << 16 | (y[v] & ~kMarked);
+          else y[v] = walk(y[v]);
+        }
+      }
+      store_quad(c, i, (uint32_t)n32, (int32_t)y[0], (int32_t)y[1], (int32_t)y[2], (int32_t)y[3]);
+    }
+    __syncthreads();  // also orders the chains' slots after the quads stored above
+    const uint32_t listed = min(s_count, G::kList);
+    for (uint32_t k = (uint32_t)tid; k < listed; k += G::kThreads)
+      c[s_list[k] >> 16] = (int32_t)walk((s_list[k] & 0xFFFFu) | kMarked);
   }
 }
+
 
 // ---------------------------------------------------------------- Code 5
 // Multinomial resampling with one independent uniform per particle, as Code 5
@@ -2312,29 +2384,33 @@ hipError_t launch_scan_scheme(int scheme, const void* w, int64_t n, Key key, uin
 
 // One workgroup per segment (or for one vector): the strata schemes in tiers
 // of segment length, the multinomial scheme and longer segments through
-// k_scan_batched.  max_len: longest segment (0 = unknown).
+// k_scan_batched.  max_len: longest segment (0 = unknown).  c: the permuted
+// ancestry too (strata schemes, max_len known and at most kOneWgMax).
 template <typename T, int SCHEME>
 hipError_t launch_batched_t(const T* w, int64_t n_total, const int64_t* offsets,
                             uint32_t n_filters, int64_t max_len, Key key, uint32_t offset,
-                            uint32_t filter_base, int32_t* a, uint32_t* flags,
+                            uint32_t filter_base, int32_t* a, int32_t* c, uint32_t* flags,
                             hipStream_t stream) {
   int64_t above = 0;
   if constexpr (SCHEME != SCHEME_MULTINOMIAL) {
     if (!offsets) max_len = n_total;
     const bool equal = max_len > 0 && max_len * (int64_t)n_filters == n_total;
-    auto tier = [&](auto kernel, int threads, int64_t upto) {
+    auto tier = [&](auto plain, auto perm, int threads, int64_t upto) {
       // a tier is left to the next one where every segment is longer, or where
       // few segments would only add launches
       if (max_len > 0 && above >= max_len) return;
       if ((max_len <= 0 || max_len > upto) && (equal || (upto < kOneWgMax && n_filters <= 256)))
         return;
-      hipLaunchKernelGGL(kernel, dim3(n_filters), dim3(threads), 0, stream, w, n_total, offsets,
-                         above, key, offset, filter_base, a, flags);
+      hipLaunchKernelGGL(c ? perm : plain, dim3(n_filters), dim3(threads), 0, stream, w, n_total,
+                         offsets, above, key, offset, filter_base, a, c, flags);
       above = upto;
     };
-    tier(k_scan_one<T, SCHEME, 1>, OneWg<1>::kThreads, 1024);
-    tier(k_scan_one<T, SCHEME, 4>, OneWg<4>::kThreads, 4096);
-    tier(k_scan_one<T, SCHEME, 16>, OneWg<16>::kThreads, kOneWgMax);
+    tier(k_scan_one<T, SCHEME, 1, false>, k_scan_one<T, SCHEME, 1, true>, OneWg<1>::kThreads,
+         1024);
+    tier(k_scan_one<T, SCHEME, 4, false>, k_scan_one<T, SCHEME, 4, true>, OneWg<4>::kThreads,
+         4096);
+    tier(k_scan_one<T, SCHEME, 16, false>, k_scan_one<T, SCHEME, 16, true>, OneWg<16>::kThreads,
+         kOneWgMax);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess || (max_len > 0 && max_len <= kOneWgMax)) return e;
   }
@@ -2347,18 +2423,18 @@ template <typename T>
 hipError_t launch_batched_scheme(int scheme, const void* w, int64_t n_total,
                                  const int64_t* offsets, uint32_t n_filters, int64_t max_len,
                                  Key key, uint32_t offset, uint32_t filter_base, int32_t* a,
-                                 uint32_t* flags, hipStream_t stream) {
+                                 int32_t* c, uint32_t* flags, hipStream_t stream) {
   const T* wt = (const T*)w;
   switch (scheme) {
     case SCHEME_MULTINOMIAL:
       return launch_batched_t<T, SCHEME_MULTINOMIAL>(wt, n_total, offsets, n_filters, max_len, key,
-                                                     offset, filter_base, a, flags, stream);
+                                                     offset, filter_base, a, c, flags, stream);
     case SCHEME_STRATIFIED:
       return launch_batched_t<T, SCHEME_STRATIFIED>(wt, n_total, offsets, n_filters, max_len, key,
-                                                    offset, filter_base, a, flags, stream);
+                                                    offset, filter_base, a, c, flags, stream);
     default:
       return launch_batched_t<T, SCHEME_SYSTEMATIC>(wt, n_total, offsets, n_filters, max_len, key,
-                                                    offset, filter_base, a, flags, stream);
+                                                    offset, filter_base, a, c, flags, stream);
   }
 }
 
@@ -2580,11 +2656,11 @@ hipError_t launch_scan_claimed(int scheme, bool f64, const void* w, int64_t n, K
 hipError_t launch_scan_batched(int scheme, bool f64, const void* w, int64_t n_total,
                                const int64_t* offsets, uint32_t n_filters, int64_t max_len,
                                Key key, uint32_t offset, uint32_t filter_base, int32_t* a,
-                               uint32_t* flags, hipStream_t stream) {
+                               uint32_t* flags, hipStream_t stream, int32_t* c) {
   return f64 ? launch_batched_scheme<double>(scheme, w, n_total, offsets, n_filters, max_len, key,
-                                             offset, filter_base, a, flags, stream)
+                                             offset, filter_base, a, c, flags, stream)
              : launch_batched_scheme<float>(scheme, w, n_total, offsets, n_filters, max_len, key,
-                                            offset, filter_base, a, flags, stream);
+                                            offset, filter_base, a, c, flags, stream);
 }
 
 }  // namespace pfr

@@ -163,3 +163,38 @@ def test_permutation_fused_into_a_batch(scheme, dtype, short):
             assert np.array_equal(c[s], oracle.permute(a[s])[0]), (f, n)
     m = pfr()
     assert int(host(fl)[0]) == m.FLAG_BAD_WEIGHTS | m.FLAG_ZERO_TOTAL
+
+
+@pytest.mark.parametrize("scheme", SCHEMES)
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("max_len", [1024, 4096, 16384])
+def test_permutation_in_one_workgroup(scheme, dtype, max_len):
+    """Segments of every tier with the permutation in the same launch, chains
+    long enough for the list and past its end, invalid and zero segments; and
+    single vectors."""
+    sizes = [n for n in (1, 0, 2, 5, 255, 1023, 1024, 1025, 4095, 4096, 4097, 9000, 16383, 16384)
+             if n <= max_len] * 3
+    kinds = [0.0, 4.0, "wide", "one", "drift"]
+    ws = []
+    for f, n in enumerate(sizes):
+        k = kinds[f % 5]
+        ws.append(np.linspace(0.01, 1.0, n).astype(dtype) if k == "drift" else
+                  weights(k, n, dtype) if n else np.zeros(0, dtype))
+    ws[4][:] = 0
+    ws[5][3] = np.inf
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    w = dev(np.concatenate(ws))
+    fl = new_flags()
+    kw = dict(seed=3, filter_base=1, offsets=dev(off), max_len=max_len)
+    a, c = pfr().resample_permuted(scheme, w, flags=fl, **kw)
+    a, c = host(a), host(c)
+    assert np.array_equal(a, host(getattr(pfr(), "resample_" + scheme)(w, **kw)))
+    for f, n in enumerate(sizes):
+        if n:
+            s = slice(off[f], off[f + 1])
+            assert np.array_equal(c[s], oracle.permute(a[s])[0]), (f, n)
+            if n <= 4096:
+                a1, c1 = pfr().resample_permuted(scheme, dev(ws[f]), seed=3, filter_base=1 + f)
+                assert np.array_equal(host(a1), a[s]) and np.array_equal(host(c1), c[s]), (f, n)
+    m = pfr()
+    assert int(host(fl)[0]) == m.FLAG_BAD_WEIGHTS | m.FLAG_ZERO_TOTAL
