@@ -558,7 +558,10 @@ __device__ __forceinline__ uint64_t quantize_nb(T v, int scale) {
     const float t = floorf(ldexpf(v, scale));
     const float hi = floorf(t * 0x1p-32f);
     const float lo = __builtin_fmaf(hi, -0x1p32f, t);
-    return ((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo;
+    // the pair as one value, or sums of it become two additions
+    uint64_t q = ((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo;
+    asm("" : "+v"(q));
+    return q;
   } else {
     typedef WTraits<T> Tr;
     const uint64_t b = Tr::bits(v);
@@ -572,7 +575,27 @@ __device__ __forceinline__ uint64_t quantize_nb(T v, int scale) {
 }
 
 // u64 -> binary64, rounded once (the high half converts exactly).
-__device__ __forceinline__ double u64_to_f64(uint64_t x) { return (double)x; }
+__device__ __forceinline__ double u64_to_f64(uint64_t x) {
+  uint32_t hi = (uint32_t)(x >> 32);
+  asm("" : "+v"(hi));  // a 32-bit conversion
+  return __fma_rn((double)hi, 0x1p32, (double)(uint32_t)x);
+}
+
+// r (or a point p) of the local prefix L by a block's affine map, clamped to
+// the block's upper end; the whole block sum is that end exactly.  No branch:
+// the two selects cost less than the exec masks of one.
+__device__ __forceinline__ double affine_r(uint64_t L, uint64_t total, double c, double lo,
+                                           double hi) {
+  const double rv = fmin(__fma_rn(u64_to_f64(L), c, lo), hi);
+  return L == total ? hi : rv;
+}
+
+// O(r) = #{s : s + 1 - u_s <= r}, exactly, for 0 <= r <= n < 2^31 and
+// t = 1 - u_m in (0, 1], m = floor(r): m + [frac(r) >= t].  At r = n the
+// fraction is 0, so any t gives n.
+__device__ __forceinline__ uint32_t cum_at(double r, double t) {
+  return (uint32_t)(int32_t)r + (__builtin_amdgcn_fract(r) >= t ? 1u : 0u);
+}
 
 // Record of the block at base (one wave): validity, reference exponent, sum.
 template <typename T>
@@ -635,9 +658,7 @@ __device__ __forceinline__ void block_r_wave(const T* __restrict__ w, int64_t n,
   // block's range, as in exact arithmetic
 #pragma unroll
   for (int v = 0; v < kWPer; ++v) {
-    const uint64_t Lv = off + q[v];
-    const double rv = __fma_rn(u64_to_f64(Lv), c, R.lo);
-    R.r[v] = (Lv == total || rv > R.hi) ? R.hi : rv;
+    R.r[v] = affine_r(off + q[v], total, c, R.lo, R.hi);
   }
 }
 
@@ -757,26 +778,14 @@ __device__ __forceinline__ void emit_block_wave(const T* __restrict__ w, int64_t
     }
     wave_lds_sync();
   }
-  // O(r) = #{s : s + 1 - u_s <= r}, exactly: m = floor(r), frac(r) >= 1 - u_m
-  // (0 <= r <= n < 2^31, so m converts exactly to 32 bits)
   const int32_t n32 = (int32_t)n, mlo32 = (int32_t)m_lo;
-  auto cum_sys = [&](double rv) -> uint32_t {
-    const double mf = floor(rv);
-    const int32_t m = (int32_t)mf;
-    return m >= n32 ? (uint32_t)n32 : (uint32_t)m + ((rv - mf) >= t_sys ? 1u : 0u);
-  };
+  auto cum_sys = [&](double rv) -> uint32_t { return cum_at(rv, t_sys); };
   auto cum_tab = [&](double rv) -> uint32_t {
-    const double mf = floor(rv);
-    const int32_t m = (int32_t)mf;
-    const double t = 1.0 - u_offset(L->u[m >= n32 ? 0 : m - mlo32]);
-    return m >= n32 ? (uint32_t)n32 : (uint32_t)m + ((rv - mf) >= t ? 1u : 0u);
+    const int32_t m = (int32_t)rv;
+    return cum_at(rv, 1.0 - u_offset(L->u[m >= n32 ? 0 : m - mlo32]));
   };
   auto cum_draw = [&](double rv) -> uint32_t {
-    const double mf = floor(rv);
-    const int32_t m = (int32_t)mf;
-    if (m >= n32) return (uint32_t)n32;
-    const double t = 1.0 - u_offset(stratum_word(key, filter, offset, m));
-    return (uint32_t)m + ((rv - mf) >= t ? 1u : 0u);
+    return cum_at(rv, 1.0 - u_offset(stratum_word(key, filter, offset, (int32_t)rv)));
   };
   uint32_t O[kWPer];
   uint32_t O_lo, O_hi;
@@ -941,9 +950,7 @@ __device__ __forceinline__ void emit_multi_wave(const T* __restrict__ w, int64_t
       double pv[2];
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
-        const uint64_t Lv = off + q[2 * k + h];
-        const double v = __fma_rn(u64_to_f64(Lv), ce, p_base);
-        pv[h] = (Lv == total || v > p_top) ? p_top : v;
+        pv[h] = affine_r(off + q[2 * k + h], total, ce, p_base, p_top);
       }
       P2[k] = make_double2(pv[0], pv[1]);
     }
@@ -1215,10 +1222,7 @@ __device__ __forceinline__ void wg_block_r(const uint64_t (&q)[kPer], uint64_t o
   R.lo = rm(C.Cb);
   R.hi = rm(C.Cb1);
   const double c = ldexp(rm.Nd * rm.invQ, C.gscale - scale);
-  auto r_of = [&](uint64_t L) -> double {
-    const double rv = __fma_rn(u64_to_f64(L), c, R.lo);
-    return (L == total || rv > R.hi) ? R.hi : rv;
-  };
+  auto r_of = [&](uint64_t L) -> double { return affine_r(L, total, c, R.lo, R.hi); };
   R.prev = off ? r_of(off) : R.lo;  // (no weight before: the block's lower end)
 #pragma unroll
   for (int v = 0; v < kPer; ++v) R.r[v] = r_of(off + q[v]);
@@ -1360,8 +1364,6 @@ __global__ __launch_bounds__(kT) void k_scan_emit_b(const T* __restrict__ w, int
   wg_block_r(q, off, &L.ps, rec.scale, c, n, R);
   if (!(R.hi > R.lo) && !claim) return;  // an empty range has no outputs
 
-  // O(r) = #{s : s + 1 - u_s <= r}, exactly: m = floor(r), frac(r) >= 1 - u_m
-  // (0 <= r <= n < 2^31, so m converts exactly to 32 bits)
   const int32_t n32 = (int32_t)n;
   const int32_t m_lo = (int32_t)floor(R.lo);
   const int32_t m_hi = min(n32 - 1, (int32_t)floor(R.hi));
@@ -1383,13 +1385,10 @@ __global__ __launch_bounds__(kT) void k_scan_emit_b(const T* __restrict__ w, int
     __syncthreads();
   }
   auto cum = [&](double rv) -> uint32_t {
-    const double mf = floor(rv);
-    const int32_t m = (int32_t)mf;
-    if (m >= n32) return (uint32_t)n32;
-    const double t = SYSTEMATIC ? t_sys
-                     : table    ? 1.0 - u_offset(L.u[m - m_lo])
-                                : 1.0 - u_offset(stratum_word(key, filter, offset, m));
-    return (uint32_t)m + ((rv - mf) >= t ? 1u : 0u);
+    if (SYSTEMATIC) return cum_at(rv, t_sys);
+    const int32_t m = (int32_t)rv;
+    return cum_at(rv, 1.0 - u_offset(table ? L.u[m >= n32 ? 0 : m - m_lo]
+                                           : stratum_word(key, filter, offset, m)));
   };
   uint32_t O[kPer];
   const uint32_t Oprev = cum(R.prev);
@@ -1605,11 +1604,7 @@ __global__ __launch_bounds__(kT) void k_scan_emit_mb(const T* __restrict__ w, in
       const double p_base = L.top[e], p_top = L.top[e + 1];
       double pv[kPer];
 #pragma unroll
-      for (int v = 0; v < kPer; ++v) {
-        const uint64_t Lv = before + p[v];
-        const double t = __fma_rn(u64_to_f64(Lv), ce, p_base);
-        pv[v] = (Lv == total || t > p_top) ? p_top : t;
-      }
+      for (int v = 0; v < kPer; ++v) pv[v] = affine_r(before + p[v], total, ce, p_base, p_top);
       double2* P2 = reinterpret_cast<double2*>(L.P) + tid * (kPer / 2);
       P2[0] = make_double2(pv[0], pv[1]);
       P2[1] = make_double2(pv[2], pv[3]);
@@ -1790,10 +1785,8 @@ __global__ __launch_bounds__(OneWg<NB>::kThreads,
   const double t_sys =
       SYSTEMATIC ? 1.0 - u_offset(draw_uniform(key, 0, DOM_STRATA, 0, filter, offset).x) : 0.0;
   auto cum = [&](double rv) -> int32_t {
-    const double mf = floor(rv);
-    const int32_t m = (int32_t)mf;
-    const double t = SYSTEMATIC ? t_sys : 1.0 - u_offset(u[m >= n32 ? 0 : m]);
-    return m >= n32 ? n32 : m + ((rv - mf) >= t ? 1 : 0);
+    const int32_t m = (int32_t)rv;
+    return (int32_t)cum_at(rv, SYSTEMATIC ? t_sys : 1.0 - u_offset(u[m >= n32 ? 0 : m]));
   };
 #pragma unroll
   for (int r = 0; r < G::kR; ++r) {
@@ -1808,10 +1801,7 @@ __global__ __launch_bounds__(OneWg<NB>::kThreads,
       o += k < (part & 3) ? sk : 0ull;
       total += sk;
     }
-    auto r_of = [&](uint64_t L) -> double {
-      const double rv = __fma_rn(u64_to_f64(L), c, lo);
-      return (L == total || rv > hi) ? hi : rv;
-    };
+    auto r_of = [&](uint64_t L) -> double { return affine_r(L, total, c, lo, hi); };
     int32_t p = cum(o ? r_of(o) : lo);
     const int32_t i = r * 4 * G::kThreads + 4 * tid;
 #pragma unroll
@@ -1821,7 +1811,8 @@ __global__ __launch_bounds__(OneWg<NB>::kThreads,
         o += quantize_nb(x[r][v], scale[r]);
       }
       const int32_t O = cum(r_of(kAgain ? o : o + q[kAgain ? 0 : r][v]));
-      if (O > p && i + v < n32) {
+      // (past the end O stays at the block's upper end: no marker)
+      if (O > p) {
         M[p] = i + v;
         if (PERM) claimed |= 1u << (4 * r + v);
       }
