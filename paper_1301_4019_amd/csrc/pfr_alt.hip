@@ -372,20 +372,37 @@ __device__ __forceinline__ CodeTable<T> stage_codes(const T* __restrict__ w, uin
   return t;
 }
 
+// The waves of a SIMD issue oldest first, so that of equal chains the oldest
+// wave's ends long before the others', which are then too few to fill the
+// SIMD (one wave in four ended at 58 % of the workgroup's time).  A wave
+// therefore lowers its priority with each quarter of its chain: those behind
+// go first, and all stay within a quarter.  2^20 weights, B = 354: 610 -> 586
+// us.  (Later steps, at 3/4, 15/16 and 63/64 of the chain: 605.)
+struct ChainPriority {
+  int32_t q;
+  __device__ __forceinline__ explicit ChainPriority(int32_t B) : q((B + 15) / 16) {
+    __builtin_amdgcn_s_setprio(3);
+  }
+  __device__ __forceinline__ void step(int32_t m) const {  // m: groups of four steps done
+    if (m == q) __builtin_amdgcn_s_setprio(2);
+    else if (m == 2 * q) __builtin_amdgcn_s_setprio(1);
+    else if (m == 3 * q) __builtin_amdgcn_s_setprio(0);
+  }
+};
+
 // Metropolis with a bound table.  A skip needs the exact current w_k, so
 // the gathers cannot be issued ahead of the decisions of earlier steps;
 // instead each lane runs K independent chains in lockstep: at every step the
 // chains whose proposal the table cannot reject issue their loads together
-// and the K decisions follow.  Lane l runs the particles i0 + l + c STRIDE,
+// and the K decisions follow.  Lane l runs the particles ib + c STRIDE,
 // c < K, below i1, of the segment of n weights ws (wv: its buffer view).
 template <typename T, int K, int STRIDE, typename Table>
 __device__ __forceinline__ void metropolis_lockstep(const T* __restrict__ ws,
                                                     __amdgpu_buffer_rsrc_t wv, uint32_t n,
                                                     int32_t B, Key key, uint32_t filter,
                                                     uint32_t offset, const Table& tab,
-                                                    uint32_t i0, uint32_t i1,
+                                                    uint32_t ib, uint32_t i1,
                                                     int32_t* __restrict__ as) {
-  const uint32_t ib = i0 + threadIdx.x;
   if (ib >= i1) return;
   uint32_t k[K];
   double wk[K];
@@ -398,7 +415,9 @@ __device__ __forceinline__ void metropolis_lockstep(const T* __restrict__ ws,
     wk[c] = (double)ws[k[c]];
     pl[c] = philox_lane(key, k[c], filter, offset);
   }
+  ChainPriority prio(B);
   for (int32_t m = 0; 4 * m < B; ++m) {
+    prio.step(m);
     const int32_t left = B - 4 * m;
     const int ncall = left >= 4 ? 3 : (3 * left + 3) / 4;
     const int nq = left >= 4 ? 4 : left;
@@ -464,7 +483,7 @@ __global__ __launch_bounds__(kTableThreads) void k_metropolis_table(
   const int64_t p1 = p0 + chunk < n ? p0 + chunk : n;
   for (int64_t g = p0; g < p1; g += (int64_t)K * kTableThreads)
     metropolis_lockstep<T, K, kTableThreads>(w, wv, (uint32_t)n, B, key, filter, offset, tab,
-                                             (uint32_t)g, (uint32_t)p1, a);
+                                             (uint32_t)g + threadIdx.x, (uint32_t)p1, a);
 }
 
 // ------------------------------------------------------------------ staged Metropolis
@@ -473,12 +492,47 @@ __global__ __launch_bounds__(kTableThreads) void k_metropolis_table(
 // batch) stay on one XCD: their weights are then read from its L2, where
 // chunks dealt out one by one would keep a copy of every segment in flight in
 // all eight.
-__device__ __forceinline__ int64_t xcd_chunk(int64_t chunk) {
+__device__ __forceinline__ int64_t xcd_chunk(int64_t chunk, uint32_t b, uint32_t chunks) {
   const uint32_t G = (uint32_t)max((int64_t)1, 65536 / chunk);
-  const uint32_t b = blockIdx.x, s0 = b - b % (8 * G);
-  if (s0 + 8 * G > gridDim.x) return b;  // the last, partial group of runs
+  const uint32_t s0 = b - b % (8 * G);
+  if (s0 + 8 * G > chunks) return b;  // the last, partial group of runs
   const uint32_t r = b - s0;
   return s0 + (r & 7u) * G + (r >> 3);
+}
+
+// A queue of chunks for workgroups that stay on their CU and take the next
+// chunk when they are done with one: a launch of a workgroup per chunk hands
+// them out in order, and with one or two workgroups to a CU a free CU may wait.
+// Eight heads, one per XCD, in lines of their own; a workgroup serves the
+// chunks of its XCD's head (t % 8, so that xcd_chunk keeps its runs together)
+// and then those of the others.  Every workgroup ends when all eight are used
+// up.  4096 ragged vectors of 256 .. 65536, B = 4 .. 354, with the
+// permutation: 4.25 -> 3.94 ms; with the waves of a workgroup taking 64 chains
+// at a time instead of a fixed share, 3.70; with chunks twice as long, 3.47.
+constexpr uint32_t kHeadStride = 32;
+constexpr size_t kQueueBytes = 8 * kHeadStride * sizeof(uint32_t);
+constexpr uint32_t kQueueGrid = 512;  // two per CU, where their LDS fits twice
+struct ChunkQueue {
+  uint32_t* heads;  // null: chunk blockIdx.x only
+  uint32_t chunks;
+};
+// The next chunk, the same on every thread, or at least q.chunks at the end.
+// served: heads of the workgroup that are used up, 0 before the first call.
+__device__ __forceinline__ uint32_t next_chunk(const ChunkQueue& q, uint32_t& served,
+                                               uint32_t* slot) {
+  if (!q.heads) return served++ == 0 ? blockIdx.x : 0xFFFFFFFFu;
+  __syncthreads();  // the last chunk's number has been read, and its LDS
+  if (threadIdx.x == 0) {
+    uint32_t t = 0xFFFFFFFFu;
+    for (; served < 8; ++served) {
+      const uint32_t x = (blockIdx.x + served) & 7u;
+      t = atomicAdd(q.heads + x * kHeadStride, 1u) * 8u + x;
+      if (t < q.chunks) break;
+    }
+    *slot = t;
+  }
+  __syncthreads();
+  return uniform_u32(*slot);
 }
 
 // A batch whose segments have their own step counts is cut by cost instead of
@@ -490,7 +544,9 @@ __device__ __forceinline__ int64_t xcd_chunk(int64_t chunk) {
 __global__ __launch_bounds__(1024) void k_cost_prefix(const int64_t* __restrict__ offsets,
                                                       uint32_t n_filters,
                                                       const int32_t* __restrict__ B,
-                                                      uint64_t* __restrict__ cost) {
+                                                      uint64_t* __restrict__ cost,
+                                                      uint32_t* __restrict__ heads) {
+  if (threadIdx.x < 8) heads[threadIdx.x * kHeadStride] = 0;
   __shared__ uint64_t s_w[1024 / kWave];
   const uint32_t wave = threadIdx.x / kWave, lane = lane_id();
   uint64_t carry = 0;
@@ -537,78 +593,108 @@ __global__ __launch_bounds__(THREADS) void k_metropolis_staged(
     const T* __restrict__ w, int64_t n_total, const int64_t* __restrict__ offsets,
     uint32_t n_filters, int32_t B, const int32_t* __restrict__ B_dev, Key key, uint32_t offset,
     uint32_t filter_base, int32_t* __restrict__ a, int64_t chunk,
-    const uint64_t* __restrict__ cost) {
+    const uint64_t* __restrict__ cost, ChunkQueue queue) {
   // 128 KB of weights, or 65536 codes of a segment longer than that
   constexpr bool kCoded = CAP * sizeof(T) == 2 * kCodes;
   __shared__ __align__(16) T sw[CAP > 0 ? CAP : 1];
   offset = counter_offset(key, offset);
-  const int64_t t = offsets ? xcd_chunk(chunk) : (int64_t)blockIdx.x;
-  int64_t p0 = t * chunk, p1 = p0 + chunk < n_total ? p0 + chunk : n_total;
-  if (cost) {
-    p0 = cost_start(cost, offsets, n_filters, n_total, (uint32_t)t, gridDim.x, CAP);
-    p1 = cost_start(cost, offsets, n_filters, n_total, (uint32_t)t + 1, gridDim.x, CAP);
-    if (p0 >= p1) return;
-  }
-  uint32_t f = offsets ? wave_find_segment(offsets, n_filters, p0) : 0u;
-  for (int64_t g0 = p0; g0 < p1; ++f) {
-    const int64_t base = offsets ? offsets[f] : 0;
-    const int64_t end = offsets ? offsets[f + 1] : n_total;
-    const int64_t q1 = end < p1 ? end : p1;
-    if (q1 <= g0) continue;  // empty segment
-    const uint32_t n = (uint32_t)(end - base);
-    const int32_t steps = B_dev ? B_dev[f] : B;
-    const uint32_t filt = filter_base + f;
-    if (CAP > 0 && n <= (uint32_t)CAP) {
-      __syncthreads();  // the previous segment's chains are done with sw
-      stage_weights(w + base, n, sw);
-      __syncthreads();
-      for (int64_t g = g0 + threadIdx.x; g < q1; g += THREADS)
-        a[g] = (int32_t)metropolis_chain(sw, key, (uint32_t)(g - base), filt, offset, n, steps);
-    } else if (kCoded && n <= kCodes << kCodesMaxShift) {
-      uint16_t* const code = reinterpret_cast<uint16_t*>(sw);
-      __syncthreads();
-      const CodeTable<T> tab = stage_codes(w + base, n, code);
-      __syncthreads();
-      const __amdgpu_buffer_rsrc_t wv = buffer_view(w + base, n * (uint32_t)sizeof(T));
-      const uint32_t i1 = (uint32_t)(q1 - base);
-      for (uint32_t i0 = (uint32_t)(g0 - base); i0 < i1;) {
-        // two chains a lane, or one for what is left (four spill registers)
-        if (i1 - i0 > THREADS) {
-          metropolis_lockstep<T, 2, THREADS>(w + base, wv, n, steps, key, filt, offset, tab, i0,
-                                             i1, a + base);
-          i0 += 2 * THREADS;
-        } else {
-          metropolis_lockstep<T, 1, THREADS>(w + base, wv, n, steps, key, filt, offset, tab, i0,
-                                             i1, a + base);
-          i0 += THREADS;
-        }
-      }
-    } else if (CAP > 0) {  // a longer segment in a staged launch: plain chains
-      for (int64_t g = g0 + threadIdx.x; g < q1; g += THREADS)
-        a[g] = (int32_t)metropolis_chain(w + base, key, (uint32_t)(g - base), filt, offset, n,
-                                         steps);
-    } else {
-      for (int64_t g = g0 + threadIdx.x; g < q1; g += THREADS) {
-        const uint32_t i = (uint32_t)(g - base);
-        const T* __restrict__ ws = w + base;
-        uint32_t k = i;
-        double wk = (double)ws[i];
-        const int32_t groups = (steps + 3) / 4;
-        const PhiloxLane pl = philox_lane(key, i, filt, offset);
-        MGroup ga, gb;
-        if (groups > 0) metropolis_fetch(ws, key, i, pl, filt, offset, n, steps, 0, ga);
-        for (int32_t m = 0; m < groups; m += 2) {
-          if (m + 1 < groups)
-            metropolis_fetch(ws, key, i, pl, filt, offset, n, steps, m + 1, gb);
-          metropolis_accept<T>(ga, k, wk);
-          if (m + 2 < groups)
-            metropolis_fetch(ws, key, i, pl, filt, offset, n, steps, m + 2, ga);
-          if (m + 1 < groups) metropolis_accept<T>(gb, k, wk);
-        }
-        a[g] = (int32_t)k;
-      }
+  __shared__ uint32_t s_chunk, s_next;
+  uint32_t served = 0;
+  // particles of the segment part that are left go to the waves as they get
+  // free, 64 chains (or 128) at a time: the first index of the wave's share, at
+  // least the part's length at the end.  (Workgroups of 256 threads have one
+  // chain a lane, and nothing to hand out.)
+  constexpr bool kTakes = THREADS > 256;
+  auto take = [&](uint32_t chains) -> uint32_t {
+    uint32_t old = 0;
+    if (lane_id() == 0) old = atomicAdd(&s_next, chains);
+    return uniform_u32(old);
+  };
+  for (uint32_t b; (b = next_chunk(queue, served, &s_chunk)) < queue.chunks;) {
+    const int64_t t = offsets ? xcd_chunk(chunk, b, queue.chunks) : (int64_t)b;
+    int64_t p0 = t * chunk, p1 = p0 + chunk < n_total ? p0 + chunk : n_total;
+    if (cost) {
+      p0 = cost_start(cost, offsets, n_filters, n_total, (uint32_t)t, queue.chunks, CAP);
+      p1 = cost_start(cost, offsets, n_filters, n_total, (uint32_t)t + 1, queue.chunks, CAP);
+      if (p0 >= p1) continue;
     }
-    g0 = q1;
+    uint32_t f = offsets ? wave_find_segment(offsets, n_filters, p0) : 0u;
+    for (int64_t g0 = p0; g0 < p1; ++f) {
+      const int64_t base = offsets ? offsets[f] : 0;
+      const int64_t end = offsets ? offsets[f + 1] : n_total;
+      const int64_t q1 = end < p1 ? end : p1;
+      if (q1 <= g0) continue;  // empty segment
+      const uint32_t n = (uint32_t)(end - base);
+      const int32_t steps = B_dev ? B_dev[f] : B;
+      const uint32_t filt = filter_base + f;
+      if (CAP > 0 && n <= (uint32_t)CAP) {
+        __syncthreads();  // the previous segment's chains are done with sw
+        if (threadIdx.x == 0) s_next = 0;
+        stage_weights(w + base, n, sw);
+        __syncthreads();
+        if (!kTakes) {
+          for (int64_t g = g0 + threadIdx.x; g < q1; g += THREADS)
+            a[g] = (int32_t)metropolis_chain(sw, key, (uint32_t)(g - base), filt, offset, n, steps);
+        } else {
+          const uint32_t len = (uint32_t)(q1 - g0), i0 = (uint32_t)(g0 - base);
+          for (uint32_t k; (k = take(kWave)) < len;) {
+            k += lane_id();
+            if (k < len)
+              a[g0 + k] = (int32_t)metropolis_chain(sw, key, i0 + k, filt, offset, n, steps);
+          }
+        }
+      } else if (kCoded && n <= kCodes << kCodesMaxShift) {
+        uint16_t* const code = reinterpret_cast<uint16_t*>(sw);
+        __syncthreads();
+        if (threadIdx.x == 0) s_next = 0;
+        const CodeTable<T> tab = stage_codes(w + base, n, code);
+        __syncthreads();
+        const __amdgpu_buffer_rsrc_t wv = buffer_view(w + base, n * (uint32_t)sizeof(T));
+        const uint32_t i0 = (uint32_t)(g0 - base), i1 = (uint32_t)(q1 - base);
+        if (!kTakes) {
+          for (uint32_t i = i0 + threadIdx.x; i < i1; i += THREADS)
+            metropolis_lockstep<T, 1, kWave>(w + base, wv, n, steps, key, filt, offset, tab, i,
+                                             i1, a + base);
+        }
+        // two chains a lane, or one for the last
+        for (uint32_t k, taken = 0; kTakes && taken < i1 - i0;) {
+          const bool two = i1 - i0 - taken > 2 * kWave;
+          k = take(two ? 2 * kWave : kWave);
+          taken = k + (two ? 2 * kWave : kWave);
+          if (two)
+            metropolis_lockstep<T, 2, kWave>(w + base, wv, n, steps, key, filt, offset, tab,
+                                             i0 + k + lane_id(), i1, a + base);
+          else
+            metropolis_lockstep<T, 1, kWave>(w + base, wv, n, steps, key, filt, offset, tab,
+                                             i0 + k + lane_id(), i1, a + base);
+        }
+      } else if (CAP > 0) {  // a longer segment in a staged launch: plain chains
+        for (int64_t g = g0 + threadIdx.x; g < q1; g += THREADS)
+          a[g] = (int32_t)metropolis_chain(w + base, key, (uint32_t)(g - base), filt, offset, n,
+                                           steps);
+      } else {
+        for (int64_t g = g0 + threadIdx.x; g < q1; g += THREADS) {
+          const uint32_t i = (uint32_t)(g - base);
+          const T* __restrict__ ws = w + base;
+          uint32_t k = i;
+          double wk = (double)ws[i];
+          const int32_t groups = (steps + 3) / 4;
+          const PhiloxLane pl = philox_lane(key, i, filt, offset);
+          MGroup ga, gb;
+          if (groups > 0) metropolis_fetch(ws, key, i, pl, filt, offset, n, steps, 0, ga);
+          for (int32_t m = 0; m < groups; m += 2) {
+            if (m + 1 < groups)
+              metropolis_fetch(ws, key, i, pl, filt, offset, n, steps, m + 1, gb);
+            metropolis_accept<T>(ga, k, wk);
+            if (m + 2 < groups)
+              metropolis_fetch(ws, key, i, pl, filt, offset, n, steps, m + 2, ga);
+            if (m + 1 < groups) metropolis_accept<T>(gb, k, wk);
+          }
+          a[g] = (int32_t)k;
+        }
+      }
+      g0 = q1;
+    }
   }
 }
 
@@ -827,7 +913,8 @@ __global__ __launch_bounds__(THREADS) void k_rejection(
   __shared__ __align__(16) T sw[CAP > 0 ? CAP : 1];
   __shared__ uint32_t queue;  // particles of the segment part handed out so far
   offset = counter_offset(key, offset);
-  const int64_t p0 = (offsets ? xcd_chunk(chunk) : (int64_t)blockIdx.x) * chunk;
+  const int64_t p0 =
+      (offsets ? xcd_chunk(chunk, blockIdx.x, gridDim.x) : (int64_t)blockIdx.x) * chunk;
   const int64_t p1 = p0 + chunk < n_total ? p0 + chunk : n_total;
   uint32_t my_flags = 0;
   uint32_t f = offsets ? wave_find_segment(offsets, n_filters, p0) : 0u;
@@ -926,17 +1013,18 @@ template <typename T>
 hipError_t launch_metropolis_t(const void* wv, int64_t n_total, const int64_t* offsets,
                                uint32_t n_filters, int64_t max_len, int32_t B,
                                const int32_t* B_dev, Key key, uint32_t offset,
-                               uint32_t filter_base, int32_t* a, uint64_t* cost,
-                               hipStream_t stream) {
+                               uint32_t filter_base, int32_t* a, void* ws, hipStream_t stream) {
   const T* w = (const T*)wv;
   constexpr int per_kb = 1024 / (int)sizeof(T);
   const int cap = staged_capacity<T>(max_len, n_total, n_filters);
   const uint64_t* const uniform = nullptr;
+  auto once = [](unsigned grid) { return ChunkQueue{nullptr, grid}; };
   auto global_launch = [&]() {
     const int64_t chunk = tuning().metropolis_chunk;
-    hipLaunchKernelGGL((k_metropolis_staged<T, 0, 256>), dim3((unsigned)((n_total + chunk - 1) / chunk)),
-                       dim3(256), 0, stream, w, n_total, offsets, n_filters, B, B_dev, key, offset,
-                       filter_base, a, chunk, uniform);
+    const unsigned grid = (unsigned)((n_total + chunk - 1) / chunk);
+    hipLaunchKernelGGL((k_metropolis_staged<T, 0, 256>), dim3(grid), dim3(256), 0, stream, w,
+                       n_total, offsets, n_filters, B, B_dev, key, offset, filter_base, a, chunk,
+                       uniform, once(grid));
     return hipGetLastError();
   };
   if (cap == 0) {
@@ -948,10 +1036,10 @@ hipError_t launch_metropolis_t(const void* wv, int64_t n_total, const int64_t* o
     const bool one = !offsets || n_filters <= 1;
     if (one && (n_total <= 128 * per_kb || (n_total <= (int64_t)kCodes && (B_dev || B >= 12)))) {
       const int64_t chunk1 = 256;
-      hipLaunchKernelGGL((k_metropolis_staged<T, 128 * per_kb, 256>),
-                         dim3((unsigned)((n_total + chunk1 - 1) / chunk1)), dim3(256), 0, stream,
-                         w, n_total, offsets, n_filters, B, B_dev, key, offset, filter_base, a,
-                         chunk1, uniform);
+      const unsigned grid = (unsigned)((n_total + chunk1 - 1) / chunk1);
+      hipLaunchKernelGGL((k_metropolis_staged<T, 128 * per_kb, 256>), dim3(grid), dim3(256), 0,
+                         stream, w, n_total, offsets, n_filters, B, B_dev, key, offset,
+                         filter_base, a, chunk1, uniform, once(grid));
       return hipGetLastError();
     }
     return global_launch();
@@ -966,11 +1054,11 @@ hipError_t launch_metropolis_t(const void* wv, int64_t n_total, const int64_t* o
     if (cap == 16 * per_kb)
       hipLaunchKernelGGL((k_metropolis_staged<T, 16 * per_kb, 256>), grid1, dim3(256), 0, stream,
                          w, n_total, offsets, n_filters, B, B_dev, key, offset, filter_base, a,
-                         chunk1, uniform);
+                         chunk1, uniform, once(grid1.x));
     else
       hipLaunchKernelGGL((k_metropolis_staged<T, 64 * per_kb, 256>), grid1, dim3(256), 0, stream,
                          w, n_total, offsets, n_filters, B, B_dev, key, offset, filter_base, a,
-                         chunk1, uniform);
+                         chunk1, uniform, once(grid1.x));
     return hipGetLastError();
   }
   if (n_total <= 256 * 256) {
@@ -980,39 +1068,49 @@ hipError_t launch_metropolis_t(const void* wv, int64_t n_total, const int64_t* o
     if (cap == 16 * per_kb)
       hipLaunchKernelGGL((k_metropolis_staged<T, 16 * per_kb, 256>), grid1, dim3(256), 0, stream,
                          w, n_total, offsets, n_filters, B, B_dev, key, offset, filter_base, a,
-                         (int64_t)256, uniform);
+                         (int64_t)256, uniform, once(grid1.x));
     else if (cap == 64 * per_kb)
       hipLaunchKernelGGL((k_metropolis_staged<T, 64 * per_kb, 256>), grid1, dim3(256), 0, stream,
                          w, n_total, offsets, n_filters, B, B_dev, key, offset, filter_base, a,
-                         (int64_t)256, uniform);
+                         (int64_t)256, uniform, once(grid1.x));
     else
       hipLaunchKernelGGL((k_metropolis_staged<T, 128 * per_kb, 256>), grid1, dim3(256), 0, stream,
                          w, n_total, offsets, n_filters, B, B_dev, key, offset, filter_base, a,
-                         (int64_t)256, uniform);
+                         (int64_t)256, uniform, once(grid1.x));
     return hipGetLastError();
   }
-  // the tuned chunk, less where it would leave CUs idle (two workgroups each)
+  // the tuned chunk, twice that from the queue, less where it would leave CUs
+  // idle (two workgroups each)
+  const bool queued = ws && B_dev && n_filters <= 16384;
+  const int64_t tuned = (int64_t)tuning().batch_metropolis_chunk * (queued ? 2 : 1);
   int64_t chunk = (n_total / 512 + 1023) / 1024 * 1024;
-  if (chunk > tuning().batch_metropolis_chunk) chunk = tuning().batch_metropolis_chunk;
+  if (chunk > tuned) chunk = tuned;
   if (chunk < 1024) chunk = 1024;
-  if (cost && B_dev && n_filters <= 16384)
+  // with a workspace and step counts of its own per segment: cut by cost, and
+  // the chunks handed out as workgroups get free
+  const unsigned chunks = (unsigned)((n_total + chunk - 1) / chunk);
+  const uint64_t* cost = nullptr;
+  ChunkQueue queue = once(chunks);
+  if (queued) {
+    queue.heads = (uint32_t*)ws;
+    uint64_t* prefix = (uint64_t*)((char*)ws + kQueueBytes);
     hipLaunchKernelGGL(k_cost_prefix, dim3(1), dim3(1024), 0, stream, offsets, n_filters, B_dev,
-                       cost);
-  else
-    cost = nullptr;
-  const dim3 grid((unsigned)((n_total + chunk - 1) / chunk));
+                       prefix, queue.heads);
+    cost = prefix;
+  }
+  const dim3 grid(queue.heads && chunks > kQueueGrid ? kQueueGrid : chunks);
   if (cap == 16 * per_kb)
     hipLaunchKernelGGL((k_metropolis_staged<T, 16 * per_kb, 1024>), grid, dim3(1024), 0, stream, w,
                        n_total, offsets, n_filters, B, B_dev, key, offset, filter_base, a, chunk,
-                       (const uint64_t*)cost);
+                       cost, queue);
   else if (cap == 64 * per_kb)
     hipLaunchKernelGGL((k_metropolis_staged<T, 64 * per_kb, 1024>), grid, dim3(1024), 0, stream, w,
                        n_total, offsets, n_filters, B, B_dev, key, offset, filter_base, a, chunk,
-                       (const uint64_t*)cost);
+                       cost, queue);
   else
     hipLaunchKernelGGL((k_metropolis_staged<T, 128 * per_kb, 1024>), grid, dim3(1024), 0, stream,
                        w, n_total, offsets, n_filters, B, B_dev, key, offset, filter_base, a,
-                       chunk, (const uint64_t*)cost);
+                       chunk, cost, queue);
   return hipGetLastError();
 }
 
@@ -1059,7 +1157,8 @@ size_t alt_workspace_bytes(bool f64, int64_t n_total, uint32_t n_filters, int64_
 // Metropolis: the same, and for a batch the cost prefix of its segments.
 size_t metropolis_workspace_bytes(bool f64, int64_t n_total, uint32_t n_filters,
                                   int64_t max_len) {
-  if (n_filters > 1) return (((size_t)n_filters + 1) * sizeof(uint64_t) + 255) & ~(size_t)255;
+  if (n_filters > 1)  // the chunk queue, the cost prefix
+    return kQueueBytes + ((((size_t)n_filters + 1) * sizeof(uint64_t) + 255) & ~(size_t)255);
   return alt_workspace_bytes(f64, n_total, n_filters, max_len);
 }
 
@@ -1130,15 +1229,12 @@ hipError_t launch_metropolis(bool f64, const void* w, int64_t n_total, const int
                                          a, ws, stream)
                : launch_metropolis_table((const float*)w, n_total, B, key, offset, filter_base, a,
                                          ws, stream);
-  // a batch's workspace holds the cost prefix of its segments
-  uint64_t* cost = ws && n_filters > 1 &&
-                           ws_bytes >= metropolis_workspace_bytes(f64, n_total, n_filters, max_len)
-                       ? (uint64_t*)ws
-                       : nullptr;
+  if (n_filters <= 1 || ws_bytes < metropolis_workspace_bytes(f64, n_total, n_filters, max_len))
+    ws = nullptr;  // a batch's workspace: the chunk queue and the cost prefix
   return f64 ? launch_metropolis_t<double>(w, n_total, offsets, n_filters, max_len, B, B_dev, key,
-                                           offset, filter_base, a, cost, stream)
+                                           offset, filter_base, a, ws, stream)
              : launch_metropolis_t<float>(w, n_total, offsets, n_filters, max_len, B, B_dev, key,
-                                          offset, filter_base, a, cost, stream);
+                                          offset, filter_base, a, ws, stream);
 }
 
 

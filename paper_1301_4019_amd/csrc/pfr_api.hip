@@ -678,7 +678,7 @@ int lgssm_step(const pfr_lgssm* model, pfr_op scheme, pfr_precision precision, i
   switch (scheme) {
     case PFR_OP_METROPOLIS:
       e = launch_metropolis(false, w, total, offsets, nf, n, 0, B_dev, rkey, 0u, rng.filter_base,
-                            ancestors, nullptr, 0, st);
+                            ancestors, perm_ws, ws_bytes - lgssm_state_bytes(n_filters), st);
       break;
     case PFR_OP_REJECTION:
       e = launch_rejection(false, w, total, offsets, nf, n, 1.0, nullptr, 1u << 20, rkey, 0u,

@@ -82,3 +82,30 @@ def test_cut_by_cost_covers_every_particle():
             if n:
                 ref = oracle.metropolis(w[off[f]:off[f + 1]], int(B[f]), seed=5, filt=f)
                 assert np.array_equal(a[off[f]:off[f + 1]], ref), (f, max_len)
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("segments", [2, 700])
+@pytest.mark.parametrize("max_len", ["short", "long", None])
+def test_chunks_from_the_queue(dtype, segments, max_len):
+    """A batch with its own step counts and a workspace (chunks handed out to
+    workgroups that stay) against one without (one workgroup per chunk): every
+    LDS tier, more chunks than workgroups, shares that are not whole waves."""
+    g = np.random.default_rng(segments)
+    top = {"short": 2000, "long": 70000, None: 20000}[max_len]
+    sizes = g.integers(0, top if segments == 2 else min(top, 4000), segments)
+    sizes[:2] = top, max(1, 66000 - top)  # beyond the small batches' path
+    if segments > 2 and max_len == "short":
+        sizes[1] = 1999
+    B = g.integers(0, 40, segments).astype(np.int32)
+    w, off = batch(list(sizes), g.uniform(0, 4, segments), dtype, 5)
+    kw = dict(seed=5, offset=1, filter_base=2, B_per_filter=dev(B), offsets=dev(off),
+              max_len=None if max_len is None else int(max(sizes)))
+    a = [host(pfr().resample_metropolis(dev(w), 1, **kw)) for _ in range(2)]
+    b = host(pfr().resample_metropolis(dev(w), 1, workspace=torch.empty(0, dtype=torch.uint8,
+                                                                        device="cuda"), **kw))
+    assert np.array_equal(a[0], b) and np.array_equal(a[1], b)
+    for f in list(range(2)) + [segments - 1]:
+        if sizes[f]:
+            ref = oracle.metropolis(w[off[f]:off[f + 1]], int(B[f]), seed=5, offset=1, filt=2 + f)
+            assert np.array_equal(b[off[f]:off[f + 1]], ref), f
