@@ -100,6 +100,9 @@ hipError_t launch_scan_batched(int scheme, bool f64, const void* w, int64_t n_to
                                uint32_t* flags, hipStream_t stream, int32_t* c = nullptr);
 // Longest segment that the strata schemes resample in one workgroup and launch.
 constexpr int64_t kOneWgMax = 16384;
+// Longest vector, of those that need no workspace, that the multinomial scheme
+// resamples block-parallel when it gets one.
+constexpr int64_t kSmallMultinomial = 1 << 18;
 
 // Code 5 with independent uniforms (single vectors, exact prefix).
 size_t multinomial_iid_workspace_bytes(int64_t n);

@@ -1492,7 +1492,7 @@ __global__ __launch_bounds__(kT) void k_scan_emit_mb(const T* __restrict__ w, in
                                                      const BlockRec* __restrict__ recs,
                                                      const uint64_t* __restrict__ esums,
                                                      const uint64_t* __restrict__ evals,
-                                                     int32_t* __restrict__ a,
+                                                     uint32_t straight, int32_t* __restrict__ a,
                                                      uint32_t* __restrict__ flags,
                                                      uint32_t* __restrict__ claim) {
   constexpr int kE = (int)(kDirectMulti / kT);  // exponential blocks per thread
@@ -1519,7 +1519,7 @@ __global__ __launch_bounds__(kT) void k_scan_emit_mb(const T* __restrict__ w, in
   }
   wg_markers_clear(&L.ex);
   if (tid < (int)(kDirectMulti / 32)) L.used[tid] = 0;
-  const WgCarry c = direct_carries(nb, b, recs, rec, &L.cs, 0u);
+  const WgCarry c = direct_carries(nb, b, recs, rec, &L.cs, straight);
   if (flags && b == 0 && tid == 0 && c.status) atomicOr(flags, c.status);
   if (c.status & (FLAG_BAD_WEIGHTS | FLAG_ZERO_TOTAL)) {
     block_identity(P0, n, tid, kT, a, claim);
@@ -2340,9 +2340,14 @@ hipError_t launch_scan_t(const void* wv, int64_t n, Key key, uint32_t offset, ui
     }
   }
   if constexpr (multi) {
-    if (nb <= (uint32_t)tuning().direct_max_blocks && nb <= kGrp && nbe <= kDirectMulti) {
+    // a vector that k_scan_batched resamples without a workspace: its carries,
+    // which it forms straight at the global scale
+    const bool one_wg = n <= (int64_t)tuning().single_wg_max;
+    if ((nb <= (uint32_t)tuning().direct_max_blocks || one_wg) && nb <= kGrp &&
+        nbe <= kDirectMulti) {
       hipLaunchKernelGGL((k_scan_emit_mb<T>), dim3(nb), dim3(kT), 0, stream, w, n, nb, nbe, key,
-                         offset, filter, recs, esums, (const uint64_t*)evals, a, flags, claim);
+                         offset, filter, recs, esums, (const uint64_t*)evals,
+                         one_wg ? kStraight : 0u, a, flags, claim);
       return hipGetLastError();
     }
   }

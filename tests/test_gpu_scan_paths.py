@@ -198,3 +198,23 @@ def test_permutation_in_one_workgroup(scheme, dtype, max_len):
                 assert np.array_equal(host(a1), a[s]) and np.array_equal(host(c1), c[s]), (f, n)
     m = pfr()
     assert int(host(fl)[0]) == m.FLAG_BAD_WEIGHTS | m.FLAG_ZERO_TOTAL
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("n", [1, 2, 10, 1022, 1023, 1024, 2049, 4095, 4096])
+def test_short_multinomial_with_and_without_workspace(dtype, n):
+    """Two launches with a workspace, one workgroup without; blocks so far
+    apart that the carries' truncation shows; and with the permutation."""
+    m = pfr()
+    none = torch.empty(0, dtype=torch.uint8, device="cuda")
+    apart = np.ldexp(1.0, -30 * (np.arange(n) // 1024)) * np.random.default_rng(n).random(n)
+    for w in ([weights(k, n, dtype) for k in (0.0, 4.0, "wide", "one")] +
+              [apart.astype(dtype), np.zeros(n, dtype)]):
+        w = dev(w)
+        fl, fl0 = new_flags(), new_flags()
+        a = host(m.resample_multinomial(w, seed=4, offset=1, filter_base=3, flags=fl))
+        b = host(m.resample_multinomial(w, seed=4, offset=1, filter_base=3, flags=fl0,
+                                        workspace=none))
+        assert np.array_equal(a, b) and int(host(fl)[0]) == int(host(fl0)[0])
+        a2, c = m.resample_permuted("multinomial", w, seed=4, offset=1, filter_base=3)
+        assert np.array_equal(host(a2), a) and np.array_equal(host(c), oracle.permute(a)[0])
