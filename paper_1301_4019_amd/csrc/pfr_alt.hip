@@ -10,29 +10,6 @@
 
 namespace pfr {
 
-// Per-particle context for ragged batches: where the particle's segment starts
-// and how long it is.  A single vector is one segment.
-struct SegCtx {
-  int64_t base;
-  uint32_t n;
-  uint32_t f;
-};
-
-__device__ __forceinline__ SegCtx seg_of(const int64_t* __restrict__ offsets, uint32_t n_filters,
-                                         int64_t n_total, int64_t g) {
-  SegCtx c;
-  if (!offsets) {
-    c.base = 0;
-    c.n = (uint32_t)n_total;
-    c.f = 0;
-  } else {
-    c.f = find_segment(offsets, n_filters, g);
-    c.base = offsets[c.f];
-    c.n = (uint32_t)(offsets[c.f + 1] - c.base);
-  }
-  return c;
-}
-
 // ------------------------------------------------------------------ Metropolis
 // Lane i runs B steps of an independent Metropolis chain started at k = i.
 // Step s takes (j, u) from words 3s, 3s+1, 3s+2 of the lane's Philox stream

@@ -425,22 +425,6 @@ __global__ __launch_bounds__(256) void k_claim_min(const int32_t* __restrict__ a
   }
 }
 
-// e[i] = a_i if position i won its claim (d[a_i] == i), else -1 - a_i.
-__global__ __launch_bounds__(256) void k_mark(const int32_t* __restrict__ a, int64_t n_total,
-                                              const int64_t* __restrict__ offsets,
-                                              uint32_t n_filters, int64_t min_len,
-                                              const int32_t* __restrict__ d,
-                                              int32_t* __restrict__ e) {
-  bool bad = false;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g < n_total; g += stride) {
-    const SegIdx s = seg_index(offsets, n_filters, n_total, g);
-    if (s.n < min_len) continue;
-    const int64_t ai = anc_at(a, s, s.i, bad);
-    e[g] = d[s.base + ai] == s.i ? (int32_t)ai : (int32_t)(-1 - ai);
-  }
-}
-
 // Backward walk on the ancestry itself (unsorted input, no marked ancestry):
 // from an unclaimed slot j, y = j; while position y won its claim
 // (d[a_y] == y) step to y = a_y; then c_j = a_y.  The same walk as k_resolve

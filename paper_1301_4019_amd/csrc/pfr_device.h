@@ -174,10 +174,6 @@ __device__ __forceinline__ uint32_t lane_id() {
   return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
 }
 __device__ __forceinline__ uint64_t ballot(bool p) { return __ballot(p); }
-__device__ __forceinline__ uint64_t lanemask_lt() {
-  const uint32_t l = lane_id();
-  return l == 0 ? 0ull : (~0ull >> (64 - l));
-}
 __device__ __forceinline__ uint32_t shfl_u32(uint32_t v, int src) {
   return (uint32_t)__builtin_amdgcn_ds_bpermute(src << 2, (int)v);
 }
