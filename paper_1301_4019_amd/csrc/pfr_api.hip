@@ -704,8 +704,10 @@ int lgssm_step(const pfr_lgssm* model, pfr_op scheme, pfr_precision precision, i
   bool permutes = false;  // the resampler permutes too
   switch (scheme) {
     case PFR_OP_METROPOLIS:
+      // equal chunks, not by cost: the filters have one length and nearly one
+      // step count (16 steps of 1024 filters of 16384 8.36 ms, by cost 8.72)
       e = launch_metropolis(false, w, total, offsets, nf, n, 0, B_dev, rkey, 0u, rng.filter_base,
-                            ancestors, perm_ws, ws_bytes - lgssm_state_bytes(n_filters), st);
+                            ancestors, nullptr, 0, st);
       break;
     case PFR_OP_REJECTION:
       e = launch_rejection(false, w, total, offsets, nf, n, 1.0, nullptr, 1u << 20, rkey, 0u,
