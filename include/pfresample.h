@@ -152,7 +152,8 @@ PFR_API int pfr_workspace_init(void* ws, size_t ws_bytes, void* stream);
  * needs one (PFR_EWORKSPACE without); a batch (n_filters > 1) runs
  * block-parallel with one and one workgroup per segment without one (a NULL
  * workspace), with identical results.  The floating-point precision modes
- * ignore a batch workspace.
+ * ignore a batch workspace.  A short multinomial vector needs none, but runs
+ * faster with the one that pfr_workspace_bytes reports (the same result).
  */
 
 /* The scaled prefix r_i = n W_i / W_n (binary64, r_{n-1} = n) that the
@@ -222,8 +223,8 @@ PFR_API int resample_systematic(const void* w, pfr_dtype dtype, const pfr_segmen
  * long vector of less than 2^31 bytes of weights, a table of power-of-two
  * weight bounds per bucket of particles that lets most rejected proposals
  * skip the load of w_j, and for a batch with B_dev the running cost of its
- * segments, by which the work is split; it changes the speed, never the
- * result. */
+ * segments, by which the work is split, and the queue it is handed out from;
+ * it changes the speed, never the result. */
 PFR_API int resample_metropolis(const void* w, pfr_dtype dtype, const pfr_segments* seg, int32_t B,
                         const int32_t* B_dev, pfr_rng rng, int32_t* ancestors, void* ws,
                         size_t ws_bytes, void* stream);
@@ -270,7 +271,9 @@ typedef struct {
 } pfr_scheme_params;
 
 /* Bytes of workspace for resample_permuted (256-byte aligned; zero it once
- * with pfr_workspace_init). */
+ * with pfr_workspace_init).  The resampler's part, at the end, may be left off
+ * for a Metropolis batch and for a multinomial vector of at most
+ * single_wg_max particles. */
 PFR_API size_t pfr_resample_permuted_workspace_bytes(pfr_op scheme, const pfr_segments* seg,
                                                      pfr_dtype dtype);
 

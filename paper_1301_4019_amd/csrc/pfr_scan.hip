@@ -28,9 +28,9 @@
 //           multinomial scheme (whose points are kept for the emission).
 //   carries turn the records into the global scale, the exact carries C_b and
 //           the total, and scan the exponential-block sums.  With at most
-//           direct_max_blocks blocks and no exponential blocks this step is
-//           folded into the emission: every emit workgroup reduces all records
-//           itself, which costs less than one more launch.
+//           direct_max_blocks blocks this step is folded into the emission:
+//           every emit workgroup reduces all records (and block sums) itself,
+//           which costs less than one more launch.
 //   emit    each block rebuilds its exact prefix, I = C_b + local prefix, and
 //           r = n I / Q: one block per workgroup of four waves with its own
 //           carries, one block per wave (16 consecutive weights per lane)
