@@ -28,7 +28,8 @@
  *     pfr_workspace_bytes() bytes, 256-byte aligned, and must be set to zero
  *     once (pfr_workspace_init) before their first use; the library keeps
  *     them in a reusable state after every call.  Calls that share a
- *     workspace must be ordered (same stream, or synchronised).
+ *     workspace must be ordered (same stream, or synchronised); they may come
+ *     from several host threads, whose calls on one workspace take turns.
  *   - Outputs must not alias inputs.
  *   - Random numbers come from Philox4x32-10 (Salmon et al., SC'11) with
  *     counter (index, domain << 28 | step, filter, offset) and key = seed, so

@@ -17,6 +17,7 @@ import collections
 import ctypes
 import functools
 import os
+import threading
 
 from . import _lib
 from ._lib import (FLAG_BAD_ANCESTOR, FLAG_BAD_COUNTS, FLAG_BAD_STEP, FLAG_BAD_WEIGHTS,
@@ -162,7 +163,8 @@ def _rng(seed, offset, filter_base, offset_dev=None):
 class _WorkspaceCache:
     """Workspaces are zeroed once and reused; calls sharing one must be
     ordered, so there is one per (device, stream, op, size): calls on
-    different streams never share a cached workspace.  The least recently
+    different streams never share a cached workspace, and those of several
+    host threads on one stream take turns in the library.  The least recently
     used ones are dropped once the cached bytes exceed the budget
     ($PFR_WS_CACHE_BYTES, default 4 GiB); a dropped workspace goes back to
     torch's stream-ordered allocator, so work already enqueued on its stream
@@ -172,23 +174,28 @@ class _WorkspaceCache:
         self.budget = int(budget)
         self.items = collections.OrderedDict()
         self.bytes = 0
+        self.lock = threading.Lock()
 
     def get(self, key):
-        ws = self.items.get(key)
-        if ws is not None:
-            self.items.move_to_end(key)
-        return ws
+        with self.lock:
+            ws = self.items.get(key)
+            if ws is not None:
+                self.items.move_to_end(key)
+            return ws
 
     def put(self, key, ws):
-        self.items[key] = ws
-        self.bytes += ws.numel()
-        while self.bytes > self.budget and len(self.items) > 1:
-            _, old = self.items.popitem(last=False)
-            self.bytes -= old.numel()
+        with self.lock:
+            replaced = self.items.pop(key, None)  # another thread's, as new as this one
+            self.items[key] = ws
+            self.bytes += ws.numel() - (0 if replaced is None else replaced.numel())
+            while self.bytes > self.budget and len(self.items) > 1:
+                _, old = self.items.popitem(last=False)
+                self.bytes -= old.numel()
 
     def clear(self):
-        self.items.clear()
-        self.bytes = 0
+        with self.lock:
+            self.items.clear()
+            self.bytes = 0
 
 
 _WS_CACHE = _WorkspaceCache(int(os.environ.get("PFR_WS_CACHE_BYTES", 4 << 30)))

@@ -76,6 +76,32 @@ bool overlaps(const void* a, size_t abytes, const void* b, size_t bbytes) {
 
 int launch_result(hipError_t e) { return e == hipSuccess ? PFR_OK : PFR_ELAUNCH; }
 
+// A call's launches hand data on through its workspace, so they have to stand
+// together in the stream: a call of another host thread on the same workspace
+// and stream, which the rule "ordered calls may share a workspace" allows, may
+// come before or after them but not between.  Every entry point therefore holds
+// the lock of its workspace while it launches (the entry points only: what they
+// call does not lock).  Calls on different workspaces meet only when their
+// addresses share one of the kWsLocks locks.
+constexpr int kWsLocks = 64;
+std::mutex g_ws_mu[kWsLocks];
+class WsLock {
+ public:
+  explicit WsLock(const void* ws)
+      : mu_(ws ? &g_ws_mu[(((uintptr_t)ws >> 8) * 0x9E3779B97F4A7C15ull) >> 58] : nullptr) {
+    if (mu_) mu_->lock();
+  }
+  ~WsLock() {
+    if (mu_) mu_->unlock();
+  }
+  WsLock(const WsLock&) = delete;
+  WsLock& operator=(const WsLock&) = delete;
+
+ private:
+  std::mutex* mu_;
+};
+static_assert(kWsLocks == 1 << (64 - 58), "the hash's leading bits choose the lock");
+
 // pfr_set_checks: the precondition checks run before the calls they cover.
 std::atomic<int> g_checks{0};
 bool checks_on() { return g_checks.load(std::memory_order_relaxed) != 0; }
@@ -244,6 +270,7 @@ int pfr_scaled_prefix(const void* w, pfr_dtype dtype, const pfr_segments* seg,
   if (overlaps(w, (size_t)s.n_total * dtype_size(dtype), r_out, rb) || overlaps(ws, need, r_out, rb))
     return PFR_EINVAL;
   const hipStream_t st = (hipStream_t)stream;
+  const WsLock lock(ws);
   if (precision == PFR_SCAN_EXACT)
     return launch_result(launch_scan_r(dtype == PFR_F64, w, s.n_total, r_out, ws, dev_flags, st));
   return launch_result(launch_fscan_r((int)precision, dtype == PFR_F64, w, s.n_total, r_out, ws,
@@ -259,6 +286,7 @@ int pfr_workspace_init(void* ws, size_t ws_bytes, void* stream) {
 int resample_multinomial(const void* w, pfr_dtype dtype, const pfr_segments* seg,
                          pfr_precision precision, pfr_rng rng, int32_t* ancestors, void* ws,
                          size_t ws_bytes, uint32_t* dev_flags, void* stream) {
+  const WsLock lock(ws);
   return collective(SCHEME_MULTINOMIAL, w, dtype, seg, precision, rng, ancestors, ws, ws_bytes,
                     dev_flags, stream);
 }
@@ -280,6 +308,7 @@ int resample_multinomial_iid(const void* w, pfr_dtype dtype, const pfr_segments*
   if (overlaps(ws, need, ancestors, (size_t)s.n_total * 4) ||
       overlaps(ws, need, w, (size_t)s.n_total * dtype_size(dtype)))
     return PFR_EINVAL;
+  const WsLock lock(ws);
   return launch_result(launch_multinomial_iid(dtype == PFR_F64, w, s.n_total, make_key(rng),
                                               rng.offset, rng.filter_base, ancestors, ws,
                                               dev_flags, (hipStream_t)stream));
@@ -288,6 +317,7 @@ int resample_multinomial_iid(const void* w, pfr_dtype dtype, const pfr_segments*
 int resample_stratified(const void* w, pfr_dtype dtype, const pfr_segments* seg,
                         pfr_precision precision, pfr_rng rng, int32_t* ancestors, void* ws,
                         size_t ws_bytes, uint32_t* dev_flags, void* stream) {
+  const WsLock lock(ws);
   return collective(SCHEME_STRATIFIED, w, dtype, seg, precision, rng, ancestors, ws, ws_bytes,
                     dev_flags, stream);
 }
@@ -295,13 +325,19 @@ int resample_stratified(const void* w, pfr_dtype dtype, const pfr_segments* seg,
 int resample_systematic(const void* w, pfr_dtype dtype, const pfr_segments* seg,
                         pfr_precision precision, pfr_rng rng, int32_t* ancestors, void* ws,
                         size_t ws_bytes, uint32_t* dev_flags, void* stream) {
+  const WsLock lock(ws);
   return collective(SCHEME_SYSTEMATIC, w, dtype, seg, precision, rng, ancestors, ws, ws_bytes,
                     dev_flags, stream);
 }
 
-int resample_metropolis(const void* w, pfr_dtype dtype, const pfr_segments* seg, int32_t B,
-                        const int32_t* B_dev, pfr_rng rng, int32_t* ancestors, void* ws,
-                        size_t ws_bytes, void* stream) {
+}  // extern "C"
+
+namespace {
+
+// resample_metropolis (its workspace is locked by the caller)
+int metropolis(const void* w, pfr_dtype dtype, const pfr_segments* seg, int32_t B,
+               const int32_t* B_dev, pfr_rng rng, int32_t* ancestors, void* ws, size_t ws_bytes,
+               void* stream) {
   SegInfo s;
   int rc = check_segments(seg, &s);
   if (rc) return rc;
@@ -324,12 +360,8 @@ int resample_metropolis(const void* w, pfr_dtype dtype, const pfr_segments* seg,
                                          (hipStream_t)stream));
 }
 
-}  // extern "C"
-
-namespace {
-
 // resample_rejection, with the bound check of the precondition checks unless
-// the bound need not hold (partial rejection control)
+// the bound need not hold (partial rejection control); locked by the caller
 int rejection(const void* w, pfr_dtype dtype, const pfr_segments* seg, double w_max,
               const double* w_max_dev, uint32_t max_trials, pfr_rng rng, int32_t* ancestors,
               void* ws, size_t ws_bytes, uint32_t* dev_flags, void* stream, bool bounded) {
@@ -361,10 +393,18 @@ int rejection(const void* w, pfr_dtype dtype, const pfr_segments* seg, double w_
 
 extern "C" {
 
+int resample_metropolis(const void* w, pfr_dtype dtype, const pfr_segments* seg, int32_t B,
+                        const int32_t* B_dev, pfr_rng rng, int32_t* ancestors, void* ws,
+                        size_t ws_bytes, void* stream) {
+  const WsLock lock(ws);
+  return metropolis(w, dtype, seg, B, B_dev, rng, ancestors, ws, ws_bytes, stream);
+}
+
 int resample_rejection(const void* w, pfr_dtype dtype, const pfr_segments* seg, double w_max,
                        const double* w_max_dev, uint32_t max_trials, pfr_rng rng,
                        int32_t* ancestors, void* ws, size_t ws_bytes, uint32_t* dev_flags,
                        void* stream) {
+  const WsLock lock(ws);
   return rejection(w, dtype, seg, w_max, w_max_dev, max_trials, rng, ancestors, ws, ws_bytes,
                    dev_flags, stream, true);
 }
@@ -384,6 +424,7 @@ int resample_partial_rejection(const void* w, pfr_dtype dtype, const pfr_segment
         (w && overlaps(weights_out, wb, w, wb)))
       return PFR_EINVAL;
   }
+  const WsLock lock(ws);
   rc = rejection(w, dtype, seg, v_max, v_max_dev, max_trials, rng, ancestors, ws, ws_bytes,
                  dev_flags, stream, false);
   if (rc || s.n_total == 0) return rc;
@@ -403,14 +444,19 @@ int offspring_to_ancestors(const int32_t* offspring, const pfr_segments* seg, in
     return PFR_EINVAL;
   const size_t need = o2a_workspace_bytes(s.n_total);
   if (!ws || ws_bytes < need || !aligned256(ws)) return PFR_EWORKSPACE;
+  const WsLock lock(ws);
   return launch_result(launch_offspring_to_ancestors(offspring, s.n_total, s.offsets, s.n_filters,
                                                      ancestors, ws, dev_flags,
                                                      (hipStream_t)stream));
 }
 
-int permute_ancestors(const int32_t* ancestors, const pfr_segments* seg, int32_t sorted_hint,
-                      int32_t* permuted, void* ws, size_t ws_bytes, uint32_t* dev_flags,
-                      void* stream) {
+}  // extern "C"
+
+namespace {
+
+// permute_ancestors (its workspace is locked by the caller)
+int permute(const int32_t* ancestors, const pfr_segments* seg, int32_t sorted_hint,
+            int32_t* permuted, void* ws, size_t ws_bytes, uint32_t* dev_flags, void* stream) {
   SegInfo s;
   int rc = check_segments(seg, &s);
   if (rc) return rc;
@@ -432,10 +478,6 @@ int permute_ancestors(const int32_t* ancestors, const pfr_segments* seg, int32_t
                                       sorted_hint != 0, permuted, ws, need, dev_flags,
                                       (hipStream_t)stream));
 }
-
-}  // extern "C"
-
-namespace {
 
 // Scratch of permute_ancestors_noalloc: the claim vector and the marked
 // ancestry (4 + 4 bytes per particle, each part 256-byte aligned) of up to
@@ -468,6 +510,13 @@ int noalloc_scratch(void** out) {
 }  // namespace
 
 extern "C" {
+
+int permute_ancestors(const int32_t* ancestors, const pfr_segments* seg, int32_t sorted_hint,
+                      int32_t* permuted, void* ws, size_t ws_bytes, uint32_t* dev_flags,
+                      void* stream) {
+  const WsLock lock(ws);
+  return permute(ancestors, seg, sorted_hint, permuted, ws, ws_bytes, dev_flags, stream);
+}
 
 int permute_ancestors_noalloc(const int32_t* ancestors, const pfr_segments* seg,
                               int32_t sorted_hint, int32_t* permuted, uint32_t* dev_flags,
@@ -523,6 +572,7 @@ int effective_sample_size(const void* w, pfr_dtype dtype, const pfr_segments* se
   if (overlaps(ws, need, ess, ebytes) ||
       (s.n_total > 0 && overlaps(w, (size_t)s.n_total * dtype_size(dtype), ess, ebytes)))
     return PFR_EINVAL;
+  const WsLock lock(ws);
   return launch_result(launch_ess(dtype == PFR_F64, w, s.n_total, s.offsets, s.n_filters, ess, ws,
                                   dev_flags, (hipStream_t)stream));
 }
@@ -586,6 +636,7 @@ int resample_permuted(pfr_op scheme, const void* w, pfr_dtype dtype, const pfr_s
   if (!ws || ws_bytes < need || !aligned256(ws)) return PFR_EWORKSPACE;
   if (overlaps(ws, need, ancestors, abytes) || overlaps(ws, need, permuted, abytes))
     return PFR_EINVAL;
+  const WsLock lock(ws);
   void* rws = (char*)ws + perm;  // the resampler's own workspace
   size_t rbytes = ws_bytes - perm;
   if (optional && (overlaps(rws, rbytes, ancestors, abytes) ||
@@ -640,17 +691,16 @@ int resample_permuted(pfr_op scheme, const void* w, pfr_dtype dtype, const pfr_s
                       dev_flags, stream);
       break;
     case PFR_OP_METROPOLIS:
-      rc = resample_metropolis(w, dtype, seg, params->B, params->B_dev, rng, ancestors, rws,
-                               rbytes, stream);
+      rc = metropolis(w, dtype, seg, params->B, params->B_dev, rng, ancestors, rws, rbytes,
+                      stream);
       break;
     default:
-      rc = resample_rejection(w, dtype, seg, params->w_max, params->w_max_dev, params->max_trials,
-                              rng, ancestors, rws, rbytes, dev_flags, stream);
+      rc = rejection(w, dtype, seg, params->w_max, params->w_max_dev, params->max_trials, rng,
+                     ancestors, rws, rbytes, dev_flags, stream, true);
       break;
   }
   if (rc) return rc;
-  return permute_ancestors(ancestors, seg, sorted_out ? 1 : 0, permuted, ws, perm, dev_flags,
-                           stream);
+  return permute(ancestors, seg, sorted_out ? 1 : 0, permuted, ws, perm, dev_flags, stream);
 }
 
 size_t lgssm_workspace_bytes(int32_t n_filters, int32_t n) {
@@ -671,6 +721,7 @@ int lgssm_init(const pfr_lgssm* model, int32_t n_filters, int32_t n, pfr_rng rng
     return PFR_EWORKSPACE;
   Key key = make_key(rng);
   key.offset_dev = nullptr;
+  const WsLock lock(ws);
   return launch_result(launch_lgssm_init(n_filters, n, model->s0, key, rng.offset,
                                          rng.filter_base, x, w, log_z, B_dev, t_dev,
                                          lgssm_state(ws, n_filters), (hipStream_t)stream));
@@ -693,6 +744,7 @@ int lgssm_step(const pfr_lgssm* model, pfr_op scheme, pfr_precision precision, i
   const int64_t total = (int64_t)n_filters * n;
   if (overlaps(ancestors, (size_t)total * 4, permuted, (size_t)total * 4)) return PFR_EINVAL;
   const hipStream_t st = (hipStream_t)stream;
+  const WsLock lock(ws);
   const FilterState state = lgssm_state(ws, n_filters);
   const int64_t* offsets = state.offsets;
   void* perm_ws = (char*)ws + lgssm_state_bytes(n_filters);
