@@ -164,7 +164,8 @@ class _WorkspaceCache:
     """Workspaces are zeroed once and reused; calls sharing one must be
     ordered, so there is one per (device, stream, op, size): calls on
     different streams never share a cached workspace, and those of several
-    host threads on one stream take turns in the library.  The least recently
+    host threads on one stream take turns in the library.  Calls that are being
+    captured do not use it (_workspace).  The least recently
     used ones are dropped once the cached bytes exceed the budget
     ($PFR_WS_CACHE_BYTES, default 4 GiB); a dropped workspace goes back to
     torch's stream-ordered allocator, so work already enqueued on its stream
@@ -211,24 +212,45 @@ def new_workspace(nbytes: int, device=None):
     torch = _torch()
     nbytes = max(256, (int(nbytes) + 255) // 256 * 256)
     ws = torch.empty(nbytes, dtype=torch.uint8, device=device or "cuda")
+    _zero_workspace(ws, nbytes)
+    return ws
+
+
+def _zero_workspace(ws, nbytes):
     _lib.check(_lib.load().pfr_workspace_init(_ptr(ws), nbytes, _stream()), "workspace_init")
+
+
+def _own_workspace(op, need, device, stream):
+    """The workspace of a call that was given none: the cached one of this
+    device, stream (the current one), operation and size.  While the stream is
+    being captured, one from the graph's own memory instead: torch captures all
+    graphs on one stream by default and may replay two of them at the same
+    time, and a graph outlives what the cache drops.  It is let go after the
+    call, as any tensor of the graph is that nothing refers to any more.  Only
+    the counts' expansion starts from zeros; the others write what they read."""
+    torch = _torch()
+    if torch._C._cuda_isCurrentStreamCapturing():
+        ws = torch.empty(need, dtype=torch.uint8, device=device)
+        if op == _lib.OP_OFFSPRING_TO_ANCESTORS:
+            _zero_workspace(ws, need)
+        return ws
+    key = (device, stream, op, need)
+    ws = _WS_CACHE.get(key)
+    if ws is None:
+        ws = new_workspace(need, device)
+        _WS_CACHE.put(key, ws)
     return ws
 
 
 def _workspace(op, seg, dtype_code, device, ws, stream):
-    """(workspace, its bytes): the caller's, or the cached one of this device,
-    stream (the current one), operation and size."""
+    """(workspace, its bytes): the caller's, or one of the binding's."""
     if ws is not None:
         return ws, ws.numel()
     need = _lib.load().pfr_workspace_bytes(op, ctypes.byref(seg), dtype_code)
     if need == 0:
         return None, 0
-    key = (device, stream, op, need)
-    cached = _WS_CACHE.get(key)
-    if cached is None:
-        cached = new_workspace(need, device)
-        _WS_CACHE.put(key, cached)
-    return cached, cached.numel()
+    ws = _own_workspace(op, need, device, stream)
+    return ws, ws.numel()
 
 
 def _out_like(n, device, out):
@@ -381,11 +403,7 @@ def resample_permuted(scheme, w, seed=0, offset=0, filter_base=0, precision=SCAN
     need = int(lib.pfr_resample_permuted_workspace_bytes(op, ctypes.byref(seg), dt))
     stream = _stream()
     if workspace is None:
-        key = (w.device, stream, "permuted", op, need)
-        workspace = _WS_CACHE.get(key)
-        if workspace is None:
-            workspace = new_workspace(need, w.device)
-            _WS_CACHE.put(key, workspace)
+        workspace = _own_workspace(("permuted", op), need, w.device, stream)
     params = _lib.SchemeParams(int(precision), int(B), None if B_per_filter is None
                                else B_per_filter.data_ptr(), float(w_max),
                                None if w_max_per_filter is None else w_max_per_filter.data_ptr(),
