@@ -7,6 +7,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <initializer_list>
 #include <mutex>
 
 #include "pfresample.h"
@@ -72,6 +73,18 @@ bool aligned256(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 255u) 
 bool overlaps(const void* a, size_t abytes, const void* b, size_t bbytes) {
   const uintptr_t a0 = (uintptr_t)a, b0 = (uintptr_t)b;
   return a0 < b0 + bbytes && b0 < a0 + abytes;
+}
+
+// An optional workspace that lies over one of the call's arrays is left alone:
+// the call runs without one, as it did before it could use any.
+struct Range {
+  const void* p;
+  size_t bytes;
+};
+bool clear_of(const void* ws, size_t bytes, std::initializer_list<Range> arrays) {
+  for (const Range& r : arrays)
+    if (r.p && overlaps(ws, bytes, r.p, r.bytes)) return false;
+  return true;
 }
 
 int launch_result(hipError_t e) { return e == hipSuccess ? PFR_OK : PFR_ELAUNCH; }
@@ -197,8 +210,9 @@ int collective(int scheme, const void* w, pfr_dtype dtype, const pfr_segments* s
     // against 17.9 us, 4096 16.0 against 35.5); the results are the same
     if (small_multinomial(scheme, s) && ws && aligned256(ws)) {
       const ScanLayout L = scan_layout(s.n_total, true);
-      if (ws_bytes >= L.total && !overlaps(ws, L.total, a, (size_t)s.n_total * 4) &&
-          !overlaps(ws, L.total, w, (size_t)s.n_total * dtype_size(dtype)))
+      const size_t n = (size_t)s.n_total;
+      if (ws_bytes >= L.total && clear_of(ws, L.total, {{a, n * 4}, {w, n * dtype_size(dtype)},
+                                                        {rng.offset_dev, 4}, {dev_flags, 4}}))
         return launch_result(launch_scan(scheme, dtype == PFR_F64, w, s.n_total, key, rng.offset,
                                          rng.filter_base, a, ws, dev_flags, st));
     }
@@ -348,6 +362,15 @@ int metropolis(const void* w, pfr_dtype dtype, const pfr_segments* seg, int32_t 
   if (overlaps(w, (size_t)s.n_total * dtype_size(dtype), ancestors, (size_t)s.n_total * 4))
     return PFR_EINVAL;
   if (ws && !aligned256(ws)) return PFR_EWORKSPACE;
+  if (ws && s.n_filters > 1) {  // a batch needs none
+    const size_t used = metropolis_workspace_bytes(dtype == PFR_F64, s.n_total, s.n_filters,
+                                                   s.max_len);
+    const size_t n = (size_t)s.n_total, nf = (size_t)s.n_filters;
+    if (ws_bytes < used || !clear_of(ws, used, {{ancestors, n * 4}, {w, n * dtype_size(dtype)},
+                                                {B_dev, nf * 4}, {s.offsets, (nf + 1) * 8},
+                                                {rng.offset_dev, 4}}))
+      ws = nullptr;
+  }
   if (checks_on()) {
     rc = launch_result(launch_check_weights(dtype == PFR_F64, w, s.n_total, s.offsets,
                                             s.n_filters, false, 0.0, nullptr, nullptr,
@@ -639,9 +662,8 @@ int resample_permuted(pfr_op scheme, const void* w, pfr_dtype dtype, const pfr_s
   const WsLock lock(ws);
   void* rws = (char*)ws + perm;  // the resampler's own workspace
   size_t rbytes = ws_bytes - perm;
-  if (optional && (overlaps(rws, rbytes, ancestors, abytes) ||
-                   overlaps(rws, rbytes, permuted, abytes) ||
-                   overlaps(rws, rbytes, w, (size_t)s.n_total * dtype_size(dtype))))
+  if (optional && !clear_of(rws, rbytes, {{ancestors, abytes}, {permuted, abytes},
+                                          {w, (size_t)s.n_total * dtype_size(dtype)}}))
     rbytes = 0;
   const bool sorted_out = scheme <= PFR_OP_SYSTEMATIC;  // collective schemes
   const hipStream_t st = (hipStream_t)stream;
