@@ -87,7 +87,8 @@ typedef enum {
 #define PFR_FLAG_TRIAL_CAP 2u    /* rejection: a particle rejected max_trials proposals; it keeps a_i = i */
 #define PFR_FLAG_BAD_COUNTS 4u   /* offspring negative or not summing to n (see offspring_to_ancestors);
                                     also raised by a batched collective call whose segment exceeds
-                                    PFR_MAX_BATCH_SEGMENT (that segment gets the identity) */
+                                    PFR_MAX_BATCH_SEGMENT or a wrong max_len (that segment may
+                                    get the identity) */
 #define PFR_FLAG_BAD_WEIGHTS 8u  /* a weight is negative, NaN or infinite: output is the identity */
 #define PFR_FLAG_BAD_ANCESTOR 16u /* permute: an ancestor outside [0, n) is replaced by its own index */
 #define PFR_FLAG_BAD_STEP 32u    /* lgssm_step: step index t outside [1, T]; the state is left unchanged */

@@ -1671,8 +1671,8 @@ template <typename T, int SCHEME, int NB, bool PERM>
 __global__ __launch_bounds__(OneWg<NB>::kThreads,
                              NB == 16 && sizeof(T) == 4 ? 8 : 1) void k_scan_one(
     const T* __restrict__ w_all, int64_t n_total, const int64_t* __restrict__ offsets,
-    int64_t above, Key key, uint32_t offset, uint32_t filter_base, int32_t* __restrict__ a_all,
-    int32_t* __restrict__ c_all, uint32_t* __restrict__ flags) {
+    int64_t above, bool last, Key key, uint32_t offset, uint32_t filter_base,
+    int32_t* __restrict__ a_all, int32_t* __restrict__ c_all, uint32_t* __restrict__ flags) {
   typedef OneWg<NB> G;
   constexpr bool SYSTEMATIC = SCHEME == SCHEME_SYSTEMATIC;
   static_assert(SCHEME != SCHEME_MULTINOMIAL, "strata schemes only");
@@ -1685,7 +1685,17 @@ __global__ __launch_bounds__(OneWg<NB>::kThreads,
   const uint32_t f = blockIdx.x;
   const int64_t base = offsets ? offsets[f] : 0;
   const int64_t n = offsets ? offsets[f + 1] - base : n_total;
-  if (n <= above || n > (int64_t)NB * kBlock) return;  // another launch's segment
+  if (n <= above) return;  // another launch's segment
+  if (n > (int64_t)NB * kBlock) {
+    // another launch's, or longer than the batch's max_len: identity + flag
+    if (!last) return;
+    for (int64_t i = threadIdx.x; i < n; i += G::kThreads) {
+      a_all[base + i] = (int32_t)i;
+      if (PERM) c_all[base + i] = (int32_t)i;
+    }
+    if (threadIdx.x == 0 && flags) atomicOr(flags, FLAG_BAD_COUNTS);
+    return;
+  }
   const T* __restrict__ w = w_all + base;
   int32_t* __restrict__ a = a_all + base;
   const uint32_t filter = filter_base + f;
@@ -2380,8 +2390,9 @@ hipError_t launch_scan_scheme(int scheme, const void* w, int64_t n, Key key, uin
 
 // One workgroup per segment (or for one vector): the strata schemes in tiers
 // of segment length, the multinomial scheme and longer segments through
-// k_scan_batched.  max_len: longest segment (0 = unknown).  c: the permuted
-// ancestry too (strata schemes, max_len known and at most kOneWgMax).
+// k_scan_batched.  max_len: longest segment (0 = unknown); the tier that ends
+// the call for it gives longer ones the identity.  c: the permuted ancestry
+// too (strata schemes, max_len known and at most kOneWgMax).
 template <typename T, int SCHEME>
 hipError_t launch_batched_t(const T* w, int64_t n_total, const int64_t* offsets,
                             uint32_t n_filters, int64_t max_len, Key key, uint32_t offset,
@@ -2397,8 +2408,9 @@ hipError_t launch_batched_t(const T* w, int64_t n_total, const int64_t* offsets,
       if (max_len > 0 && above >= max_len) return;
       if ((max_len <= 0 || max_len > upto) && (equal || (upto < kOneWgMax && n_filters <= 256)))
         return;
+      const bool last = max_len > 0 && max_len <= upto;
       hipLaunchKernelGGL(c ? perm : plain, dim3(n_filters), dim3(threads), 0, stream, w, n_total,
-                         offsets, above, key, offset, filter_base, a, c, flags);
+                         offsets, above, last, key, offset, filter_base, a, c, flags);
       above = upto;
     };
     tier(k_scan_one<T, SCHEME, 1, false>, k_scan_one<T, SCHEME, 1, true>, OneWg<1>::kThreads,
