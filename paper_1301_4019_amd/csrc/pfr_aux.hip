@@ -570,11 +570,49 @@ __device__ __forceinline__ void load_quad(const int32_t* __restrict__ as, uint32
   }
 }
 
+// A segment that no launch of the call was made for (longer than the batch's
+// max_len) by one workgroup in global memory: lowest claimers by atomic minimum
+// into d, then the backward walk of k_resolve_ad.  The claims are read past the
+// CU's own cache, where the atomics are.  Slow, and never taken by a call whose
+// max_len holds.
+template <int THREADS>
+__device__ void permute_unforeseen(const int32_t* __restrict__ a, int64_t n, int32_t* d,
+                                   int32_t* __restrict__ c, bool& bad) {
+  auto anc = [&](int64_t i) -> int64_t {
+    const int64_t v = a[i];
+    const bool out = v < 0 || v >= n;
+    bad |= out;
+    return out ? i : v;
+  };
+  auto claim = [&](int64_t j) -> int32_t {
+    return __hip_atomic_load(&d[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
+  for (int64_t j = threadIdx.x; j < n; j += THREADS)
+    __hip_atomic_store(&d[j], (int32_t)n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __threadfence();
+  __syncthreads();
+  for (int64_t i = threadIdx.x; i < n; i += THREADS) atomicMin(&d[anc(i)], (int32_t)i);
+  __threadfence();
+  __syncthreads();
+  for (int64_t j = threadIdx.x; j < n; j += THREADS) {
+    if (claim(j) < (int32_t)n) {
+      c[j] = (int32_t)j;
+      continue;
+    }
+    int64_t y = j, ay = anc(j);
+    while (claim(ay) == (int32_t)y) {  // (the chain's slots are distinct: it ends)
+      y = ay;
+      ay = anc(y);
+    }
+    c[j] = (int32_t)ay;
+  }
+}
+
 template <int CAP, int THREADS>
 __global__ __launch_bounds__(THREADS) void k_permute_lds(
     const int32_t* __restrict__ a, int64_t n_total, const int64_t* __restrict__ offsets,
-    int64_t above, int64_t upto, bool sorted, int32_t* __restrict__ c,
-    uint32_t* __restrict__ flags) {
+    int64_t above, int64_t upto, bool last, bool sorted, int32_t* __restrict__ d,
+    int32_t* __restrict__ c, uint32_t* __restrict__ flags) {
   constexpr int kBytes = perm_buffer(CAP);
   constexpr uint32_t WIN = kBytes / 4;         // slots of a claim window
   constexpr bool kOnePass = kBytes >= 3 * CAP;  // entries and claim bytes fit together
@@ -587,7 +625,13 @@ __global__ __launch_bounds__(THREADS) void k_permute_lds(
   __shared__ uint32_t slow[kSlow], n_slow;
   const int64_t base = offsets ? offsets[blockIdx.x] : 0;
   const int64_t n64 = offsets ? offsets[blockIdx.x + 1] - base : n_total;
-  if (n64 <= above || n64 > upto || n64 > CAP) return;  // another launch's segment
+  if (n64 <= above || (n64 > upto && !last)) return;  // another launch's segment
+  if (n64 > CAP) {
+    bool out = false;
+    permute_unforeseen<THREADS>(a + base, n64, d + base, c + base, out);
+    if (flags && ballot(out) != 0 && lane_id() == 0) atomicOr(flags, FLAG_BAD_ANCESTOR);
+    return;
+  }
   const uint32_t n = (uint32_t)n64, nq = (n + 3) / 4;
   const bool packed = CAP <= 32768 || n <= 32768u;
   const uint32_t tid = threadIdx.x, lane = lane_id();
@@ -1368,7 +1412,7 @@ hipError_t launch_permute(const int32_t* a, int64_t n_total, const int64_t* offs
     else
       hipLaunchKernelGGL((k_permute_lds<kPermMid, 1024>), dim3(1), dim3(1024), 0, stream, a,
                          n_total, (const int64_t*)nullptr, (int64_t)0, (int64_t)kPermSingleMax,
-                         sorted, c, flags);
+                         false, sorted, d, c, flags);
     return hipGetLastError();
   }
   if (offsets && n_filters > 1) {
@@ -1394,18 +1438,16 @@ hipError_t launch_permute(const int32_t* a, int64_t n_total, const int64_t* offs
       if (upto[t] < need && (equal || n_filters <= kSlots[upto[1] < need ? (upto[2] < need ? 3 : 2) : 1]))
         continue;
       const dim3 g(n_filters);
-      if (t == 0)
-        hipLaunchKernelGGL((k_permute_lds<kPermShort, 256>), g, dim3(256), 0, stream, a, n_total,
-                           offsets, above, upto[t], sorted, c, flags);
-      else if (t == 1)
-        hipLaunchKernelGGL((k_permute_lds<kPermMid, 1024>), g, dim3(1024), 0, stream, a, n_total,
-                           offsets, above, upto[t], sorted, c, flags);
-      else if (t == 2)
-        hipLaunchKernelGGL((k_permute_lds<kPermLong, 1024>), g, dim3(1024), 0, stream, a, n_total,
-                           offsets, above, upto[t], sorted, c, flags);
-      else
-        hipLaunchKernelGGL((k_permute_lds<kPermBatchMax, 1024>), g, dim3(1024), 0, stream, a,
-                           n_total, offsets, above, upto[t], sorted, c, flags);
+      // (the tier that ends the call takes what is longer than max_len too)
+      const bool last = max_len > 0 && max_len <= top && upto[t] >= need;
+      auto launch = [&](auto kernel, int threads) {
+        hipLaunchKernelGGL(kernel, g, dim3(threads), 0, stream, a, n_total, offsets, above, upto[t],
+                           last, sorted, d, c, flags);
+      };
+      if (t == 0) launch(k_permute_lds<kPermShort, 256>, 256);
+      else if (t == 1) launch(k_permute_lds<kPermMid, 1024>, 1024);
+      else if (t == 2) launch(k_permute_lds<kPermLong, 1024>, 1024);
+      else launch(k_permute_lds<kPermBatchMax, 1024>, 1024);
       above = upto[t];
     }
     hipError_t e0 = hipGetLastError();
