@@ -45,6 +45,8 @@
 // segments, or inside one workgroup per segment.
 #include "pfr_kernels.h"
 
+#include <algorithm>
+
 namespace pfr {
 
 namespace {
@@ -2409,8 +2411,12 @@ hipError_t launch_batched_t(const T* w, int64_t n_total, const int64_t* offsets,
       if ((max_len <= 0 || max_len > upto) && (equal || (upto < kOneWgMax && n_filters <= 256)))
         return;
       const bool last = max_len > 0 && max_len <= upto;
-      hipLaunchKernelGGL(c ? perm : plain, dim3(n_filters), dim3(threads), 0, stream, w, n_total,
-                         offsets, above, last, key, offset, filter_base, a, c, flags);
+      // (a launch holds fewer than 2^32 threads: 4 M segments of 1024)
+      const uint32_t most = (uint32_t)((((uint64_t)1 << 32) - 1) / (uint64_t)threads);
+      for (uint32_t f0 = 0; f0 < n_filters; f0 += most)
+        hipLaunchKernelGGL(c ? perm : plain, dim3(std::min(most, n_filters - f0)), dim3(threads), 0,
+                           stream, w, n_total, offsets ? offsets + f0 : nullptr, above, last, key,
+                           offset, filter_base + f0, a, c, flags);
       above = upto;
     };
     tier(k_scan_one<T, SCHEME, 1, false>, k_scan_one<T, SCHEME, 1, true>, OneWg<1>::kThreads,
