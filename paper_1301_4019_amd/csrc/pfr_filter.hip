@@ -18,6 +18,7 @@
 // counter (i, INIT<<28, f, offset), its propagation noise at step t the counter
 // (i, NOISE<<28 | t, f, offset); a standard normal is formed from words 0 and
 // 1 by the Box-Muller transform with u1 = (x0 + 1) 2^-32 and u2 = x1 2^-32.
+#include "pfr_filter_math.h"
 #include "pfr_kernels.h"
 
 namespace pfr {
@@ -25,39 +26,15 @@ namespace pfr {
 namespace {
 
 // ---------------------------------------------------------------- functions
-// The move needs a logarithm, a square root, a cosine and an exponential per
-// particle in binary64; the general library functions (argument reduction for
-// any argument, special cases) were most of its time.  Here the arguments are
-// known: u1 = y 2^-32 with y a whole number in [1, 2^32], an angle that is a
-// whole number of 2^-32 turns, and a log-weight at most 0.  The errors are a
-// few units in the last place of binary64, as the library's.
-//   -log u1   y = m 2^e; a table of 128 intervals of m gives rc ~ 1 / m and
-//             -log rc, and log(m rc) is a short series in r = m rc - 1 (m from
-//             sqrt 2 up counts as m / 2, so that u1 near 1 keeps its relative
-//             precision: kk = 0, -log rc = 0)
-//   cos       a table of 256 angles and the addition theorem
-//   exp       2^k e^r, |r| <= ln 2 / 2, the exponential series to r^13 / 13!
-//             (below 2^-52 of the sum beyond)
-// lgssm_init forms the tables in the workspace; a workgroup copies them to LDS.
-constexpr int kLogBins = 128, kCosBins = 256;
-constexpr int kHalfBin = 53;  // m from 1 + 53/128 = 1.4140625 on
-constexpr double kLn2Hi = 0x1.62e42fefa3800p-1;   // ln 2 to 42 bits: times 0..32 exact
-constexpr double kLn2Lo = 0x1.ef35793c76730p-45;  // ln 2 - kLn2Hi
-
-struct MathTables {
-  double2 lg[kLogBins];  // rc (times 1/2 where m counts as m / 2), -log rc
-  double2 cs[kCosBins];  // cosine and sine of 2 pi i / 256
-};
-
+// lgssm_init forms the tables of pfr_filter_math.h in the workspace; a
+// workgroup copies them to LDS.
 __device__ __forceinline__ void fill_tables(MathTables* T, int tid, int threads) {
   for (int i = tid; i < kCosBins; i += threads)
-    T->cs[i] = make_double2(cospi(i * (2.0 / kCosBins)), sinpi(i * (2.0 / kCosBins)));
+    T->cs[i] = MathPair{cospi(i * (2.0 / kCosBins)), sinpi(i * (2.0 / kCosBins))};
   for (int i = tid; i < kLogBins; i += threads) {
-    const bool half = i >= kHalfBin;
-    const double c = (1.0 + (i + 0.5) / kLogBins) * (half ? 0.5 : 1.0);
-    // the intervals at 1: rc = 1, so that log u1 = log(1 + r) there
-    const double rc = (i == 0 || i == kLogBins - 1) ? 1.0 : (double)(float)(1.0 / c);
-    T->lg[i] = make_double2(half ? 0.5 * rc : rc, rc == 1.0 ? 0.0 : -log(rc));
+    const LogEntry t = kLogTable[i];
+    T->lg[i] = MathPair{t.rc, t.hi};
+    T->lo[i] = t.lo;
   }
 }
 static_assert(sizeof(MathTables) == kFilterTableBytes, "table bytes of the filter state");
@@ -67,28 +44,9 @@ __device__ __forceinline__ void load_tables(MathTables* T, const void* __restric
     reinterpret_cast<uint4*>(T)[i] = reinterpret_cast<const uint4*>(src)[i];
 }
 
-// -log((x + 1) 2^-32)
-__device__ __forceinline__ double neg_log_u1(uint32_t x, const MathTables* T) {
-  const uint64_t yb = (uint64_t)__double_as_longlong((double)x + 1.0);
-  const uint32_t hi = (uint32_t)(yb >> 32);
-  const uint32_t i = (hi >> 13) & (kLogBins - 1);
-  const double m = __longlong_as_double(
-      (long long)((yb & 0xFFFFFFFFFFFFFull) | 0x3FF0000000000000ull));
-  const int kk = 1023 + 32 - (int)(hi >> 20) - (i >= (uint32_t)kHalfBin ? 1 : 0);
-  const double2 t = T->lg[i];
-  const double r = __fma_rn(m, t.x, -1.0);  // |r| below 2^-7
-  double p = __fma_rn(r, 1.0 / 7.0, -1.0 / 6.0);
-  p = __fma_rn(p, r, 1.0 / 5.0);
-  p = __fma_rn(p, r, -1.0 / 4.0);
-  p = __fma_rn(p, r, 1.0 / 3.0);
-  p = __fma_rn(p, r, -1.0 / 2.0);
-  const double log1 = __fma_rn(p * r, r, r);  // log(1 + r)
-  const double kd = (double)kk;
-  return __fma_rn(kd, kLn2Hi, __fma_rn(kd, kLn2Lo, -t.y) - log1);
-}
-
 // Square root of t = 0 or 2^-40 < t < 2^10: the reciprocal square root
-// estimate, a coupled Newton step (Goldschmidt), then one on the root.
+// estimate, a coupled Newton step (Goldschmidt), then one on the root.  The
+// correctly rounded root of 2 neg_log_u1(x) for each of the 2^32 words x.
 __device__ __forceinline__ double sqrt_pos(double t) {
   const double y = __builtin_amdgcn_rsq(t);
   double g = t * y, h = 0.5 * y;
@@ -98,39 +56,6 @@ __device__ __forceinline__ double sqrt_pos(double t) {
   d = __fma_rn(-g, g, t);
   g = __fma_rn(d, h, g);
   return t == 0.0 ? 0.0 : g;
-}
-
-// cos(2 pi x 2^-32)
-__device__ __forceinline__ double cos_turns(uint32_t x, const MathTables* T) {
-  const uint32_t v = x + 0x800000u;
-  const double2 t = T->cs[v >> 24];
-  const double d = (double)((int32_t)(v & 0xFFFFFFu) - 0x800000) * (6.283185307179586 * 0x1p-32);
-  const double z = d * d;
-  const double cm = z * __fma_rn(z, __fma_rn(z, -1.0 / 720.0, 1.0 / 24.0), -0.5);  // cos d - 1
-  const double s3 = __fma_rn(z, __fma_rn(z, -1.0 / 5040.0, 1.0 / 120.0), -1.0 / 6.0);
-  const double sn = __fma_rn(d * z, s3, d);
-  return __fma_rn(t.x, cm, __fma_rn(-t.y, sn, t.x));
-}
-
-// exp(x) for x <= 0 (NaN stays NaN)
-__device__ __forceinline__ double exp_neg(double x) {
-  x = x < -800.0 ? -800.0 : x;  // below -746 the result is 0
-  const double k = rint(x * 1.4426950408889634);
-  const double rh = __fma_rn(k, -kLn2Hi, x), rl = k * kLn2Lo;  // rh exact
-  const double r = rh - rl, rest = (rh - r) - rl;
-  double p = __fma_rn(r, 1.0 / 6227020800.0, 1.0 / 479001600.0);
-  p = __fma_rn(p, r, 1.0 / 39916800.0);
-  p = __fma_rn(p, r, 1.0 / 3628800.0);
-  p = __fma_rn(p, r, 1.0 / 362880.0);
-  p = __fma_rn(p, r, 1.0 / 40320.0);
-  p = __fma_rn(p, r, 1.0 / 5040.0);
-  p = __fma_rn(p, r, 1.0 / 720.0);
-  p = __fma_rn(p, r, 1.0 / 120.0);
-  p = __fma_rn(p, r, 1.0 / 24.0);
-  p = __fma_rn(p, r, 1.0 / 6.0);
-  p = __fma_rn(p, r, 0.5);
-  p = __fma_rn(p * r, r, rest);  // e^(r + rest) - 1 - r
-  return ldexp(1.0 + (r + p), (int)k);
 }
 
 __device__ __forceinline__ double normal_bm(uint32_t x0, uint32_t x1, const MathTables* T) {

@@ -194,7 +194,7 @@ hipError_t launch_prc_weights(bool f64, const void* w, int64_t n_total, const in
 // lgssm_init: segment offsets, the block prefixes of the collective schemes
 // (bstart, estart: n_filters + 1 each), the move's count of workgroups and its
 // function tables.
-constexpr size_t kFilterTableBytes = 6144;
+constexpr size_t kFilterTableBytes = 7168;
 struct FilterState {
   int64_t* offsets;
   uint32_t *done, *bstart, *estart;
