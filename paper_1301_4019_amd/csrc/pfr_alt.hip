@@ -69,9 +69,7 @@ __device__ __forceinline__ void metropolis_accept(const MGroup& g, uint32_t& k, 
 // A workgroup takes the particles [p0, p1) of the global array (chunk per
 // workgroup) and walks the segments that overlap them; a segment of at most
 // CAP weights is first copied into LDS, so that every random weight load of
-// its chains is an LDS read.  Longer segments load from global memory, with
-// the gathers of the next group of steps in flight while the current group
-// is decided.  The chains do not depend on the launch shape.
+// its chains is an LDS read.  The chains do not depend on the launch shape.
 // Four consecutive weights; a segment starts anywhere, so the wide access is
 // aligned to one weight only.
 template <typename T>
@@ -565,6 +563,42 @@ __device__ __forceinline__ int64_t cost_start(const uint64_t* __restrict__ cost,
   return offsets[f] + (int64_t)(i < n ? i : n);
 }
 
+// Chains of one vector that gather from global memory (chunk particles per
+// workgroup), the gathers of the next group of steps in flight while the
+// current group is decided.  Bound by the gathers' latency in short vectors and
+// their rate in long ones; without the batches' segments, queue and cost cuts
+// it keeps eight waves per SIMD (2^18 binary32 weights, 1 / 8 steps: 7.4 / 17.4
+// us, as a case of the batch kernel 9.1 / 18.7).
+template <typename T>
+__global__ __launch_bounds__(256) void k_metropolis_global(const T* __restrict__ w, int64_t n_total,
+                                                           int32_t B,
+                                                           const int32_t* __restrict__ B_dev,
+                                                           Key key, uint32_t offset, uint32_t filt,
+                                                           int32_t* __restrict__ a,
+                                                           int64_t chunk) {
+  offset = counter_offset(key, offset);
+  const int64_t p0 = (int64_t)blockIdx.x * chunk;
+  const int64_t p1 = p0 + chunk < n_total ? p0 + chunk : n_total;
+  const uint32_t n = (uint32_t)n_total;
+  const int32_t steps = B_dev ? B_dev[0] : B;
+  const int32_t groups = (steps + 3) / 4;
+  for (int64_t g = p0 + threadIdx.x; g < p1; g += 256) {
+    const uint32_t i = (uint32_t)g;
+    uint32_t k = i;
+    double wk = (double)w[i];
+    const PhiloxLane pl = philox_lane(key, i, filt, offset);
+    MGroup ga, gb;
+    if (groups > 0) metropolis_fetch(w, key, i, pl, filt, offset, n, steps, 0, ga);
+    for (int32_t m = 0; m < groups; m += 2) {
+      if (m + 1 < groups) metropolis_fetch(w, key, i, pl, filt, offset, n, steps, m + 1, gb);
+      metropolis_accept<T>(ga, k, wk);
+      if (m + 2 < groups) metropolis_fetch(w, key, i, pl, filt, offset, n, steps, m + 2, ga);
+      if (m + 1 < groups) metropolis_accept<T>(gb, k, wk);
+    }
+    a[g] = (int32_t)k;
+  }
+}
+
 template <typename T, int CAP, int THREADS>
 __global__ __launch_bounds__(THREADS) void k_metropolis_staged(
     const T* __restrict__ w, int64_t n_total, const int64_t* __restrict__ offsets,
@@ -573,7 +607,7 @@ __global__ __launch_bounds__(THREADS) void k_metropolis_staged(
     const uint64_t* __restrict__ cost, ChunkQueue queue) {
   // 128 KB of weights, or 65536 codes of a segment longer than that
   constexpr bool kCoded = CAP * sizeof(T) == 2 * kCodes;
-  __shared__ __align__(16) T sw[CAP > 0 ? CAP : 1];
+  __shared__ __align__(16) T sw[CAP];
   offset = counter_offset(key, offset);
   __shared__ uint32_t s_chunk, s_next;
   uint32_t served = 0;
@@ -604,7 +638,7 @@ __global__ __launch_bounds__(THREADS) void k_metropolis_staged(
       const uint32_t n = (uint32_t)(end - base);
       const int32_t steps = B_dev ? B_dev[f] : B;
       const uint32_t filt = filter_base + f;
-      if (CAP > 0 && n <= (uint32_t)CAP) {
+      if (n <= (uint32_t)CAP) {
         __syncthreads();  // the previous segment's chains are done with sw
         if (threadIdx.x == 0) s_next = 0;
         stage_weights(w + base, n, sw);
@@ -645,30 +679,10 @@ __global__ __launch_bounds__(THREADS) void k_metropolis_staged(
             metropolis_lockstep<T, 1, kWave>(w + base, wv, n, steps, key, filt, offset, tab,
                                              i0 + k + lane_id(), i1, a + base);
         }
-      } else if (CAP > 0) {  // a longer segment in a staged launch: plain chains
+      } else {  // a longer segment in a staged launch: plain chains
         for (int64_t g = g0 + threadIdx.x; g < q1; g += THREADS)
           a[g] = (int32_t)metropolis_chain(w + base, key, (uint32_t)(g - base), filt, offset, n,
                                            steps);
-      } else {
-        for (int64_t g = g0 + threadIdx.x; g < q1; g += THREADS) {
-          const uint32_t i = (uint32_t)(g - base);
-          const T* __restrict__ ws = w + base;
-          uint32_t k = i;
-          double wk = (double)ws[i];
-          const int32_t groups = (steps + 3) / 4;
-          const PhiloxLane pl = philox_lane(key, i, filt, offset);
-          MGroup ga, gb;
-          if (groups > 0) metropolis_fetch(ws, key, i, pl, filt, offset, n, steps, 0, ga);
-          for (int32_t m = 0; m < groups; m += 2) {
-            if (m + 1 < groups)
-              metropolis_fetch(ws, key, i, pl, filt, offset, n, steps, m + 1, gb);
-            metropolis_accept<T>(ga, k, wk);
-            if (m + 2 < groups)
-              metropolis_fetch(ws, key, i, pl, filt, offset, n, steps, m + 2, ga);
-            if (m + 1 < groups) metropolis_accept<T>(gb, k, wk);
-          }
-          a[g] = (int32_t)k;
-        }
       }
       g0 = q1;
     }
@@ -999,9 +1013,8 @@ hipError_t launch_metropolis_t(const void* wv, int64_t n_total, const int64_t* o
   auto global_launch = [&]() {
     const int64_t chunk = tuning().metropolis_chunk;
     const unsigned grid = (unsigned)((n_total + chunk - 1) / chunk);
-    hipLaunchKernelGGL((k_metropolis_staged<T, 0, 256>), dim3(grid), dim3(256), 0, stream, w,
-                       n_total, offsets, n_filters, B, B_dev, key, offset, filter_base, a, chunk,
-                       uniform, once(grid));
+    hipLaunchKernelGGL(k_metropolis_global<T>, dim3(grid), dim3(256), 0, stream, w, n_total, B,
+                       B_dev, key, offset, filter_base, a, chunk);
     return hipGetLastError();
   };
   if (cap == 0) {
