@@ -488,14 +488,13 @@ constexpr uint32_t kHeadStride = 32;
 constexpr size_t kQueueBytes = 8 * kHeadStride * sizeof(uint32_t);
 constexpr uint32_t kQueueGrid = 512;  // two per CU, where their LDS fits twice
 struct ChunkQueue {
-  uint32_t* heads;  // null: chunk blockIdx.x only
+  uint32_t* heads;
   uint32_t chunks;
 };
 // The next chunk, the same on every thread, or at least q.chunks at the end.
 // served: heads of the workgroup that are used up, 0 before the first call.
 __device__ __forceinline__ uint32_t next_chunk(const ChunkQueue& q, uint32_t& served,
                                                uint32_t* slot) {
-  if (!q.heads) return served++ == 0 ? blockIdx.x : 0xFFFFFFFFu;
   __syncthreads();  // the last chunk's number has been read, and its LDS
   if (threadIdx.x == 0) {
     uint32_t t = 0xFFFFFFFFu;
@@ -599,8 +598,13 @@ __global__ __launch_bounds__(256) void k_metropolis_global(const T* __restrict__
   }
 }
 
-template <typename T, int CAP, int THREADS>
-__global__ __launch_bounds__(THREADS) void k_metropolis_staged(
+// QUEUED: a batch cut by cost, chunks from the queue; else chunk blockIdx.x.
+// Where the LDS holds two workgroups of 1024 threads, the registers have to as
+// well: eight waves per SIMD.  With the queue's scalars in every form it was
+// seven, and one workgroup (4096 segments of 256, 16 / 100 steps: 109 / 513 us,
+// with two 73 / 329).
+template <typename T, int CAP, int THREADS, bool QUEUED>
+__global__ __launch_bounds__(THREADS, CAP * sizeof(T) <= 65536 ? 8 : 1) void k_metropolis_staged(
     const T* __restrict__ w, int64_t n_total, const int64_t* __restrict__ offsets,
     uint32_t n_filters, int32_t B, const int32_t* __restrict__ B_dev, Key key, uint32_t offset,
     uint32_t filter_base, int32_t* __restrict__ a, int64_t chunk,
@@ -613,23 +617,24 @@ __global__ __launch_bounds__(THREADS) void k_metropolis_staged(
   uint32_t served = 0;
   // particles of the segment part that are left go to the waves as they get
   // free, 64 chains (or 128) at a time: the first index of the wave's share, at
-  // least the part's length at the end.  (Workgroups of 256 threads have one
-  // chain a lane, and nothing to hand out.)
+  // least the part's length at the end.  (Workgroups of 256 threads, and parts of
+  // at most a chain per thread, have nothing to hand out: the shares in order
+  // keep short segments' waves even over the SIMDs.)
   constexpr bool kTakes = THREADS > 256;
   auto take = [&](uint32_t chains) -> uint32_t {
     uint32_t old = 0;
     if (lane_id() == 0) old = atomicAdd(&s_next, chains);
     return uniform_u32(old);
   };
-  for (uint32_t b; (b = next_chunk(queue, served, &s_chunk)) < queue.chunks;) {
+  for (uint32_t b = blockIdx.x;;) {
+    if (QUEUED && (b = next_chunk(queue, served, &s_chunk)) >= queue.chunks) break;
     const int64_t t = offsets ? xcd_chunk(chunk, b, queue.chunks) : (int64_t)b;
     int64_t p0 = t * chunk, p1 = p0 + chunk < n_total ? p0 + chunk : n_total;
-    if (cost) {
+    if (QUEUED) {
       p0 = cost_start(cost, offsets, n_filters, n_total, (uint32_t)t, queue.chunks, CAP);
       p1 = cost_start(cost, offsets, n_filters, n_total, (uint32_t)t + 1, queue.chunks, CAP);
-      if (p0 >= p1) continue;
     }
-    uint32_t f = offsets ? wave_find_segment(offsets, n_filters, p0) : 0u;
+    uint32_t f = offsets && p0 < p1 ? wave_find_segment(offsets, n_filters, p0) : 0u;
     for (int64_t g0 = p0; g0 < p1; ++f) {
       const int64_t base = offsets ? offsets[f] : 0;
       const int64_t end = offsets ? offsets[f + 1] : n_total;
@@ -643,17 +648,13 @@ __global__ __launch_bounds__(THREADS) void k_metropolis_staged(
         if (threadIdx.x == 0) s_next = 0;
         stage_weights(w + base, n, sw);
         __syncthreads();
-        if (!kTakes) {
-          for (int64_t g = g0 + threadIdx.x; g < q1; g += THREADS)
-            a[g] = (int32_t)metropolis_chain(sw, key, (uint32_t)(g - base), filt, offset, n, steps);
-        } else {
-          const uint32_t len = (uint32_t)(q1 - g0), i0 = (uint32_t)(g0 - base);
-          for (uint32_t k; (k = take(kWave)) < len;) {
-            k += lane_id();
-            if (k < len)
-              a[g0 + k] = (int32_t)metropolis_chain(sw, key, i0 + k, filt, offset, n, steps);
-          }
-        }
+        const uint32_t len = (uint32_t)(q1 - g0), i0 = (uint32_t)(g0 - base);
+        const bool shares = kTakes && len > (uint32_t)THREADS;
+        for (uint32_t k = shares ? take(kWave) + lane_id() : threadIdx.x;
+             shares ? uniform_u32(k) < len : k < len;
+             k = shares ? take(kWave) + lane_id() : k + THREADS)
+          if (k < len)
+            a[g0 + k] = (int32_t)metropolis_chain(sw, key, i0 + k, filt, offset, n, steps);
       } else if (kCoded && n <= kCodes << kCodesMaxShift) {
         uint16_t* const code = reinterpret_cast<uint16_t*>(sw);
         __syncthreads();
@@ -686,6 +687,7 @@ __global__ __launch_bounds__(THREADS) void k_metropolis_staged(
       }
       g0 = q1;
     }
+    if (!QUEUED) break;
   }
 }
 
@@ -1027,7 +1029,7 @@ hipError_t launch_metropolis_t(const void* wv, int64_t n_total, const int64_t* o
     if (one && (n_total <= 128 * per_kb || (n_total <= (int64_t)kCodes && (B_dev || B >= 12)))) {
       const int64_t chunk1 = 256;
       const unsigned grid = (unsigned)((n_total + chunk1 - 1) / chunk1);
-      hipLaunchKernelGGL((k_metropolis_staged<T, 128 * per_kb, 256>), dim3(grid), dim3(256), 0,
+      hipLaunchKernelGGL((k_metropolis_staged<T, 128 * per_kb, 256, false>), dim3(grid), dim3(256), 0,
                          stream, w, n_total, offsets, n_filters, B, B_dev, key, offset,
                          filter_base, a, chunk1, uniform, once(grid));
       return hipGetLastError();
@@ -1042,11 +1044,11 @@ hipError_t launch_metropolis_t(const void* wv, int64_t n_total, const int64_t* o
     const int64_t chunk1 = 256;
     const dim3 grid1((unsigned)((n_total + chunk1 - 1) / chunk1));
     if (cap == 16 * per_kb)
-      hipLaunchKernelGGL((k_metropolis_staged<T, 16 * per_kb, 256>), grid1, dim3(256), 0, stream,
+      hipLaunchKernelGGL((k_metropolis_staged<T, 16 * per_kb, 256, false>), grid1, dim3(256), 0, stream,
                          w, n_total, offsets, n_filters, B, B_dev, key, offset, filter_base, a,
                          chunk1, uniform, once(grid1.x));
     else
-      hipLaunchKernelGGL((k_metropolis_staged<T, 64 * per_kb, 256>), grid1, dim3(256), 0, stream,
+      hipLaunchKernelGGL((k_metropolis_staged<T, 64 * per_kb, 256, false>), grid1, dim3(256), 0, stream,
                          w, n_total, offsets, n_filters, B, B_dev, key, offset, filter_base, a,
                          chunk1, uniform, once(grid1.x));
     return hipGetLastError();
@@ -1056,15 +1058,15 @@ hipError_t launch_metropolis_t(const void* wv, int64_t n_total, const int64_t* o
     // one short vector, so that its long chains spread over the chip
     const dim3 grid1((unsigned)((n_total + 255) / 256));
     if (cap == 16 * per_kb)
-      hipLaunchKernelGGL((k_metropolis_staged<T, 16 * per_kb, 256>), grid1, dim3(256), 0, stream,
+      hipLaunchKernelGGL((k_metropolis_staged<T, 16 * per_kb, 256, false>), grid1, dim3(256), 0, stream,
                          w, n_total, offsets, n_filters, B, B_dev, key, offset, filter_base, a,
                          (int64_t)256, uniform, once(grid1.x));
     else if (cap == 64 * per_kb)
-      hipLaunchKernelGGL((k_metropolis_staged<T, 64 * per_kb, 256>), grid1, dim3(256), 0, stream,
+      hipLaunchKernelGGL((k_metropolis_staged<T, 64 * per_kb, 256, false>), grid1, dim3(256), 0, stream,
                          w, n_total, offsets, n_filters, B, B_dev, key, offset, filter_base, a,
                          (int64_t)256, uniform, once(grid1.x));
     else
-      hipLaunchKernelGGL((k_metropolis_staged<T, 128 * per_kb, 256>), grid1, dim3(256), 0, stream,
+      hipLaunchKernelGGL((k_metropolis_staged<T, 128 * per_kb, 256, false>), grid1, dim3(256), 0, stream,
                          w, n_total, offsets, n_filters, B, B_dev, key, offset, filter_base, a,
                          (int64_t)256, uniform, once(grid1.x));
     return hipGetLastError();
@@ -1088,19 +1090,20 @@ hipError_t launch_metropolis_t(const void* wv, int64_t n_total, const int64_t* o
                        prefix, queue.heads);
     cost = prefix;
   }
-  const dim3 grid(queue.heads && chunks > kQueueGrid ? kQueueGrid : chunks);
+  const dim3 grid(queued && chunks > kQueueGrid ? kQueueGrid : chunks);
+  auto launch = [&](auto plain, auto from_queue) {
+    hipLaunchKernelGGL(queued ? from_queue : plain, grid, dim3(1024), 0, stream, w, n_total, offsets,
+                       n_filters, B, B_dev, key, offset, filter_base, a, chunk, cost, queue);
+  };
   if (cap == 16 * per_kb)
-    hipLaunchKernelGGL((k_metropolis_staged<T, 16 * per_kb, 1024>), grid, dim3(1024), 0, stream, w,
-                       n_total, offsets, n_filters, B, B_dev, key, offset, filter_base, a, chunk,
-                       cost, queue);
+    launch(k_metropolis_staged<T, 16 * per_kb, 1024, false>,
+           k_metropolis_staged<T, 16 * per_kb, 1024, true>);
   else if (cap == 64 * per_kb)
-    hipLaunchKernelGGL((k_metropolis_staged<T, 64 * per_kb, 1024>), grid, dim3(1024), 0, stream, w,
-                       n_total, offsets, n_filters, B, B_dev, key, offset, filter_base, a, chunk,
-                       cost, queue);
+    launch(k_metropolis_staged<T, 64 * per_kb, 1024, false>,
+           k_metropolis_staged<T, 64 * per_kb, 1024, true>);
   else
-    hipLaunchKernelGGL((k_metropolis_staged<T, 128 * per_kb, 1024>), grid, dim3(1024), 0, stream,
-                       w, n_total, offsets, n_filters, B, B_dev, key, offset, filter_base, a,
-                       chunk, cost, queue);
+    launch(k_metropolis_staged<T, 128 * per_kb, 1024, false>,
+           k_metropolis_staged<T, 128 * per_kb, 1024, true>);
   return hipGetLastError();
 }
 
