@@ -224,8 +224,8 @@ PFR_API int resample_systematic(const void* w, pfr_dtype dtype, const pfr_segmen
  * workspace (may be NULL, ws_bytes 0) holds, for a single
  * long vector of less than 2^31 bytes of weights, a table of power-of-two
  * weight bounds per bucket of particles that lets most rejected proposals
- * skip the load of w_j, and for a batch with B_dev the running cost of its
- * segments, by which the work is split, and the queue it is handed out from;
+ * skip the load of w_j, and for a batch of up to 4096 segments with B_dev the
+ * running cost of its segments, by which the work is split, and the queue it is handed out from;
  * it changes the speed, never the result. */
 PFR_API int resample_metropolis(const void* w, pfr_dtype dtype, const pfr_segments* seg, int32_t B,
                         const int32_t* B_dev, pfr_rng rng, int32_t* ancestors, void* ws,

@@ -481,29 +481,47 @@ __device__ __forceinline__ int64_t xcd_chunk(int64_t chunk, uint32_t b, uint32_t
 // Eight heads, one per XCD, in lines of their own; a workgroup serves the
 // chunks of its XCD's head (t % 8, so that xcd_chunk keeps its runs together)
 // and then those of the others.  Every workgroup ends when all eight are used
-// up.  4096 ragged vectors of 256 .. 65536, B = 4 .. 354, with the
+// up.  Up to kQueueFilters segments: with more of them the shares even out by
+// themselves, and the cost prefix is longer (16384 segments of 64 .. 512, fewer
+// than 8 / 60 / 200 steps: without 106 / 356 / 985 us, with 121 / 363 / 939;
+// 8192 of 512 .. 2048 106 / 418 / 1220 and 124 / 461 / 1397; 4096 of 128 .. 4096
+// 72 / 268 / 806 and 72 / 248 / 660).  4096 ragged vectors of 256 .. 65536, B = 4 .. 354, with the
 // permutation: 4.25 -> 3.94 ms; with the waves of a workgroup taking 64 chains
 // at a time instead of a fixed share, 3.70; with chunks twice as long, 3.47.
 constexpr uint32_t kHeadStride = 32;
 constexpr size_t kQueueBytes = 8 * kHeadStride * sizeof(uint32_t);
 constexpr uint32_t kQueueGrid = 512;  // two per CU, where their LDS fits twice
+constexpr uint32_t kQueueFilters = 4096;
 struct ChunkQueue {
   uint32_t* heads;
   uint32_t chunks;
 };
 // The next chunk, the same on every thread, or at least q.chunks at the end.
-// served: heads of the workgroup that are used up, 0 before the first call.
-__device__ __forceinline__ uint32_t next_chunk(const ChunkQueue& q, uint32_t& served,
-                                               uint32_t* slot) {
+// The first is the workgroup's own number (gridDim.x is at most q.chunks, and a
+// multiple of 8 when it is less); the heads count those beyond.  Eight lanes look
+// at all heads at once, so that the end, when nothing is left, costs one load
+// and not an atomic per head (64 segments of 4096, which have a workgroup per
+// chunk and no queue to look at: 21 -> 16 us).
+__device__ __forceinline__ uint32_t next_chunk(const ChunkQueue& q, bool first, uint32_t* slot) {
+  if (first) return blockIdx.x;
+  if (gridDim.x >= q.chunks) return q.chunks;
   __syncthreads();  // the last chunk's number has been read, and its LDS
-  if (threadIdx.x == 0) {
-    uint32_t t = 0xFFFFFFFFu;
-    for (; served < 8; ++served) {
-      const uint32_t x = (blockIdx.x + served) & 7u;
-      t = atomicAdd(q.heads + x * kHeadStride, 1u) * 8u + x;
+  if (threadIdx.x < kWave) {
+    const uint32_t lane = lane_id(), x = (blockIdx.x + lane) & 7u;  // its own XCD's first
+    uint32_t t = q.chunks;
+    while (true) {
+      uint32_t c = 0;
+      if (lane < 8)
+        c = __hip_atomic_load(q.heads + x * kHeadStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const uint64_t some = ballot(lane < 8 && gridDim.x + c * 8u + x < q.chunks);
+      if (some == 0) break;  // (heads only grow: nothing will come)
+      const uint32_t pick = (blockIdx.x + (uint32_t)__ffsll((long long)some) - 1u) & 7u;
+      if (lane == 0) c = atomicAdd(q.heads + pick * kHeadStride, 1u);
+      t = gridDim.x + uniform_u32(c) * 8u + pick;
       if (t < q.chunks) break;
+      t = q.chunks;
     }
-    *slot = t;
+    if (lane == 0) *slot = t;
   }
   __syncthreads();
   return uniform_u32(*slot);
@@ -515,29 +533,44 @@ __device__ __forceinline__ uint32_t next_chunk(const ChunkQueue& q, uint32_t& se
 // rounded to whole passes of the workgroup.  Equal chunks leave the chip
 // waiting for the last ones of B = 354 (4096 ragged vectors
 // of 256 .. 65536 particles, B = 4 .. 354: 4.94 against 3.87 ms).
+// One workgroup, four segments per thread and round; bound by the latency of
+// its rounds (4096 segments: one per thread and round 10 us, four 4).
 __global__ __launch_bounds__(1024) void k_cost_prefix(const int64_t* __restrict__ offsets,
                                                       uint32_t n_filters,
                                                       const int32_t* __restrict__ B,
                                                       uint64_t* __restrict__ cost,
                                                       uint32_t* __restrict__ heads) {
+  constexpr int kF = 4;
   if (threadIdx.x < 8) heads[threadIdx.x * kHeadStride] = 0;
   __shared__ uint64_t s_w[1024 / kWave];
   const uint32_t wave = threadIdx.x / kWave, lane = lane_id();
   uint64_t carry = 0;
-  for (uint32_t f0 = 0; f0 < n_filters; f0 += 1024) {
-    const uint32_t f = f0 + threadIdx.x;
-    const uint64_t x = f < n_filters ? (uint64_t)(offsets[f + 1] - offsets[f]) *
-                                           (uint64_t)(max(B[f], 0) + 2)
-                                     : 0ull;
-    const uint64_t incl = wave_incl_add_u64(x);
+  for (uint32_t f0 = kF * threadIdx.x; f0 - kF * threadIdx.x < n_filters; f0 += kF * 1024) {
+    int64_t o[kF + 1];
+    int32_t b[kF];
+#pragma unroll
+    for (int k = 0; k <= kF; ++k) o[k] = offsets[min(f0 + k, n_filters)];
+#pragma unroll
+    for (int k = 0; k < kF; ++k) b[k] = B[min(f0 + k, n_filters - 1)];
+    uint64_t x[kF], sum = 0;
+#pragma unroll
+    for (int k = 0; k < kF; ++k) {  // (no particles past the end)
+      x[k] = sum;
+      sum += (uint64_t)(o[k + 1] - o[k]) * ((uint64_t)max(b[k], 0) + 2);
+    }
+    const uint64_t incl = wave_incl_add_u64(sum);
     if (lane == kWave - 1) s_w[wave] = incl;
     __syncthreads();
-    uint64_t before = carry + incl - x;
+    uint64_t before = carry + incl - sum;
+#pragma unroll
     for (uint32_t w2 = 0; w2 < 1024 / kWave; ++w2) {
-      before += w2 < wave ? s_w[w2] : 0ull;
-      carry += s_w[w2];
+      const uint64_t t = s_w[w2];
+      before += w2 < wave ? t : 0ull;
+      carry += t;
     }
-    if (f < n_filters) cost[f] = before;
+#pragma unroll
+    for (int k = 0; k < kF; ++k)
+      if (f0 + k < n_filters) cost[f0 + k] = before + x[k];
     __syncthreads();
   }
   if (threadIdx.x == 0) cost[n_filters] = carry;
@@ -614,7 +647,6 @@ __global__ __launch_bounds__(THREADS, CAP * sizeof(T) <= 65536 ? 8 : 1) void k_m
   __shared__ __align__(16) T sw[CAP];
   offset = counter_offset(key, offset);
   __shared__ uint32_t s_chunk, s_next;
-  uint32_t served = 0;
   // particles of the segment part that are left go to the waves as they get
   // free, 64 chains (or 128) at a time: the first index of the wave's share, at
   // least the part's length at the end.  (Workgroups of 256 threads, and parts of
@@ -626,8 +658,9 @@ __global__ __launch_bounds__(THREADS, CAP * sizeof(T) <= 65536 ? 8 : 1) void k_m
     if (lane_id() == 0) old = atomicAdd(&s_next, chains);
     return uniform_u32(old);
   };
-  for (uint32_t b = blockIdx.x;;) {
-    if (QUEUED && (b = next_chunk(queue, served, &s_chunk)) >= queue.chunks) break;
+  for (bool first = true;; first = false) {
+    const uint32_t b = QUEUED ? next_chunk(queue, first, &s_chunk) : blockIdx.x;
+    if (b >= queue.chunks) break;
     const int64_t t = offsets ? xcd_chunk(chunk, b, queue.chunks) : (int64_t)b;
     int64_t p0 = t * chunk, p1 = p0 + chunk < n_total ? p0 + chunk : n_total;
     if (QUEUED) {
@@ -1073,7 +1106,7 @@ hipError_t launch_metropolis_t(const void* wv, int64_t n_total, const int64_t* o
   }
   // the tuned chunk, twice that from the queue, less where it would leave CUs
   // idle (two workgroups each)
-  const bool queued = ws && B_dev && n_filters <= 16384;
+  const bool queued = ws && B_dev && n_filters <= kQueueFilters;
   const int64_t tuned = (int64_t)tuning().batch_metropolis_chunk * (queued ? 2 : 1);
   int64_t chunk = (n_total / 512 + 1023) / 1024 * 1024;
   if (chunk > tuned) chunk = tuned;
@@ -1150,6 +1183,7 @@ size_t alt_workspace_bytes(bool f64, int64_t n_total, uint32_t n_filters, int64_
 // Metropolis: the same, and for a batch the cost prefix of its segments.
 size_t metropolis_workspace_bytes(bool f64, int64_t n_total, uint32_t n_filters,
                                   int64_t max_len) {
+  if (n_filters > kQueueFilters) return 0;
   if (n_filters > 1)  // the chunk queue, the cost prefix
     return kQueueBytes + ((((size_t)n_filters + 1) * sizeof(uint64_t) + 255) & ~(size_t)255);
   return alt_workspace_bytes(f64, n_total, n_filters, max_len);
