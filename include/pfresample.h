@@ -220,7 +220,8 @@ PFR_API int resample_systematic(const void* w, pfr_dtype dtype, const pfr_segmen
  * No collective operation: the chains are independent, so the output does
  * not depend on the launch shape.  Segments of up to 16K (float32) or 8K
  * (float64) weights, and with pfr_segments.max_len set up to 32K / 16K, are
- * staged in LDS, and of segments up to 256K 16-bit bounds of the weights.  The
+ * staged in LDS, and of segments up to 256K in a large batch, where the steps
+ * pay for it, 16-bit bounds of the weights.  The
  * workspace (may be NULL, ws_bytes 0) holds, for a single
  * long vector of less than 2^31 bytes of weights, a table of power-of-two
  * weight bounds per bucket of particles that lets most rejected proposals

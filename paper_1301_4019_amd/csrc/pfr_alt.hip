@@ -6,6 +6,7 @@
 // the Philox counter, never on which lane or wave did the work, so every
 // launch shape gives the same bits.
 #include "pfr_kernels.h"
+#include <algorithm>
 #include <cstring>
 
 namespace pfr {
@@ -291,9 +292,22 @@ __device__ BoundTable load_bound_table(const uint32_t* __restrict__ nib_g,
 // the exact test would not take (their code is the largest, or the comparison
 // fails), so the result is the plain chain's for any input.  Measured on 256
 // segments of 60000 binary32 weights against plain chains, whose gathers miss
-// the L2: B = 354 133 -> 735 G steps/s, B = 16 130 -> 509.
+// the L2: B = 354 294 -> 624 G steps/s, B = 16 281 -> 534.
 constexpr uint32_t kCodes = 65536;  // 128 KB
 constexpr uint32_t kCodesMaxShift = 2;
+// Whether a workgroup's part of a segment pays for the segment's codes: its
+// particles times the steps (or trials) of each must be a share of the n weights
+// to be read.  That share is smaller where the chip is full (chunks of 5120 up:
+// the plain gathers wait for one another, and the codes are staged many times
+// over one another's chains) than where a workgroup runs alone; in batches small
+// enough for one chain per thread the codes never paid.  Binary32 weights, plain /
+// codes: 256 segments of 60000, 2 / 4 steps 144 / 131, 247 / 178 us; 64 of 262143,
+// 4 / 12 / 16 steps 311 / 514, 807 / 882, 1010 / 1082; 6 of 100000, 16 / 30 / 60
+// steps 43 / 49, 77 / 77, 147 / 135; 4 of 60000, 120 steps 109 / 139.
+__device__ __forceinline__ bool codes_pay(int64_t chunk, int64_t part, uint32_t n, double each) {
+  const double work = (double)part * each;
+  return chunk > 1024 && work >= (chunk >= 5120 ? 0.4 : 1.0) * (double)n;
+}
 __device__ __forceinline__ uint32_t bound16(float v) {
   return (uint32_t)(((uint64_t)__float_as_uint(v) + 0xFFFFu) >> 16);  // -NaN: 0x10000, cut to 0xFFFF
 }
@@ -337,11 +351,21 @@ __device__ __forceinline__ CodeTable<T> stage_codes(const T* __restrict__ w, uin
       const uint32_t j = (n & ~3u) + threadIdx.x;
       code[j] = (uint16_t)enc(w[j]);
     }
-  } else {
-    for (uint32_t b = threadIdx.x; b <= (n - 1) >> t.shift; b += blockDim.x) {
-      uint32_t c = 0;
-      for (uint32_t j = b << t.shift; j < min((b + 1) << t.shift, n); ++j) c = max(c, enc(w[j]));
-      code[b] = (uint16_t)c;
+  } else {  // two or four weights a code
+    const bool four = t.shift == 2;
+    auto put = [&](uint32_t q, uint32_t a, uint32_t b) {
+      if (four) code[q] = (uint16_t)max(a, b);
+      else reinterpret_cast<uint32_t*>(code)[q] = a | (b << 16);
+    };
+#pragma unroll 4
+    for (uint32_t q = threadIdx.x; q < n / 4; q += blockDim.x) {
+      const Weights4<T> x = load_weights4(w + 4 * q);
+      put(q, max(enc(x.v[0]), enc(x.v[1])), max(enc(x.v[2]), enc(x.v[3])));
+    }
+    if (threadIdx.x == 0 && (n & 3u)) {
+      uint32_t c[4] = {0, 0, 0, 0};
+      for (uint32_t k = 0; k < (n & 3u); ++k) c[k] = enc(w[(n & ~3u) + k]);
+      put(n / 4, max(c[0], c[1]), max(c[2], c[3]));
     }
   }
   return t;
@@ -490,7 +514,6 @@ __device__ __forceinline__ int64_t xcd_chunk(int64_t chunk, uint32_t b, uint32_t
 // at a time instead of a fixed share, 3.70; with chunks twice as long, 3.47.
 constexpr uint32_t kHeadStride = 32;
 constexpr size_t kQueueBytes = 8 * kHeadStride * sizeof(uint32_t);
-constexpr uint32_t kQueueGrid = 512;  // two per CU, where their LDS fits twice
 constexpr uint32_t kQueueFilters = 4096;
 struct ChunkQueue {
   uint32_t* heads;
@@ -643,7 +666,7 @@ __global__ __launch_bounds__(THREADS, CAP * sizeof(T) <= 65536 ? 8 : 1) void k_m
     uint32_t filter_base, int32_t* __restrict__ a, int64_t chunk,
     const uint64_t* __restrict__ cost, ChunkQueue queue) {
   // 128 KB of weights, or 65536 codes of a segment longer than that
-  constexpr bool kCoded = CAP * sizeof(T) == 2 * kCodes;
+  constexpr bool kCoded = THREADS == 1024 && CAP * sizeof(T) == 2 * kCodes;
   __shared__ __align__(16) T sw[CAP];
   offset = counter_offset(key, offset);
   __shared__ uint32_t s_chunk, s_next;
@@ -688,7 +711,8 @@ __global__ __launch_bounds__(THREADS, CAP * sizeof(T) <= 65536 ? 8 : 1) void k_m
              k = shares ? take(kWave) + lane_id() : k + THREADS)
           if (k < len)
             a[g0 + k] = (int32_t)metropolis_chain(sw, key, i0 + k, filt, offset, n, steps);
-      } else if (kCoded && n <= kCodes << kCodesMaxShift) {
+      } else if (kCoded && n <= kCodes << kCodesMaxShift &&
+                 codes_pay(chunk, q1 - g0, n, (double)steps)) {
         uint16_t* const code = reinterpret_cast<uint16_t*>(sw);
         __syncthreads();
         if (threadIdx.x == 0) s_next = 0;
@@ -696,13 +720,8 @@ __global__ __launch_bounds__(THREADS, CAP * sizeof(T) <= 65536 ? 8 : 1) void k_m
         __syncthreads();
         const __amdgpu_buffer_rsrc_t wv = buffer_view(w + base, n * (uint32_t)sizeof(T));
         const uint32_t i0 = (uint32_t)(g0 - base), i1 = (uint32_t)(q1 - base);
-        if (!kTakes) {
-          for (uint32_t i = i0 + threadIdx.x; i < i1; i += THREADS)
-            metropolis_lockstep<T, 1, kWave>(w + base, wv, n, steps, key, filt, offset, tab, i,
-                                             i1, a + base);
-        }
         // two chains a lane, or one for the last
-        for (uint32_t k, taken = 0; kTakes && taken < i1 - i0;) {
+        for (uint32_t k, taken = 0; taken < i1 - i0;) {
           const bool two = i1 - i0 - taken > 2 * kWave;
           k = take(two ? 2 * kWave : kWave);
           taken = k + (two ? 2 * kWave : kWave);
@@ -922,12 +941,26 @@ __device__ void rejection_wave_range(const T* ws, __amdgpu_buffer_rsrc_t wv, uin
   }
 }
 
+// Trials per particle to expect of the particles [i0, i1) of a segment, from
+// the first trials of as many as the workgroup has threads.
+template <typename T>
+__device__ __forceinline__ double mean_trials(const T* __restrict__ w, uint32_t i0, uint32_t i1,
+                                              uint32_t filt, double wmax, Key key,
+                                              uint32_t offset) {
+  const uint32_t i = i0 + threadIdx.x;
+  const bool in = i < i1;
+  const uint4 x = draw(key, i, DOM_TRIAL, 0, filt, offset);
+  const int won = __syncthreads_count(in && u_accept(x.z) * wmax <= (double)w[in ? i : i0]);
+  return (double)min(i1 - i0, blockDim.x) / (double)max(won, 1);
+}
+
 // A workgroup takes the particles [p0, p1) and walks the segments that overlap
 // them; the waves hand out each segment part among themselves (an LDS
 // counter reset between the part's barriers).  A segment of at most CAP
-// weights is first copied into LDS, of a longer one its bound codes (256
-// vectors of 60000 binary32 weights at 1.8 % acceptance: 9.2 ms with gathers
-// from global memory, 2.2 ms with codes).  The chunks go to the XCDs in runs
+// weights is first copied into LDS, of a longer one its bound codes where they
+// pay for it (256 vectors of 60000 binary32 weights at 1.3 % acceptance: 4.3 ms
+// with gathers from global memory, 2.1 ms with codes; at 71 %: 91 and 112 us).
+// The chunks go to the XCDs in runs
 // that share a segment (xcd_chunk).
 template <typename T, int CAP, int THREADS>
 __global__ __launch_bounds__(THREADS) void k_rejection(
@@ -935,7 +968,7 @@ __global__ __launch_bounds__(THREADS) void k_rejection(
     uint32_t n_filters, double w_max, const double* __restrict__ w_max_dev, uint32_t max_trials,
     Key key, uint32_t offset, uint32_t filter_base, int32_t* __restrict__ a,
     uint32_t* __restrict__ flags, int64_t chunk) {
-  constexpr bool kCoded = CAP * sizeof(T) == 2 * kCodes;
+  constexpr bool kCoded = THREADS == 1024 && CAP * sizeof(T) == 2 * kCodes;
   __shared__ __align__(16) T sw[CAP > 0 ? CAP : 1];
   __shared__ uint32_t queue;  // particles of the segment part handed out so far
   offset = counter_offset(key, offset);
@@ -964,7 +997,8 @@ __global__ __launch_bounds__(THREADS) void k_rejection(
       __syncthreads();
       rejection_wave_range<false>((const T*)sw, none, n, filt, wmax, i0, i1, max_trials, key,
                                   offset, af, my_flags, NoTable{}, &queue);
-    } else if (kCoded && !tiny && wmax <= 0x1p127 && n <= kCodes << kCodesMaxShift) {
+    } else if (kCoded && !tiny && wmax <= 0x1p127 && n <= kCodes << kCodesMaxShift &&
+               codes_pay(chunk, i1 - i0, n, mean_trials(wf, i0, i1, filt, wmax, key, offset))) {
       // (a product beyond binary32's range could exceed the code of an infinity)
       const CodeTable<T> tab = stage_codes(wf, n, reinterpret_cast<uint16_t*>(sw));
       __syncthreads();
@@ -1035,6 +1069,19 @@ int staged_capacity(int64_t max_len, int64_t n_total, uint32_t n_filters) {
   return (int)(128 * per_kb);
 }
 
+// Particles per workgroup of 1024 threads of a batch: as many as `most`, in
+// whole rounds of the workgroups that the chip holds at once, which are two to a
+// CU, or one with the 128 KB tier (16 segments of 40000 binary32 weights, 4
+// steps: 313 chunks, a second round for the last 57, 23 us, 209 chunks 17; 30 of
+// 150000 at 2 % acceptance: 275 chunks 272 us, 489 chunks 207).
+template <typename T>
+int64_t batch_chunk(int cap, int64_t n_total, int64_t most) {
+  const int64_t slots = cap * (int64_t)sizeof(T) > 65536 ? 256 : 512;
+  const int64_t rounds = (n_total + slots * most - 1) / (slots * most);
+  const int64_t even = (n_total + slots * rounds - 1) / (slots * rounds);
+  return std::min(most, (even + 1023) / 1024 * 1024);
+}
+
 template <typename T>
 hipError_t launch_metropolis_t(const void* wv, int64_t n_total, const int64_t* offsets,
                                uint32_t n_filters, int64_t max_len, int32_t B,
@@ -1045,29 +1092,26 @@ hipError_t launch_metropolis_t(const void* wv, int64_t n_total, const int64_t* o
   const int cap = staged_capacity<T>(max_len, n_total, n_filters);
   const uint64_t* const uniform = nullptr;
   auto once = [](unsigned grid) { return ChunkQueue{nullptr, grid}; };
-  auto global_launch = [&]() {
-    const int64_t chunk = tuning().metropolis_chunk;
+  if (cap == 0) {
+    // one vector of up to 128 KB of weights: staged as below (one workgroup per
+    // CU for the LDS); a longer one gathers from global memory, with at most the
+    // tuned number of chains per workgroup, and few enough to use every CU (60000
+    // binary32 weights, 16 / 354 steps: 2048 30 / 541 us, 256 9 / 90; as bound codes
+    // in LDS 14 / 105)
+    if (n_total <= 128 * per_kb) {
+      const int64_t chunk1 = 256;
+      const unsigned grid = (unsigned)((n_total + chunk1 - 1) / chunk1);
+      hipLaunchKernelGGL((k_metropolis_staged<T, 128 * per_kb, 256, false>), dim3(grid), dim3(256),
+                         0, stream, w, n_total, offsets, n_filters, B, B_dev, key, offset,
+                         filter_base, a, chunk1, uniform, once(grid));
+      return hipGetLastError();
+    }
+    const int64_t chunk =
+        std::min<int64_t>(tuning().metropolis_chunk, (n_total / 256 + 255) / 256 * 256);
     const unsigned grid = (unsigned)((n_total + chunk - 1) / chunk);
     hipLaunchKernelGGL(k_metropolis_global<T>, dim3(grid), dim3(256), 0, stream, w, n_total, B,
                        B_dev, key, offset, filter_base, a, chunk);
     return hipGetLastError();
-  };
-  if (cap == 0) {
-    // one vector of up to 128 KB of weights, or of up to 65536 codes: staged
-    // as below (one workgroup per CU for the LDS), otherwise chains gather
-    // from global memory.  Staging the codes pays from about a dozen steps
-    // (60000 binary32 weights, 16 / 354 steps: global 30 / 541 us, staged
-    // 14 / 105 us; at 4 steps the staging is most of the call).
-    const bool one = !offsets || n_filters <= 1;
-    if (one && (n_total <= 128 * per_kb || (n_total <= (int64_t)kCodes && (B_dev || B >= 12)))) {
-      const int64_t chunk1 = 256;
-      const unsigned grid = (unsigned)((n_total + chunk1 - 1) / chunk1);
-      hipLaunchKernelGGL((k_metropolis_staged<T, 128 * per_kb, 256, false>), dim3(grid), dim3(256), 0,
-                         stream, w, n_total, offsets, n_filters, B, B_dev, key, offset,
-                         filter_base, a, chunk1, uniform, once(grid));
-      return hipGetLastError();
-    }
-    return global_launch();
   }
   // segments longer than the LDS tier run in the same launch
   if (!offsets || n_filters <= 1) {
@@ -1105,12 +1149,13 @@ hipError_t launch_metropolis_t(const void* wv, int64_t n_total, const int64_t* o
     return hipGetLastError();
   }
   // the tuned chunk, twice that from the queue, less where it would leave CUs
-  // idle (two workgroups each)
+  // idle
   const bool queued = ws && B_dev && n_filters <= kQueueFilters;
-  const int64_t tuned = (int64_t)tuning().batch_metropolis_chunk * (queued ? 2 : 1);
-  int64_t chunk = (n_total / 512 + 1023) / 1024 * 1024;
-  if (chunk > tuned) chunk = tuned;
-  if (chunk < 1024) chunk = 1024;
+  // (from the queue twice the tuned chunk, but several to a workgroup)
+  const int64_t tuned = tuning().batch_metropolis_chunk;
+  const int64_t chunk =
+      queued ? std::min(2 * tuned, std::max<int64_t>(1024, (n_total / 512 + 1023) / 1024 * 1024))
+             : batch_chunk<T>(cap, n_total, tuned);
   // with a workspace and step counts of its own per segment: cut by cost, and
   // the chunks handed out as workgroups get free
   const unsigned chunks = (unsigned)((n_total + chunk - 1) / chunk);
@@ -1123,7 +1168,8 @@ hipError_t launch_metropolis_t(const void* wv, int64_t n_total, const int64_t* o
                        prefix, queue.heads);
     cost = prefix;
   }
-  const dim3 grid(queued && chunks > kQueueGrid ? kQueueGrid : chunks);
+  const unsigned stay = cap * sizeof(T) > 65536 ? 256 : 512;  // what the chip holds at once
+  const dim3 grid(queued && chunks > stay ? stay : chunks);
   auto launch = [&](auto plain, auto from_queue) {
     hipLaunchKernelGGL(queued ? from_queue : plain, grid, dim3(1024), 0, stream, w, n_total, offsets,
                        n_filters, B, B_dev, key, offset, filter_base, a, chunk, cost, queue);
@@ -1323,9 +1369,8 @@ hipError_t launch_rejection_t(const void* wv, int64_t n_total, const int64_t* of
   }
   // the tuned chunk, less where it would leave CUs idle (64 vectors of 4000 at
   // 1.8 % acceptance: 85 us against 818; 64 of 30000: 312 against 716)
-  int64_t chunk = (n_total / 512 + 1023) / 1024 * 1024;
-  if (chunk > (int64_t)tuning().batch_rejection_per_wave * 16)
-    chunk = (int64_t)tuning().batch_rejection_per_wave * 16;
+  const int64_t chunk =
+      batch_chunk<T>(cap, n_total, (int64_t)tuning().batch_rejection_per_wave * 16);
   const dim3 grid((unsigned)((n_total + chunk - 1) / chunk));
   if (cap == 16 * per_kb)
     hipLaunchKernelGGL((k_rejection<T, 16 * per_kb, 1024>), grid, dim3(1024), 0, stream, w,
