@@ -2261,9 +2261,11 @@ __global__ __launch_bounds__(kT) void k_seg_emit_w(
                                                    offset, as, &L[wave], seg_claim(sc, f));
 }
 
-// Multinomial emission of the segmented batch, one block per wave.
+// Multinomial emission of the segmented batch, one block per wave; three waves
+// per SIMD (168 registers; binary64 took 169 and ran two: 1024 segments of 16384
+// 313 us, with three 272).
 template <typename T>
-__global__ __launch_bounds__(kT) void k_seg_emit_mw(
+__global__ __launch_bounds__(kT, 3) void k_seg_emit_mw(
     const T* __restrict__ w, const int64_t* __restrict__ offsets, uint32_t n_filters, Key key,
     uint32_t offset, uint32_t filter_base, const uint32_t* __restrict__ bstart,
     const uint32_t* __restrict__ estart, const BlockRec* __restrict__ recs,
