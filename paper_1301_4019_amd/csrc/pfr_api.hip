@@ -175,6 +175,33 @@ bool block_parallel_batch(int scheme, const SegInfo& s) {
   return s.n_filters > 1 && !(s.max_len > 0 && s.max_len <= one_wg);
 }
 
+// Resampling alone, of a batch that one workgroup per segment can take
+// (strata schemes): false where its workgroups, which cost nearly the same
+// for any length up to the capacity of their tier, would mostly be idle and
+// the block-parallel kernels are faster.  One workgroup per segment against
+// block-parallel, us, systematic in binary32 and stratified in binary64:
+//   up to 256 segments, or small: 256 of 1..16384 16.2 / 29.9, 18.7 / 32.4
+//   full tiers: 5592 of 3000 72 / 78, 80 / 112; of 2048 (half) 92 / 79, 99 / 110
+//   equal lengths: 1280 of 5734 38.8 / 44.3, 56.6 / 57.6; 2560 68.9 / 68.5,
+//     105 / 91; 1280 of 6553 40 / 51, 59 / 66; 2560 71 / 79, 109 / 107
+//   others above 4096, a launch for each tier: 2130 of 4..16384 (4 M
+//     particles) 49.0 / 42.6, 61 / 51; 532 (1 M) 33.5 / 26.9, 31 / 28.6
+//   others up to 4096: stratified always; systematic, 4 M particles in
+//     segments of 1..2048 43.5 / 46.7, 16 M 139 / 129, but of 4..2048 (330 on
+//     average) 255 / 272 and of 1..4096 98.5 / 100 (8 M 56 / 60)
+// (Together with the permutation one launch is faster throughout.)
+bool one_workgroup_each(int scheme, const SegInfo& s) {
+  const int64_t m = s.max_len, F = s.n_filters, n = s.n_total, M = 1 << 20;
+  if (m <= std::max(1024, tuning().batch_scan_wg_max_len) || F <= 256) return true;
+  const int64_t cap = m <= 4096 ? 4096 : kOneWgMax;
+  if (3 * n >= 2 * F * cap) return true;
+  if (cap == 4096)
+    return scheme == SCHEME_STRATIFIED || n <= 700 * F || 2 * n <= 9 * M ||
+           (m * F != n && 15 * n >= 7 * F * cap);
+  if (m * F == n) return 2 * n <= (8 * m >= 3 * cap ? 18 : 15) * M;
+  return 4 * n <= 3 * M;
+}
+
 int collective(int scheme, const void* w, pfr_dtype dtype, const pfr_segments* seg,
                pfr_precision precision, pfr_rng rng, int32_t* a, void* ws, size_t ws_bytes,
                uint32_t* dev_flags, void* stream, const SegClaim& sc = SegClaim(),
@@ -196,7 +223,8 @@ int collective(int scheme, const void* w, pfr_dtype dtype, const pfr_segments* s
       return launch_result(launch_fscan_batched(scheme, (int)precision, dtype == PFR_F64, w,
                                                 s.n_total, s.offsets, s.n_filters, key,
                                                 rng.offset, rng.filter_base, a, dev_flags, st));
-    if (ws && block_parallel_batch(scheme, s)) {
+    const bool blocks = block_parallel_batch(scheme, s);
+    if (ws && blocks) {
       const SegLayout SL = seg_layout(s.n_total, s.n_filters, scheme == SCHEME_MULTINOMIAL);
       if (ws_bytes < SL.total || !aligned256(ws)) return PFR_EWORKSPACE;
       if (overlaps(ws, SL.total, a, (size_t)s.n_total * 4)) return PFR_EINVAL;
@@ -204,6 +232,18 @@ int collective(int scheme, const void* w, pfr_dtype dtype, const pfr_segments* s
                                                  s.offsets, s.n_filters, key, rng.offset,
                                                  rng.filter_base, a, ws, dev_flags, st, nullptr,
                                                  nullptr, sc));
+    }
+    if (ws && aligned256(ws) && !blocks && !permuted && s.n_filters > 1 &&
+        scheme != SCHEME_MULTINOMIAL && !one_workgroup_each(scheme, s)) {
+      const SegLayout SL = seg_layout(s.n_total, s.n_filters, false);
+      const size_t n = (size_t)s.n_total;
+      if (ws_bytes >= SL.total &&
+          clear_of(ws, SL.total, {{a, n * 4}, {w, n * dtype_size(dtype)},
+                                  {s.offsets, ((size_t)s.n_filters + 1) * 8}, {rng.offset_dev, 4},
+                                  {dev_flags, 4}}))
+        return launch_result(launch_scan_segmented(scheme, dtype == PFR_F64, w, s.n_total,
+                                                   s.offsets, s.n_filters, key, rng.offset,
+                                                   rng.filter_base, a, ws, dev_flags, st));
     }
     // one short multinomial vector: with a workspace in two launches over
     // many workgroups, without one in one workgroup (1000 particles 11.0
