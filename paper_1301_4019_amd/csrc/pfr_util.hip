@@ -405,8 +405,12 @@ __global__ __launch_bounds__(256) void k_ess_finish(int64_t n_total,
 // that walks a row of its own leaves partly written lines: 2000000 rows of
 // three words 47 against 21 us).  With one element per thread and a 64-bit
 // division for its row, 500009 particles of four binary32 components took 16.2
-// us, now 6.8; of 33 108, now 49.  With contiguous columns a thread takes its
-// particles' components one by one.
+// us, now 6.8; of 33 108, now 49.  With other strides, so with contiguous
+// columns, a thread takes two components of its four particles at a time: a
+// wait for loads waits for the stores before them as well, which made one at a
+// time slow (1000 particles of 100 binary64 components 86 us, now 50; 500009
+// of 8 24.8, now 19.7; 20000 of 100 binary32 ones 86, now 75), and four
+// outgrow the registers of eight waves per SIMD.
 constexpr int kCopyTile = 1024;
 constexpr int kCopyPer = kCopyTile / 256;
 constexpr int kRowPieces = 1;
@@ -425,9 +429,9 @@ __device__ __forceinline__ bool copy_source(const int32_t* __restrict__ cs_, int
 // A 16-byte piece in registers (an array of HIP's vector struct goes to LDS).
 typedef uint32_t Piece16 __attribute__((ext_vector_type(4)));
 
-// LANES: rows by `lanes` threads each, a power of two up to 64
+// LANES: rows by `lanes` threads each, a power of two up to kRowLanes
 template <typename E, bool LANES>
-__global__ __launch_bounds__(256) void k_copy(const int32_t* __restrict__ c, int64_t n_total,
+__global__ __launch_bounds__(256, 8) void k_copy(const int32_t* __restrict__ c, int64_t n_total,
                                               const int64_t* __restrict__ offsets,
                                               uint32_t n_filters, E* __restrict__ x, int32_t dim,
                                               int64_t ps, int64_t cs, int32_t lanes,
@@ -473,15 +477,33 @@ __global__ __launch_bounds__(256) void k_copy(const int32_t* __restrict__ c, int
       }
     }
   } else {
-    for (int k = 0; k < dim; ++k) {
-      E v[kCopyPer];
+    constexpr int kComps = 2;  // (the remainder one by one)
+    const E* from[kCopyPer];
+    E* to[kCopyPer];
 #pragma unroll
-      for (int u = 0; u < kCopyPer; ++u)
-        if (go[u]) v[u] = xs[ci[u] * ps + k * cs];
-#pragma unroll
-      for (int u = 0; u < kCopyPer; ++u)
-        if (go[u]) xs[(p0 + threadIdx.x + 256 * u) * ps + k * cs] = v[u];
+    for (int u = 0; u < kCopyPer; ++u) {
+      from[u] = xs + ci[u] * ps;
+      to[u] = xs + (p0 + threadIdx.x + 256 * u) * ps;
     }
+    auto move = [&](auto K) {
+      E v[kCopyPer][K.value];
+#pragma unroll
+      for (int u = 0; u < kCopyPer; ++u)
+        if (go[u])
+#pragma unroll
+          for (int j = 0; j < K.value; ++j) v[u][j] = from[u][j * cs];
+#pragma unroll
+      for (int u = 0; u < kCopyPer; ++u) {
+        if (go[u])
+#pragma unroll
+          for (int j = 0; j < K.value; ++j) to[u][j * cs] = v[u][j];
+        from[u] += K.value * cs;
+        to[u] += K.value * cs;
+      }
+    };
+    int k = 0;
+    for (; k + kComps <= dim; k += kComps) move(std::integral_constant<int, kComps>());
+    for (; k < dim; ++k) move(std::integral_constant<int, 1>());
   }
   if (flags && ballot(bad) != 0 && lane_id() == 0) atomicOr(flags, FLAG_BAD_ANCESTOR);
 }
