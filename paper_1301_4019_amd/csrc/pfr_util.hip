@@ -61,8 +61,7 @@ uint32_t slot_count(int64_t n_total, uint32_t n_filters) {
 // writer per phase; values that appear in no run keep their zero.
 //
 // Segments of at most kA2oCap particles (batches) are converted in LDS by one
-// workgroup each.  Longer segments are cut into tiles of kA2oTile offspring
-// slots: a tile finds the range of positions holding its values with two
+// workgroup each.  Longer segments are cut into tiles of offspring slots: a tile finds the range of positions holding its values with two
 // wave-wide 64-ary searches, runs the two phases over that range into an LDS
 // count array and writes its slots once.  An unsorted ancestry goes through
 // counting: LDS histograms over windows of values for segments of up to
@@ -70,7 +69,10 @@ uint32_t slot_count(int64_t n_total, uint32_t n_filters) {
 // as in Code 12, for longer ones.
 constexpr int kA2oCap = 16384;
 constexpr int kA2oStagedThreads = 1024;
-constexpr int kA2oTile = 1024;  // values; 500009 of them: 4096 15.5 us, 1024 7.3 us
+// tiles of one vector (500009 values: 4096 15.5 us, 1024 7.3 us) and of a
+// batch, whose tiles search for their segment and mostly leave again (1024
+// segments of 16384, unsorted: 1024 106 us, 4096 73; sorted 93 and 86)
+constexpr int kA2oTile = 1024, kA2oBatchTile = 4096;
 constexpr int kA2oThreads = 256;
 
 __global__ __launch_bounds__(kA2oStagedThreads) void k_a2o_staged(
@@ -175,19 +177,20 @@ __device__ __forceinline__ int64_t wave_lower_bound(const int32_t* __restrict__ 
   return lo + __popcll(ballot(p < hi && (int64_t)a[p] < v));
 }
 
+template <int TILE>
 __global__ __launch_bounds__(kA2oThreads) void k_a2o_sorted_tiles(
     const int32_t* __restrict__ a, int64_t n_total, const int64_t* __restrict__ offsets,
     uint32_t n_filters, int64_t min_len, int32_t* __restrict__ o,
     uint32_t* __restrict__ flags) {
-  __shared__ int32_t cnt[kA2oTile];
+  __shared__ int32_t cnt[TILE];
   __shared__ int64_t s_range[2];
   SlotSeg s;
-  if (!slot_segment<kA2oTile>(offsets, n_filters, n_total, blockIdx.x, s)) return;
+  if (!slot_segment<TILE>(offsets, n_filters, n_total, blockIdx.x, s)) return;
   if (s.n < min_len) return;  // converted in LDS by k_a2o_staged
   const int tid = (int)threadIdx.x, wave = tid / kWave;
   const int32_t* __restrict__ as = a + s.base;
-  const int64_t j0 = s.p * kA2oTile;
-  const int tile = (int)min((int64_t)kA2oTile, s.n - j0);
+  const int64_t j0 = s.p * TILE;
+  const int tile = (int)min((int64_t)TILE, s.n - j0);
   for (int j = tid; j < tile; j += kA2oThreads) cnt[j] = 0;
   if (wave < 2) {
     const int64_t r = wave_lower_bound(as, s.n, wave == 0 ? j0 : j0 + tile);
@@ -214,19 +217,21 @@ __global__ __launch_bounds__(kA2oThreads) void k_a2o_sorted_tiles(
 }
 
 // Unsorted segments longer than kA2oWinMax: zero pass, then one atomic
-// addition per ancestor, both over tiles of kA2oTile positions per workgroup.
+// addition per ancestor, both over tiles of TILE positions per workgroup.
+template <int TILE>
 __global__ __launch_bounds__(kA2oThreads) void k_a2o_zero(int64_t n_total,
                                                           const int64_t* __restrict__ offsets,
                                                           uint32_t n_filters, int64_t min_len,
                                                           int32_t* __restrict__ o) {
   SlotSeg s;
-  if (!slot_segment<kA2oTile>(offsets, n_filters, n_total, blockIdx.x, s)) return;
+  if (!slot_segment<TILE>(offsets, n_filters, n_total, blockIdx.x, s)) return;
   if (s.n < min_len) return;
-  const int64_t j0 = s.p * kA2oTile;
-  const int tile = (int)min((int64_t)kA2oTile, s.n - j0);
+  const int64_t j0 = s.p * TILE;
+  const int tile = (int)min((int64_t)TILE, s.n - j0);
   for (int j = (int)threadIdx.x; j < tile; j += kA2oThreads) o[s.base + j0 + j] = 0;
 }
 
+template <int TILE>
 __global__ __launch_bounds__(kA2oThreads) void k_a2o_atomic(const int32_t* __restrict__ a,
                                                             int64_t n_total,
                                                             const int64_t* __restrict__ offsets,
@@ -234,10 +239,10 @@ __global__ __launch_bounds__(kA2oThreads) void k_a2o_atomic(const int32_t* __res
                                                             int32_t* __restrict__ o,
                                                             uint32_t* __restrict__ flags) {
   SlotSeg s;
-  if (!slot_segment<kA2oTile>(offsets, n_filters, n_total, blockIdx.x, s)) return;
+  if (!slot_segment<TILE>(offsets, n_filters, n_total, blockIdx.x, s)) return;
   if (s.n < min_len) return;
-  const int64_t i0 = s.p * kA2oTile;
-  const int tile = (int)min((int64_t)kA2oTile, s.n - i0);
+  const int64_t i0 = s.p * TILE;
+  const int tile = (int)min((int64_t)TILE, s.n - i0);
   bool bad = false;
   for (int i = (int)threadIdx.x; i < tile; i += kA2oThreads) {
     const int64_t v = a[s.base + i0 + i];
@@ -558,9 +563,14 @@ hipError_t launch_ancestors_to_offspring(const int32_t* a, int64_t n_total, cons
       if (max_len > 0 && max_len <= kA2oCap) return hipSuccess;
       min_len = kA2oCap + 1;
     }
-    const uint32_t slots = slot_count<kA2oTile>(n_total, n_filters);
-    hipLaunchKernelGGL(k_a2o_sorted_tiles, dim3(slots), dim3(kA2oThreads), 0, stream, a, n_total,
-                       offsets, n_filters, min_len, o, flags);
+    if (offsets)
+      hipLaunchKernelGGL(k_a2o_sorted_tiles<kA2oBatchTile>,
+                         dim3(slot_count<kA2oBatchTile>(n_total, n_filters)), dim3(kA2oThreads), 0,
+                         stream, a, n_total, offsets, n_filters, min_len, o, flags);
+    else
+      hipLaunchKernelGGL(k_a2o_sorted_tiles<kA2oTile>, dim3(slot_count<kA2oTile>(n_total, 1)),
+                         dim3(kA2oThreads), 0, stream, a, n_total, offsets, n_filters, min_len, o,
+                         flags);
     return hipGetLastError();
   }
   // a batch may hold both kinds of segment; each kernel skips the other kind
@@ -575,11 +585,17 @@ hipError_t launch_ancestors_to_offspring(const int32_t* a, int64_t n_total, cons
   }
   if (!any_long) return hipSuccess;
   const int64_t min_len = kA2oWinMax + 1;
-  const uint32_t slots = slot_count<kA2oTile>(n_total, n_filters);
-  hipLaunchKernelGGL(k_a2o_zero, dim3(slots), dim3(kA2oThreads), 0, stream, n_total, offsets,
-                     n_filters, min_len, o);
-  hipLaunchKernelGGL(k_a2o_atomic, dim3(slots), dim3(kA2oThreads), 0, stream, a, n_total,
-                     offsets, n_filters, min_len, o, flags);
+  auto count = [&](auto zero, auto add, uint32_t slots) {
+    hipLaunchKernelGGL(zero, dim3(slots), dim3(kA2oThreads), 0, stream, n_total, offsets,
+                       n_filters, min_len, o);
+    hipLaunchKernelGGL(add, dim3(slots), dim3(kA2oThreads), 0, stream, a, n_total, offsets,
+                       n_filters, min_len, o, flags);
+  };
+  if (offsets)
+    count(k_a2o_zero<kA2oBatchTile>, k_a2o_atomic<kA2oBatchTile>,
+          slot_count<kA2oBatchTile>(n_total, n_filters));
+  else
+    count(k_a2o_zero<kA2oTile>, k_a2o_atomic<kA2oTile>, slot_count<kA2oTile>(n_total, 1));
   return hipGetLastError();
 }
 
