@@ -1425,10 +1425,22 @@ hipError_t launch_permute(const int32_t* a, int64_t n_total, const int64_t* offs
     // do not fill the chip once.  The one workgroup of a long segment takes
     // 30 to 70 us, so below kPermLongTotal particles the global kernels,
     // spread over the chip, run the long ones (four of 60000: 22 against 67
-    // us; 256 of them 313 against 68 us).
+    // us; 256 of them 313 against 68 us).  So do they where the LDS tiers come
+    // on top of the global kernels, for which the batch has longer segments or
+    // none that are known of, and too little would be left to them: by the
+    // average segment and, for a sorted ancestry, whose global kernels are
+    // fast, by the particles (global against LDS and global, us: 30 of 2^16 ..
+    // 2^17.9 sorted 120 / 190, unsorted 329 / 394; 60 of 2^15.8 .. 2^16.2 121 /
+    // 163 and 312 / 275; 100 of 2^14.5 .. 2^17 sorted 121 / 154; 200 of 2^15 ..
+    // 2^16.5 332 / 304; 100 of 2^15 .. 2^16 142 / 113; 64 of them 63 / 78).
     const int64_t mid = tuning().batch_permute_lds_max;
     const bool equal = max_len > 0 && max_len * (int64_t)n_filters == n_total;
-    const bool spread = n_total < kPermLongTotal;
+    const bool bounded = max_len > 0 && max_len <= kPermBatchMax;
+    const int64_t mean = n_total / (int64_t)n_filters;
+    const bool beyond = sorted ? mean > kPermBatchMax || n_total < 2 * kPermLongTotal ||
+                                     (mean > 52000 && n_total < 4 * kPermLongTotal)
+                               : 4 * mean > 5 * kPermBatchMax;
+    const bool spread = n_total < kPermLongTotal || (!bounded && beyond);
     const int64_t top = spread ? mid : kPermBatchMax;
     const int64_t upto[4] = {kPermShort, mid, kPermLong, kPermBatchMax};
     constexpr uint32_t kSlots[4] = {0, 512, 256, 256};  // workgroups the chip holds at once
