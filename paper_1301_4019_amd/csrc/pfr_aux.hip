@@ -732,10 +732,14 @@ __global__ __launch_bounds__(THREADS) void k_permute_lds(
       for (uint32_t q = tid; q < nq; q += THREADS) {
         int32_t x[4];
         load_quad(as, q, n, x);
+        // (an ancestor repeated in its quad has claimed already: 16384 particles
+        // of one ancestor, whose claims all meet in one word, 23.2 -> 13.4 us)
+        uint32_t claimed = 0xFFFFFFFFu;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
           const uint32_t i = 4 * q + k, s = anc(i, x[k]) - w0;
-          if (s < ns && i < n) atomicMin(&d[s], i);
+          if (s < ns && i < n && s != claimed) atomicMin(&d[s], i);
+          claimed = s;
         }
       }
       __syncthreads();
