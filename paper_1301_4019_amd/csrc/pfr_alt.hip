@@ -480,9 +480,21 @@ __global__ __launch_bounds__(kTableThreads) void k_metropolis_table(
   const __amdgpu_buffer_rsrc_t wv = buffer_view(w, (uint32_t)(n * (int64_t)sizeof(T)));
   const int64_t p0 = (int64_t)blockIdx.x * chunk;
   const int64_t p1 = p0 + chunk < n ? p0 + chunk : n;
-  for (int64_t g = p0; g < p1; g += (int64_t)K * kTableThreads)
-    metropolis_lockstep<T, K, kTableThreads>(w, wv, (uint32_t)n, B, key, filter, offset, tab,
-                                             (uint32_t)g + threadIdx.x, (uint32_t)p1, a);
+  for (int64_t g = p0; g < p1; g += (int64_t)K * kTableThreads) {
+    const uint32_t i = (uint32_t)g + threadIdx.x;
+    // a remainder of one or two chains a lane runs those alone (B = 354, us:
+    // 2^20 + 1 particles 1543 -> 1429, 2^20 + 2^17 2126 -> 1883, 1.5 M
+    // 3417 -> 2834)
+    if (K > 1 && p1 - g <= kTableThreads)
+      metropolis_lockstep<T, 1, kTableThreads>(w, wv, (uint32_t)n, B, key, filter, offset, tab, i,
+                                               (uint32_t)p1, a);
+    else if (K > 2 && p1 - g <= 2 * kTableThreads)
+      metropolis_lockstep<T, 2, kTableThreads>(w, wv, (uint32_t)n, B, key, filter, offset, tab, i,
+                                               (uint32_t)p1, a);
+    else
+      metropolis_lockstep<T, K, kTableThreads>(w, wv, (uint32_t)n, B, key, filter, offset, tab, i,
+                                               (uint32_t)p1, a);
+  }
 }
 
 // ------------------------------------------------------------------ staged Metropolis
