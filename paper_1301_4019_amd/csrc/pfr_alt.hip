@@ -84,9 +84,16 @@ __device__ __forceinline__ Weights4<T> load_weights4(const T* __restrict__ w) {
   return Weights4<T>{{t.x, t.y, t.z, t.w}};
 }
 
-// A segment of n weights into LDS (16-byte aligned), 16 bytes a lane.
+// A segment of n weights into LDS (16-byte aligned), 16 bytes a lane, or a
+// weight each where the threads suffice (the last of n, when they are not a
+// multiple of four, are a second wait: 65536 segments of 128 .. 256 without
+// max_len, one step, 368 -> 347 us).
 template <typename T>
 __device__ __forceinline__ void stage_weights(const T* __restrict__ w, uint32_t n, T* sw) {
+  if (n <= blockDim.x) {
+    if (threadIdx.x < n) sw[threadIdx.x] = w[threadIdx.x];
+    return;
+  }
 #pragma unroll 4
   for (uint32_t q = threadIdx.x; q < n / 4; q += blockDim.x) {
     const Weights4<T> t = load_weights4(w + 4 * q);
@@ -442,16 +449,22 @@ __device__ __forceinline__ void metropolis_lockstep(const T* __restrict__ ws,
         uint32_t j[K];
         double u[K], v[K];
         bool need[K];
+        T raw[K];
 #pragma unroll
         for (int c = 0; c < K; ++c) {
           j[c] = index_draw(x[c][3 * q], x[c][3 * q + 1], n);
           u[c] = u_accept(x[c][3 * q + 2]);
           need[c] = !tab.rejects(u[c], wk[c], j[c]);
         }
-        // the K gathers go out together; lanes with nothing to load read zero
+        // the K gathers go out together (the scheduler, left to itself, may wait
+        // for the first before the second: 256 segments of 60000, 100 steps, 1870
+        // -> 2045 us); lanes with nothing to load read zero
 #pragma unroll
         for (int c = 0; c < K; ++c)
-          v[c] = (double)buffer_gather<T>(wv, need[c] ? j[c] * (uint32_t)sizeof(T) : kNoLoad);
+          raw[c] = buffer_gather<T>(wv, need[c] ? j[c] * (uint32_t)sizeof(T) : kNoLoad);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int c = 0; c < K; ++c) v[c] = (double)raw[c];
 #pragma unroll
         for (int c = 0; c < K; ++c) {
           // selects, not a branch: the gathered value is used on every lane,
@@ -713,16 +726,18 @@ __global__ __launch_bounds__(THREADS, CAP * sizeof(T) <= 65536 ? 8 : 1) void k_m
       const uint32_t filt = filter_base + f;
       if (n <= (uint32_t)CAP) {
         __syncthreads();  // the previous segment's chains are done with sw
-        if (threadIdx.x == 0) s_next = 0;
-        stage_weights(w + base, n, sw);
-        __syncthreads();
         const uint32_t len = (uint32_t)(q1 - g0), i0 = (uint32_t)(g0 - base);
         const bool shares = kTakes && len > (uint32_t)THREADS;
-        for (uint32_t k = shares ? take(kWave) + lane_id() : threadIdx.x;
-             shares ? uniform_u32(k) < len : k < len;
-             k = shares ? take(kWave) + lane_id() : k + THREADS)
+        if (shares && threadIdx.x == 0) s_next = 0;
+        stage_weights(w + base, n, sw);
+        __syncthreads();
+        uint32_t k0 = shares ? take(kWave) : uniform_u32(threadIdx.x & ~(uint32_t)(kWave - 1));
+        while (k0 < len) {
+          const uint32_t k = k0 + lane_id();
           if (k < len)
             a[g0 + k] = (int32_t)metropolis_chain(sw, key, i0 + k, filt, offset, n, steps);
+          k0 = shares ? take(kWave) : k0 + THREADS;
+        }
       } else if (kCoded && n <= kCodes << kCodesMaxShift &&
                  codes_pay(chunk, q1 - g0, n, (double)steps)) {
         uint16_t* const code = reinterpret_cast<uint16_t*>(sw);
@@ -1081,16 +1096,22 @@ int staged_capacity(int64_t max_len, int64_t n_total, uint32_t n_filters) {
   return (int)(128 * per_kb);
 }
 
-// Particles per workgroup of 1024 threads of a batch: as many as `most`, in
-// whole rounds of the workgroups that the chip holds at once, which are two to a
-// CU, or one with the 128 KB tier (16 segments of 40000 binary32 weights, 4
-// steps: 313 chunks, a second round for the last 57, 23 us, 209 chunks 17; 30 of
-// 150000 at 2 % acceptance: 275 chunks 272 us, 489 chunks 207).
-template <typename T>
-int64_t batch_chunk(int cap, int64_t n_total, int64_t most) {
-  const int64_t slots = cap * (int64_t)sizeof(T) > 65536 ? 256 : 512;
-  const int64_t rounds = (n_total + slots * most - 1) / (slots * most);
-  const int64_t even = (n_total + slots * rounds - 1) / (slots * rounds);
+// Particles per workgroup of 1024 threads of a batch: as many as `most`, less
+// where that would leave CUs idle (two workgroups each).
+int64_t chunk_for(int64_t n_total, int64_t most) {
+  return std::min(most, std::max<int64_t>(1024, (n_total / 512 + 1023) / 1024 * 1024));
+}
+// The same where most segments are too long for the 128 KB tier, so that nearly
+// every chunk is one part of one segment: equal chunks in whole rounds of the
+// workgroups that the chip holds at once, one to a CU (16 of 40000 binary32
+// weights, 4 steps: 313 chunks, a second round for the last 57, 23 us, 209 chunks
+// 17; 64 of 2^15 .. 2^16, rejection at 4 %: 492 chunks 121 us, 246 103).  Chunks
+// of several short segments differ in cost, and small ones even that out (500 of
+// 2^8 .. 2^14 binary64 weights, 100 steps: 464 chunks 340 us, 232 375).
+int64_t batch_chunk(int cap, size_t weight, int64_t n_total, uint32_t n_filters, int64_t most) {
+  if (cap * weight <= 65536 || n_total / n_filters <= cap) return chunk_for(n_total, most);
+  const int64_t rounds = (n_total + 256 * most - 1) / (256 * most);
+  const int64_t even = (n_total + 256 * rounds - 1) / (256 * rounds);
   return std::min(most, (even + 1023) / 1024 * 1024);
 }
 
@@ -1166,8 +1187,8 @@ hipError_t launch_metropolis_t(const void* wv, int64_t n_total, const int64_t* o
   // (from the queue twice the tuned chunk, but several to a workgroup)
   const int64_t tuned = tuning().batch_metropolis_chunk;
   const int64_t chunk =
-      queued ? std::min(2 * tuned, std::max<int64_t>(1024, (n_total / 512 + 1023) / 1024 * 1024))
-             : batch_chunk<T>(cap, n_total, tuned);
+      queued ? chunk_for(n_total, 2 * tuned)
+             : batch_chunk(cap, sizeof(T), n_total, n_filters, tuned);
   // with a workspace and step counts of its own per segment: cut by cost, and
   // the chunks handed out as workgroups get free
   const unsigned chunks = (unsigned)((n_total + chunk - 1) / chunk);
@@ -1381,8 +1402,8 @@ hipError_t launch_rejection_t(const void* wv, int64_t n_total, const int64_t* of
   }
   // the tuned chunk, less where it would leave CUs idle (64 vectors of 4000 at
   // 1.8 % acceptance: 85 us against 818; 64 of 30000: 312 against 716)
-  const int64_t chunk =
-      batch_chunk<T>(cap, n_total, (int64_t)tuning().batch_rejection_per_wave * 16);
+  const int64_t chunk = batch_chunk(cap, sizeof(T), n_total, n_filters,
+                                    (int64_t)tuning().batch_rejection_per_wave * 16);
   const dim3 grid((unsigned)((n_total + chunk - 1) / chunk));
   if (cap == 16 * per_kb)
     hipLaunchKernelGGL((k_rejection<T, 16 * per_kb, 1024>), grid, dim3(1024), 0, stream, w,
