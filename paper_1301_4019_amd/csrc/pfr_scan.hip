@@ -1489,8 +1489,7 @@ struct MultiWgLds {
 
 template <typename T>
 __global__ __launch_bounds__(kT) void k_scan_emit_mb(const T* __restrict__ w, int64_t n,
-                                                     uint32_t nb, uint32_t nbe, Key key,
-                                                     uint32_t offset, uint32_t filter,
+                                                     uint32_t nb, uint32_t nbe,
                                                      const BlockRec* __restrict__ recs,
                                                      const uint64_t* __restrict__ esums,
                                                      const uint64_t* __restrict__ evals,
@@ -2147,7 +2146,9 @@ __device__ __forceinline__ uint32_t* seg_claim(const SegClaim& c, uint32_t f) {
   return c.claim ? c.claim + (size_t)c.tstart[f] * (kSegTile / 32) : nullptr;
 }
 
-template <typename T, bool MULTI>
+// Records of the segmented multinomial batch: a workgroup per weight block,
+// then one per exponential block.
+template <typename T>
 __global__ __launch_bounds__(kT) void k_seg_records(
     const T* __restrict__ w, const int64_t* __restrict__ offsets, uint32_t n_filters,
     uint32_t grid_b, Key key, uint32_t offset, uint32_t filter_base,
@@ -2163,7 +2164,7 @@ __global__ __launch_bounds__(kT) void k_seg_records(
     const int64_t n = offsets[f + 1] - base;
     const BlockRec r = block_record(w + base, n, (int64_t)(g - bstart[f]) * kBlock, &s);
     if (threadIdx.x == 0) recs[g] = r;
-  } else if (MULTI) {
+  } else {
     const uint32_t g = blockIdx.x - grid_b;
     if (g >= estart[n_filters]) return;
     const uint32_t f = wave_find_segment<uint32_t>(estart, n_filters, g);
@@ -2176,8 +2177,7 @@ __global__ __launch_bounds__(kT) void k_seg_records(
   }
 }
 
-// Weight records of the segmented batch, one block per wave (strata schemes;
-// the multinomial scheme keeps k_seg_records for its exponential blocks).
+// Weight records of the segmented batch, one block per wave (strata schemes).
 template <typename T>
 __global__ __launch_bounds__(kT) void k_seg_records_w(const T* __restrict__ w,
                                                       const int64_t* __restrict__ offsets,
@@ -2354,14 +2354,18 @@ hipError_t launch_scan_t(const void* wv, int64_t n, Key key, uint32_t offset, ui
     }
   }
   if constexpr (multi) {
-    // a vector that k_scan_batched resamples without a workspace: its carries,
-    // which it forms straight at the global scale
+    // up to kGrp blocks, one group, the workgroup's own carries win at every
+    // length (against the carry kernel and one block per wave: 2^18 20.6 / 41.7
+    // us, 2^19 23.6 / 43.8, 2^20 32.4 / 47.3); more would take a second level of
+    // carries in every workgroup.  straight: a vector that
+    // k_scan_batched resamples without a workspace, whose carries that forms at
+    // the global scale at once
     const bool one_wg = n <= (int64_t)tuning().single_wg_max;
     if ((nb <= (uint32_t)tuning().direct_max_blocks || one_wg) && nb <= kGrp &&
         nbe <= kDirectMulti) {
-      hipLaunchKernelGGL((k_scan_emit_mb<T>), dim3(nb), dim3(kT), 0, stream, w, n, nb, nbe, key,
-                         offset, filter, recs, esums, (const uint64_t*)evals,
-                         one_wg ? kStraight : 0u, a, flags, claim);
+      hipLaunchKernelGGL((k_scan_emit_mb<T>), dim3(nb), dim3(kT), 0, stream, w, n, nb, nbe,
+                         recs, esums, (const uint64_t*)evals, one_wg ? kStraight : 0u, a, flags,
+                         claim);
       return hipGetLastError();
     }
   }
@@ -2476,7 +2480,7 @@ hipError_t launch_segmented_t(const T* w, int64_t n_total, const int64_t* offset
   }
   const uint32_t wgs_b = (L.grid_b + kWavesPerWG - 1) / kWavesPerWG;
   if constexpr (multi)
-    hipLaunchKernelGGL((k_seg_records<T, multi>), dim3(L.grid_b + L.grid_e), dim3(kT), 0, stream,
+    hipLaunchKernelGGL((k_seg_records<T>), dim3(L.grid_b + L.grid_e), dim3(kT), 0, stream,
                        w, offsets, n_filters, L.grid_b, key, offset, filter_base, bstart, estart,
                        recs, esums, evals);
   else
