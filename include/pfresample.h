@@ -455,14 +455,19 @@ typedef struct {
                                        [0, PFR_MAX_BATCH_SEGMENT]; the stratified and systematic
                                        schemes do so up to 16384 in any case */
     int32_t batch_stage_max_kb;     /* Metropolis / rejection: largest LDS tier for staging a
-                                       segment's weights (16, 64 or 128 KB); longer segments
-                                       gather from global memory in the same launch */
-    int32_t batch_metropolis_chunk; /* particles per 1024-thread workgroup of the batched
-                                       Metropolis kernel, a multiple of 1024 in [1024, 65536] */
+                                       segment's weights (16, 64 or 128 KB).  In the same launch
+                                       longer segments gather from global memory, with the
+                                       128 KB tier through 16-bit bounds of their weights in LDS
+                                       up to 262144 weights, where they pay */
+    int32_t batch_metropolis_chunk; /* at most this many particles per 1024-thread workgroup of
+                                       the batched Metropolis kernel, twice as many where the
+                                       workgroups take chunks from a queue (step counts of their
+                                       own per segment); a multiple of 1024 in [1024, 65536] */
     int32_t batch_rejection_per_wave; /* particles per wave of the batched rejection kernel
                                        [64, 4096] */
     int32_t batch_permute_lds_max;  /* segments up to this length are permuted in LDS, one
-                                       workgroup each (4096, 8192 or 16384) */
+                                       workgroup each (4096, 8192 or 16384); in large batches
+                                       those up to 65536 are as well */
 } pfr_tuning;
 
 PFR_API void pfr_tuning_defaults(pfr_tuning* t);

@@ -322,7 +322,6 @@ __device__ __forceinline__ uint64_t wave_incl_add_u64(uint64_t x) {
   x += dpp_u64<kDppBcast31, 0xC>(0ull, x);
   return x;
 }
-// Inclusive max-scan of values >= -1.
 __device__ __forceinline__ uint32_t wave_incl_add_u32(uint32_t x) {
   x += dpp_u32<kDppShr1>(0u, x);
   x += dpp_u32<kDppShr2>(0u, x);

@@ -301,7 +301,8 @@ hipError_t launch_lgssm_move(int32_t n_filters, int32_t n, double phi, double q,
                        filter_base,
                        c, x, w, logz, B_dev, flags);
   };
-  // by LDS: eleven, two and one workgroups to a CU, and filters too long for it
+  // workgroups to a CU: eight (by waves), two and one (by LDS); filters too
+  // long for LDS below
   if (n <= 2048) launch(k_lg_move<2048, 256>, 256);
   else if (n <= 16384) launch(k_lg_move<16384, 1024>, 1024);
   else if (n <= 32768) launch(k_lg_move<32768, 1024>, 1024);
