@@ -403,19 +403,16 @@ __global__ __launch_bounds__(256) void k_ess_finish(int64_t n_total,
 // overwritten (c_{c_i} != c_i) is left alone and flagged, which keeps the
 // step race-free for any input.  Element (g, k) of the state (particle g,
 // component k) sits at x[g * ps + k * cs].  A workgroup takes a tile of
-// kCopyTile particles of one segment, four per thread, whose ancestry reads,
-// checks and first components are in flight together.  A row (cs == 1) is
-// copied in the widest pieces its length, stride and address allow: by one
+// kCopyTile particles of one segment, four per thread, whose ancestry reads
+// and checks are in flight together.  A row (cs == 1) is copied in the widest pieces its length, stride and address allow: by one
 // thread when that is one piece, else by a power of two of lanes (a thread
 // that walks a row of its own leaves partly written lines: 2000000 rows of
 // three words 47 against 21 us).  With one element per thread and a 64-bit
 // division for its row, 500009 particles of four binary32 components took 16.2
-// us, now 6.8; of 33 108, now 49.  With other strides, so with contiguous
-// columns, a thread takes two components of its four particles at a time: a
-// wait for loads waits for the stores before them as well, which made one at a
-// time slow (1000 particles of 100 binary64 components 86 us, now 50; 500009
-// of 8 24.8, now 19.7; 20000 of 100 binary32 ones 86, now 75), and four
-// outgrow the registers of eight waves per SIMD.
+// us, now 6.8; of 33 108, now 49.  With contiguous
+// columns a thread takes two components at a time (a wait for loads waits for
+// the stores before them as well: 1000 particles of 100 binary64 components 58
+// us one at a time, now 34) of one particle after the other or of all four.
 constexpr int kCopyTile = 1024;
 constexpr int kCopyPer = kCopyTile / 256;
 constexpr int kRowPieces = 1;
@@ -434,8 +431,11 @@ __device__ __forceinline__ bool copy_source(const int32_t* __restrict__ cs_, int
 // A 16-byte piece in registers (an array of HIP's vector struct goes to LDS).
 typedef uint32_t Piece16 __attribute__((ext_vector_type(4)));
 
-// LANES: rows by `lanes` threads each, a power of two up to kRowLanes
-template <typename E, bool LANES>
+// kCopyLanes: rows by `lanes` threads each, a power of two up to kRowLanes;
+// kCopyThread: a row of one piece, or the columns of one particle after the
+// other; kCopyAbreast: the columns of four particles at once
+enum CopyMode { kCopyLanes, kCopyThread, kCopyAbreast };
+template <typename E, CopyMode MODE>
 __global__ __launch_bounds__(256, 8) void k_copy(const int32_t* __restrict__ c, int64_t n_total,
                                               const int64_t* __restrict__ offsets,
                                               uint32_t n_filters, E* __restrict__ x, int32_t dim,
@@ -460,7 +460,7 @@ __global__ __launch_bounds__(256, 8) void k_copy(const int32_t* __restrict__ c, 
     const int il = (int)threadIdx.x + 256 * u;
     go[u] = il < tile && copy_source(cseg, p0 + il, s.n, ci[u], bad);
   }
-  if constexpr (LANES) {
+  if constexpr (MODE == kCopyLanes) {
     __shared__ int32_t src[kCopyTile];  // sources of the tile's rows, -1: stays
 #pragma unroll
     for (int u = 0; u < kCopyPer; ++u)
@@ -482,7 +482,6 @@ __global__ __launch_bounds__(256, 8) void k_copy(const int32_t* __restrict__ c, 
       }
     }
   } else {
-    constexpr int kComps = 2;  // (the remainder one by one)
     const E* from[kCopyPer];
     E* to[kCopyPer];
 #pragma unroll
@@ -490,15 +489,16 @@ __global__ __launch_bounds__(256, 8) void k_copy(const int32_t* __restrict__ c, 
       from[u] = xs + ci[u] * ps;
       to[u] = xs + (p0 + threadIdx.x + 256 * u) * ps;
     }
-    auto move = [&](auto K) {
+    // components k .. k + K - 1 of the particles u0 .. u1 - 1
+    auto move = [&](auto K, int u0, int u1) {
       E v[kCopyPer][K.value];
 #pragma unroll
-      for (int u = 0; u < kCopyPer; ++u)
+      for (int u = u0; u < u1; ++u)
         if (go[u])
 #pragma unroll
           for (int j = 0; j < K.value; ++j) v[u][j] = from[u][j * cs];
 #pragma unroll
-      for (int u = 0; u < kCopyPer; ++u) {
+      for (int u = u0; u < u1; ++u) {
         if (go[u])
 #pragma unroll
           for (int j = 0; j < K.value; ++j) to[u][j * cs] = v[u][j];
@@ -506,9 +506,18 @@ __global__ __launch_bounds__(256, 8) void k_copy(const int32_t* __restrict__ c, 
         to[u] += K.value * cs;
       }
     };
-    int k = 0;
-    for (; k + kComps <= dim; k += kComps) move(std::integral_constant<int, kComps>());
-    for (; k < dim; ++k) move(std::integral_constant<int, 1>());
+    auto walk = [&](int u0, int u1) {
+      int k = 0;
+      for (; k + 2 <= dim; k += 2) move(std::integral_constant<int, 2>(), u0, u1);
+      if (k < dim) move(std::integral_constant<int, 1>(), u0, u1);
+    };
+    if constexpr (MODE == kCopyAbreast) {
+      walk(0, kCopyPer);
+    } else {
+#pragma unroll
+      for (int u = 0; u < kCopyPer; ++u)
+        if (go[u]) walk(u, u + 1);
+    }
   }
   if (flags && ballot(bad) != 0 && lane_id() == 0) atomicOr(flags, FLAG_BAD_ANCESTOR);
 }
@@ -641,15 +650,24 @@ hipError_t launch_copy(const int32_t* c, int64_t n_total, const int64_t* offsets
   int32_t lanes = 1;
   if (rows && dim > kRowPieces)
     while (lanes < dim && lanes < kRowLanes) lanes <<= 1;
+  // columns: one particle after the other while the state stays in the caches,
+  // four abreast where more has to be in flight (one / four, us: 500009
+  // particles, 8 binary64 components 18.7 / 20.2, 16 40 / 35; 16 binary32 22 / 26,
+  // 64 89 / 83, 100 bytes 74 / 109; 2^20 of two binary64 15.9 / 18.7; 2000000 of 16
+  // bytes 56 / 43, of 4 binary32 34 / 33, of 16 118 / 101)
+  const double state = (double)n_total * dim * (double)elem_bytes;
+  const bool abreast = !rows && ((n_total >= 1500000 && state >= 24e6) ||
+                                 (elem_bytes >= 4 && state >= 48e6));
   const uint32_t grid = slot_count<kCopyTile>(n_total, n_filters);
   auto launch = [&](auto* xp) {
     typedef std::remove_pointer_t<decltype(xp)> E;
-    if (lanes > 1)
-      hipLaunchKernelGGL((k_copy<E, true>), dim3(grid), dim3(256), 0, stream, c, n_total, offsets,
-                         n_filters, xp, dim, ps, cs, lanes, flags);
-    else
-      hipLaunchKernelGGL((k_copy<E, false>), dim3(grid), dim3(256), 0, stream, c, n_total,
-                         offsets, n_filters, xp, dim, ps, cs, lanes, flags);
+    auto go = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, stream, c, n_total, offsets, n_filters,
+                         xp, dim, ps, cs, lanes, flags);
+    };
+    if (lanes > 1) go(k_copy<E, kCopyLanes>);
+    else if (abreast) go(k_copy<E, kCopyAbreast>);
+    else go(k_copy<E, kCopyThread>);
   };
   switch (elem_bytes) {
     case 1: launch((uint8_t*)x); break;

@@ -23,3 +23,16 @@ def test_columns(dtype, n, D, pad):
     want[:D, pad // 2:pad // 2 + n] = x[c.long()].t()
     pfr.copy_particles(c, x)
     assert torch.equal(buf, want)
+
+
+@pytest.mark.parametrize("n,D,dtype", [(1500001, 17, torch.uint8), (1500001, 3, torch.complex128),
+                                       (500009, 13, torch.float64), (48000, 255, torch.float32)])
+def test_large_states(n, D, dtype):
+    """States on the other side of the rule that copies four particles abreast."""
+    import paper_1301_4019_amd as pfr
+    w = torch.rand(n, generator=torch.Generator().manual_seed(n)).cuda() ** 4
+    _, c = pfr.resample_permuted("systematic", w, seed=2)
+    x = torch.randint(0, 100, (D, n), device="cuda").to(dtype).t()
+    want = x[c.long()]
+    pfr.copy_particles(c, x)
+    assert torch.equal(x, want)
