@@ -69,10 +69,13 @@ uint32_t slot_count(int64_t n_total, uint32_t n_filters) {
 // as in Code 12, for longer ones.
 constexpr int kA2oCap = 16384;
 constexpr int kA2oStagedThreads = 1024;
-// tiles of one vector (500009 values: 4096 15.5 us, 1024 7.3 us) and of a
-// batch, whose tiles search for their segment and mostly leave again (1024
-// segments of 16384, unsorted: 1024 106 us, 4096 73; sorted 93 and 86)
-constexpr int kA2oTile = 1024, kA2oBatchTile = 4096;
+// tiles of one vector (500009 values: 4096 15.5 us, 1024 7.3), where small ones
+// fill the chip, and of a batch, whose tiles search for their segment and mostly
+// leave again (1024 segments of 16384, unsorted: 1024 106 us, 4096 73; sorted 93
+// and 86), or of a long vector, which fills it anyway (sorted, 5 M values: 4096
+// 27.3, 1024 25.5; 2^23 36 and 39; 2^25 119 and 142)
+constexpr int kA2oTile = 1024, kA2oLargeTile = 4096;
+constexpr int64_t kA2oLarge = 3 << 21;
 constexpr int kA2oThreads = 256;
 
 __global__ __launch_bounds__(kA2oStagedThreads) void k_a2o_staged(
@@ -572,9 +575,9 @@ hipError_t launch_ancestors_to_offspring(const int32_t* a, int64_t n_total, cons
       if (max_len > 0 && max_len <= kA2oCap) return hipSuccess;
       min_len = kA2oCap + 1;
     }
-    if (offsets)
-      hipLaunchKernelGGL(k_a2o_sorted_tiles<kA2oBatchTile>,
-                         dim3(slot_count<kA2oBatchTile>(n_total, n_filters)), dim3(kA2oThreads), 0,
+    if (offsets || n_total > kA2oLarge)
+      hipLaunchKernelGGL(k_a2o_sorted_tiles<kA2oLargeTile>,
+                         dim3(slot_count<kA2oLargeTile>(n_total, n_filters)), dim3(kA2oThreads), 0,
                          stream, a, n_total, offsets, n_filters, min_len, o, flags);
     else
       hipLaunchKernelGGL(k_a2o_sorted_tiles<kA2oTile>, dim3(slot_count<kA2oTile>(n_total, 1)),
@@ -601,8 +604,8 @@ hipError_t launch_ancestors_to_offspring(const int32_t* a, int64_t n_total, cons
                        n_filters, min_len, o, flags);
   };
   if (offsets)
-    count(k_a2o_zero<kA2oBatchTile>, k_a2o_atomic<kA2oBatchTile>,
-          slot_count<kA2oBatchTile>(n_total, n_filters));
+    count(k_a2o_zero<kA2oLargeTile>, k_a2o_atomic<kA2oLargeTile>,
+          slot_count<kA2oLargeTile>(n_total, n_filters));
   else
     count(k_a2o_zero<kA2oTile>, k_a2o_atomic<kA2oTile>, slot_count<kA2oTile>(n_total, 1));
   return hipGetLastError();
