@@ -1436,13 +1436,15 @@ hipError_t launch_permute(const int32_t* a, int64_t n_total, const int64_t* offs
     // fast, by the particles (global against LDS and global, us: 30 of 2^16 ..
     // 2^17.9 sorted 120 / 190, unsorted 329 / 394; 60 of 2^15.8 .. 2^16.2 121 /
     // 163 and 312 / 275; 100 of 2^14.5 .. 2^17 sorted 121 / 154; 200 of 2^15 ..
-    // 2^16.5 332 / 304; 100 of 2^15 .. 2^16 142 / 113; 64 of them 63 / 78).
+    // 2^16.5 332 / 304; without max_len 100 of 60000 174 / 117, 100 of 2^15 .. 2^16
+    // 142 / 113, 64 of them 63 / 78).
     const int64_t mid = tuning().batch_permute_lds_max;
     const bool equal = max_len > 0 && max_len * (int64_t)n_filters == n_total;
     const bool bounded = max_len > 0 && max_len <= kPermBatchMax;
     const int64_t mean = n_total / (int64_t)n_filters;
     const bool beyond = sorted ? mean > kPermBatchMax || n_total < 2 * kPermLongTotal ||
-                                     (mean > 52000 && n_total < 4 * kPermLongTotal)
+                                     (max_len > 0 && mean > 52000 &&
+                                      n_total < 4 * kPermLongTotal)
                                : 4 * mean > 5 * kPermBatchMax;
     const bool spread = n_total < kPermLongTotal || (!bounded && beyond);
     const int64_t top = spread ? mid : kPermBatchMax;
