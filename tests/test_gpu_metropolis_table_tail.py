@@ -21,3 +21,13 @@ def test_remainder(dtype, chunks):
         w = inputs.weights(n, 2.0, seed=chunk, dtype=dtype)
         a = pfr.resample_metropolis(torch.from_numpy(w).cuda(), 61, seed=5).cpu().numpy()
         assert np.array_equal(a, oracle.metropolis_mt(w, 61, seed=5)), chunk
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("n", [65535, 65536, 65537])
+def test_shortest(n, dtype):
+    """Both sides of the length from which the table is used."""
+    import paper_1301_4019_amd as pfr
+    w = inputs.weights(n, 2.0, seed=n, dtype=dtype)
+    a = pfr.resample_metropolis(torch.from_numpy(w).cuda(), 61, seed=5).cpu().numpy()
+    assert np.array_equal(a, oracle.metropolis_mt(w, 61, seed=5))
