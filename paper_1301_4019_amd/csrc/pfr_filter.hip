@@ -129,8 +129,8 @@ __global__ __launch_bounds__(kFT) void k_lg_init(int32_t n_filters, int32_t n, d
 // and written once.  Longer filters (CAP = 0) copy first and go through x
 // twice.  A thread takes quads of consecutive particles.  Every workgroup
 // counts itself once it has read t; the last one advances it.  VALU bound
-// (about 150 instructions a particle, a Philox call among them): 1024 filters of
-// 16384 188 -> 99 us (library functions, three passes over x).
+// (172 VALU instructions a particle, a Philox call among them): 1024 filters of
+// 16384 188 -> 105 us (library functions, three passes over x).
 typedef float QuadF __attribute__((ext_vector_type(4), aligned(4)));
 typedef int32_t QuadI __attribute__((ext_vector_type(4), aligned(4)));
 
