@@ -2074,18 +2074,19 @@ __global__ __launch_bounds__(kT) void k_scan_batched(const T* __restrict__ w, in
 // given, estart[f] (exponential blocks) and tstart[f] (tiles of kSegTile slots
 // of the fused permutation).  One workgroup, four segments per thread and
 // round; bound by the latency of its rounds (4096 segments 5.7 us; one segment
-// per thread of 256, 19.6).
-constexpr int kPrefixThreads = 1024;
-__global__ __launch_bounds__(kPrefixThreads) void k_seg_prefix(const int64_t* __restrict__ offsets,
-                                                               uint32_t n_filters,
-                                                               uint32_t* __restrict__ bstart,
-                                                               uint32_t* __restrict__ estart,
-                                                               uint32_t* __restrict__ tstart) {
-  constexpr int kF = 4, kW = kPrefixThreads / kWave;
+// per thread of 256, 19.6) and, with few segments, by its size (four: 1024
+// threads 3.8 us, 64 threads 1.8).
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void k_seg_prefix(const int64_t* __restrict__ offsets,
+                                                        uint32_t n_filters,
+                                                        uint32_t* __restrict__ bstart,
+                                                        uint32_t* __restrict__ estart,
+                                                        uint32_t* __restrict__ tstart) {
+  constexpr int kF = 4, kW = THREADS / kWave;
   __shared__ uint32_t s_b[kW], s_e[kW], s_t[kW];
   const uint32_t tid = threadIdx.x, wave = tid / kWave;
   uint32_t cb = 0, ce = 0, ct = 0;  // totals of the rounds before (below 2^32, as the layouts' are)
-  for (uint32_t base = 0; base < n_filters; base += kF * kPrefixThreads) {
+  for (uint32_t base = 0; base < n_filters; base += kF * THREADS) {
     const uint32_t f0 = base + kF * tid;
     int64_t o[kF + 1];
 #pragma unroll
@@ -2473,8 +2474,13 @@ hipError_t launch_segmented_t(const T* w, int64_t n_total, const int64_t* offset
   if (!bstart) {  // (else the caller keeps the block prefixes)
     bstart = (uint32_t*)(base + L.bstart);
     estart = multi ? (uint32_t*)(base + L.estart) : nullptr;
-    hipLaunchKernelGGL(k_seg_prefix, dim3(1), dim3(kPrefixThreads), 0, stream, offsets, n_filters,
-                       bstart, estart, sc.tstart);
+    auto prefix = [&](auto kernel, int threads) {
+      hipLaunchKernelGGL(kernel, dim3(1), dim3(threads), 0, stream, offsets, n_filters, bstart,
+                         estart, sc.tstart);
+    };
+    if (n_filters <= 256) prefix(k_seg_prefix<64>, 64);
+    else if (n_filters <= 1024) prefix(k_seg_prefix<256>, 256);
+    else prefix(k_seg_prefix<1024>, 1024);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
