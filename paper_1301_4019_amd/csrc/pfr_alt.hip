@@ -683,9 +683,13 @@ __global__ __launch_bounds__(256) void k_metropolis_global(const T* __restrict__
 // Where the LDS holds two workgroups of 1024 threads, the registers have to as
 // well: eight waves per SIMD.  With the queue's scalars in every form it was
 // seven, and one workgroup (4096 segments of 256, 16 / 100 steps: 109 / 513 us,
-// with two 73 / 329).
+// with two 73 / 329).  The workgroups of 256 threads, a wave per SIMD, keep the
+// registers that the chain alone would have, and in binary32 a plain loop (one
+// vector of 16384, 354 steps: in shares 62.7 us, so 58.4; of 4097 in binary64
+// 64.7 and 66.2).
 template <typename T, int CAP, int THREADS, bool QUEUED>
-__global__ __launch_bounds__(THREADS, CAP * sizeof(T) <= 65536 ? 8 : 1) void k_metropolis_staged(
+__global__ __launch_bounds__(THREADS, THREADS > 256 && CAP * sizeof(T) <= 65536 ? 8 : 1)
+void k_metropolis_staged(
     const T* __restrict__ w, int64_t n_total, const int64_t* __restrict__ offsets,
     uint32_t n_filters, int32_t B, const int32_t* __restrict__ B_dev, Key key, uint32_t offset,
     uint32_t filter_base, int32_t* __restrict__ a, int64_t chunk,
@@ -731,12 +735,17 @@ __global__ __launch_bounds__(THREADS, CAP * sizeof(T) <= 65536 ? 8 : 1) void k_m
         if (shares && threadIdx.x == 0) s_next = 0;
         stage_weights(w + base, n, sw);
         __syncthreads();
-        uint32_t k0 = shares ? take(kWave) : uniform_u32(threadIdx.x & ~(uint32_t)(kWave - 1));
-        while (k0 < len) {
-          const uint32_t k = k0 + lane_id();
-          if (k < len)
+        if constexpr (!kTakes && sizeof(T) == 4) {
+          for (uint32_t k = threadIdx.x; k < len; k += THREADS)
             a[g0 + k] = (int32_t)metropolis_chain(sw, key, i0 + k, filt, offset, n, steps);
-          k0 = shares ? take(kWave) : k0 + THREADS;
+        } else {
+          uint32_t k0 = shares ? take(kWave) : uniform_u32(threadIdx.x & ~(uint32_t)(kWave - 1));
+          while (k0 < len) {
+            const uint32_t k = k0 + lane_id();
+            if (k < len)
+              a[g0 + k] = (int32_t)metropolis_chain(sw, key, i0 + k, filt, offset, n, steps);
+            k0 = shares ? take(kWave) : k0 + THREADS;
+          }
         }
       } else if (kCoded && n <= kCodes << kCodesMaxShift &&
                  codes_pay(chunk, q1 - g0, n, (double)steps)) {
