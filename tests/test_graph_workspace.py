@@ -54,6 +54,19 @@ def test_captured_calls_get_their_own_workspace(monkeypatch):
 
 
 @pytest.mark.gpu
+def test_default_stream_cannot_be_captured():
+    """What lets a call on it go without asking."""
+    torch = pytest.importorskip("torch")
+    torch.zeros(1, device="cuda")
+    assert pfr._stream() == 0 and torch.cuda.default_stream().cuda_stream == 0
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        inside = pfr._stream()
+        torch.zeros(1, device="cuda")
+    assert inside != 0
+
+
+@pytest.mark.gpu
 def test_graphs_replayed_on_two_streams():
     torch = pytest.importorskip("torch")
     n = 300000
